@@ -9,13 +9,8 @@ struct bf16_t { uint16_t v; };
 typedef _Float16 f16_t;
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t u) { return __uint_as_float((uint32_t)u << 16); }
-// round-to-nearest-even; NaN stays NaN
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
-  uint32_t x = __float_as_uint(f);
-  if ((x & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-  x += 0x7fffu + ((x >> 16) & 1u);
-  return (uint16_t)(x >> 16);
-}
+// round-to-nearest-even; NaN stays NaN (one conversion instruction on gfx950; written out it was six)
+__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 template <class T> struct Conv;
 template <> struct Conv<float> {

@@ -299,7 +299,7 @@ void fast_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits
   if (!c->x_ssq && gemm_wants_row_inv(a, EPI_LOGITS)) { KScope k(c, tgt ? SPEC_KCLASS_NORM : -1); launch_row_inv_x(a, st); }
   { KScope k(c, tgt ? SPEC_KCLASS_GEMM_HEAD : -1); launch_gemm_mfma(c->run.dtype, a, EPI_LOGITS, st); }
   { KScope k(c, tgt ? SPEC_KCLASS_OTHER : -1);
-    launch_argmax_partials(a.part_val, a.part_idx, Mh, last_of_q, m.p_head.NT, m.desc.vocab, q, arg_stride, arg_out, st); }
+    launch_argmax_partials(a.part_val, a.part_idx, Mh, last_of_q, gemm_head_partials(a), m.desc.vocab, q, arg_stride, arg_out, st); }
 }
 
 }  // namespace spec

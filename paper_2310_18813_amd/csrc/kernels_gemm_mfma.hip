@@ -435,60 +435,79 @@ static void launch_epi(const GemmArgs &a, int epi, dim3 grid, dim3 block, size_t
   }
 }
 
-// Wide outputs go to the LDS-tiled kernel (same bits, weights fetched once per up to 256 rows) from 65 rows
-// on, the widest (gate-up, LM head) already from 33: the streaming kernel's waves each fetch their own copy
-// of the activations, the tiled kernel shares them through LDS.  The narrow residual GEMMs run it one k-slice
-// per workgroup when the context has the scratch for the slices: worth the second kernel from 33 rows on
-// when a slice has at least 32 steps (down projection), and from 5 row passes of the streaming kernel.
-static bool goes_to_tile_kernel(const GemmArgs &a, int epi) {
-  const bool split_ok = a.part && a.KS > 1 && (a.N & 3) == 0 && (a.KT / a.KS >= 32 || a.M > 256);
-  const int tile_min_m = a.NT >= 1024 ? 33 : 65;
-  return a.NT >= 64 && (epi != EPI_RESIDUAL ? a.M >= tile_min_m : (split_ok && a.M >= 33));
+// Strips (NB) and row tiles (MT) per workgroup of the streaming kernel.  Neither changes any result.
+// A compute unit keeps a bounded number of cache-line requests in flight, and that is what a launch here is bound
+// by; a workgroup asks for NB weight fragments (from HBM the first time a strip is read, from L2 for the other row
+// passes) and MT activation fragments (L2) per 32-k step, so the unit with the most workgroups sets the time:
+// ceil(workgroups / units) * (NB * weight cost + MT * activation cost), with a request that goes to HBM about three
+// times as dear as one that hits L2 (measured).  Against doubling NB up to MT: QKV at d_model 4096 with 17..64
+// rows 27..36 -> 23..31 us (three strips per workgroup: one workgroup per unit).  Small matrices (a draft model's)
+// come out with two row tiles per workgroup and more row passes: their few strips then spread over more units.
+// Returns the estimate in us: 4 us and 12.8 ns (more with more row passes) per step and thousand cost units (within 10 %
+// from 36 to 256 rows on the matrices of the 7B, 13B and 33B widths).
+static double choose_stream(const GemmArgs &a, int &MT, int &NB) {
+  const int n_cu = a.n_cu > 0 ? a.n_cu : 256, mt_max = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 4;
+  static const int cand[] = {1, 2, 3, 4, 6, 8};
+  long best = -1;
+  MT = mt_max; NB = 1;
+  for (int mt = mt_max; mt >= 1; mt >>= 1) {
+    const int passes = (a.M + mt * 16 - 1) / (mt * 16);
+    for (int nb : cand) {
+      if (mt == 1 && nb > 1) break;  // one row tile per workgroup is built with one strip only
+      const long wgs = (long)((a.NT + nb - 1) / nb) * passes;
+      const long per_cu = (wgs + n_cu - 1) / n_cu;
+      const long w_cost = (3000 + 1000 * (passes - 1)) / passes;  // per strip and step, averaged over the row passes
+      const long cost = per_cu * (nb * w_cost + mt * 1000);
+      if (best < 0 || cost < best) { best = cost; NB = nb; MT = mt; }
+    }
+  }
+  const int passes = (a.M + MT * 16 - 1) / (MT * 16);
+  return 4.0 + 1e-6 * best * a.KT * (12.8 + 1.4 * std::min(passes - 1, 3));
+}
+
+// Which kernel: the streaming one up to 32 rows, beyond whichever the estimates say is faster (all give the same bits).
+// The tiled kernel shares the activations of a workgroup through LDS and reads a weight once per up to 256 rows; narrow
+// outputs leave it too few workgroups unless each takes one k-slice and a second kernel adds the slices.  Measured
+// (us; streaming / tiled / split): 15360 x 5120 at 64 rows 40 / 35 / -, 12288 x 4096 at 64 rows 27 / 29 / -; 4096 x 4096
+// at 128, 256 and 512 rows 17 / 22 / -, 25 / 23 / - and - / 33 / 50; 4096 x 11008 at 64, 256 and 1024 rows - / 52 / 27,
+// - / 52 / 43 and - / 105 / 142.
+enum GemmRoute { ROUTE_STREAM, ROUTE_TILE, ROUTE_SPLIT };
+static GemmRoute route(const GemmArgs &a, int epi) {
+  if (a.M <= 32 || a.NT < 16) return ROUTE_STREAM;
+  // the slices of a split launch are at least 32 steps long (shorter ones at up to 256 rows: no faster than streaming)
+  const bool split_ok = epi == EPI_RESIDUAL && a.part && a.KS > 1 && (a.KT / a.KS >= 32 || (a.M > 256 && a.KT / a.KS >= 2));
+  if (a.tune & 0xff) return split_ok ? ROUTE_SPLIT : ROUTE_TILE;  // a pinned wave tile (test / tuning aid)
+  int MT, NB;
+  const double stream = choose_stream(a, MT, NB), tile = gemm_tile_us(a, false);
+  if (split_ok && gemm_tile_us(a, true) < std::min(stream, tile)) return ROUTE_SPLIT;
+  return tile < 0.95 * stream ? ROUTE_TILE : ROUTE_STREAM;
 }
 bool gemm_can_leave_ssq(const GemmArgs &a) {  // the row-wise reduction keeps the fp16 row in LDS: rows of up to 8192
-  return a.x_out && a.M > 64 && (a.N & 31) == 0 && a.N <= 8192 && goes_to_tile_kernel(a, EPI_RESIDUAL);
+  return a.x_out && a.M > 64 && (a.N & 31) == 0 && a.N <= 8192 && route(a, EPI_RESIDUAL) == ROUTE_SPLIT;
 }
 bool gemm_wants_row_inv(const GemmArgs &a, int epi) {
-  return a.M > 0 && goes_to_tile_kernel(a, epi) && gemm_tile_wants_row_inv(a, epi);
+  return a.M > 0 && route(a, epi) == ROUTE_TILE && gemm_tile_wants_row_inv(a, epi);
 }
+
+int gemm_head_partials(const GemmArgs &a) { return route(a, EPI_LOGITS) == ROUTE_TILE ? gemm_tile_head_partials(a) : a.NT; }
 
 template <class T>
 static void launch_gemm_t(GemmArgs a, int epi, hipStream_t st) {
   if (a.M <= 0) return;
-  if (goes_to_tile_kernel(a, epi)) {
-    launch_gemm_tile(std::is_same<T, bf16_t>::value ? SPEC_DTYPE_BF16 : SPEC_DTYPE_F16, a, epi, st);
+  const GemmRoute r = route(a, epi);
+  if (r != ROUTE_STREAM) {
+    launch_gemm_tile(std::is_same<T, bf16_t>::value ? SPEC_DTYPE_BF16 : SPEC_DTYPE_F16, a, epi, r == ROUTE_SPLIT, st);
     return;
   }
+  a.n_part = a.NT;
   if (launch_gemm_rowres(std::is_same<T, bf16_t>::value ? SPEC_DTYPE_BF16 : SPEC_DTYPE_F16, a, epi, st)) return;
   const int KS = a.KS;
-  // rows per pass: MT tiles of 16; strips per workgroup: NB.  Neither changes any result.
-  // A compute unit keeps a bounded number of cache-line requests in flight, and that is what a launch here is bound
-  // by; a workgroup asks for NB weight fragments (from HBM the first time a strip is read, from L2 for the other row
-  // passes) and MT activation fragments (L2) per 32-k step, so the unit with the most workgroups sets the time:
-  // ceil(workgroups / units) * (NB * weight cost + MT * activation cost), with a request that goes to HBM about three
-  // times as dear as one that hits L2 (measured).  Against doubling NB up to MT: QKV at d_model 4096 with 17..64
-  // rows 27..36 -> 23..31 us (three strips per workgroup: one workgroup per unit).  Small matrices (a draft model's)
-  // come out with two row tiles per workgroup and more row passes: their few strips then spread over more units.
-  const int n_cu = a.n_cu > 0 ? a.n_cu : 256;
-  const int mt_max = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 4;
-  int MT = mt_max, NB = 1;
-  if (mt_max > 1 && epi != EPI_LOGITS) {
-    static const int cand[] = {1, 2, 3, 4, 6, 8};
-    long best = -1;
-    for (int mt = mt_max; mt >= 1; mt >>= 1) {
-      const int passes = (a.M + mt * 16 - 1) / (mt * 16);
-      for (int nb : cand) {
-        if (mt == 1 && nb > 1) break;  // one row tile per workgroup is built with one strip only
-        const long wgs = (long)((a.NT + nb - 1) / nb) * passes;
-        const long per_cu = (wgs + n_cu - 1) / n_cu;
-        const long w_cost = (3000 + 1000 * (passes - 1)) / passes;  // per strip and step, averaged over the row passes
-        const long cost = per_cu * (nb * w_cost + mt * 1000);
-        if (best < 0 || cost < best) { best = cost; NB = nb; MT = mt; }
-      }
-    }
-  } else if (mt_max > 1) {
+  int MT, NB;
+  choose_stream(a, MT, NB);
+  if (epi == EPI_LOGITS && a.M > 16) {
     // the LM head, with its arg-max epilogue per strip, measured better with fewer strips per workgroup than that
     // estimate picks: as many as row tiles while 160 workgroups remain
+    MT = a.M <= 32 ? 2 : 4; NB = 1;
     const int passes = (a.M + MT * 16 - 1) / (MT * 16);
     while (NB < MT && (a.NT / (NB * 2)) * passes >= 160) NB *= 2;
     if (MT == 4 && NB == 4 && (a.NT / 8) * passes >= 160) NB = 8;
@@ -532,7 +551,7 @@ void launch_gemm_mfma(int dtype, const GemmArgs &a, int epi, hipStream_t st) {
 
 // Second stage of the fused arg-max: one block per row over the per-strip partials.
 // row_step > 0: output row m takes the partials of GEMM row m * row_step + row_step - 1 (the last row of its group).
-__global__ void k_argmax_partials(const float *__restrict__ pv, const int32_t *__restrict__ pi, int row_step, int NT, int V,
+__global__ void k_argmax_partials(const float *__restrict__ pv, const int32_t *__restrict__ pi, int row_step, int n_part, int V,
                                   int q, int out_stride, int32_t *__restrict__ out) {
   __shared__ float shv[4];
   __shared__ int shi[4];
@@ -540,7 +559,7 @@ __global__ void k_argmax_partials(const float *__restrict__ pv, const int32_t *_
   float bv = -INFINITY;
   int bi = 0x7fffffff;
   const size_t src = row_step > 0 ? (size_t)m * row_step + row_step - 1 : (size_t)m;
-  for (int t = threadIdx.x; t < NT; t += 256) argmax_combine(bv, bi, pv[src * NT + t], pi[src * NT + t]);
+  for (int t = threadIdx.x; t < n_part; t += 256) argmax_combine(bv, bi, pv[src * n_part + t], pi[src * n_part + t]);
   wave_argmax(bv, bi);
   if ((threadIdx.x & 63) == 0) { shv[threadIdx.x >> 6] = bv; shi[threadIdx.x >> 6] = bi; }
   __syncthreads();
@@ -550,10 +569,10 @@ __global__ void k_argmax_partials(const float *__restrict__ pv, const int32_t *_
     out[(size_t)(m / q) * out_stride + m % q] = bi;
   }
 }
-void launch_argmax_partials(const float *pv, const int32_t *pi, int M, int row_step, int NT, int V, int q, int out_stride,
+void launch_argmax_partials(const float *pv, const int32_t *pi, int M, int row_step, int n_part, int V, int q, int out_stride,
                             int32_t *out, hipStream_t st) {
   if (M <= 0) return;
-  hipLaunchKernelGGL(k_argmax_partials, dim3(M), dim3(256), 0, st, pv, pi, row_step, NT, V, q, out_stride, out);
+  hipLaunchKernelGGL(k_argmax_partials, dim3(M), dim3(256), 0, st, pv, pi, row_step, n_part, V, q, out_stride, out);
 }
 
 }  // namespace spec

@@ -8,9 +8,8 @@
 //   16-row tiles; workgroup tile = 2*NBW strips x 4*MTW row tiles.
 //   Per 32-k step the workgroup needs 2*NBW weight fragments and 4*MTW activation
 //   fragments of 1 KB each.  Weights and activations are both stored in fragment order in
-//   global memory, so a fragment is one 16-byte load per lane, issued three steps ahead, parked
-//   in registers and written to the LDS stage nobody reads; the waves then read their fragments
-//   back with one 16-byte LDS load per lane, conflict-free.
+//   global memory, so a fragment is one 16-byte load per lane that goes straight to LDS, several
+//   steps ahead, and the waves read it back with one conflict-free 16-byte LDS load per lane.
 //
 // Wide outputs (QKV, gate-up / fc1, LM head) walk all of k in one workgroup.  Narrow outputs (the
 // residual GEMMs, N = d_model) would leave most CUs idle that way: there each workgroup takes
@@ -19,26 +18,65 @@
 // Results are bit-identical to the streaming kernel: the same instruction, every k-slice a
 // chain of MFMAs from zero in ascending k, the slices added in order, the same epilogue code.
 #include "mfma_tiles.h"
+#include <algorithm>
+#include <cmath>
 
 namespace spec {
 
 #pragma clang fp contract(off)
 
-// Three LDS stages of fragments.  Global loads run three steps ahead of the LDS writes through
-// three register sets (global -> VGPR -> LDS; direct global->LDS loads into deeper rings of stages run at
-// the same rate on this part and were measured no faster for this loop: the operand stream itself, weights
-// from HBM mixed with activations from L2 through one CU's vector L1, is what bounds it).
-// The waves read their fragments of step k+1 into a second set of fragment registers before they
-// issue the MFMAs of step k, so the LDS pipe, the global loads and the matrix pipe of a SIMD work at
-// the same time, with one barrier per step.
-template <class T, int MTW, int NBW, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
+// One fragment of 1 KB from `base` (uniform) straight to LDS byte offset `lds` (uniform), lane l's 16 bytes at 16 l.
+// Written out because the compiler, which would have to assume that every LDS read depends on such a load, waits for
+// all of them in front of each read; here the waits are placed by hand (vmcnt before the barrier that publishes a slot).
+__device__ __forceinline__ void load_frag_to_lds(const unsigned char *base, unsigned lane_off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+}
+// the same for all lanes (mask -1, uniform) or for none (0); counted by vmcnt either way
+__device__ __forceinline__ void load_frag_to_lds_masked(const unsigned char *base, unsigned lane_off, unsigned lds, int mask) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(lds),
+               "v"(lane_off), "s"(base), "s"(mask) : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "wait count field");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Fragments of one 32-k step of a workgroup, and the ring of LDS slots that hold one step each: as deep as LDS allows,
+// since the loads in flight are what the small tiles, which stream weights for few rows, are bound by.
+template <int MTW, int NBW> struct TileShape {
+  static constexpr int NBG = 2 * NBW, MTG = 4 * MTW, FRAGS = NBG + MTG;
+  static constexpr int SLOT = FRAGS * 1024;
+  static constexpr int FIT = 160 / FRAGS;
+  static constexpr int RING = FIT > 16 ? 16 : FIT;
+  static constexpr size_t LDS = (size_t)RING * SLOT;
+  static_assert(RING >= 4, "a step being read, the next one, the one being freed, and one in flight");
+};
+
+__host__ __device__ constexpr bool tile_takes_row_sums(int MTW) { return MTW == 1; }
+
+// activation fragments of the next step whose reads go out behind the first nb strips of a step: none behind the last
+// strip, since the next step needs them all at once
+__host__ __device__ constexpr int x_reads_upto(int nb, int MTW, int NBW) { return nb >= NBW - 1 ? MTW : nb * MTW / (NBW - 1); }
+// pins the instruction order of a step: strip by strip MTW multiplies, then its weight fragment's read and its share of
+// the MTW activation fragments' reads
+template <int MTW, int NBW, int NB = 0>
+__device__ __forceinline__ void pin_step() {
+  if constexpr (NB < NBW) {
+    __builtin_amdgcn_sched_group_barrier(0x008, MTW, 0);                                             // MFMAs
+    __builtin_amdgcn_sched_group_barrier(0x100, 1 + x_reads_upto(NB + 1, MTW, NBW) - x_reads_upto(NB, MTW, NBW), 0);  // LDS reads
+    pin_step<MTW, NBW, NB + 1>();
+  }
+}
+
+// NORM: what is folded in front (0 nothing, 1 RMS norm, 2 LayerNorm).  T: the cache's type (EPI_QKV only).
+template <class T, int MTW, int NBW, int EPI, int NORM>
+__global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int NBG = 2 * NBW, MTG = 4 * MTW;
-  constexpr int FRAGS = NBG + MTG;  // 1 KB fragments per stage
-  constexpr int STAGE = FRAGS * 1024;
-  constexpr int LPW = (FRAGS + 7) / 8;  // fragments each wave fetches per step
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  using S = TileShape<MTW, NBW>;
+  constexpr int NBG = S::NBG, MTG = S::MTG, FRAGS = S::FRAGS, SLOT = S::SLOT, RING = S::RING;
+  constexpr int LPW = (FRAGS + 7) / 8;  // fragments each wave fetches per step (the last one: only some waves)
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wn = w & 1, wm = w >> 1;
   const int c = lane & 15, g = lane >> 4;
   constexpr bool PARTIAL = EPI == EPI_PARTIAL;
@@ -51,17 +89,20 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
     slice_id = id & 7;
     pass = rest % a.passes;
     G = rest / a.passes;
-  } else {  // all passes of a strip group on one XCD (see the streaming kernel)
-    const int id = blockIdx.x;
+  } else {
+    // workgroups are dealt round-robin to the 8 XCDs: all row passes of a strip group on one XCD, in blocks of up to 8
+    // passes, so that the 32 workgroups an XCD runs at a time are 8 passes x 4 groups and share both operands in its L2
+    const int id = blockIdx.x, gpx = (a.groups + 7) >> 3;
     int rest = id >> 3;
-    pass = rest % a.passes;
-    rest /= a.passes;
-    if (PARTIAL) {  // one k-slice per workgroup, the strip groups of a slice neighbours in launch order
-      const int gpx = (a.groups + 7) >> 3;
-      slice_id = rest / gpx;
-      rest %= gpx;
+    if (PARTIAL) {  // one k-slice per workgroup, slice by slice
+      slice_id = rest / (gpx * a.passes);
+      rest %= gpx * a.passes;
     }
-    G = rest * 8 + (id & 7);
+    const int blk = rest / (gpx * 8);
+    rest -= blk * gpx * 8;
+    const int in_blk = min(8, a.passes - blk * 8);
+    pass = blk * 8 + rest % in_blk;
+    G = (rest / in_blk) * 8 + (id & 7);
   }
   if (G >= a.groups) return;
   const int kt_per = a.KT / a.KS;
@@ -71,25 +112,25 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
   const int mtile0 = pass * MTG;
   const int m_tiles = (a.M + 15) >> 4;
 
-  // fragment f of a stage: f < NBG weight strip nt0 + f; else activation tile f - NBG.
-  // Wave w fetches fragments w, w + 8, ...; every wave issues exactly LPW loads and LDS writes per step (a
-  // wave with nothing left repeats the last fragment: the same bytes to the same place) so that the step is
-  // branch-free and one wait count fits all waves.
-  const u32x4_v *src[LPW];
-  int dst[LPW];
+  // Fragment f of a step: f < NBG weight strip nt0 + f; else activation tile f - NBG.  Wave w fetches f = w, w + 8, ...
+  const unsigned char *src[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    const int f = w + 8 * i;
-    const int fc = min(f, FRAGS - 1);
-    dst[i] = fc * 1024 + lane * 16;
-    if (fc < NBG) {
-      const int nt = min(nt0 + fc, a.NT - 1);
-      src[i] = (const u32x4_v *)a.W + (size_t)nt * a.KT * 64 + lane;
-    } else {
-      const int tile = min(mtile0 + fc - NBG, m_tiles - 1);
-      src[i] = (const u32x4_v *)a.X + (size_t)tile * a.KT * 64 + lane;
-    }
+    const int f = min(w + 8 * i, FRAGS - 1);
+    const size_t row = f < NBG ? (size_t)min(nt0 + f, a.NT - 1) : (size_t)min(mtile0 + f - NBG, m_tiles - 1);
+    src[i] = (const unsigned char *)(f < NBG ? a.W : a.X) + (row * a.KT + kt_lo) * 1024;
   }
+  const unsigned lane_off = lane * 16;
+  // not every wave has an LPW-th fragment: those without issue its load with no lane, so that all count alike
+  const int last_mask = __builtin_amdgcn_readfirstlane(w < FRAGS - 8 * (LPW - 1) ? -1 : 0);
+  auto fetch1 = [&](int i, size_t k, unsigned lds) {
+    if (i < LPW - 1 || FRAGS % 8 == 0) load_frag_to_lds(src[i] + k, lane_off, lds + i * 8 * 1024);
+    else load_frag_to_lds_masked(src[i] + k, lane_off, lds + i * 8 * 1024, last_mask);
+  };
+  // step kt of this wave's fragments into ring position `at`; beyond the end the last step is fetched again: nobody
+  // reads it, and no wait count depends on where the end lies
+  auto fetch_k = [&](int kt) { return (size_t)min(kt, KTL - 1) * 1024; };
+  auto fetch_lds = [&](int at) { return (unsigned)(at * SLOT + w * 1024); };
 
   f32x4_v cur[NBW][MTW], tot[NBW][MTW];
 #pragma unroll
@@ -100,170 +141,133 @@ __global__ __launch_bounds__(512) void k_gemm_tile(GemmArgs a) {
       tot[nb][mt] = (f32x4_v){0.f, 0.f, 0.f, 0.f};
     }
 
-  // Folded norm.  With one row tile per wave the sum of squares comes from the operand fragments inside the
-  // loop (frag_ssq: per lane, one chain per k-slice, slices added in order), where it costs nothing; with larger
-  // wave tiles the loop has no issue slots to spare (measured: +10 %) and k_row_inv_x has left 1 / rms per row.
-  constexpr bool FOLD_EPI = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_RELU || EPI == EPI_LOGITS;
-  constexpr bool INLOOP = FOLD_EPI && MTW == 1;
-  const bool inloop = INLOOP && a.fold_x;
-  const bool lnx = a.fold_x && a.wsum;  // the folded norm is a LayerNorm: the plain sums as well
-  float ssq_cur = 0.f, ssq_tot = 0.f, sum_cur = 0.f, sum_tot = 0.f;
+  // Folded norm.  With one row tile per wave the row sums of squares (and the plain sums of a LayerNorm) come from the
+  // operand fragments inside the loop, beside the multiplies (frag_ssq: per lane, one chain per k-slice, slices added in
+  // order).  With more they hold up the multiplies of a step, which all waves start together: 7 to 18 us per launch at
+  // 80 to 256 rows (whichever wave tile), against the 5 us of k_row_inv_x, which then has run before.
+  constexpr bool INLOOP = NORM != 0 && tile_takes_row_sums(MTW);
+  float ssq_cur[MTW], ssq_tot[MTW], sum_cur[MTW], sum_tot[MTW];
+#pragma unroll
+  for (int mt = 0; mt < MTW; ++mt) ssq_cur[mt] = ssq_tot[mt] = sum_cur[mt] = sum_tot[mt] = 0.f;
 
-  u32x4_v r0[LPW], r1[LPW], r2[LPW];  // three steps on their way from global memory
-  auto fetch = [&](u32x4_v (&r)[LPW], int kt) {
+  // Fragments in registers.  A weight fragment takes the next step's behind its last multiply; the activation
+  // fragments, which every strip multiplies, alternate between two sets.  The reads then spread evenly over the
+  // multiplies of a step (the CU's LDS queue is short: read in a burst at the end of the step, with all waves in
+  // phase behind the barrier, they cost as much time as the multiplies).
+  u32x4_v wf[NBW], xa[MTW], xb[MTW];
+  const unsigned char *w_base = smem + lane * 16 + wn * NBW * 1024, *x_base = smem + lane * 16 + (NBG + wm * MTW) * 1024;
+  auto rd = [](const unsigned char *p) { return *(const u32x4_v *)p; };
+
+  auto slice_end = [&]() {  // the slice's chains join the running totals, in slice order (a chain that starts from +0 never
+#pragma unroll               // ends at -0: adding the first one to +0 keeps its bits)
+    for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) r[i] = src[i][(size_t)(kt_lo + min(kt, KTL - 1)) * 64];
+      for (int mt = 0; mt < MTW; ++mt) {
+        tot[nb][mt][0] += cur[nb][mt][0]; tot[nb][mt][1] += cur[nb][mt][1];
+        tot[nb][mt][2] += cur[nb][mt][2]; tot[nb][mt][3] += cur[nb][mt][3];
+      }
+    if (INLOOP) {
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt) { ssq_tot[mt] += ssq_cur[mt]; sum_tot[mt] += sum_cur[mt]; }
+    }
   };
-  auto stash = [&](const u32x4_v (&r)[LPW], int stage) {
+  // One step: the multiplies of the fragments at hand (x), strip by strip, and the reads of the next step's (xn) from
+  // ring position `at`; the fetches of a later step (offset fk, to flds) go out between them.
+  // `first`: the first step of a k-slice, whose chains start from zero.
+  auto step = [&](auto first, const u32x4_v (&x)[MTW], u32x4_v (&xn)[MTW], int at, size_t fk, unsigned flds) {
+    constexpr bool FIRST = decltype(first)::value;
+    const unsigned char *wp = w_base + at * SLOT, *xp = x_base + at * SLOT;
+    if (INLOOP) {
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) *(u32x4_v *)(smem + stage * STAGE + dst[i]) = r[i];
+      for (int mt = 0; mt < MTW; ++mt) {
+        ssq_cur[mt] = frag_ssq(x[mt], FIRST ? 0.f : ssq_cur[mt]);
+        if (NORM == 2) sum_cur[mt] = frag_sum(x[mt], FIRST ? 0.f : sum_cur[mt]);
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt) {
+        if (FIRST) cur[nb][mt] = Mfma16::run(wf[nb], x[mt], (f32x4_v){0.f, 0.f, 0.f, 0.f});
+        else cur[nb][mt] = Mfma16::run(wf[nb], x[mt], cur[nb][mt]);
+      }
+      wf[nb] = rd(wp + nb * 1024);
+#pragma unroll
+      for (int mt = x_reads_upto(nb, MTW, NBW); mt < x_reads_upto(nb + 1, MTW, NBW); ++mt) xn[mt] = rd(xp + mt * 1024);
+#pragma unroll
+      for (int i = nb * LPW / NBW; i < (nb + 1) * LPW / NBW; ++i) fetch1(i, fk, flds);
+    }
+    pin_step<MTW, NBW>();
   };
-  struct Frags { u32x4_v wf[NBW], xf[MTW]; };
-  auto read_frags = [&](Frags &f, int stage) {
-    const unsigned char *sb = smem + stage * STAGE + lane * 16;
-#pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) f.wf[nb] = *(const u32x4_v *)(sb + (wn * NBW + nb) * 1024);
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) f.xf[mt] = *(const u32x4_v *)(sb + (NBG + wm * MTW + mt) * 1024);
-  };
-  // A bare barrier, not __syncthreads(): the fence of the latter would wait for the global loads in
-  // flight.  Ordered by hand: before it this wave's LDS writes are done; the NBW + MTW fragment reads
-  // issued after them may still be on their way (LDS operations of a wave complete in order).
-  auto step_end = [&]() {
-    static_assert(NBW + MTW <= 15, "wait count field");
-    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(NBW + MTW) : "memory");
+  // A bare barrier, not __syncthreads(): the fence of the latter would wait for the loads in flight.
+  auto publish = [&](auto left) {  // this wave's loads are done but for those of the last `left` steps; then meet
+    constexpr int L = decltype(left)::value;
+    wait_loads<L * LPW>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
 
-  int in_slice = 0, slice = 0;
-  auto mfmas = [&](const Frags &f) {
+  // Step kt lives at ring position kt % RING.  At the top of step kt the registers hold (or await) its fragments, and
+  // the barrier there says that step kt + 1 is in LDS.  Behind it every wave is done with step kt - 1 (its multiplies
+  // are under way), whose position takes step kt + RING - 1.
+  int at = 0, kt = 0;
+  auto turn = [&](auto first, const u32x4_v (&x)[MTW], u32x4_v (&xn)[MTW]) {
+    publish(std::integral_constant<int, RING - 3>{});
+    const unsigned flds = fetch_lds(at == 0 ? RING - 1 : at - 1);
+    at = at + 1 == RING ? 0 : at + 1;
+    step(first, x, xn, at, fetch_k(kt + RING - 1), flds);
+    ++kt;
+  };
+#pragma unroll
+  for (int s = 0; s < RING - 1; ++s)
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) fetch1(i, fetch_k(s), fetch_lds(s));
+  publish(std::integral_constant<int, RING - 2>{});
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): with no scalar load left under way the waits on LDS reads in the loop are exact counts
+#pragma unroll
+  for (int mt = 0; mt < MTW; ++mt) xa[mt] = rd(x_base + mt * 1024);
+#pragma unroll
+  for (int nb = 0; nb < NBW; ++nb) wf[nb] = rd(w_base + nb * 1024);
+  while (kt < KTL) {  // a k-slice per round; the steps in pairs, since the activation fragments alternate
+    turn(std::true_type{}, xa, xb);
+    int left = kt_per - 1;
+    for (; left > 1; left -= 2) {
+      turn(std::false_type{}, xb, xa);
+      turn(std::false_type{}, xa, xb);
+    }
+    if (left) {
+      turn(std::false_type{}, xb, xa);
+    } else {
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt) xa[mt] = xb[mt];
+    }
+    slice_end();
+  }
+  wait_loads<0>();  // drain the over-fetched tail before the epilogue
+  float rv[MTW], mv[MTW];  // 1 / rms (LayerNorm: 1 / std and mean) of this lane's rows
+#pragma unroll
+  for (int mt = 0; mt < MTW; ++mt) {
+    rv[mt] = 1.0f; mv[mt] = 0.f;
+    if (INLOOP) {
+      if (NORM == 2) row_ln_from_lane(ssq_tot[mt], sum_tot[mt], a.ss_d, a.ss_eps, rv[mt], mv[mt]);
+      else rv[mt] = row_inv_from_lane_ssq(ssq_tot[mt], a.ss_d, a.ss_eps);
+    } else if (NORM != 0) {
+      const int m = min((mtile0 + wm * MTW + mt) * 16 + c, a.M - 1);
+      rv[mt] = a.rinv_ws[m];
+      if (a.wsum) mv[mt] = a.mean_ws[m];
+    }
+  }
+  if (PARTIAL) {  // the slice's chain as it is; k_partial_reduce adds the slices in order
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
-      for (int mt = 0; mt < MTW; ++mt) cur[nb][mt] = Mfma16::run(f.wf[nb], f.xf[mt], cur[nb][mt]);
-    if (inloop) {
-      ssq_cur = frag_ssq(f.xf[0], ssq_cur);
-      if (lnx) sum_cur = frag_sum(f.xf[0], sum_cur);
-    }
-  };
-  auto slice_end = [&]() {
-    if (++in_slice == kt_per) {  // slice finished: add it to the running total, in slice order
-#pragma unroll
-      for (int nb = 0; nb < NBW; ++nb)
-#pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-          if (slice == 0) tot[nb][mt] = cur[nb][mt];
-          else {
-            tot[nb][mt][0] += cur[nb][mt][0]; tot[nb][mt][1] += cur[nb][mt][1];
-            tot[nb][mt][2] += cur[nb][mt][2]; tot[nb][mt][3] += cur[nb][mt][3];
-          }
-          cur[nb][mt] = (f32x4_v){0.f, 0.f, 0.f, 0.f};
-        }
-      if (inloop) {
-        ssq_tot = slice == 0 ? ssq_cur : ssq_tot + ssq_cur;
-        ssq_cur = 0.f;
-        sum_tot = slice == 0 ? sum_cur : sum_tot + sum_cur;
-        sum_cur = 0.f;
+      for (int mt = 0; mt < MTW; ++mt) {
+        const int nt = nt0 + wn * NBW + nb, m = (mtile0 + wm * MTW + mt) * 16 + c, n = nt * 16 + 4 * g;
+        if (nt < a.NT && m < a.M) *(f32x4_v *)(a.part + ((size_t)slice_id * a.part_rows + m) * a.N + n) = tot[nb][mt];
       }
-      in_slice = 0;
-      ++slice;
-    }
-  };
-
-  // prologue: steps 0 and 1 into LDS stages 0 and 1, steps 2, 3, 4 into the register sets, fragments of step 0
-  Frags f0, f1;
-  fetch(r0, 0);
-  fetch(r1, 1);
-  fetch(r2, 2);
-  stash(r0, 0);
-  fetch(r0, 3);
-  stash(r1, 1);
-  fetch(r1, 4);
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  read_frags(f0, 0);
-  // Step j lives in LDS stage j % 3.  Invariant at the top of step kt: stages kt % 3 and (kt+1) % 3 hold
-  // steps kt and kt+1; every wave's reads of stage (kt+2) % 3 (step kt-1) have returned (their MFMAs were
-  // issued before the last barrier); the fragment set of parity kt&1 holds step kt or is on its way; the
-  // register set of the step holds step kt+2 (possibly still in flight).  Fragment sets alternate, register
-  // sets and stages rotate with period three: the loop is unrolled by six so that each has a fixed role
-  // per copy and the compiler's wait-count bookkeeping stays exact.
-  // The instruction order inside a step is pinned: the LDS queue of the CU is short, and a wave that
-  // issues its LDS traffic in one burst waits for queue slots before it reaches its MFMAs.  Spread between
-  // the MFMAs (writes first, then reads: the wait before the barrier counts on that order) the LDS and
-  // global-memory instructions find their slots while the matrix pipe works.
-  auto interleave = [&]() {
-    constexpr int NM = NBW * MTW, NO = 2 * LPW + NBW + MTW;  // MFMAs; other instructions: writes, loads, reads
-#pragma unroll
-    for (int i = 0, o = 0; i < NM; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-      // others due after MFMA i: spread evenly, in program order (writes, global loads, reads)
-      const int due = ((i + 1) * NO) / NM;
-      for (; o < due; ++o) {
-        if (o < LPW) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);            // LDS write
-        else if (o < 2 * LPW) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
-        else __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                    // LDS read
-      }
-    }
-  };
-#define SPEC_TILE_STEP(fcur, fnext, rset, kt_, i_)                               \
-  {                                                                              \
-    stash(rset, ((i_) + 2) % 3);                                                 \
-    fetch(rset, (kt_) + 5);                                                      \
-    read_frags(fnext, ((i_) + 1) % 3);                                           \
-    mfmas(fcur);                                                                 \
-    interleave();                                                                \
-    slice_end();                                                                 \
-    step_end();                                                                  \
+  } else {
+    wave_epilogue<T, PARTIAL ? EPI_RESIDUAL : EPI, MTW, NBW>(a, tot, nt0 + wn * NBW, mtile0 + wm * MTW, lane, rv, mv);
   }
-  int kt = 0;
-  for (; kt + 5 < KTL; kt += 6) {
-    SPEC_TILE_STEP(f0, f1, r2, kt, 0)
-    SPEC_TILE_STEP(f1, f0, r0, kt + 1, 1)
-    SPEC_TILE_STEP(f0, f1, r1, kt + 2, 2)
-    SPEC_TILE_STEP(f1, f0, r2, kt + 3, 3)
-    SPEC_TILE_STEP(f0, f1, r0, kt + 4, 4)
-    SPEC_TILE_STEP(f1, f0, r1, kt + 5, 5)
-  }
-  if (kt < KTL) SPEC_TILE_STEP(f0, f1, r2, kt, 0)
-  if (kt + 1 < KTL) SPEC_TILE_STEP(f1, f0, r0, kt + 1, 1)
-  if (kt + 2 < KTL) SPEC_TILE_STEP(f0, f1, r1, kt + 2, 2)
-  if (kt + 3 < KTL) SPEC_TILE_STEP(f1, f0, r2, kt + 3, 3)
-  if (kt + 4 < KTL) SPEC_TILE_STEP(f0, f1, r0, kt + 4, 4)
-#undef SPEC_TILE_STEP
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // drain the over-fetched tail before the epilogue
-  // 1 / rms of this lane's rows, fetched only now: the loop has no register to spare for them
-  float rv[MTW], mv[MTW];
-#pragma unroll
-  for (int mt = 0; mt < MTW; ++mt) {
-    const int m = (mtile0 + wm * MTW + mt) * 16 + c;
-    rv[mt] = 1.0f; mv[mt] = 0.f;
-    if (FOLD_EPI && !INLOOP && a.fold_x && m < a.M) {
-      rv[mt] = a.rinv_ws[m];
-      if (lnx) mv[mt] = a.mean_ws[m];
-    }
-  }
-  if (inloop) {
-    if (lnx) row_ln_from_lane(ssq_tot, sum_tot, a.ss_d, a.ss_eps, rv[0], mv[0]);
-    else rv[0] = row_inv_from_lane_ssq(ssq_tot, a.ss_d, a.ss_eps);
-  }
-
-#pragma unroll
-  for (int nb = 0; nb < NBW; ++nb)
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-      const int nt = nt0 + wn * NBW + nb, m = (mtile0 + wm * MTW + mt) * 16 + c;
-      if (PARTIAL) {  // the slice's chain as it is; k_partial_reduce adds the slices in order
-        const int n = nt * 16 + 4 * g;
-        if (nt < a.NT && m < a.M && n < a.N)
-          *(f32x4_v *)(a.part + ((size_t)slice_id * a.part_rows + m) * a.N + n) = tot[nb][mt];
-      } else {
-        tile_epilogue<T, EPI == EPI_PARTIAL ? EPI_RESIDUAL : EPI>(a, tot[nb][mt], nt, m, g,
-                                                                 rv[mt], mv[mt]);
-      }
-    }
 }
 
 // ((P_0 + P_1) + ...) + P_{KS-1} for four consecutive outputs; with eight slices all loads go out before the first add
@@ -287,7 +291,6 @@ __device__ __forceinline__ f32x4_v sum_slices(const float *__restrict__ p, size_
 
 // Second half of a split residual GEMM: out = ((P_0 + P_1) + ...) + P_{KS-1}, then the same epilogue as
 // everywhere (scale, bias, h += out).  One thread per four consecutive outputs of a row.
-template <class T>
 __global__ __launch_bounds__(256) void k_partial_reduce(GemmArgs a) {
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   const int n4 = a.N >> 2;
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(256) void k_partial_reduce(GemmArgs a) {
   const int m = (int)(idx / n4), n = (int)(idx % n4) * 4;
   const float *p = a.part + (size_t)m * a.N + n;
   const size_t stride = (size_t)a.part_rows * a.N;
-  tile_epilogue<T, EPI_RESIDUAL>(a, sum_slices(p, stride, a.KS), n >> 4, m, (n & 15) >> 2);
+  tile_epilogue<f16_t, EPI_RESIDUAL>(a, sum_slices(p, stride, a.KS), n >> 4, m, (n & 15) >> 2);
 }
 
 
@@ -307,7 +310,6 @@ __global__ __launch_bounds__(256) void k_partial_reduce(GemmArgs a) {
 // which then need not run.  a.ssq_ks = the k-slices of the next GEMM (at most 8).
 // A LayerNorm folded into the next GEMM (a.mean_ws set) wants the plain sums too, taken the same way (frag_sum):
 // a.mean_ws[m] = the row's mean and a.rinv_ws[m] = 1 / std, as row_ln_from_lane computes them.
-template <class T>
 __global__ __launch_bounds__(1024) void k_partial_reduce_rows(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char reduce_smem[];
   op_t *xs = (op_t *)reduce_smem;  // [N] fp16: the updated row as the next GEMM will read it
@@ -406,68 +408,101 @@ __global__ __launch_bounds__(512) void k_row_inv_x(const void *__restrict__ X, i
   }
 }
 
-template <class T, int MTW, int NBW, int EPI>
+// blocks < 0: preparation pass (the kernel may use more than the default 64 KB of LDS)
+template <class T, int MTW, int NBW, int EPI, int NORM>
 static void launch_one(const GemmArgs &a, int blocks, hipStream_t st) {
-  constexpr size_t lds = 3 * (size_t)(2 * NBW + 4 * MTW) * 1024;
-  if (blocks < 0) {  // preparation pass: the kernel may use more than the default 64 KB of LDS
-    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    return;
-  }
-  hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI>), dim3(blocks), dim3(512), lds, st, a);
+  constexpr size_t lds = TileShape<MTW, NBW>::LDS;
+  if (blocks < 0)
+    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  else
+    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM>), dim3(blocks), dim3(512), lds, st, a);
 }
 
-template <class T, int MTW, int NBW>
-static void launch_epi_tile(const GemmArgs &a, int epi, int blocks, hipStream_t st) {
+template <class T, int MTW, int NBW, int EPI>
+static void launch_norm(const GemmArgs &a, int blocks, hipStream_t st) {
+  if (tile_takes_row_sums(MTW) && a.wsum) launch_one<T, MTW, NBW, EPI, tile_takes_row_sums(MTW) ? 2 : 1>(a, blocks, st);
+  else launch_one<T, MTW, NBW, EPI, 1>(a, blocks, st);
+}
+
+template <int MTW, int NBW>
+static void launch_epi_tile(int dtype, const GemmArgs &a, int epi, int blocks, hipStream_t st) {
   switch (epi) {
-    case EPI_QKV: launch_one<T, MTW, NBW, EPI_QKV>(a, blocks, st); break;
-    case EPI_SWIGLU: launch_one<T, MTW, NBW, EPI_SWIGLU>(a, blocks, st); break;
-    case EPI_RELU: launch_one<T, MTW, NBW, EPI_RELU>(a, blocks, st); break;
-    case EPI_PARTIAL: launch_one<T, MTW, NBW, EPI_PARTIAL>(a, blocks, st); break;
-    default: launch_one<T, MTW, NBW, EPI_LOGITS>(a, blocks, st); break;
+    case EPI_QKV:
+      if (dtype == SPEC_DTYPE_BF16) launch_norm<bf16_t, MTW, NBW, EPI_QKV>(a, blocks, st);
+      else launch_norm<f16_t, MTW, NBW, EPI_QKV>(a, blocks, st);
+      break;
+    case EPI_SWIGLU: launch_norm<f16_t, MTW, NBW, EPI_SWIGLU>(a, blocks, st); break;
+    case EPI_RELU: launch_norm<f16_t, MTW, NBW, EPI_RELU>(a, blocks, st); break;
+    case EPI_LOGITS: launch_norm<f16_t, MTW, NBW, EPI_LOGITS>(a, blocks, st); break;
+    case EPI_PARTIAL: launch_one<f16_t, MTW, NBW, EPI_PARTIAL, 0>(a, blocks, st); break;
+    default: launch_one<f16_t, MTW, NBW, EPI_RESIDUAL, 0>(a, blocks, st); break;
   }
 }
 
-template <class T, int MTW>
-static void launch_nb_tile(const GemmArgs &a, int NBW, int epi, int blocks, hipStream_t st) {
-  if (NBW == 2) launch_epi_tile<T, MTW, 2>(a, epi, blocks, st);
-  else if (NBW == 3) launch_epi_tile<T, MTW, 3>(a, epi, blocks, st);
-  else launch_epi_tile<T, MTW, 4>(a, epi, blocks, st);
+template <int MTW>
+static void launch_nb_tile(int dtype, const GemmArgs &a, int NBW, int epi, int blocks, hipStream_t st) {
+  if (NBW == 2) launch_epi_tile<MTW, 2>(dtype, a, epi, blocks, st);
+  else if (NBW == 3) launch_epi_tile<MTW, 3>(dtype, a, epi, blocks, st);
+  else if (NBW == 4) launch_epi_tile<MTW, 4>(dtype, a, epi, blocks, st);
+  else launch_epi_tile<MTW, 6>(dtype, a, epi, blocks, st);
 }
 
-// Wave tile (MTW 16-row tiles x NBW strips) for M rows and NT strips.  One workgroup occupies a CU, so
-// a launch takes ceil(workgroups / CUs) rounds of KT steps.  Measured on MI355X a step costs about
-// 150 + 45 * MTW * NBW + 40 * (MTW + NBW) clocks (two waves per SIMD at 16 clocks per MFMA are 32 of the
-// 45; the last term is the LDS traffic).
-static void choose_tile(int M, int NT, int n_cu, int steps, int wg_mult, int &MTW, int &NBW) {
-  long best = -1;
-  for (int mt = 1; mt <= 4; ++mt)
-    for (int nb = 2; nb <= 4; ++nb) {
-      const int passes = (M + 64 * mt - 1) / (64 * mt);
-      const int wgs = passes * ((NT + 2 * nb - 1) / (2 * nb)) * wg_mult;
-      const int rounds = (wgs + n_cu - 1) / n_cu;
-      // per round: the steps, plus filling the pipeline and the epilogue (about 2 us)
-      const long cost = (long)rounds * ((long)steps * (150 + 45 * mt * nb + 40 * (mt + nb)) + 5000);
-      if (best < 0 || cost < best || (cost == best && mt * nb > MTW * NBW)) { best = cost; MTW = mt; NBW = nb; }
+static void launch_shape(int dtype, const GemmArgs &a, int MTW, int NBW, int epi, int blocks, hipStream_t st) {
+  if (MTW == 1) launch_nb_tile<1>(dtype, a, NBW, epi, blocks, st);
+  else if (MTW == 2) launch_nb_tile<2>(dtype, a, NBW, epi, blocks, st);
+  else if (MTW == 3) launch_nb_tile<3>(dtype, a, NBW, epi, blocks, st);
+  else launch_nb_tile<4>(dtype, a, NBW, epi, blocks, st);
+}
+
+// Wave tile (MTW 16-row tiles x NBW strips) for a launch, and how long it takes, in us.  A workgroup occupies a CU, so
+// a launch runs in rounds of n_cu workgroups.  Fitted to a sweep of all 16 shapes over 36 .. 8128 rows, seven weight
+// matrices of the 7B, 13B and 33B widths, whole and split by k-slice (1300 launches; rms error 11 %): per step a
+// constant for the meeting of the waves and the multiplies (us per tile) beside the fetches (us per KB), which overlap
+// in part; per round the pipeline's filling and the epilogue; and no launch is faster than its weights stream from HBM.
+// Over the sweep's 117 (matrix, row count) cells the shape it picks is 0.6 % slower than the best one, 11 % at worst.
+constexpr int TILE_MT[4] = {1, 2, 3, 4}, TILE_NB[4] = {2, 3, 4, 6};
+static double tile_us(int mt, int nb, int M, int NT, int n_cu, int steps, int wg_mult, double w_bytes) {
+  const int passes = (M + 64 * mt - 1) / (64 * mt);
+  const int wgs = passes * ((NT + 2 * nb - 1) / (2 * nb)) * wg_mult;
+  const int rounds = (wgs + n_cu - 1) / n_cu;
+  const double mul = 0.0113 * mt * nb, load = 0.0087 * (2 * nb + 4 * mt);
+  const double raw = rounds * (1.35 + 0.396 * mt * nb + steps * (0.066 + std::sqrt(mul * mul + load * load)));
+  return 3.0 + std::max(raw, w_bytes / 5.3e6) + 0.1 * raw;
+}
+static double choose_tile(int M, int NT, int n_cu, int steps, int wg_mult, double w_bytes, int &MTW, int &NBW) {
+  double best = 0.0;
+  for (int mt : TILE_MT)
+    for (int nb : TILE_NB) {
+      const double us = tile_us(mt, nb, M, NT, n_cu, steps, wg_mult, w_bytes);
+      if (best == 0.0 || us < best) { best = us; MTW = mt; NBW = nb; }
     }
+  return best;
 }
 
-// wave tile of the launch for these arguments (epi as given by the caller, EPI_RESIDUAL = split by k-slice)
-static void tile_for(const GemmArgs &a, int epi, int &MTW, int &NBW) {
+// Wave tile of the launch for these arguments; returns its estimate in us.  split: each workgroup takes one k-slice of
+// its tile and a second kernel adds the slices (4.3 us, and 8 us per million outputs for the slices' way through memory).
+static double tile_for(const GemmArgs &a, bool split, int &MTW, int &NBW) {
+  const int n_cu = a.n_cu > 0 ? a.n_cu : 256, steps = split ? a.KT / a.KS : a.KT, wg_mult = split ? a.KS : 1;
+  const double w_bytes = 1024.0 * a.NT * a.KT, second = split ? 4.3 + 7.9e-6 * a.M * a.N : 0.0;
   const int f_mt = a.tune & TUNE_TILE_MTW_MASK, f_nb = (a.tune >> TUNE_TILE_NBW_SHIFT) & 0xf;
-  if (f_mt >= 1 && f_mt <= 4 && f_nb >= 2 && f_nb <= 4) { MTW = f_mt; NBW = f_nb; return; }  // test / tuning aid
-  const bool split = epi == EPI_RESIDUAL;
+  if (f_mt >= 1 && f_mt <= 4 && f_nb >= 2 && f_nb <= 6 && f_nb != 5) {  // test / tuning aid
+    MTW = f_mt; NBW = f_nb;
+    return second + tile_us(MTW, NBW, a.M, a.NT, n_cu, steps, wg_mult, w_bytes);
+  }
   MTW = 2; NBW = 2;
-  choose_tile(a.M, a.NT, a.n_cu > 0 ? a.n_cu : 256, split ? a.KT / a.KS : a.KT, split ? a.KS : 1, MTW, NBW);
+  return second + choose_tile(a.M, a.NT, n_cu, steps, wg_mult, w_bytes, MTW, NBW);
+}
+double gemm_tile_us(const GemmArgs &a, bool split) {
+  int MTW, NBW;
+  return tile_for(a, split, MTW, NBW);
 }
 
-// With more than one row tile per wave the kernel reads 1 / rms of its rows from a.rinv_ws: the caller runs
-// launch_row_inv_x first when this says so.
+// With more than one row tile per wave the kernel reads 1 / rms of its rows from a.rinv_ws: the caller runs launch_row_inv_x first when this says so.
 bool gemm_tile_wants_row_inv(const GemmArgs &a, int epi) {
   if (!a.fold_x || (epi != EPI_QKV && epi != EPI_SWIGLU && epi != EPI_RELU && epi != EPI_LOGITS)) return false;
   int MTW, NBW;
-  tile_for(a, epi, MTW, NBW);
-  return MTW > 1;
+  tile_for(a, false, MTW, NBW);
+  return !tile_takes_row_sums(MTW);
 }
 void launch_row_inv_x(const GemmArgs &a, hipStream_t st) {
   if (a.M <= 0) return;
@@ -475,43 +510,42 @@ void launch_row_inv_x(const GemmArgs &a, hipStream_t st) {
                      a.wsum ? a.mean_ws : nullptr);
 }
 
-template <class T>
-static void launch_tile_t(GemmArgs a, int epi, hipStream_t st) {
+void gemm_tile_prepare() {
+  GemmArgs a{};
+  const float one = 1.f;
+  for (int ln = 0; ln < 2; ++ln) {
+    a.wsum = ln ? &one : nullptr;  // never read: selects the kernels with a LayerNorm
+    for (int epi : {(int)EPI_RESIDUAL, (int)EPI_QKV, (int)EPI_SWIGLU, (int)EPI_RELU, (int)EPI_PARTIAL, (int)EPI_LOGITS})
+      for (int mt : TILE_MT)
+        for (int nb : TILE_NB)
+          for (int dtype : {(int)SPEC_DTYPE_BF16, (int)SPEC_DTYPE_F16}) launch_shape(dtype, a, mt, nb, epi, -1, nullptr);
+  }
+}
+
+// EPI_LOGITS: a wave leaves one arg-max partial per row for its NBW strips
+int gemm_tile_head_partials(const GemmArgs &a) {
   int MTW, NBW;
-  tile_for(a, epi, MTW, NBW);
-  const bool split = epi == EPI_RESIDUAL;  // narrow outputs: one k-slice per workgroup, slices added by a second kernel
+  tile_for(a, false, MTW, NBW);
+  return 2 * ((a.NT + 2 * NBW - 1) / (2 * NBW));
+}
+
+void launch_gemm_tile(int dtype, GemmArgs a, int epi, bool split, hipStream_t st) {
+  int MTW, NBW;
+  tile_for(a, split, MTW, NBW);
+  a.n_part = 2 * ((a.NT + 2 * NBW - 1) / (2 * NBW));
   if (split) epi = EPI_PARTIAL;
   a.passes = (a.M + 64 * MTW - 1) / (64 * MTW);
   a.groups = (a.NT + 2 * NBW - 1) / (2 * NBW);
   const int blocks = split ? (a.KS == 8 ? a.groups * a.passes * 8 : ((a.groups + 7) / 8) * 8 * a.passes * a.KS)
                            : a.passes == 1 ? a.groups : ((a.groups + 7) / 8) * 8 * a.passes;
-  if (MTW == 1) launch_nb_tile<T, 1>(a, NBW, epi, blocks, st);
-  else if (MTW == 2) launch_nb_tile<T, 2>(a, NBW, epi, blocks, st);
-  else if (MTW == 3) launch_nb_tile<T, 3>(a, NBW, epi, blocks, st);
-  else launch_nb_tile<T, 4>(a, NBW, epi, blocks, st);
-  const int rr_threads = std::min(1024, ((a.N >> 2) + 63) / 64 * 64);  // one float4 of outputs per thread where that fits
+  launch_shape(dtype, a, MTW, NBW, epi, blocks, st);
   if (split && a.ssq_ks > 0 && a.x_out) {
-    hipLaunchKernelGGL(k_partial_reduce_rows<T>, dim3(a.M), dim3(rr_threads), (size_t)a.N * sizeof(op_t), st, a);
+    const int rr_threads = std::min(1024, ((a.N >> 2) + 63) / 64 * 64);  // one float4 of outputs per thread where that fits
+    hipLaunchKernelGGL(k_partial_reduce_rows, dim3(a.M), dim3(rr_threads), (size_t)a.N * sizeof(op_t), st, a);
   } else if (split) {
     const size_t total = (size_t)a.M * (a.N >> 2);
-    hipLaunchKernelGGL(k_partial_reduce<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_partial_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
   }
-}
-
-void gemm_tile_prepare() {
-  GemmArgs a{};
-  for (int epi : {(int)EPI_QKV, (int)EPI_SWIGLU, (int)EPI_RELU, (int)EPI_PARTIAL, (int)EPI_LOGITS})
-    for (int nbw = 2; nbw <= 4; ++nbw) {
-      launch_nb_tile<bf16_t, 1>(a, nbw, epi, -1, nullptr); launch_nb_tile<f16_t, 1>(a, nbw, epi, -1, nullptr);
-      launch_nb_tile<bf16_t, 2>(a, nbw, epi, -1, nullptr); launch_nb_tile<f16_t, 2>(a, nbw, epi, -1, nullptr);
-      launch_nb_tile<bf16_t, 3>(a, nbw, epi, -1, nullptr); launch_nb_tile<f16_t, 3>(a, nbw, epi, -1, nullptr);
-      launch_nb_tile<bf16_t, 4>(a, nbw, epi, -1, nullptr); launch_nb_tile<f16_t, 4>(a, nbw, epi, -1, nullptr);
-    }
-}
-
-void launch_gemm_tile(int dtype, GemmArgs a, int epi, hipStream_t st) {
-  if (dtype == SPEC_DTYPE_BF16) launch_tile_t<bf16_t>(a, epi, st);
-  else launch_tile_t<f16_t>(a, epi, st);
 }
 
 }  // namespace spec

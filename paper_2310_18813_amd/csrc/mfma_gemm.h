@@ -54,7 +54,7 @@ struct GemmArgs {
   // mean goes beside rinv_ws.
   const float *wsum;
   float *mean_ws;
-  float *part;               // EPI_RESIDUAL with more than 64 rows: scratch [KS][part_rows][N] fp32, or null
+  float *part;               // EPI_RESIDUAL with more than 32 rows: scratch [KS][part_rows][N] fp32, or null
   int part_rows;             // M rounded up to 16
   void *q, *kc, *vc;         // EPI_QKV: q [M][d] fp32 (un-rounded: the attention kernel decides how to feed it), caches in the model dtype
   const int32_t *row_pos;    // EPI_QKV: absolute position per row, -1 = dead row
@@ -65,8 +65,9 @@ struct GemmArgs {
   int f;
   float *logits;             // EPI_LOGITS: optional [M][N] fp32
   int logit_step;            // EPI_LOGITS: > 1: only the last row of every group of logit_step rows is dumped, as row m / logit_step
-  float *part_val;           // EPI_LOGITS: [M][NT]
+  float *part_val;           // EPI_LOGITS: [M][n_part] arg-max partials (at most NT per row)
   int32_t *part_idx;
+  int n_part;                // filled by the launcher
 };
 
 // The kernels take GemmArgs by value: it is the explicit part of their kernel-argument segment (the code objects
@@ -93,7 +94,12 @@ void launch_fold_ln(int dtype, int mode, const PackedDims &p, int d, int hd, con
                     const void *ln_bias, const void *packed, float *wsum, float *bias, hipStream_t st);
 void launch_rope_table(int L, int hd, float theta, float2 *tab, hipStream_t st);
 void launch_gemm_mfma(int dtype, const GemmArgs &a, int epi, hipStream_t st);
-void launch_gemm_tile(int dtype, GemmArgs a, int epi, hipStream_t st);  // more than 64 rows, wide outputs
+// more than 32 rows; split (EPI_RESIDUAL with a.part): one k-slice per workgroup, added up by a second kernel
+void launch_gemm_tile(int dtype, GemmArgs a, int epi, bool split, hipStream_t st);
+double gemm_tile_us(const GemmArgs &a, bool split);  // its estimated time
+// EPI_LOGITS: arg-max partials per row the launch for these arguments leaves
+int gemm_head_partials(const GemmArgs &a);
+int gemm_tile_head_partials(const GemmArgs &a);
 // Folded norm: true when the launch for these arguments reads 1 / rms of its rows from a.rinv_ws (tiled kernel
 // with more than one row tile per wave); launch_row_inv_x then has to run first.  Every other launch takes the
 // value from its own operand fragments.
@@ -104,7 +110,7 @@ void launch_row_inv_x(const GemmArgs &a, hipStream_t st);
 // 1 / rms of the updated rows behind (set ssq_ks, ss_d, ss_eps and rinv_ws before the launch): the consumer then needs
 // no k_row_inv_x.
 bool gemm_can_leave_ssq(const GemmArgs &a);
-void launch_argmax_partials(const float *pv, const int32_t *pi, int M, int row_step, int NT, int V, int q, int out_stride,
+void launch_argmax_partials(const float *pv, const int32_t *pi, int M, int row_step, int n_part, int V, int q, int out_stride,
                             int32_t *out, hipStream_t st);
 // once per context, with its device current: lets the kernels that need it use more than 64 KB of LDS
 void gemm_tile_prepare();

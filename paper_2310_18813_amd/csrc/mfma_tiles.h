@@ -21,6 +21,11 @@ struct Mfma16 {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_v, a), __builtin_bit_cast(f16x8_v, b), c,
                                                   0, 0, 0);
   }
+  // d = A * B, in d's own registers: written out so that the chain's registers stay in place across the two kinds of
+  // step (as a builtin with a zero operand it got registers of its own, and the largest wave tile spilled)
+  static __device__ __forceinline__ void run_from_zero(u32x4_v a, u32x4_v b, f32x4_v &d) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "+v"(d) : "v"(a), "v"(b));
+  }
 };
 
 // Folded norm, consumer side: the sum of squares of a row of activations is taken from the fp16 operand
@@ -70,6 +75,22 @@ __device__ __forceinline__ float row_inv_from_lane_ssq(float t, int d, float eps
   return 1.0f / sqrtf(t / (float)d + eps);
 }
 
+// Values on their way to a GEMM operand: rounded to fp16, clamped to its range, every clamp counted in *sat (or not,
+// sat null); NaN passes through.  One test of the largest magnitude covers the group: clamping is the rare case.
+template <int N>
+__device__ __forceinline__ void to_op_group(const float (&x)[N], op_t (&o)[N], unsigned int *sat) {
+  float big = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) big = fmaxf(big, fabsf(x[i]));
+  if (big > 65504.f) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = to_op_counted(x[i], sat);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = (op_t)x[i];
+  }
+}
+
 // h[m][n..n+3] += v (scaled, biased): the residual update of one lane's four outputs; o4 = the updated values
 // rounded to the next GEMM's operand type (also written to x_out in fragment order when that is set).
 __device__ __forceinline__ void residual_update(const GemmArgs &a, f32x4_v v, int n, int m, op_t (&o4)[4]) {
@@ -83,10 +104,41 @@ __device__ __forceinline__ void residual_update(const GemmArgs &a, f32x4_v v, in
   o.x += v[0]; o.y += v[1]; o.z += v[2]; o.w += v[3];
   *p = o;
   if (a.x_out) {  // the next GEMM's activations: the updated row, rounded to fp16
-    o4[0] = to_op_counted(o.x, a.sat); o4[1] = to_op_counted(o.y, a.sat);
-    o4[2] = to_op_counted(o.z, a.sat); o4[3] = to_op_counted(o.w, a.sat);
+    const float x4[4] = {o.x, o.y, o.z, o.w};
+    to_op_group(x4, o4, a.sat);
     *(uint2 *)((op_t *)a.x_out + xpack_index(m, n, a.N >> 5)) = *(const uint2 *)o4;
   }
+}
+
+// EPI_LOGITS: where row m of the logits is dumped, if it is
+__device__ __forceinline__ float *logits_row(const GemmArgs &a, int m) {
+  if (!a.logits) return nullptr;
+  if (a.logit_step <= 1) return a.logits + (size_t)m * a.N;
+  return m % a.logit_step == a.logit_step - 1 ? a.logits + (size_t)(m / a.logit_step) * a.N : nullptr;
+}
+// EPI_LOGITS: the four lane groups' candidates for row m -> partial p of the row (lowest index wins ties)
+__device__ __forceinline__ void row_argmax_out(const GemmArgs &a, float bv, int bi, int m, int p, bool live, int g) {
+#pragma unroll
+  for (int o = 16; o <= 32; o <<= 1) {
+    const float ov = __shfl_xor(bv, o, 64);
+    const int oi = __shfl_xor(bi, o, 64);
+    argmax_combine(bv, bi, ov, oi);
+  }
+  if (live && g == 0) {
+    a.part_val[(size_t)m * a.n_part + p] = bv;
+    a.part_idx[(size_t)m * a.n_part + p] = bi;
+  }
+}
+
+__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.0f + __expf(-gate)) * up; }
+
+// The sequence (row group) m / q_rows of row m without an integer division: a float product, made exact by one step
+// either way.
+__device__ __forceinline__ int row_group(int m, int q_rows, float inv_q) {
+  int b = (int)(((float)m + 0.5f) * inv_q);
+  b += ((b + 1) * q_rows <= m) ? 1 : 0;
+  b -= (b * q_rows > m) ? 1 : 0;
+  return b;
 }
 
 // ------------------------------------------------------------------------- epilogues
@@ -118,15 +170,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int 
     if (live && n < a.N) {
       // No per-lane integer division (it would be most of this epilogue).  A strip of 16 stored rows lies
       // inside one head of one of q, k, v (d and hd are multiples of 16), and the strip number is the same for
-      // the whole wave: its place is scalar arithmetic.  The row's sequence m / q_rows comes from a float
-      // product, made exact by one step either way.
+      // the whole wave: its place is scalar arithmetic.
       const int base = __builtin_amdgcn_readfirstlane(nt) * 16;
       const int region = base / a.d, cc0 = base - region * a.d, hh = cc0 / a.hd;
       const int cc = cc0 + 4 * g, e = cc - hh * a.hd;
       const int pos = a.row_pos[m];
-      int b = (int)(((float)m + 0.5f) * (1.0f / (float)a.q_rows));
-      b += ((b + 1) * a.q_rows <= m) ? 1 : 0;
-      b -= (b * a.q_rows > m) ? 1 : 0;
+      int b = row_group(m, a.q_rows, 1.0f / (float)a.q_rows);
       if (a.seq_groups > 1) b /= a.seq_groups;  // prefill passes only
       if (region < 2) {
         float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
@@ -152,41 +201,238 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int 
   } else if (EPI == EPI_SWIGLU) {
     const int j = n >> 1;  // stored rows n..n+3 = gate_j, up_j, gate_{j+1}, up_{j+1}
     if (live && j < a.f) {
-      const float r0 = v[0] / (1.0f + __expf(-v[0])) * v[1], r1 = v[2] / (1.0f + __expf(-v[2])) * v[3];
-      op_t o2[2] = {to_op_counted(r0, a.sat), to_op_counted(r1, a.sat)};
+      const float r2[2] = {swiglu(v[0], v[1]), swiglu(v[2], v[3])};
+      op_t o2[2];
+      to_op_group(r2, o2, a.sat);
       const size_t at = xpack_index(m, j, a.f >> 5);
       *(uint32_t *)((op_t *)a.act + at) = *(const uint32_t *)o2;
     }
   } else if (EPI == EPI_RELU) {
     if (live && n < a.N) {
+      float r4[4];
       op_t o4[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o4[i] = to_op_counted(v[i] > 0.f ? v[i] : 0.f, a.sat);
+      for (int i = 0; i < 4; ++i) r4[i] = v[i] > 0.f ? v[i] : 0.f;
+      to_op_group(r4, o4, a.sat);
       const size_t at = xpack_index(m, n, a.N >> 5);
       *(uint2 *)((op_t *)a.act + at) = *(const uint2 *)o4;
     }
   } else {  // EPI_LOGITS: optional dump, per-strip arg-max partial (lowest index wins ties)
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    float *dump = nullptr;  // debug / parity only
-    if (live && a.logits) {
-      if (a.logit_step <= 1) dump = a.logits + (size_t)m * a.N;
-      else if (m % a.logit_step == a.logit_step - 1) dump = a.logits + (size_t)(m / a.logit_step) * a.N;
-    }
+    float *dump = live ? logits_row(a, m) : nullptr;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (n + i < a.N) {
         if (dump) dump[n + i] = v[i];
         argmax_combine(bv, bi, v[i], n + i);
       }
-    for (int o = 16; o <= 32; o <<= 1) {
-      float ov = __shfl_xor(bv, o, 64);
-      int oi = __shfl_xor(bi, o, 64);
-      argmax_combine(bv, bi, ov, oi);
+    row_argmax_out(a, bv, bi, m, nt, live, g);
+  }
+}
+
+// Four lanes 4k .. 4k+3 hold four 16-bit values each: lane 4k+i returns value i of all four lanes, in lane order.
+__device__ __forceinline__ uint2 quad_transpose(uint2 v, int lane) {
+  auto swap = [](uint32_t x, auto perm) {  // lane exchange inside the quad
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(perm)::value, 0xf, 0xf, true);
+  };
+  // halves: even lanes keep values 0, 1 (and take the odd neighbour's), odd lanes 2, 3 -> x = (value a: lanes l, l+1), y = (value a+1)
+  const bool odd = lane & 1, high = lane & 2;
+  const uint32_t give = odd ? v.x : v.y, keep = odd ? v.y : v.x;
+  const uint32_t got = swap(give, std::integral_constant<int, 0xB1>{});  // quad_perm 1,0,3,2
+  const uint32_t lo = odd ? got : keep, hi = odd ? keep : got;            // the even lane's pair, the odd lane's pair
+  uint32_t x = (lo & 0xffffu) | (hi << 16), y = (lo >> 16) | (hi & 0xffff0000u);
+  // even lanes now hold values 0 (x) and 1 (y) of two lanes, odd lanes values 2 and 3; lanes 0, 1 keep x of both pairs
+  // of lanes, lanes 2, 3 keep y
+  const uint32_t give2 = high ? x : y, keep2 = high ? y : x;
+  const uint32_t got2 = swap(give2, std::integral_constant<int, 0x4E>{});  // quad_perm 2,3,0,1
+  uint2 r = high ? make_uint2(got2, keep2) : make_uint2(keep2, got2);
+  // lane 0: value 0, lane 1: value 2, lane 2: value 1, lane 3: value 3 -> put 1 and 2 in their places
+  r.x = swap(r.x, std::integral_constant<int, 0xD8>{});  // quad_perm 0,2,1,3
+  r.y = swap(r.y, std::integral_constant<int, 0xD8>{});
+  return r;
+}
+
+// The epilogue of a wave's NBW x MTW finished tiles (strips nt0 .., row tiles mtile0 ..): per output the arithmetic of
+// tile_epilogue, with what depends on the row alone fetched once per row and every load ahead of the strip that uses
+// it.  Tile by tile, the chain row position -> rotary entry -> store costs two memory latencies per tile: at 256 x 192
+// outputs per workgroup the QKV epilogue took 37 us, as much as 30 % of the launch.
+template <class T, int EPI, int MTW, int NBW>
+__device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[NBW][MTW], int nt0, int mtile0, int lane,
+                                              const float (&rinv)[MTW], const float (&mean)[MTW]) {
+  const int c = lane & 15, g = lane >> 4;
+  bool live[MTW];
+#pragma unroll
+  for (int mt = 0; mt < MTW; ++mt) live[mt] = (mtile0 + mt) * 16 + c < a.M;
+  const bool lnx = a.wsum != nullptr;
+  // (acc - mean * wsum) * scale * rinv + bias of the four outputs of a tile
+  auto finish = [&](f32x4_v v, int mt, const float4 &b4, const float4 &w4) {
+    if (EPI != EPI_RESIDUAL && lnx) {
+      v[0] -= mean[mt] * w4.x; v[1] -= mean[mt] * w4.y; v[2] -= mean[mt] * w4.z; v[3] -= mean[mt] * w4.w;
     }
-    if (live && g == 0) {
-      a.part_val[(size_t)m * a.NT + nt] = bv;
-      a.part_idx[(size_t)m * a.NT + nt] = bi;
+    v[0] *= a.out_scale; v[1] *= a.out_scale; v[2] *= a.out_scale; v[3] *= a.out_scale;  // exact: a power of two
+    if (EPI != EPI_RESIDUAL) { v[0] *= rinv[mt]; v[1] *= rinv[mt]; v[2] *= rinv[mt]; v[3] *= rinv[mt]; }
+    if (a.bias) { v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w; }
+    return v;
+  };
+  float4 b4[NBW], w4[NBW];
+#pragma unroll
+  for (int nb = 0; nb < NBW; ++nb) {
+    const int n = min(nt0 + nb, a.NT - 1) * 16 + 4 * g;
+    if (a.bias) b4[nb] = *(const float4 *)(a.bias + n);
+    if (EPI != EPI_RESIDUAL && lnx) w4[nb] = *(const float4 *)(a.wsum + n);
+  }
+  if (EPI == EPI_LOGITS) {  // optional dump; one arg-max partial per row for all strips of the wave
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt) {
+      const int m = (mtile0 + mt) * 16 + c;
+      float *dump = live[mt] ? logits_row(a, m) : nullptr;
+      float bv = -INFINITY;
+      int bi = 0x7fffffff;
+#pragma unroll
+      for (int nb = 0; nb < NBW; ++nb) {
+        const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
+        const int n = (nt0 + nb) * 16 + 4 * g;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + i < a.N) {
+            if (dump) dump[n + i] = v[i];
+            argmax_combine(bv, bi, v[i], n + i);
+          }
+      }
+      row_argmax_out(a, bv, bi, m, nt0 / NBW, live[mt], g);
+    }
+  } else if (EPI == EPI_SWIGLU || EPI == EPI_RELU) {
+    // fragment order: a strip of 16 outputs (8 after SwiGLU) is 512 (256) consecutive bytes of its row tile
+    unsigned char *row[MTW];
+    const size_t tile_bytes = (size_t)(EPI == EPI_SWIGLU ? a.f : a.N) * 32;
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt)
+      row[mt] = (unsigned char *)a.act + (size_t)(mtile0 + mt) * tile_bytes + c * 16 +
+                (EPI == EPI_SWIGLU ? g * 4 : (g >> 1) * 256 + (g & 1) * 8);
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+      if (nt0 + nb >= a.NT) break;
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt) {
+        const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
+        if (EPI == EPI_SWIGLU) {
+          const float r2[2] = {swiglu(v[0], v[1]), swiglu(v[2], v[3])};
+          op_t o2[2];
+          if (live[mt]) {
+            to_op_group(r2, o2, a.sat);
+            *(uint32_t *)(row[mt] + (size_t)(nt0 + nb) * 256) = *(const uint32_t *)o2;
+          }
+        } else {
+          float r4[4];
+          op_t o4[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) r4[i] = v[i] > 0.f ? v[i] : 0.f;
+          if (live[mt]) {
+            to_op_group(r4, o4, a.sat);
+            *(uint2 *)(row[mt] + (size_t)(nt0 + nb) * 512) = *(const uint2 *)o4;
+          }
+        }
+      }
+    }
+  } else if (EPI == EPI_RESIDUAL) {
+    float4 o[MTW];
+    auto load_h = [&](int nb) {
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt)
+        if (live[mt]) o[mt] = *(const float4 *)(a.h + (size_t)((mtile0 + mt) * 16 + c) * a.N + (nt0 + nb) * 16 + 4 * g);
+    };
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+      if (nt0 + nb >= a.NT) break;
+      load_h(nb);
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt) {
+        const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
+        const float x4[4] = {o[mt].x + v[0], o[mt].y + v[1], o[mt].z + v[2], o[mt].w + v[3]};
+        op_t o4[4];
+        if (live[mt]) {
+          *(float4 *)(a.h + (size_t)((mtile0 + mt) * 16 + c) * a.N + (nt0 + nb) * 16 + 4 * g) = make_float4(x4[0], x4[1], x4[2], x4[3]);
+          if (a.x_out) {
+            to_op_group(x4, o4, a.sat);
+            *(uint2 *)((unsigned char *)a.x_out + (size_t)(mtile0 + mt) * a.N * 32 + (size_t)(nt0 + nb) * 512 + c * 16 +
+                       (g >> 1) * 256 + (g & 1) * 8) = *(const uint2 *)o4;
+          }
+        }
+      }
+    }
+  } else {  // EPI_QKV
+    // A strip of 16 stored rows lies inside one head of one of q, k, v: its place is scalar arithmetic.  What depends on
+    // the row (cache rows of its sequence and position) is worked out once per row tile.
+    const int first = __builtin_amdgcn_readfirstlane(nt0) * 16;
+    int region = first / a.d, cc0 = first - region * a.d;
+    const int half = a.hd >> 1, hd_shift = a.hd == 128 ? 7 : 6;
+    const float inv_q = 1.0f / (float)a.q_rows;
+    int pos[MTW];
+    T *krow[MTW], *vrow[MTW];
+    bool quads[MTW];  // same for the wave: every four rows of the tile hold four consecutive positions of one sequence from a
+                      // multiple of four on, as the passes of a prefill do; their values are then stored together
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt) pos[mt] = live[mt] ? a.row_pos[(mtile0 + mt) * 16 + c] : -1;
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt) {
+      int b = row_group((mtile0 + mt) * 16 + c, a.q_rows, inv_q);
+      if (a.seq_groups > 1) b /= a.seq_groups;
+      const size_t seq0 = (size_t)b * a.H * a.L_pad * a.hd;
+      const int p0 = max(pos[mt], 0);
+      krow[mt] = (T *)a.kc + seq0 + (size_t)p0 * a.hd;
+      vrow[mt] = (T *)a.vc + seq0 + (size_t)(p0 / KV_VBLOCK) * a.hd * KV_VBLOCK + p0 % KV_VBLOCK;
+      quads[mt] = (a.q_rows & 3) == 0 && __all(pos[mt] >= 0 && (pos[mt] & 3) == (lane & 3) && pos[mt] == __shfl(pos[mt], lane & ~3, 64) + (lane & 3));
+    }
+    float4 cs[2][MTW];  // (cos, sin) of the two rotary pairs: this strip's and the next one's
+    auto load_cs = [&](int nb, int cc) {  // column cc of q or k
+      const float2 *tab = a.rope + (((cc & (a.hd - 1)) + 4 * g) >> 1);
+#pragma unroll
+      for (int mt = 0; mt < MTW; ++mt) cs[nb & 1][mt] = *(const float4 *)(tab + (size_t)max(pos[mt], 0) * half);
+    };
+    if (a.rope && region < 2) load_cs(0, cc0);
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+      if (nt0 + nb >= a.NT) break;
+      const int next_cc0 = cc0 + 16 == a.d ? 0 : cc0 + 16, next_region = cc0 + 16 == a.d ? region + 1 : region;
+      if (nb + 1 < NBW && a.rope && next_region < 2) load_cs(nb + 1, next_cc0);
+      const int hh = cc0 >> hd_shift, e = (cc0 & (a.hd - 1)) + 4 * g;
+      const size_t head = (size_t)hh * a.L_pad * a.hd;
+      if (region < 2) {
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt) {
+          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
+          float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
+          if (a.rope && pos[mt] >= 0) {
+            const float4 t = cs[nb & 1][mt];
+            r0 = v[0] * t.x - v[1] * t.y; r1 = v[1] * t.x + v[0] * t.y;
+            r2 = v[2] * t.z - v[3] * t.w; r3 = v[3] * t.z + v[2] * t.w;
+          }
+          if (region == 0) {  // queries stay fp32 (see tile_epilogue)
+            if (live[mt]) *(float4 *)((float *)a.q + (size_t)((mtile0 + mt) * 16 + c) * a.d + cc0 + 4 * g) = make_float4(r0, r1, r2, r3);
+          } else {
+            T o4[4];
+            Conv<T>::st(o4, 0, r0); Conv<T>::st(o4, 1, r1); Conv<T>::st(o4, 2, r2); Conv<T>::st(o4, 3, r3);
+            if (pos[mt] >= 0) *(uint2 *)(krow[mt] + head + e) = *(const uint2 *)o4;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt) {
+          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
+          T o4[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) Conv<T>::st(o4, i, v[i]);
+          if (quads[mt]) {  // four rows of one element per lane: their positions are neighbours in the cache
+            const uint2 o = quad_transpose(*(const uint2 *)o4, lane);
+            *(uint2 *)(vrow[mt] - (lane & 3) + head + (size_t)(e + (lane & 3)) * KV_VBLOCK) = o;
+          } else if (pos[mt] >= 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) vrow[mt][head + (size_t)(e + i) * KV_VBLOCK] = o4[i];
+          }
+        }
+      }
+      region = next_region; cc0 = next_cc0;
     }
   }
 }
