@@ -200,7 +200,7 @@ static GemmArgs base_args(const spec_ctx *c, const PackedDims &p, const void *W,
 
 // One pre-norm decoder layer over the M rows of the pass; max_pos is an upper bound of the
 // largest row position (sizes the attention grid; chunks past a sequence's end exit at once).
-void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, int seq_groups, int max_pos, hipStream_t st) {
+void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, int max_pos, hipStream_t st) {
   const spec_model_desc &D = m.desc;
   const int dt = c->run.dtype, M = B * q_rows, d = D.d_model;
   const LayerW &L = m.layers[layer];
@@ -237,7 +237,7 @@ void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
     GemmArgs a = base_args(c, m.p_qkv, L.wqkv, L.s_qkv, L.bqkv, ws.x, M);
     consume_norm(a, L.wsum_qkv);
     a.q = ws.q; a.kc = kc; a.vc = vc; a.row_pos = ws.row_pos; a.rope = m.rope;
-    a.q_rows = q_rows; a.d = d; a.hd = m.hd; a.H = D.n_heads; a.L_pad = m.L_pad; a.seq_groups = seq_groups;
+    a.q_rows = q_rows; a.d = d; a.hd = m.hd; a.H = D.n_heads; a.L_pad = m.L_pad; a.grp_seq = grp_seq;
     row_inv_first(a, EPI_QKV);
     KScope k(c, tgt ? SPEC_KCLASS_GEMM_QKV : -1);
     launch_gemm_mfma(dt, a, EPI_QKV, st);
@@ -248,7 +248,8 @@ void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
     t.q = ws.q; t.kc = kc; t.vc = vc; t.row_pos = ws.row_pos; t.out = ws.attn;
     t.part_acc = ws.attn_part; t.part_ml = ws.attn_ml;
     t.B = B; t.q_rows = q_rows; t.H = D.n_heads; t.hd = m.hd; t.L_pad = m.L_pad;
-    t.seq_groups = seq_groups;
+    t.grp_seq = grp_seq;
+    t.part_rows = c->M_max;
     t.shape = c->attn_shape;
     t.n_cu = c->n_cu;
     t.NC = std::min(c->NC_max, attn_chunk_of(std::max(max_pos, 0)) + 1);
@@ -257,7 +258,7 @@ void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
   {
     KScope k(c, tgt ? SPEC_KCLASS_GEMM_O : -1);
     GemmArgs a = base_args(c, m.p_o, L.wo, L.s_o, L.bo, ws.attn, M);
-    a.h = ws.h; a.part = ws.gemm_part; a.part_rows = (M + 15) / 16 * 16;
+    a.h = ws.h; a.part = M <= c->part_rows ? ws.gemm_part : nullptr; a.part_rows = (M + 15) / 16 * 16;
     produce_norm(a);
     launch_gemm_mfma(dt, a, EPI_RESIDUAL, st);
   }
@@ -273,7 +274,7 @@ void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
   {
     KScope k(c, tgt ? SPEC_KCLASS_GEMM_FFN_OUT : -1);
     GemmArgs a = base_args(c, m.p_2, L.w2, L.s_2, L.b2, ws.act, M);
-    a.h = ws.h; a.part = ws.gemm_part; a.part_rows = (M + 15) / 16 * 16;
+    a.h = ws.h; a.part = M <= c->part_rows ? ws.gemm_part : nullptr; a.part_rows = (M + 15) / 16 * 16;
     produce_norm(a);
     launch_gemm_mfma(dt, a, EPI_RESIDUAL, st);
   }

@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_attn_split(AttnArgs a) {
   const int d = a.H * HD;
   QFrags<T, HD> qf;
   load_q<T, HD>(qf, (const float *)a.q + (size_t)w.m_row * d + (size_t)hh * HD, w.g);
-  const size_t cbh = a.seq_groups > 1 ? (size_t)(b / a.seq_groups) * a.H + hh : (size_t)bh;  // whose cache: the group's sequence
+  const size_t cbh = a.grp_seq ? (size_t)a.grp_seq[b] * a.H + hh : (size_t)bh;  // whose cache: the group's sequence
   const T *kbase = (const T *)a.kc + cbh * a.L_pad * HD;
   const T *vbase = (const T *)a.vc + cbh * (a.L_pad / KV_VBLOCK) * HD * KV_VBLOCK;
   float m_run, l_run;
@@ -300,19 +300,21 @@ __global__ void k_attn_merge(AttnArgs a) {
 }
 
 // Launch shape 2: one wave per (sequence, head) walks all chunks, merging in registers.
-template <class T, int HD>
+// The groups of a prefill are in ascending position order within their sequence: launched last first, so that the short
+// ones fill the gaps the long ones leave at the end.
+template <class T, int HD, bool STREAM>
 __global__ __launch_bounds__(256) void k_attn_seq(AttnArgs a) {  // launched with 64: the bound only keeps the register budget
   constexpr int HT = HD / 16;
   const int lane = threadIdx.x & 63;
-  const int bh = blockIdx.x;  // a workgroup is one wave
-  if (bh >= a.B * a.H) return;
+  if ((int)blockIdx.x >= a.B * a.H) return;
+  const int bh = a.grp_seq ? a.B * a.H - 1 - (int)blockIdx.x : (int)blockIdx.x;  // a workgroup is one wave
   const int hh = bh % a.H, b = bh / a.H;
   const WaveSetup w = wave_setup(a, b, lane);
   const int d = a.H * HD;
   const float scale = rsqrtf((float)HD) * LOG2E;  // score scale in base-2 exponent units
   QFrags<T, HD> qf;
   load_q<T, HD>(qf, (const float *)a.q + (size_t)w.m_row * d + (size_t)hh * HD, w.g);
-  const size_t cbh = a.seq_groups > 1 ? (size_t)(b / a.seq_groups) * a.H + hh : (size_t)bh;  // whose cache: the group's sequence
+  const size_t cbh = a.grp_seq ? (size_t)a.grp_seq[b] * a.H + hh : (size_t)bh;  // whose cache: the group's sequence
   const T *kbase = (const T *)a.kc + cbh * a.L_pad * HD;
   const T *vbase = (const T *)a.vc + cbh * (a.L_pad / KV_VBLOCK) * HD * KV_VBLOCK;
   float mr = NEG_BIG, lr = 0.f;
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(256) void k_attn_seq(AttnArgs a) {  // launched wit
     const int kend = min(attn_chunk_begin(c + 1), w.pmax + 1);
     float mc, lc;
     f32x4_v ac[HT];
-    chunk_partial<T, HD, true>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, scale, mc, lc, ac);
+    chunk_partial<T, HD, STREAM>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, scale, mc, lc, ac);
     if (k0 == 0) {
       mr = mc; lr = lc;
 #pragma unroll
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(512) void k_attn_group(AttnArgs a) {
   const float scale = rsqrtf((float)HD) * LOG2E;  // score scale in base-2 exponent units
   QFrags<T, HD> qf;
   load_q<T, HD>(qf, (const float *)a.q + (size_t)w.m_row * d + (size_t)hh * HD, w.g);
-  const size_t cbh = a.seq_groups > 1 ? (size_t)(b / a.seq_groups) * a.H + hh : (size_t)bh;  // whose cache: the group's sequence
+  const size_t cbh = a.grp_seq ? (size_t)a.grp_seq[b] * a.H + hh : (size_t)bh;  // whose cache: the group's sequence
   const T *kbase = (const T *)a.kc + cbh * a.L_pad * HD;
   const T *vbase = (const T *)a.vc + cbh * (a.L_pad / KV_VBLOCK) * HD * KV_VBLOCK;
   f32x4_v *pacc = (f32x4_v *)attn_smem;
@@ -452,14 +454,17 @@ static void launch_attn_hd(const AttnArgs &a, hipStream_t st) {
   // 303 against 276 us, 32 sequences 312 against 318)
   const double full = !group_fits ? 0.7 : a.NC <= ATTN_GROUP_MAX_WAVES ? 0.85 : 0.8;
   const bool fills = rounds == 1 || (double)pairs >= full * (double)rounds * slots;
-  const bool seq = a.shape == 2 || (a.shape == 0 && ((pairs >= ATTN_SEQ_MIN_PAIRS && fills) || a.NC == 1));
+  // (a prefill's rows are more than the partials' scratch holds: the split shape is for passes that fit)
+  const bool no_split = M > a.part_rows;
+  const bool seq = a.shape == 2 || (a.shape == 0 && ((pairs >= ATTN_SEQ_MIN_PAIRS && fills) || a.NC == 1)) || (no_split && !(group_fits && a.shape != 1));
   // few sequences: a workgroup per (sequence, head), as long as its partials fit into LDS with a wave per chunk
   const bool group = !seq && (a.shape == 3 || a.shape == 0) && group_fits;
   if (seq) {
     // workgroups of one wave: few pairs then spread over all compute units (measured, us per layer at 32 heads: 4
     // sequences x 100 positions 15.1 -> 11.8, 24 x 250 29.6 -> 26.6), and many pairs drain evenly (64 sequences x 300
     // positions 72.5 -> 71.4 against workgroups of four waves; 32 sequences x 52 heads x 2048 positions: the same)
-    hipLaunchKernelGGL((k_attn_seq<T, HD>), dim3(pairs), dim3(64), 0, st, a);
+    if (a.grp_seq) hipLaunchKernelGGL((k_attn_seq<T, HD, false>), dim3(pairs), dim3(64), 0, st, a);  // several groups read one cache
+    else hipLaunchKernelGGL((k_attn_seq<T, HD, true>), dim3(pairs), dim3(64), 0, st, a);
   } else if (group) {
     if (pairs * a.NC >= ATTN_STREAM_MIN_WAVES) launch_attn_group<T, HD, true>(a, pairs, st);
     else launch_attn_group<T, HD, false>(a, pairs, st);

@@ -20,17 +20,16 @@ namespace spec {
 // PREP (models whose RMS norm is folded into the GEMMs): the kernel also leaves what the first layer's QKV GEMM
 // consumes, the fp16 copy of the row in fragment order (the GEMM takes 1 / rms of the row from those values).
 template <class T, bool PREP>
-__global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, int P, int s_max, int L_max, int vocab, int d,
-                                 int learned_pos, int seq_groups, const int32_t *__restrict__ seq, const int32_t *__restrict__ n,
+__global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, int s_max, int L_max, int vocab, int d,
+                                 int learned_pos, const int32_t *__restrict__ grp_seq, const int32_t *__restrict__ grp_base, const int32_t *__restrict__ seq, const int32_t *__restrict__ n,
                                  const int32_t *__restrict__ kv_draft, const int32_t *__restrict__ t,
                                  const int32_t *__restrict__ seq_s, const int32_t *__restrict__ P_b,
                                  const T *__restrict__ tok_emb, const T *__restrict__ pos_emb,
                                  int32_t *__restrict__ row_tok, int32_t *__restrict__ row_pos, float *__restrict__ h,
                                  op_t *__restrict__ x, unsigned int *__restrict__ sat) {
-  // prefill with several row groups per sequence: group = m / q, sequence = group / seq_groups, and the row's
-  // offset from the pass's base position counts the sequence's earlier groups
+  // prefill: the table says which sequence a group of q rows belongs to and where it starts
   const int m = blockIdx.x, grp = m / q;
-  const int b = grp / seq_groups, i = (grp % seq_groups) * q + m % q;
+  const int b = grp_seq ? grp_seq[grp] : grp, i = m % q;
   int tok = 0, pos = -1;
   const int nb = n[b];
   // a sequence with its own cap s_b on the speculation length: its rows for proposals beyond s_b are dead
@@ -48,8 +47,8 @@ __global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, 
       pos = nb + j - 2;
       tok = t[(size_t)b * s_max + j - 2];
     }
-  } else {  // PASS_PREFILL: j is the base position
-    int p = j + i;
+  } else {  // PASS_PREFILL
+    const int p = grp_base[grp] + i;
     if (p < P_b[b] - 1) { pos = p; tok = seq[(size_t)b * L_max + p]; }  // the sequence's own prompt length
   }
   if (pos >= L_max) pos = -1;  // cannot happen when the host checks hold; never write out of range
@@ -79,16 +78,43 @@ __global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, 
 
 void launch_assemble_embed(const spec_ctx *c, const Model &m, const PassArgs &pa, hipStream_t st) {
   const int M = pa.B * pa.q;
+  const bool prefill = pa.kind == PASS_PREFILL;
   const bool prep = m.fast;  // the norms are folded into the GEMMs: they read fp16(h)
   SPEC_DISPATCH_DTYPE(c->run.dtype, T,
-    hipLaunchKernelGGL((prep ? k_assemble_embed<T, true> : k_assemble_embed<T, false>), dim3(M), dim3(256), 0, st, (int)pa.kind, pa.q, pa.j, pa.P,
+    hipLaunchKernelGGL((prep ? k_assemble_embed<T, true> : k_assemble_embed<T, false>), dim3(M), dim3(256), 0, st, (int)pa.kind, pa.q, pa.j,
                        c->run.s_max, c->run.L_max, m.desc.vocab, m.desc.d_model,
-                       (int)(m.desc.pos_kind == SPEC_POS_LEARNED), pa.seq_groups,
+                       (int)(m.desc.pos_kind == SPEC_POS_LEARNED), prefill ? c->ws.grp_seq + pa.g0 : nullptr, prefill ? c->ws.grp_base + pa.g0 : nullptr,
                        c->st.seq + (size_t)pa.b0 * c->run.L_max,
                        c->st.n + pa.b0, c->drf.kv_len ? c->drf.kv_len + pa.b0 : nullptr,
                        c->st.t + (size_t)pa.b0 * c->run.s_max, c->seq_s ? c->seq_s + pa.b0 : nullptr, c->st.P_b + pa.b0,
                        (const T *)m.tok_emb, (const T *)m.pos_emb, c->ws.row_tok, c->ws.row_pos, c->ws.h,
                        (op_t *)c->ws.x, c->st.sat));
+}
+
+// -------------------------------------------------------------------------
+// The row groups of a prefill: sequence by sequence, ceil((P_b - 1) / q) groups of q consecutive positions each, so that
+// prompts of different lengths leave no dead rows but those of their own last group.  One workgroup; a thread owns a
+// run of sequences, and a prefix sum over the runs says where its groups start.
+__global__ __launch_bounds__(256) void k_prefill_groups(int B, int q, const int32_t *__restrict__ P_b, int32_t *__restrict__ grp_seq,
+                                                        int32_t *__restrict__ grp_base) {
+  __shared__ int sh[4];
+  const int per = (B + 255) / 256, b0 = min(B, (int)threadIdx.x * per), b1 = min(B, b0 + per), lane = threadIdx.x & 63;
+  int mine = 0;
+  for (int b = b0; b < b1; ++b) mine += (P_b[b] - 1 + q - 1) / q;
+  int inc = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += up;
+  }
+  if (lane == 63) sh[threadIdx.x >> 6] = inc;
+  __syncthreads();
+  int at = inc - mine;
+  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) at += sh[w];
+  for (int b = b0; b < b1; ++b)
+    for (int base = 0; base < P_b[b] - 1; base += q, ++at) { grp_seq[at] = b; grp_base[at] = base; }
+}
+void launch_prefill_groups(const spec_ctx *c, int b0, int B, int q, hipStream_t st) {
+  hipLaunchKernelGGL(k_prefill_groups, dim3(1), dim3(256), 0, st, B, q, c->st.P_b + b0, c->ws.grp_seq, c->ws.grp_base);
 }
 
 // -------------------------------------------------------------------------

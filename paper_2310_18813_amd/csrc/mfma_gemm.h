@@ -60,7 +60,7 @@ struct GemmArgs {
   const int32_t *row_pos;    // EPI_QKV: absolute position per row, -1 = dead row
   const float2 *rope;        // EPI_QKV: (cos, sin) table [L][hd/2] or null
   int q_rows, d, hd, H, L_pad;
-  int seq_groups;            // EPI_QKV: consecutive groups of q_rows rows per sequence (0 or 1: one)
+  const int32_t *grp_seq;    // EPI_QKV, prefill: the sequence of every group of q_rows rows; null: group b is sequence b
   void *act;                 // EPI_SWIGLU / EPI_RELU: fp16, fragment order, row length f (resp. N)
   int f;
   float *logits;             // EPI_LOGITS: optional [M][N] fp32
@@ -136,7 +136,8 @@ struct AttnArgs {
   float *part_ml;           // [M][H][NC][2] running max (raw score units) and sum
   int shape;                // 0 auto, 1 split + merge, 2 one wave per (sequence, head), 3 one workgroup per (sequence, head)
   int B, q_rows, H, hd, L_pad, NC;  // NC = chunks launched (upper bound over the batch)
-  int seq_groups;           // consecutive groups of q_rows rows that belong to one sequence and share its cache (0 or 1: one)
+  const int32_t *grp_seq;   // prefill: the sequence whose cache each group of q_rows rows reads (several groups share one); null: group b is sequence b
+  int part_rows;            // rows that part_acc and part_ml have room for
   int n_cu;                 // compute units of the device (0: 256)
 };
 // Keys per split.  The chunk boundaries are fixed positions, the same for every launch shape and batch (they decide

@@ -176,7 +176,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int 
       const int cc = cc0 + 4 * g, e = cc - hh * a.hd;
       const int pos = a.row_pos[m];
       int b = row_group(m, a.q_rows, 1.0f / (float)a.q_rows);
-      if (a.seq_groups > 1) b /= a.seq_groups;  // prefill passes only
+      if (a.grp_seq) b = a.grp_seq[b];  // prefill passes only
       if (region < 2) {
         float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
         if (a.rope && pos >= 0) {
@@ -377,7 +377,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
       int b = row_group((mtile0 + mt) * 16 + c, a.q_rows, inv_q);
-      if (a.seq_groups > 1) b /= a.seq_groups;
+      if (a.grp_seq && live[mt]) b = a.grp_seq[b];
       const size_t seq0 = (size_t)b * a.H * a.L_pad * a.hd;
       const int p0 = max(pos[mt], 0);
       krow[mt] = (T *)a.kc + seq0 + (size_t)p0 * a.hd;

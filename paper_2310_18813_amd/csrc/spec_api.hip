@@ -44,6 +44,9 @@ extern "C" const char *spec_last_error(const spec_ctx *c) { return c ? c->err.c_
 // ------------------------------------------------------------------ sizing
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 constexpr int PREFILL_CHUNK = 8;
+constexpr int PREFILL_ROWS = 8192;  // most rows of a prefill pass (33B width: 116 KB of activations a row, 0.95 GB)
+constexpr int PREFILL_Q_MIN = 8;    // fewest rows of a prefill row group
+constexpr int SPLIT_ROWS = 2048;    // most rows of a residual GEMM split by k-slice: beyond, its tiles fill the chip unsplit
 constexpr int Q_LIMIT = 16;  // rows per sequence in one pass (attention query tile)
 
 static int check_model(const spec_model_desc *d, const char *who, int dtype) {
@@ -84,7 +87,9 @@ static int check_run(const spec_run_desc *r) {
 }
 
 struct Sizes {
-  int M_max, q_pass;
+  int M_max, M_pf, q_pass;
+  size_t part_rows, groups;
+  bool generic;
   size_t state, act, tgt_w, tgt_kv, drf_w, drf_kv, total;
   size_t kv_area_tgt, kv_area_drf;
   int L_pad;
@@ -113,14 +118,21 @@ static Sizes compute_sizes(const spec_model_desc *tgt, const spec_model_desc *dr
     size_t kfd = drf->ffn_kind == SPEC_FFN_SWIGLU ? 2 : 1;
     wide = std::max(wide, std::max<size_t>(3 * (size_t)drf->d_model, kfd * drf->d_ffn));
   }
-  const size_t Mp = (M + 15) / 16 * 16;  // fragment-order activation buffers hold whole 16-row tiles
-  z.act = al256(M * d * 4) + 2 * al256(Mp * d * e) + al256(Mp * d * 4) + al256(Mp * f * e) + al256(M * wide * 4) + al256(M * V * 4) +
-          3 * al256(M * 4);
+  // Rows of a prefill pass: every pass reads all weights, and the tiled GEMMs run at their best from a few thousand rows
+  // on, so as many as the prompts can have, up to PREFILL_ROWS (whole 16-row tiles: fragment-order buffers hold those).
+  const size_t prompt_rows = B * ((L + Q_LIMIT - 1) / Q_LIMIT) * Q_LIMIT;
+  const size_t Mp = (std::max<size_t>(M, std::min<size_t>(PREFILL_ROWS, prompt_rows)) + 15) / 16 * 16;
+  z.M_pf = (int)Mp;
+  z.groups = B * ((L + PREFILL_Q_MIN - 1) / PREFILL_Q_MIN);
+  z.generic = !fast_supported(*tgt, run->dtype) || (drf && !fast_supported(*drf, run->dtype));
+  z.act = al256(Mp * d * 4) + 2 * al256(Mp * d * e) + al256(Mp * d * 4) + al256(Mp * f * e) + al256((z.generic ? Mp : 0) * wide * 4) +
+          al256((z.generic ? M : 0) * V * 4) + 2 * al256(Mp * 4) + 2 * al256(z.groups * 4);
   // matrix-core path: split-KV attention partials and per-strip arg-max partials
   const size_t NC = (size_t)attn_chunk_of((int)std::max<size_t>(L, 1) - 1) + 1, NTh = (V + 15) / 16;
   z.act += al256(M * d * NC * 4) + al256(M * (d / 64 + 1) * NC * 2 * 4) + 2 * al256(M * NTh * 4);
-  if (M > 32) z.act += al256(8 * Mp * d * 4);  // k-slice sums of the split residual GEMMs
-  z.act += 2 * al256(M * 4);  // 1 / rms (or 1 / std) and mean per row (folded norm)
+  z.part_rows = Mp > 32 ? std::min<size_t>(Mp, SPLIT_ROWS) : 0;
+  z.act += al256(8 * z.part_rows * d * 4);  // k-slice sums of the split residual GEMMs
+  z.act += 2 * al256(Mp * 4);  // 1 / rms (or 1 / std) and mean per row (folded norm)
   z.tgt_w = packed_bytes(*tgt, run->dtype, run->L_max);
   z.kv_area_tgt = B * (size_t)tgt->d_model * z.L_pad;
   z.tgt_kv = 2 * al256((size_t)tgt->n_layers * z.kv_area_tgt * e);
@@ -240,6 +252,8 @@ extern "C" int spec_init(const spec_model_desc *tgt, const spec_weights *tgt_w, 
   }
   Sizes z = compute_sizes(tgt, drf, run);
   c->M_max = z.M_max;
+  c->M_pf = z.M_pf;
+  c->part_rows = (int)z.part_rows;
   char *p = (char *)d_workspace;
   const size_t B = run->B_max, L = run->L_max, s = run->s_max, M = z.M_max, e = dtype_bytes(run->dtype);
   State &S = c->st;
@@ -265,17 +279,18 @@ extern "C" int spec_init(const spec_model_desc *tgt, const spec_weights *tgt_w, 
                                            (drf->ffn_kind == SPEC_FFN_SWIGLU ? 2 : 1) * (size_t)drf->d_ffn));
   }
   Workspace &W = c->ws;
-  W.h = (float *)carve(p, M * d * 4);
-  const size_t Mp = (M + 15) / 16 * 16;
+  const size_t Mp = z.M_pf;
+  W.h = (float *)carve(p, Mp * d * 4);
   W.x = carve(p, Mp * d * e);
   W.q = carve(p, Mp * d * 4);  // fp32 on the matrix-core path, the model dtype on the generic one
   W.attn = carve(p, Mp * d * e);
   W.act = carve(p, Mp * f * e);
-  W.y32 = (float *)carve(p, M * wide * 4);
-  W.logits = (float *)carve(p, M * V * 4);
-  W.row_tok = (int32_t *)carve(p, M * 4);
-  W.row_pos = (int32_t *)carve(p, M * 4);
-  W.row_seq = (int32_t *)carve(p, M * 4);
+  W.y32 = (float *)carve(p, (z.generic ? Mp : 0) * wide * 4);
+  W.logits = (float *)carve(p, (z.generic ? M : 0) * V * 4);
+  W.row_tok = (int32_t *)carve(p, Mp * 4);
+  W.row_pos = (int32_t *)carve(p, Mp * 4);
+  W.grp_seq = (int32_t *)carve(p, z.groups * 4);
+  W.grp_base = (int32_t *)carve(p, z.groups * 4);
   {
     const size_t NC = (size_t)attn_chunk_of((int)std::max<size_t>(L, 1) - 1) + 1, NTh = (V + 15) / 16;
     c->NC_max = (int)NC;
@@ -283,9 +298,9 @@ extern "C" int spec_init(const spec_model_desc *tgt, const spec_weights *tgt_w, 
     W.attn_ml = (float *)carve(p, M * (d / 64 + 1) * NC * 2 * 4);
     W.head_part = (float *)carve(p, M * NTh * 4);
     W.head_part_idx = (int32_t *)carve(p, M * NTh * 4);
-    W.gemm_part = M > 32 ? (float *)carve(p, 8 * Mp * d * 4) : nullptr;
-    W.row_inv = (float *)carve(p, M * 4);
-    W.row_mean = (float *)carve(p, M * 4);
+    W.gemm_part = z.part_rows ? (float *)carve(p, 8 * z.part_rows * d * 4) : nullptr;
+    W.row_inv = (float *)carve(p, Mp * 4);
+    W.row_mean = (float *)carve(p, Mp * 4);
   }
 
   rc = setup_model(c, c->tgt, tgt, tgt_w, p, z.tgt_w, z.kv_area_tgt, z.tgt_kv, z.L_pad);
@@ -445,9 +460,10 @@ static int forward_pass(spec_ctx *c, Model &m, const PassArgs &pa, HeadMode head
   const size_t hbytes = (size_t)M * m.desc.d_model * sizeof(float);
   if (dump) generic_copy(c->ws.h, dump, hbytes, st);
   c->x_ssq = false;  // the rows in ws.x come from the embedding
+  const int32_t *grp_seq = pa.kind == PASS_PREFILL ? c->ws.grp_seq + pa.g0 : nullptr;
   for (int l = 0; l < m.desc.n_layers; ++l) {
-    if (m.fast) fast_layer(c, m, l, pa.B, pa.q, pa.b0, pa.seq_groups, max_pos, st);
-    else generic_layer(c, m, l, M, pa.q, pa.b0, pa.seq_groups, st);
+    if (m.fast) fast_layer(c, m, l, pa.B, pa.q, pa.b0, grp_seq, max_pos, st);
+    else generic_layer(c, m, l, M, pa.q, pa.b0, grp_seq, st);
     if (dump) generic_copy(c->ws.h, (char *)dump + (size_t)(l + 1) * hbytes, hbytes, st);
   }
   if (head != HEAD_NONE) {
@@ -467,36 +483,44 @@ static int forward_pass(spec_ctx *c, Model &m, const PassArgs &pa, HeadMode head
 }
 
 // ------------------------------------------------------------------ prefill
-// The first P-1 prompt tokens of the sequences at slots b0 .. b0+B-1 through both models, in passes of up to
-// M_max rows.  A sequence's share of a pass is cut into groups of Q_LIMIT rows (the attention query tile) at
-// consecutive positions; all groups of a sequence read and write that sequence's cache, so few sequences with
-// long prompts need few passes over the weights (one sequence, M_max >= P-1: a single pass).
-static int prefill(spec_ctx *c, int b0, int B, int P) {
-  int per = std::max(1, c->M_max / B);
-  // The tiled GEMMs' time grows in steps of 128 rows (a pass of 576 rows costs what 640 would): the largest row count
-  // that is a whole number of such steps, if it is within a quarter of the largest that fits, costs least per row
-  // (64 sequences: 8 positions per pass, 512 rows, instead of 9: 7B shape 204 -> 169 ms for 8128 prompt tokens).
-  for (int p = per; p >= 1 && 4 * p >= 3 * per; --p)
-    if ((B * p) % 128 == 0) { per = p; break; }
-  // Fewer positions per sequence than the attention's query tile holds (16) leave the tiles half empty, and every pass
-  // reads the cached prefix again: then take fewer sequences per pass and a full tile of each, where the batch
-  // divides evenly (32 sequences x 2047 prompt tokens of the 33B shape: 16 x 16 rows per pass instead of 32 x 8).
-  int Bs = B;
-  if (per < Q_LIMIT && P - 1 > per) {
-    const int fewer = B * per / Q_LIMIT;
-    if (fewer >= 1 && B % fewer == 0) { Bs = fewer; per = Q_LIMIT; }
+// All but the last prompt token of the sequences at slots b0 .. b0+B-1 through both models.  Each prompt is cut into
+// groups of q rows at consecutive positions (q: the attention's query tile, or half of it where that leaves clearly
+// fewer dead rows behind short prompts); a pass takes as many groups as fit, of any sequences -- all groups of a
+// sequence read and write that sequence's cache, and a pass appends its rows' keys and values before it attends.
+// Passes are bound by the matrix products from a few hundred rows on and by their weights below that, so few large
+// ones, of about equal size, cost least (33B width, 5 prompts of up to 2011 tokens: 252 passes of 40 rows -> 1 of 7584).
+static int prefill(spec_ctx *c, int b0, int B) {
+  const int32_t *P = c->P_host.data() + b0;
+  long long rows16 = 0, rows8 = 0;
+  for (int b = 0; b < B; ++b) {
+    rows16 += (P[b] - 1 + Q_LIMIT - 1) / Q_LIMIT * Q_LIMIT;
+    rows8 += (P[b] - 1 + PREFILL_Q_MIN - 1) / PREFILL_Q_MIN * PREFILL_Q_MIN;
   }
-  const int q = std::min(Q_LIMIT, per), g = std::max(1, per / q);
-  for (int bs = 0; bs < B; bs += Bs)
-    for (int base = 0; base < P - 1; base += g * q) {
-      const int left = P - 1 - base;
-      const int gp = std::min(g, (left + q - 1) / q);          // groups per sequence that still hold positions
-      PassArgs pa{PASS_PREFILL, Bs * gp, q, base, P, c->run.s_max, c->run.L_max, b0 + bs, gp};
-      const int max_pos = base + std::min(left, gp * q) - 1;
-      int rc = forward_pass(c, c->tgt, pa, HEAD_NONE, nullptr, nullptr, 0, max_pos);
-      if (!rc && c->drf.present) rc = forward_pass(c, c->drf, pa, HEAD_NONE, nullptr, nullptr, 0, max_pos);
-      if (rc) return rc;
+  if (rows8 == 0) return SPEC_OK;
+  const int q = 8 * rows8 < 7 * rows16 ? PREFILL_Q_MIN : Q_LIMIT;
+  const long long rows = q == Q_LIMIT ? rows16 : rows8;
+  // the caller's dump buffer of spec_set_hidden_dump holds B_max * 16 rows a slice
+  const int fit = c->hidden_dump ? std::min(c->M_pf, c->run.B_max * Q_LIMIT) : c->M_pf;
+  const long long passes = (rows + fit - 1) / fit;
+  const int per = (int)std::min<long long>(fit, ((rows + passes - 1) / passes + 255) / 256 * 256) / q;  // groups per pass
+  launch_prefill_groups(c, b0, B, q, c->stream);
+  const int groups = (int)(rows / q);
+  int b = 0, start = 0;  // the sequence the pass's first group belongs to, and that sequence's first group
+  for (int g0 = 0; g0 < groups; g0 += per) {
+    const int n = std::min(per, groups - g0);
+    int max_pos = 0;  // the largest position of the pass
+    while (start < g0 + n) {
+      const int own = (P[b] - 1 + q - 1) / q;
+      max_pos = std::max(max_pos, std::min(P[b] - 2, (g0 + n - start) * q - 1));
+      if (start + own > g0 + n) break;
+      start += own;
+      ++b;
     }
+    PassArgs pa{PASS_PREFILL, n, q, 0, b0, g0};
+    int rc = forward_pass(c, c->tgt, pa, HEAD_NONE, nullptr, nullptr, 0, max_pos);
+    if (!rc && c->drf.present) rc = forward_pass(c, c->drf, pa, HEAD_NONE, nullptr, nullptr, 0, max_pos);
+    if (rc) return rc;
+  }
   return SPEC_OK;
 }
 
@@ -541,7 +565,7 @@ static int do_reset(spec_ctx *c, int32_t B, const int32_t *d_prompt, int32_t P, 
   }
   launch_state_reset(c, d_prompt, stride, h_len != nullptr, c->stream);
   if (prefill) {
-    int rc = ::prefill(c, 0, B, P);
+    int rc = ::prefill(c, 0, B);
     if (rc) return rc;
   }
   HIPCHK(c, hipGetLastError());
@@ -580,7 +604,7 @@ extern "C" int spec_admit(spec_ctx *c, int32_t b, const int32_t *d_prompt, int32
   launch_state_admit(c, b, d_prompt, P, c->stream);
   c->P_host[(size_t)b] = P;
   c->n_ub = std::max(c->n_ub, (int)P);
-  int rc = prefill(c, b, 1, P);
+  int rc = prefill(c, b, 1);
   if (rc) return rc;
   HIPCHK(c, hipGetLastError());
   return SPEC_OK;
@@ -670,16 +694,16 @@ extern "C" int spec_draft_step(spec_ctx *c, int32_t j) {
     int lag = std::max(1, std::min(c->draft_lag, c->n_ub));
     rc = SPEC_OK;
     while (lag > q_cap && !rc) {
-      PassArgs pa{PASS_DRAFT_FIRST, c->B, q_cap, lag - q_cap, c->P, c->run.s_max, c->run.L_max};
+      PassArgs pa{PASS_DRAFT_FIRST, c->B, q_cap, lag - q_cap};
       rc = forward_pass(c, c->drf, pa, HEAD_NONE, nullptr, nullptr, 0, c->n_ub - 1);
       lag -= q_cap;
     }
     if (!rc) {
-      PassArgs pa{PASS_DRAFT_FIRST, c->B, lag, 0, c->P, c->run.s_max, c->run.L_max};
+      PassArgs pa{PASS_DRAFT_FIRST, c->B, lag, 0};
       rc = forward_pass(c, c->drf, pa, HEAD_LAST, lg, arg_out, arg_stride_used, c->n_ub - 1);
     }
   } else {
-    PassArgs pa{PASS_DRAFT_NEXT, c->B, 1, j, c->P, c->run.s_max, c->run.L_max};
+    PassArgs pa{PASS_DRAFT_NEXT, c->B, 1, j};
     rc = forward_pass(c, c->drf, pa, HEAD_LAST, lg, arg_out, arg_stride_used, c->n_ub + j - 2);
   }
   if (rc) return rc;
@@ -705,7 +729,7 @@ extern "C" int spec_verify_step(spec_ctx *c, int32_t s, float *d_logits_or_null)
     return fail(c, SPEC_ERR_STATE, "spec_verify_step: %d draft steps were run for s=%d", c->draft_j, s);
   int rc = ensure_proposals(c, s, "spec_verify_step");
   if (rc) return rc;
-  PassArgs pa{PASS_VERIFY, c->B, s + 1, 0, c->P, c->run.s_max, c->run.L_max};
+  PassArgs pa{PASS_VERIFY, c->B, s + 1, 0};
   float *lg = d_logits_or_null ? d_logits_or_null : c->smp_u ? c->smp_tl : nullptr;
   rc = forward_pass(c, c->tgt, pa, HEAD_ALL, lg, c->st.a, c->run.s_max + 1, c->n_ub - 1 + s);
   if (rc) return rc;

@@ -71,7 +71,7 @@ enum PassKind {
   PASS_VERIFY = 0,      // rows (b,i), i=0..q-1: pending token then proposals, positions n_b-1+i
   PASS_DRAFT_FIRST = 1, // rows (b,i): committed tokens at positions n_b-j-q+i; rows before kv_len_b are dead
   PASS_DRAFT_NEXT = 2,  // q = 1: proposal t_{j-1} at position n_b+j-2
-  PASS_PREFILL = 3      // rows (b,i): prompt tokens at positions base+i; rows >= P-1 are dead
+  PASS_PREFILL = 3      // rows (g,i): prompt tokens of group g's sequence at positions base_g+i; rows >= P_b-1 are dead
 };
 
 struct Workspace {
@@ -89,7 +89,8 @@ struct Workspace {
   float *gemm_part = nullptr;                      // k-slice sums of the split residual GEMMs (M_max > 32)
   float *head_part = nullptr;                      // per-strip arg-max partials (MFMA path)
   int32_t *head_part_idx = nullptr;
-  int32_t *row_tok = nullptr, *row_pos = nullptr, *row_seq = nullptr;  // [M_max]
+  int32_t *row_tok = nullptr, *row_pos = nullptr;  // [M_pf]
+  int32_t *grp_seq = nullptr, *grp_base = nullptr; // prefill: sequence (counted from the first slot) and first position of every row group
 };
 
 struct State {
@@ -114,7 +115,9 @@ struct spec_ctx {
   spec::Workspace ws;
   spec::State st;
   hipStream_t stream = nullptr;
-  int M_max = 0;
+  int M_max = 0;          // rows of a decoding pass
+  int M_pf = 0;           // rows of a prefill pass (at least M_max)
+  int part_rows = 0;      // rows ws.gemm_part has room for
   int NC_max = 1;         // attention chunks that cover L_max
   int n_ub = 0;           // host upper bound of every sequence's committed length
   // host-side bookkeeping
@@ -181,13 +184,11 @@ namespace spec {
 struct PassArgs {
   PassKind kind;
   int B, q;      // rows M = B*q
-  int j;         // draft step index (PASS_DRAFT_NEXT) / prefill base position (PASS_PREFILL) /
-                 // PASS_DRAFT_FIRST: how many positions before n_b the pass ends (0: at n_b - 1)
-  int P;         // prompt length (PASS_PREFILL)
-  int s_max, L_max;
+  int j;         // draft step index (PASS_DRAFT_NEXT) / PASS_DRAFT_FIRST: how many positions before n_b the pass ends
+                 // (0: at n_b - 1)
   int b0 = 0;    // first batch slot of the pass: its rows are the sequences b0 .. b0 + B - 1
-  int seq_groups = 1;  // PASS_PREFILL: this many consecutive groups of q rows belong to one sequence (B counts groups):
-                       // group g of a sequence holds positions base + g*q .. and all its groups share the sequence's cache
+  int g0 = 0;    // PASS_PREFILL: B counts groups of q rows at consecutive positions of one sequence, and the pass takes
+                 // the groups g0 .. g0 + B - 1 of the table in the workspace (launch_prefill_groups)
 };
 
 void launch_assemble_embed(const spec_ctx *c, const Model &m, const PassArgs &pa, hipStream_t st);
@@ -203,6 +204,7 @@ void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, i
                           const int32_t *t, int t_stride, const int32_t *seq_s, const float *u, const int32_t *n, int u_rows,
                           int32_t *a, int a_stride, hipStream_t st);
 void launch_fill_proposals(spec_ctx *c, int s, hipStream_t st);
+void launch_prefill_groups(const spec_ctx *c, int b0, int B, int q, hipStream_t st);
 void launch_copy_proposals(spec_ctx *c, const int32_t *d_tok, int s, hipStream_t st);
 void launch_state_reset(spec_ctx *c, const int32_t *d_prompt, int P_stride, bool ragged, hipStream_t st);
 void launch_state_admit(spec_ctx *c, int b, const int32_t *d_prompt, int P, hipStream_t st);
@@ -212,7 +214,7 @@ void launch_kv_convert(spec_ctx *c, const Model &m, int layer, int B, int len, v
 // generic kernels (any dtype, any shape)
 void generic_repack_top(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);
 void generic_repack_layer(spec_ctx *c, Model &m, int layer, const spec_weights *w, void *&cursor, hipStream_t st);
-void generic_layer(spec_ctx *c, const Model &m, int layer, int M, int q_rows, int b0, int seq_groups, hipStream_t st);
+void generic_layer(spec_ctx *c, const Model &m, int layer, int M, int q_rows, int b0, const int32_t *grp_seq, hipStream_t st);
 void generic_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits, hipStream_t st);
 size_t generic_packed_bytes(const spec_model_desc &d, int dtype);
 void generic_copy(const void *src, void *dst, size_t bytes, hipStream_t st);
@@ -225,7 +227,7 @@ int fail_noctx(int code, const char *fmt, ...);  // records the message spec_las
 bool fast_supported(const spec_model_desc &D, int dtype);
 size_t fast_packed_bytes(const spec_model_desc &D, int dtype, int L_max);
 bool fast_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);  // false: HIP error
-void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, int seq_groups, int max_pos, hipStream_t st);
+void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, int max_pos, hipStream_t st);
 void fast_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits_or_null, int q, int arg_stride,
                int32_t *arg_out, hipStream_t st);
 
