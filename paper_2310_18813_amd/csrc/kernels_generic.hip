@@ -1,5 +1,5 @@
 // Generic kernels: every dtype (fp32 / bf16 / fp16) and every model shape.  They are the
-// path for fp32 runs and for 16-bit shapes the MFMA kernels do not cover.  Plain ALU
+// path for the shapes the MFMA kernels (16-bit and fp32) do not cover.  Plain ALU
 // arithmetic in fp32; each output element is reduced in an order fixed by the operand
 // shapes alone (never by the number of rows in the pass), so a sequence's tokens do not
 // depend on batch size or speculation length.

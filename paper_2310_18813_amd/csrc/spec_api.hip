@@ -96,7 +96,8 @@ struct Sizes {
 };
 
 static size_t packed_bytes(const spec_model_desc &d, int dtype, int L_max) {
-  return fast_supported(d, dtype) ? fast_packed_bytes(d, dtype, L_max) : generic_packed_bytes(d, dtype);
+  if (fast_supported(d, dtype)) return fast_packed_bytes(d, dtype, L_max);
+  return fp32_supported(d, dtype) ? fp32_packed_bytes(d, L_max) : generic_packed_bytes(d, dtype);
 }
 
 static Sizes compute_sizes(const spec_model_desc *tgt, const spec_model_desc *drf, const spec_run_desc *run) {
@@ -124,7 +125,8 @@ static Sizes compute_sizes(const spec_model_desc *tgt, const spec_model_desc *dr
   const size_t Mp = (std::max<size_t>(M, std::min<size_t>(PREFILL_ROWS, prompt_rows)) + 15) / 16 * 16;
   z.M_pf = (int)Mp;
   z.groups = B * ((L + PREFILL_Q_MIN - 1) / PREFILL_Q_MIN);
-  z.generic = !fast_supported(*tgt, run->dtype) || (drf && !fast_supported(*drf, run->dtype));
+  auto is_generic = [&](const spec_model_desc &m) { return !fast_supported(m, run->dtype) && !fp32_supported(m, run->dtype); };
+  z.generic = is_generic(*tgt) || (drf && is_generic(*drf));
   z.act = al256(Mp * d * 4) + 2 * al256(Mp * d * e) + al256(Mp * d * 4) + al256(Mp * f * e) + al256((z.generic ? Mp : 0) * wide * 4) +
           al256((z.generic ? M : 0) * V * 4) + 2 * al256(Mp * 4) + 2 * al256(z.groups * 4);
   // matrix-core path: split-KV attention partials and per-strip arg-max partials
@@ -195,10 +197,13 @@ static int setup_model(spec_ctx *c, Model &m, const spec_model_desc *d, const sp
   m.hd = d->d_model / d->n_heads;
   m.L_pad = L_pad;
   m.fast = fast_supported(*d, c->run.dtype);
+  m.f32 = fp32_supported(*d, c->run.dtype);
   m.layers.resize(d->n_layers);
   void *cursor = p;
   if (m.fast) {
     if (!fast_setup_model(c, m, w, cursor, c->stream)) return fail(c, SPEC_ERR_HIP, "spec_init: weight packing failed");
+  } else if (m.f32) {
+    fp32_setup_model(c, m, w, cursor, c->stream);
   } else {
     generic_repack_top(c, m, w, cursor, c->stream);
     for (int l = 0; l < d->n_layers; ++l) generic_repack_layer(c, m, l, w, cursor, c->stream);
@@ -233,7 +238,7 @@ extern "C" int spec_init(const spec_model_desc *tgt, const spec_weights *tgt_w, 
   if ((uintptr_t)d_workspace % 256 != 0) return fail(nullptr, SPEC_ERR_WORKSPACE, "spec_init: workspace must be 256-byte aligned");
   if (workspace_bytes < need)
     return fail(nullptr, SPEC_ERR_WORKSPACE, "spec_init: workspace has %zu bytes, %zu needed", workspace_bytes, need);
-  // generic attention keeps one fp32 score per key in LDS
+  // the generic attention keeps one fp32 score per key in LDS
   if ((size_t)run->L_max * 4 + 64 > 64 * 1024)
     return fail(nullptr, SPEC_ERR_UNSUPPORTED, "spec_init: L_max above 16368 is not supported");
 
@@ -463,6 +468,7 @@ static int forward_pass(spec_ctx *c, Model &m, const PassArgs &pa, HeadMode head
   const int32_t *grp_seq = pa.kind == PASS_PREFILL ? c->ws.grp_seq + pa.g0 : nullptr;
   for (int l = 0; l < m.desc.n_layers; ++l) {
     if (m.fast) fast_layer(c, m, l, pa.B, pa.q, pa.b0, grp_seq, max_pos, st);
+    else if (m.f32) fp32_layer(c, m, l, pa.B, pa.q, pa.b0, grp_seq, st);
     else generic_layer(c, m, l, M, pa.q, pa.b0, grp_seq, st);
     if (dump) generic_copy(c->ws.h, (char *)dump + (size_t)(l + 1) * hbytes, hbytes, st);
   }
@@ -472,6 +478,8 @@ static int forward_pass(spec_ctx *c, Model &m, const PassArgs &pa, HeadMode head
     const int last_of_q = last ? pa.q : 0;  // the final norm gathers the rows that need a token
     if (m.fast) {
       fast_head(c, m, Mh, last_of_q, logits_out, last ? 1 : pa.q, arg_stride, arg_out, st);
+    } else if (m.f32) {
+      fp32_head(c, m, Mh, last_of_q, logits_out, last ? 1 : pa.q, arg_stride, arg_out, st);
     } else {
       float *lg = logits_out ? logits_out : c->ws.logits;
       generic_head(c, m, Mh, last_of_q, lg, st);

@@ -51,7 +51,8 @@ struct Model {
   bool present = false;
   spec_model_desc desc{};
   int hd = 0, L_pad = 0;
-  bool fast = false;  // MFMA kernels (16-bit dtypes with supported shapes) or generic kernels
+  bool fast = false;  // 16-bit matrix-core kernels (supported shapes) ...
+  bool f32 = false;   // ... or fp32 ones; neither: generic kernels
   // MFMA path: the norms live inside the GEMMs behind them (gain in the packed weights, 1 / rms in the epilogue)
   bool fold_ln = false;    // ... and they are LayerNorms (mean taken out in the epilogue, bias pushed through the weights)
   const float *wsum_head = nullptr, *b_head = nullptr;
@@ -219,6 +220,14 @@ void generic_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *log
 size_t generic_packed_bytes(const spec_model_desc &d, int dtype);
 void generic_copy(const void *src, void *dst, size_t bytes, hipStream_t st);
 void generic_zero(void *dst, size_t bytes, hipStream_t st);
+
+// fp32 matrix-core path (kernels_fp32.hip)
+bool fp32_supported(const spec_model_desc &D, int dtype);
+size_t fp32_packed_bytes(const spec_model_desc &D, int L_max);
+void fp32_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);
+void fp32_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, hipStream_t st);
+void fp32_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits_or_null, int q, int arg_stride,
+               int32_t *arg_out, hipStream_t st);
 
 size_t dtype_bytes(int dtype);
 int fail_noctx(int code, const char *fmt, ...);  // records the message spec_last_error(NULL) returns; returns code
