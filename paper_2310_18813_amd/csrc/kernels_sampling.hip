@@ -12,142 +12,225 @@
 // at the first rejection (never equal to the rejected proposal: its residual weight is zero), the bonus draw
 // behind s kept proposals.  Commit, roll-back, end token and budgets then work as in the greedy case.
 //
-// One workgroup per row (proposal draws) or per sequence (verification); a thread owns a contiguous chunk of the
-// vocabulary; chunk sums are added in thread order by every thread alike, so a draw depends on the row alone.
+// One workgroup per row (proposal draws) or per (sequence, place of the round) (verification).  A wave owns a contiguous
+// segment of the vocabulary and walks it 256 logits at a time, four per lane; lanes, then waves are added in a fixed
+// order by every thread alike, so a draw depends on the row alone.
+//
+// Bound by latency and by what one CU can stream: a row of 32000 logits is 128 KB and a place needs two of them.  All
+// places of a round are therefore decided at once, each as if its round reached it (draws behind the first rejection are
+// thrown away by k_sample_seal), so the rows of a round stream through B * (s + 1) CUs instead of one after the other
+// through B; a row is read once for maximum and sum together, and once more (from L2) where a token is drawn from it.
+// A thread with a contiguous chunk of its own (loads 512 bytes apart across a wave) and a pass for each of maximum and
+// sum, places in turn, took 87 us for 64 sequences x 4 places of 32000 logits with draft rows; this takes 30 us.
 #include "spec_internal.h"
 #include "device_utils.h"
+#include <algorithm>
 
 namespace spec {
 
 #pragma clang fp contract(off)
 
-constexpr int SMP_THREADS = 256;
+constexpr int SMP_THREADS = 1024;
+constexpr int SMP_WAVES = SMP_THREADS / 64;
+constexpr int SMP_STEP = 256;   // logits per wave and step: a float4 per lane
 
-struct Chunk { int k0, k1; };
-__device__ __forceinline__ Chunk my_chunk(int V) {
-  const int per = ((V + SMP_THREADS - 1) / SMP_THREADS + 3) & ~3;  // a multiple of four: chunks start 16-byte aligned
-  Chunk c;
-  c.k0 = min(V, (int)threadIdx.x * per);
-  c.k1 = min(V, c.k0 + per);
-  return c;
+// this wave's part of the row: [k0, end), k0 a multiple of SMP_STEP (empty: end <= k0)
+struct Seg { int k0, end; };
+__device__ __forceinline__ Seg my_seg(int V) {
+  const int per = ((V - 1) / (SMP_WAVES * SMP_STEP) + 1) * SMP_STEP;
+  const int k0 = (int)(threadIdx.x >> 6) * per;
+  return Seg{k0, V - k0 < per ? V : k0 + per};
 }
 
-// z[k .. k+3] (k a multiple of four), `fill` beyond the row; one 16-byte load when the row allows it
-__device__ __forceinline__ void load4z(const float *__restrict__ z, int k, int V, bool vec, float fill, float (&o)[4]) {
-  if (vec) {
-    const float4 v = *(const float4 *)(z + k);
-    o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+// z[k .. k+3] (k a multiple of four), -inf from `end` on.  VEC: one 16-byte load, for V a multiple of four and rows
+// aligned to 16 bytes; the launch chooses.  The addresses are clamped into the row instead of branched around, so that
+// the loads of several steps can be in flight together.
+template <bool VEC>
+__device__ __forceinline__ void load4z(const float *__restrict__ z, int k, int V, int end, float (&o)[4]) {
+  constexpr float fill = -INFINITY;
+  if (VEC) {
+    const float4 v = *(const float4 *)(z + min(k, V - 4));
+    const bool in = k < end;  // V and every segment's end are multiples of four here
+    o[0] = in ? v.x : fill; o[1] = in ? v.y : fill; o[2] = in ? v.z : fill; o[3] = in ? v.w : fill;
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = k + i < V ? z[k + i] : fill;
+    for (int i = 0; i < 4; ++i) {
+      const float v = z[min(k + i, V - 1)];
+      o[i] = k + i < end ? v : fill;
+    }
   }
 }
-__device__ __forceinline__ bool row_vec(const float *z, int V) { return (V & 3) == 0 && ((uintptr_t)z & 15) == 0; }
+// steps whose loads are in flight together (single loads need four addresses a step)
+template <bool VEC> constexpr int SMP_UNROLL = VEC ? 8 : 2;
 
-// Workgroup-wide maximum / sum / exclusive prefix of one value per thread.  The order of the additions is fixed by the
-// thread numbers alone (shuffles inside a wave, then the waves in order), so every thread sees the same bits and a
-// row's result does not depend on anything but the row.  sh: at least SMP_THREADS / 64 + 1 floats.
-__device__ __forceinline__ float block_max_all(float v, float *sh) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+// Exclusive prefix over the waves of one value per wave, *total = the sum over the workgroup: added in wave order, the
+// same bits in every thread.  sh: SMP_WAVES floats.
+__device__ __forceinline__ float waves_prefix(float v, float *sh, float *total) {
+  const int wv = threadIdx.x >> 6;
   __syncthreads();  // sh may still be read by the previous user
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float m = sh[0];
-#pragma unroll
-  for (int i = 1; i < SMP_THREADS / 64; ++i) m = fmaxf(m, sh[i]);
-  return m;
-}
-// inclusive prefix inside the wave (lane l: v_0 + ... + v_l, added pairwise by doubling distances), the waves' totals
-// through LDS; returns the exclusive prefix of this thread, *total = the sum over the workgroup
-__device__ __forceinline__ float block_prefix(float v, float *sh, float *total) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  float inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const float up = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += up;
-  }
-  __syncthreads();
-  if (lane == 63) sh[wv] = inc;
+  if ((threadIdx.x & 63) == 0) sh[wv] = v;
   __syncthreads();
   float before = 0.f, all = 0.f;
 #pragma unroll
-  for (int i = 0; i < SMP_THREADS / 64; ++i) {
+  for (int i = 0; i < SMP_WAVES; ++i) {
     if (i == wv) before = all;
     all += sh[i];
   }
   *total = all;
-  return before + (inc - v);
+  return before;
 }
 
-// max over the row and sum of exp((z - max) * inv_T), the same bits in every thread
-template <bool WANT_SUM = true>
-__device__ __forceinline__ void row_stats(const float *__restrict__ z, int V, float inv_T, float *sh, float &m, float &Z) {
-  const Chunk c = my_chunk(V);
-  const bool vec = row_vec(z, V);
+// maximum of a row, the same in every thread
+template <bool VEC>
+__device__ __forceinline__ float row_max(const float *__restrict__ z, int V, float *sh) {
+  const Seg g = my_seg(V);
+  const int lane4 = (threadIdx.x & 63) * 4;
+  constexpr int U = SMP_UNROLL<VEC>;
   float lm = -INFINITY;
-#pragma unroll 8
-  for (int k = c.k0; k < c.k1; k += 4) {
-    float v[4];
-    load4z(z, k, V, vec, -INFINITY, v);
-    lm = fmaxf(fmaxf(lm, v[0]), fmaxf(fmaxf(v[1], v[2]), v[3]));
-  }
-  m = block_max_all(lm, sh);
-  Z = 0.f;
-  if (!WANT_SUM) return;
-  float ls = 0.f;
-#pragma unroll 8
-  for (int k = c.k0; k < c.k1; k += 4) {
-    float v[4];
-    load4z(z, k, V, vec, -INFINITY, v);  // exp(-inf) = 0 beyond the row
+#pragma unroll 1
+  for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
+    float v[U][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ls += __expf((v[i] - m) * inv_T);
+    for (int i = 0; i < U; ++i) load4z<VEC>(z, k + i * SMP_STEP + lane4, V, g.end, v[i]);
+#pragma unroll
+    for (int i = 0; i < U; ++i) lm = fmaxf(fmaxf(lm, v[i][0]), fmaxf(fmaxf(v[i][1], v[i][2]), v[i][3]));
   }
-  block_prefix(ls, sh, &Z);
+  lm = wave_max(lm);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = lm;
+  __syncthreads();
+  float m = sh[0];
+#pragma unroll
+  for (int i = 1; i < SMP_WAVES; ++i) m = fmaxf(m, sh[i]);
+  return m;
 }
 
-// Draw with u from the weights w4(k, out) -> weights of k .. k+3 (zero beyond the row), k a multiple of four:
+// Running (maximum, sum of exp((z - maximum) * inv_T)).  -inf counts as weight 0 also while the maximum is -inf.
+__device__ __forceinline__ float rescaled(float Z, float m, float m_new, float inv_T) {
+  return m == -INFINITY ? Z : Z * __expf((m - m_new) * inv_T);
+}
+template <int U>
+__device__ __forceinline__ void stats_step(const float (&v)[U][4], float inv_T, float &m, float &Z) {
+  float mn = m;
+#pragma unroll
+  for (int i = 0; i < U; ++i) mn = fmaxf(fmaxf(mn, v[i][0]), fmaxf(fmaxf(v[i][1], v[i][2]), v[i][3]));
+  float ls = 0.f;
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ls += v[i][e] == -INFINITY ? 0.f : __expf((v[i][e] - mn) * inv_T);
+  Z = rescaled(Z, m, mn, inv_T) + ls;
+  m = mn;
+}
+
+// Maximum and sum of exp((z - max) * inv_T) of a target row and, PAIR, of a draft row, the same bits in every thread
+// (a row of -inf alone has no distribution: its sum is NaN).  sh: 4 * SMP_WAVES floats.
+struct RowStats { float m, Z; };
+template <bool VEC, bool PAIR>
+__device__ __forceinline__ void row_stats(const float *__restrict__ zp, const float *__restrict__ zq, int V, float inv_T,
+                                          float *sh, RowStats &p, RowStats &q) {
+  const Seg g = my_seg(V);
+  const int lane4 = (threadIdx.x & 63) * 4, wv = threadIdx.x >> 6;
+  constexpr int U = SMP_UNROLL<VEC>;
+  float mp = -INFINITY, Zp = 0.f, mq = -INFINITY, Zq = 0.f;
+#pragma unroll 1
+  for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
+    float v[U][4], w[U][4];
+#pragma unroll
+    for (int i = 0; i < U; ++i) load4z<VEC>(zp, k + i * SMP_STEP + lane4, V, g.end, v[i]);
+    if (PAIR) {
+#pragma unroll
+      for (int i = 0; i < U; ++i) load4z<VEC>(zq, k + i * SMP_STEP + lane4, V, g.end, w[i]);
+    }
+    stats_step<U>(v, inv_T, mp, Zp);
+    if (PAIR) stats_step<U>(w, inv_T, mq, Zq);
+  }
+  const float wmp = wave_max(mp), wZp = wave_sum(rescaled(Zp, mp, wmp, inv_T));
+  float wmq = 0.f, wZq = 0.f;
+  if (PAIR) { wmq = wave_max(mq); wZq = wave_sum(rescaled(Zq, mq, wmq, inv_T)); }
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) {
+    sh[wv] = wmp; sh[SMP_WAVES + wv] = wZp;
+    if (PAIR) { sh[2 * SMP_WAVES + wv] = wmq; sh[3 * SMP_WAVES + wv] = wZq; }
+  }
+  __syncthreads();
+  auto combine = [&](const float *s) {
+    RowStats r{s[0], 0.f};
+#pragma unroll
+    for (int i = 1; i < SMP_WAVES; ++i) r.m = fmaxf(r.m, s[i]);
+#pragma unroll
+    for (int i = 0; i < SMP_WAVES; ++i) r.Z += rescaled(s[SMP_WAVES + i], s[i], r.m, inv_T);
+    if (r.m == -INFINITY) r.Z = __builtin_nanf("");
+    return r;
+  };
+  p = combine(sh);
+  if (PAIR) q = combine(sh + 2 * SMP_WAVES);
+}
+
+// Draw with u from the weights w4(k, end, out) -> weights of k .. k+3 (zero from `end` on), k a multiple of four:
 // every thread returns the same index.  *total_out: the sum of all weights.
 template <class W4>
 __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int *sh_i, float *total_out = nullptr) {
-  const Chunk c = my_chunk(V);
+  const Seg g = my_seg(V);
+  const int lane = threadIdx.x & 63, lane4 = lane * 4, wv = threadIdx.x >> 6;
+  constexpr int U = W4::UNROLL;
   float local = 0.f;
-#pragma unroll 8
-  for (int k = c.k0; k < c.k1; k += 4) {
-    float w[4];
-    w4(k, w);
+#pragma unroll 1
+  for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
+    float w[U][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) local += w[i];
+    for (int i = 0; i < U; ++i) w4(k + i * SMP_STEP + lane4, g.end, w[i]);
+#pragma unroll
+    for (int i = 0; i < U; ++i) local += (w[i][0] + w[i][1]) + (w[i][2] + w[i][3]);
   }
+  local = wave_sum(local);
   float total;
-  const float excl = block_prefix(local, sh, &total);
+  const float excl = waves_prefix(local, sh, &total);
   if (threadIdx.x == 0) *sh_i = -1;
   if (total_out) *total_out = total;
   float x = u * total;
   if (!(x < total)) x = total * 0.99999994f;  // u < 1, but the product may round up to the total
   __syncthreads();
-  // the owner of x: the last thread with weight whose prefix does not exceed x (the prefixes come from sums in
+  // the owner of x: the last wave with weight whose prefix does not exceed x (the prefixes come from sums in
   // different associations, so "prefix <= x < prefix + local" could leave a hair's gap between neighbours)
-  if (local > 0.f && excl <= x) atomicMax(sh_i, (int)threadIdx.x);
+  if (lane == 0 && local > 0.f && excl <= x) atomicMax(sh_i, wv);
   __syncthreads();
   const int owner = *sh_i;
   __syncthreads();
-  if ((int)threadIdx.x == owner) {
+  if (wv == owner) {
     float run = excl;
-    int pick = -1, last = -1;
-  #pragma unroll 8
-  for (int k = c.k0; k < c.k1; k += 4) {
+    int pick = -1, last = -1;  // wave-wide pick; this lane's last token with weight
+#pragma unroll 1
+    for (int k = g.k0; k < g.end && pick < 0; k += SMP_STEP) {
+      const int kl = k + lane4;
       float w[4];
-      w4(k, w);
+      w4(kl, g.end, w);
+      const float mine = (w[0] + w[1]) + (w[2] + w[3]);
+      float inc = mine;  // inclusive prefix over the lanes, added pairwise by doubling distances
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const float up = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += up;
+      }
+      int own = -1;  // the first of this lane's tokens whose cumulative weight exceeds x, or the nearest one with weight
+      float c = run + (inc - mine);
+      bool past = false;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if (w[i] > 0.f) last = k + i;
-        run += w[i];
-        if (pick < 0 && run > x) pick = k + i;
+        c += w[i];
+        if (w[i] > 0.f) {
+          last = kl + i;
+          if (!past || own < 0) own = kl + i;
+        }
+        past |= c > x;
       }
+      const unsigned long long hit = __ballot(mine > 0.f && run + inc > x);
+      if (hit) pick = __shfl(own, __ffsll(hit) - 1, 64);
+      run += __shfl(inc, 63, 64);
     }
-    *sh_i = pick >= 0 ? pick : last;  // the walk may end a hair below x: then the chunk's last token
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
+    if (lane == 0) *sh_i = pick >= 0 ? pick : last;  // the walk may end a hair below x: then the segment's last token
   } else if (owner < 0 && threadIdx.x == 0) {
     *sh_i = 0;  // all weights zero or not finite: the lowest index, as the greedy rule does for a row of NaNs
   }
@@ -156,21 +239,25 @@ __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int 
 }
 
 // weights exp((z - m) * inv_T) of a row, optionally with one token removed
+template <bool VEC>
 struct ExpW {
-  const float *z; int V; bool vec; float m, inv_T; int drop;
-  __device__ __forceinline__ void operator()(int k, float (&w)[4]) const {
+  static constexpr int UNROLL = SMP_UNROLL<VEC>;
+  const float *z; int V; float m, inv_T; int drop;
+  __device__ __forceinline__ void operator()(int k, int end, float (&w)[4]) const {
     float v[4];
-    load4z(z, k, V, vec, -INFINITY, v);
+    load4z<VEC>(z, k, V, end, v);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = (k + i == drop) ? 0.f : __expf((v[i] - m) * inv_T);
+    for (int i = 0; i < 4; ++i) w[i] = (k + i == drop || k + i >= end) ? 0.f : __expf((v[i] - m) * inv_T);
   }
 };
 // residual weights max(0, p - q) of a target and a draft row
+template <bool VEC>
 struct ResidW {
-  ExpW p, q; float ip, iq;
-  __device__ __forceinline__ void operator()(int k, float (&w)[4]) const {
+  static constexpr int UNROLL = SMP_UNROLL<VEC> / 2;  // two rows a step
+  ExpW<VEC> p, q; float ip, iq;
+  __device__ __forceinline__ void operator()(int k, int end, float (&w)[4]) const {
     float a[4], b[4];
-    p(k, a); q(k, b);
+    p(k, end, a); q(k, end, b);
 #pragma unroll
     for (int i = 0; i < 4; ++i) { const float r = a[i] * ip - b[i] * iq; w[i] = r > 0.f ? r : 0.f; }
   }
@@ -185,104 +272,117 @@ __device__ __forceinline__ float uniform_at(const float *__restrict__ u, const i
 }
 
 // One proposal per sequence: a draw from softmax(logits[b] / T).  out[b * out_stride].
+template <bool VEC>
 __global__ __launch_bounds__(SMP_THREADS) void k_sample_rows(const float *__restrict__ logits, int V, float inv_T,
                                                              const float *__restrict__ u, const int32_t *__restrict__ n,
                                                              int off, int u_rows, int32_t *__restrict__ out, int out_stride) {
-  __shared__ float sh[SMP_THREADS];
+  __shared__ float sh[SMP_WAVES];
   __shared__ int sh_i;
   const int b = blockIdx.x;
   const float *z = logits + (size_t)b * V;
-  float m, Z;  // a draw needs the maximum only: its own pass over the row adds the weights up
-  row_stats<false>(z, V, inv_T, sh, m, Z);
+  const float m = row_max<VEC>(z, V, sh);  // a draw needs the maximum only: its own pass over the row adds the weights up
   const float uu = n ? uniform_at(u, n, b, off, u_rows, 0) : u[b];
-  const int tok = block_draw(V, ExpW{z, V, row_vec(z, V), m, inv_T, -1}, uu, sh, &sh_i);
+  const int tok = block_draw(V, ExpW<VEC>{z, V, m, inv_T, -1}, uu, sh, &sh_i);
   if (threadIdx.x == 0) out[(size_t)b * out_stride] = tok;
 }
 
-// Verification of one sequence's proposals; writes a[b][0..s_b] (see the head of this file).
+// Verification, one workgroup per (sequence, place j of the round), places 0 .. s_b: a[b][j] = t_{j+1} if the proposal is
+// kept, -1 - (the drawn token) if it is rejected, the bonus draw at place s_b.  k_sample_seal does the rest.
 //   tl: target logits, row b * (s + 1) + j;  dl: draft logits of step j + 1 at ((size_t)j * d_rows + b) * V, or null
+template <bool VEC>
 __global__ __launch_bounds__(SMP_THREADS) void k_sample_verify(const float *__restrict__ tl, const float *__restrict__ dl,
-                                                               int d_rows, int s, int V, float inv_T,
+                                                               int d_rows, int b0, int s, int V, float inv_T,
                                                                const int32_t *__restrict__ t, int t_stride,
                                                                const int32_t *__restrict__ seq_s,
                                                                const float *__restrict__ u, const int32_t *__restrict__ n,
                                                                int u_rows, int32_t *__restrict__ a, int a_stride) {
-  __shared__ float sh[SMP_THREADS];
+  __shared__ float sh[4 * SMP_WAVES];
   __shared__ int sh_i;
-  const int b = blockIdx.x;
+  const int b = b0 + blockIdx.x / (s + 1), j = blockIdx.x % (s + 1);
   const int sb = seq_s ? min(s, max(0, seq_s[b])) : s;
-  int32_t *ab = a + (size_t)b * a_stride;
-  for (int j = 0; j <= sb; ++j) {
-    const float *zp = tl + ((size_t)b * (s + 1) + j) * V;
-    float mp, Zp;
-    row_stats(zp, V, inv_T, sh, mp, Zp);
-    const float us = uniform_at(u, n, b, j, u_rows, 2);
-    const ExpW wp{zp, V, row_vec(zp, V), mp, inv_T, -1};
-    if (j == sb) {  // every proposal kept: the bonus draw from the target's next row
-      const int tok = block_draw(V, wp, us, sh, &sh_i);
-      if (threadIdx.x == 0) ab[j] = tok;
-      break;
-    }
-    const int tj = t[(size_t)b * t_stride + j];
-    const bool valid = tj >= 0 && tj < V;
-    const float ua = uniform_at(u, n, b, j, u_rows, 1);
-    const float pt = valid ? __expf((zp[tj] - mp) * inv_T) * (1.0f / Zp) : 0.f;
-    int tok;
-    if (dl) {
-      const float *zq = dl + ((size_t)j * d_rows + b) * V;
-      float mq, Zq;
-      row_stats(zq, V, inv_T, sh, mq, Zq);
-      const float qt = valid ? __expf((zq[tj] - mq) * inv_T) * (1.0f / Zq) : 1.f;
-      if (ua * qt < pt) {
-        if (threadIdx.x == 0) ab[j] = tj;
-        continue;
-      }
-      float total;
-      tok = block_draw(V, ResidW{wp, ExpW{zq, V, row_vec(zq, V), mq, inv_T, -1}, 1.0f / Zp, 1.0f / Zq}, us, sh, &sh_i, &total);
-      // p = q everywhere leaves no residual (not reachable with u < 1 and a valid proposal): draw from p
-      if (!(total > 0.f)) tok = block_draw(V, wp, us, sh, &sh_i);
-    } else {
-      if (ua < pt) {
-        if (threadIdx.x == 0) ab[j] = tj;
-        continue;
-      }
-      tok = block_draw(V, ExpW{zp, V, row_vec(zp, V), mp, inv_T, valid ? tj : -1}, us, sh, &sh_i);
-    }
-    if (threadIdx.x == 0) {
-      ab[j] = tok;
-      for (int i = j + 1; i <= s; ++i) ab[i] = -1;
-    }
-    break;
+  if (j > sb) return;
+  const float *zp = tl + ((size_t)b * (s + 1) + j) * V;
+  const float us = uniform_at(u, n, b, j, u_rows, 2);
+  RowStats p, q;
+  if (j == sb) {  // the bonus draw, for a round that keeps every proposal: needs the row's maximum only
+    const float m = row_max<VEC>(zp, V, sh);
+    const int tok = block_draw(V, ExpW<VEC>{zp, V, m, inv_T, -1}, us, sh, &sh_i);
+    if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = tok;
+    return;
   }
+  const int tj = t[(size_t)b * t_stride + j];
+  const bool valid = tj >= 0 && tj < V;
+  const float ua = uniform_at(u, n, b, j, u_rows, 1);
+  int res;
+  if (dl) {
+    const float *zq = dl + ((size_t)j * d_rows + b) * V;
+    row_stats<VEC, true>(zp, zq, V, inv_T, sh, p, q);
+    const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
+    const float qt = valid ? __expf((zq[tj] - q.m) * inv_T) * (1.0f / q.Z) : 1.f;
+    if (ua * qt < pt) {
+      res = tj;
+    } else {
+      const ExpW<VEC> wp{zp, V, p.m, inv_T, -1};
+      float total;
+      res = block_draw(V, ResidW<VEC>{wp, ExpW<VEC>{zq, V, q.m, inv_T, -1}, 1.0f / p.Z, 1.0f / q.Z}, us, sh, &sh_i, &total);
+      // p = q everywhere leaves no residual (not reachable with u < 1 and a valid proposal): draw from p
+      if (!(total > 0.f)) res = block_draw(V, wp, us, sh, &sh_i);
+      res = -1 - res;
+    }
+  } else {
+    row_stats<VEC, false>(zp, nullptr, V, inv_T, sh, p, q);
+    const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
+    if (ua < pt) res = tj;
+    else res = -1 - block_draw(V, ExpW<VEC>{zp, V, p.m, inv_T, valid ? tj : -1}, us, sh, &sh_i);
+  }
+  if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = res;
 }
+
+// Ends every sequence's round at its first rejection: that place gets its drawn token, the places behind it -1.  For the
+// stand-alone entry point (accepted given, no seq_s) also the count and the emitted tokens, by the longest-prefix rule.
+// 16 lanes per sequence, one per place: a round has at most 16.
+__global__ __launch_bounds__(64) void k_sample_seal(int B, int s, const int32_t *__restrict__ seq_s, int32_t *__restrict__ a,
+                                                    int a_stride, const int32_t *__restrict__ t, int32_t *__restrict__ accepted,
+                                                    int32_t *__restrict__ emitted) {
+  const int lane = threadIdx.x, j = lane & 15, b = blockIdx.x * 4 + (lane >> 4);
+  const bool on = b < B;
+  const int sb = on ? (seq_s ? min(s, max(0, seq_s[b])) : s) : -1;
+  int32_t *ab = a + (size_t)(on ? b : 0) * a_stride;
+  int v = j <= sb ? ab[j] : 0;
+  const unsigned rej = (unsigned)(__ballot(v < 0) >> (lane & 48)) & 0xffffu;
+  const int first = rej ? __ffs(rej) - 1 : 16;
+  if (j >= first) {
+    v = j == first ? -1 - v : -1;
+    if (on && j <= s) ab[j] = v;
+  }
+  if (!accepted) return;
+  const bool stop = j >= s || (on && t[(size_t)b * s + j] != v);
+  const unsigned stops = (unsigned)(__ballot(stop) >> (lane & 48)) & 0xffffu;
+  const int l = __ffs(stops) - 1;  // place s always stops
+  if (!on || j > s) return;
+  if (j == 0) accepted[b] = l;
+  emitted[(size_t)b * (s + 1) + j] = j <= l ? v : -1;
+}
+
+static bool rows_vec(const float *z, int V) { return (V & 3) == 0 && ((uintptr_t)z & 15) == 0; }
 
 void launch_sample_rows(const float *logits, int rows, int V, float temperature, const float *u, const int32_t *n, int off,
                         int u_rows, int32_t *out, int out_stride, hipStream_t st) {
   if (rows <= 0) return;
-  hipLaunchKernelGGL(k_sample_rows, dim3(rows), dim3(SMP_THREADS), 0, st, logits, V, 1.0f / temperature, u, n, off, u_rows,
+  auto k = rows_vec(logits, V) ? k_sample_rows<true> : k_sample_rows<false>;
+  hipLaunchKernelGGL(k, dim3(rows), dim3(SMP_THREADS), 0, st, logits, V, 1.0f / temperature, u, n, off, u_rows,
                      out, out_stride);
 }
 void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, int s, int V, float temperature,
                           const int32_t *t, int t_stride, const int32_t *seq_s, const float *u, const int32_t *n, int u_rows,
-                          int32_t *a, int a_stride, hipStream_t st) {
+                          int32_t *a, int a_stride, hipStream_t st, int32_t *accepted, int32_t *emitted) {
   if (B <= 0) return;
-  hipLaunchKernelGGL(k_sample_verify, dim3(B), dim3(SMP_THREADS), 0, st, tl, dl, d_rows, s, V, 1.0f / temperature, t, t_stride,
-                     seq_s, u, n, u_rows, a, a_stride);
-}
-
-// acceptance count and emitted tokens from (proposals, chosen tokens): the stand-alone entry point's last step
-__global__ void k_sample_emit(int B, int s, const int32_t *__restrict__ t, const int32_t *__restrict__ a,
-                              int32_t *__restrict__ accepted, int32_t *__restrict__ emitted) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const int32_t *ab = a + (size_t)b * (s + 1);
-  int l = 0;
-  while (l < s && t[(size_t)b * s + l] == ab[l]) ++l;
-  accepted[b] = l;
-  int32_t *e = emitted + (size_t)b * (s + 1);
-  const int32_t last = ab[l];
-  for (int i = 0; i <= s; ++i) e[i] = i < l ? ab[i] : -1;
-  e[l] = last;
+  const int per_launch = (1 << 21) / (s + 1);  // a grid holds less than 2^32 threads
+  auto k = rows_vec(tl, V) && (!dl || rows_vec(dl, V)) ? k_sample_verify<true> : k_sample_verify<false>;
+  for (int64_t b0 = 0; b0 < B; b0 += per_launch)
+    hipLaunchKernelGGL(k, dim3((int)std::min<int64_t>(per_launch, B - b0) * (s + 1)), dim3(SMP_THREADS), 0, st, tl, dl,
+                       d_rows, (int)b0, s, V, 1.0f / temperature, t, t_stride, seq_s, u, n, u_rows, a, a_stride);
+  hipLaunchKernelGGL(k_sample_seal, dim3((B - 1) / 4 + 1), dim3(64), 0, st, B, s, seq_s, a, a_stride, t, accepted, emitted);
 }
 
 }  // namespace spec
@@ -313,8 +413,7 @@ extern "C" int spec_sample_accept(void *hip_stream, const float *d_target_logits
     return fail_noctx(SPEC_ERR_INVALID_ARG, "spec_sample_accept: null pointer");
   hipStream_t st = (hipStream_t)hip_stream;
   launch_sample_verify(d_target_logits, d_draft_logits, B, B, s, vocab, temperature, d_proposals, s, nullptr, d_uniforms, nullptr,
-                       s + 1, d_chosen, s + 1, st);
-  hipLaunchKernelGGL(k_sample_emit, dim3((B + 63) / 64), dim3(64), 0, st, B, s, d_proposals, d_chosen, d_accepted, d_emitted);
+                       s + 1, d_chosen, s + 1, st, d_accepted, d_emitted);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_noctx(SPEC_ERR_HIP, "spec_sample_accept: %s", hipGetErrorString(e));
   return SPEC_OK;

@@ -203,7 +203,7 @@ void launch_sample_rows(const float *logits, int rows, int V, float temperature,
                         int u_rows, int32_t *out, int out_stride, hipStream_t st);
 void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, int s, int V, float temperature,
                           const int32_t *t, int t_stride, const int32_t *seq_s, const float *u, const int32_t *n, int u_rows,
-                          int32_t *a, int a_stride, hipStream_t st);
+                          int32_t *a, int a_stride, hipStream_t st, int32_t *accepted = nullptr, int32_t *emitted = nullptr);
 void launch_fill_proposals(spec_ctx *c, int s, hipStream_t st);
 void launch_prefill_groups(const spec_ctx *c, int b0, int B, int q, hipStream_t st);
 void launch_copy_proposals(spec_ctx *c, const int32_t *d_tok, int s, hipStream_t st);

@@ -89,6 +89,44 @@ def test_acceptance_rule_matches_the_oracle(B, V, s, point_mass):
         assert 0 < np.mean(ls) < s, "the inputs should exercise both keeping and rejecting"
 
 
+@pytest.mark.parametrize("V", [1, 5, 256, 260, 4095, 4100, 32772, 70001])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_draws_and_rule_at_the_edges_of_steps_segments_and_alignment(B, V, offset):
+    """Vocabularies around a wave's step (256), a segment per wave (4096), a register tile (32768) and beyond, rows that
+    end inside a float4, and buffers that start 4 bytes off a 16-byte boundary; masked tokens, rows of NaN and of -inf."""
+    rng = np.random.default_rng(V + offset)
+    nB, s, T = 12, 3, 0.8
+    tl, dl, props, u = _round_inputs(rng, nB, s, V, False, T)
+    if V > 8:   # a masked prefix that covers whole steps: weight 0 in the target, so never emitted unless kept
+        tl[0, :, :V // 2] = -np.inf
+
+    def dev(a):
+        buf = torch.empty(a.size + offset, dtype=torch.from_numpy(a).dtype, device=DEV)
+        buf[offset:] = torch.from_numpy(a.ravel()).to(DEV)
+        return buf[offset:].view(a.shape)
+
+    skipped = 0
+    for draft in (dl, None):
+        chosen, acc, em = (x.cpu().numpy() for x in B.spec_sample_accept(dev(tl), None if draft is None else dev(draft),
+                                                                         dev(props), dev(u), T))
+        for b in range(nB):
+            l, emitted, margin = osm.spec_sample_round(tl[b], None if draft is None else draft[:, b], props[b], u[b, :s, 1],
+                                                       u[b, :, 2], T)
+            if margin < MARGIN:
+                skipped += 1
+                continue
+            want = emitted + [-1] * (s - l)
+            assert acc[b] == l and list(em[b]) == want and list(chosen[b]) == want, (b, draft is None, chosen[b], emitted, margin)
+    assert skipped <= 3
+    z = tl[:, 0].copy()
+    z[1], z[2] = np.nan, -np.inf   # no distribution: the lowest index
+    got = B.spec_sample_tokens(dev(z), dev(u[:, 0, 0].copy()), T).cpu().numpy()
+    assert got[1] == 0 and got[2] == 0
+    for b in [0] + list(range(3, nB)):
+        tok, margin = osm.sample_token(z[b], T, float(u[b, 0, 0]))
+        assert got[b] == tok or margin < MARGIN, (b, got[b], tok, margin)
+
+
 def test_identical_draft_keeps_everything_and_bad_arguments_are_refused(B):
     rng = np.random.default_rng(5)
     nB, s, V, T = 16, 5, 2048, 1.1
