@@ -1,4 +1,4 @@
-// GEMM for more than 64 activation rows (gate-up / fc1 and the LM head: from 33 rows on).
+// GEMM for more than 32 activation rows, where its estimated time beats the streaming kernel's.
 //
 // The streaming kernel covers 64 rows per pass and re-streams the weights for every pass.
 // Here one workgroup holds up to 256 rows of a group of weight strips, so a weight byte is
