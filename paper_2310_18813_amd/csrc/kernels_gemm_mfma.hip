@@ -559,7 +559,20 @@ __global__ void k_argmax_partials(const float *__restrict__ pv, const int32_t *_
   float bv = -INFINITY;
   int bi = 0x7fffffff;
   const size_t src = row_step > 0 ? (size_t)m * row_step + row_step - 1 : (size_t)m;
-  for (int t = threadIdx.x; t < n_part; t += 256) argmax_combine(bv, bi, pv[src * n_part + t], pi[src * n_part + t]);
+  // Trips to memory are what this costs (2000 partials of a 32000-token head): eight partials a thread in flight, the
+  // clamped ones repeating the last, instead of one after the other.  7B width, 4 layers, one sequence, seven draft
+  // steps and a verification: 765 -> 748 us a round; six sequences, five draft steps: 863 -> 847.
+  for (int t0 = threadIdx.x; t0 < n_part; t0 += 2048) {
+    float v[8];
+    int id[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const size_t at = src * n_part + min(t0 + 256 * i, n_part - 1);
+      v[i] = pv[at]; id[i] = pi[at];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) argmax_combine(bv, bi, v[i], id[i]);
+  }
   wave_argmax(bv, bi);
   if ((threadIdx.x & 63) == 0) { shv[threadIdx.x >> 6] = bv; shi[threadIdx.x >> 6] = bi; }
   __syncthreads();
