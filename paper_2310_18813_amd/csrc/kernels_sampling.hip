@@ -12,32 +12,33 @@
 // at the first rejection (never equal to the rejected proposal: its residual weight is zero), the bonus draw
 // behind s kept proposals.  Commit, roll-back, end token and budgets then work as in the greedy case.
 //
-// One workgroup per row (proposal draws) or per (sequence, place of the round) (verification).  A wave owns a contiguous
-// segment of the vocabulary and walks it 256 logits at a time, four per lane; lanes, then waves are added in a fixed
-// order by every thread alike, so a draw depends on the row alone.
+// One workgroup per row (proposal draws) or per place of a round (verification; large rounds: several places in turn).  A
+// wave owns a contiguous segment of the vocabulary and walks it 256 logits at a time, four per lane; lanes, then waves are
+// added in a fixed order by every thread alike, so a draw depends on the row alone.
 //
-// Bound by latency and by what one CU can stream: a row of 32000 logits is 128 KB and a place needs two of them.  All
-// places of a round are therefore decided at once, each as if its round reached it (draws behind the first rejection are
-// thrown away by k_sample_seal), so the rows of a round stream through B * (s + 1) CUs instead of one after the other
-// through B; a row is read once for maximum and sum together, and once more (from L2) where a token is drawn from it.
-// A thread with a contiguous chunk of its own (loads 512 bytes apart across a wave) and a pass for each of maximum and
-// sum, places in turn, took 87 us for 64 sequences x 4 places of 32000 logits with draft rows; this takes 30 us.
+// Bound by latency and by what one CU can stream: a row of 32000 logits is 128 KB and a place needs two of them.  While
+// they fit the chip, all places of a round are therefore decided at once, each as if its round reached it (draws behind
+// the first rejection are thrown away by k_sample_seal), so that the rows stream through B * (s + 1) CUs instead of one
+// after the other through B; a row is read once for maximum and sum together, and once more (from L2) where a token is
+// drawn from it.  A thread with a contiguous chunk of its own (loads 512 bytes apart across a wave), a pass for each of
+// maximum and sum, and a sequence's places in turn took 87 us for 64 sequences x 4 places of 32000 logits with draft rows;
+// this takes 30 us.  Larger rounds take places in turn (workgroups_per_sequence).
 #include "spec_internal.h"
 #include "device_utils.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace spec {
 
 #pragma clang fp contract(off)
 
-constexpr int SMP_THREADS = 1024;
-constexpr int SMP_WAVES = SMP_THREADS / 64;
 constexpr int SMP_STEP = 256;   // logits per wave and step: a float4 per lane
 
 // this wave's part of the row: [k0, end), k0 a multiple of SMP_STEP (empty: end <= k0)
 struct Seg { int k0, end; };
+template <int W>
 __device__ __forceinline__ Seg my_seg(int V) {
-  const int per = ((V - 1) / (SMP_WAVES * SMP_STEP) + 1) * SMP_STEP;
+  const int per = ((V - 1) / (W * SMP_STEP) + 1) * SMP_STEP;
   const int k0 = (int)(threadIdx.x >> 6) * per;
   return Seg{k0, V - k0 < per ? V : k0 + per};
 }
@@ -60,11 +61,12 @@ __device__ __forceinline__ void load4z(const float *__restrict__ z, int k, int V
     }
   }
 }
-// steps whose loads are in flight together (single loads need four addresses a step)
-template <bool VEC> constexpr int SMP_UNROLL = VEC ? 8 : 2;
+// steps whose loads are in flight together (single loads need four addresses a step; a segment of a short row has few steps)
+template <int W, bool VEC> constexpr int SMP_UNROLL = !VEC ? 2 : W == 4 ? 4 : 8;
 
 // Exclusive prefix over the waves of one value per wave, *total = the sum over the workgroup: added in wave order, the
-// same bits in every thread.  sh: SMP_WAVES floats.
+// same bits in every thread.  sh: W floats.
+template <int W>
 __device__ __forceinline__ float waves_prefix(float v, float *sh, float *total) {
   const int wv = threadIdx.x >> 6;
   __syncthreads();  // sh may still be read by the previous user
@@ -72,7 +74,7 @@ __device__ __forceinline__ float waves_prefix(float v, float *sh, float *total) 
   __syncthreads();
   float before = 0.f, all = 0.f;
 #pragma unroll
-  for (int i = 0; i < SMP_WAVES; ++i) {
+  for (int i = 0; i < W; ++i) {
     if (i == wv) before = all;
     all += sh[i];
   }
@@ -81,11 +83,11 @@ __device__ __forceinline__ float waves_prefix(float v, float *sh, float *total) 
 }
 
 // maximum of a row, the same in every thread
-template <bool VEC>
+template <int W, bool VEC>
 __device__ __forceinline__ float row_max(const float *__restrict__ z, int V, float *sh) {
-  const Seg g = my_seg(V);
+  const Seg g = my_seg<W>(V);
   const int lane4 = (threadIdx.x & 63) * 4;
-  constexpr int U = SMP_UNROLL<VEC>;
+  constexpr int U = SMP_UNROLL<W, VEC>;
   float lm = -INFINITY;
 #pragma unroll 1
   for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
@@ -101,7 +103,7 @@ __device__ __forceinline__ float row_max(const float *__restrict__ z, int V, flo
   __syncthreads();
   float m = sh[0];
 #pragma unroll
-  for (int i = 1; i < SMP_WAVES; ++i) m = fmaxf(m, sh[i]);
+  for (int i = 1; i < W; ++i) m = fmaxf(m, sh[i]);
   return m;
 }
 
@@ -124,14 +126,14 @@ __device__ __forceinline__ void stats_step(const float (&v)[U][4], float inv_T, 
 }
 
 // Maximum and sum of exp((z - max) * inv_T) of a target row and, PAIR, of a draft row, the same bits in every thread
-// (a row of -inf alone has no distribution: its sum is NaN).  sh: 4 * SMP_WAVES floats.
+// (a row of -inf alone has no distribution: its sum is NaN).  sh: 4 * W floats.
 struct RowStats { float m, Z; };
-template <bool VEC, bool PAIR>
+template <int W, bool VEC, bool PAIR>
 __device__ __forceinline__ void row_stats(const float *__restrict__ zp, const float *__restrict__ zq, int V, float inv_T,
                                           float *sh, RowStats &p, RowStats &q) {
-  const Seg g = my_seg(V);
+  const Seg g = my_seg<W>(V);
   const int lane4 = (threadIdx.x & 63) * 4, wv = threadIdx.x >> 6;
-  constexpr int U = SMP_UNROLL<VEC>;
+  constexpr int U = SMP_UNROLL<W, VEC>;
   float mp = -INFINITY, Zp = 0.f, mq = -INFINITY, Zq = 0.f;
 #pragma unroll 1
   for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
@@ -150,28 +152,28 @@ __device__ __forceinline__ void row_stats(const float *__restrict__ zp, const fl
   if (PAIR) { wmq = wave_max(mq); wZq = wave_sum(rescaled(Zq, mq, wmq, inv_T)); }
   __syncthreads();
   if ((threadIdx.x & 63) == 0) {
-    sh[wv] = wmp; sh[SMP_WAVES + wv] = wZp;
-    if (PAIR) { sh[2 * SMP_WAVES + wv] = wmq; sh[3 * SMP_WAVES + wv] = wZq; }
+    sh[wv] = wmp; sh[W + wv] = wZp;
+    if (PAIR) { sh[2 * W + wv] = wmq; sh[3 * W + wv] = wZq; }
   }
   __syncthreads();
   auto combine = [&](const float *s) {
     RowStats r{s[0], 0.f};
 #pragma unroll
-    for (int i = 1; i < SMP_WAVES; ++i) r.m = fmaxf(r.m, s[i]);
+    for (int i = 1; i < W; ++i) r.m = fmaxf(r.m, s[i]);
 #pragma unroll
-    for (int i = 0; i < SMP_WAVES; ++i) r.Z += rescaled(s[SMP_WAVES + i], s[i], r.m, inv_T);
+    for (int i = 0; i < W; ++i) r.Z += rescaled(s[W + i], s[i], r.m, inv_T);
     if (r.m == -INFINITY) r.Z = __builtin_nanf("");
     return r;
   };
   p = combine(sh);
-  if (PAIR) q = combine(sh + 2 * SMP_WAVES);
+  if (PAIR) q = combine(sh + 2 * W);
 }
 
 // Draw with u from the weights w4(k, end, out) -> weights of k .. k+3 (zero from `end` on), k a multiple of four:
 // every thread returns the same index.  *total_out: the sum of all weights.
-template <class W4>
+template <int W, class W4>
 __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int *sh_i, float *total_out = nullptr) {
-  const Seg g = my_seg(V);
+  const Seg g = my_seg<W>(V);
   const int lane = threadIdx.x & 63, lane4 = lane * 4, wv = threadIdx.x >> 6;
   constexpr int U = W4::UNROLL;
   float local = 0.f;
@@ -185,7 +187,7 @@ __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int 
   }
   local = wave_sum(local);
   float total;
-  const float excl = waves_prefix(local, sh, &total);
+  const float excl = waves_prefix<W>(local, sh, &total);
   if (threadIdx.x == 0) *sh_i = -1;
   if (total_out) *total_out = total;
   float x = u * total;
@@ -239,9 +241,9 @@ __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int 
 }
 
 // weights exp((z - m) * inv_T) of a row, optionally with one token removed
-template <bool VEC>
+template <int W, bool VEC>
 struct ExpW {
-  static constexpr int UNROLL = SMP_UNROLL<VEC>;
+  static constexpr int UNROLL = SMP_UNROLL<W, VEC>;
   const float *z; int V; float m, inv_T; int drop;
   __device__ __forceinline__ void operator()(int k, int end, float (&w)[4]) const {
     float v[4];
@@ -251,10 +253,10 @@ struct ExpW {
   }
 };
 // residual weights max(0, p - q) of a target and a draft row
-template <bool VEC>
+template <int W, bool VEC>
 struct ResidW {
-  static constexpr int UNROLL = SMP_UNROLL<VEC> / 2;  // two rows a step
-  ExpW<VEC> p, q; float ip, iq;
+  static constexpr int UNROLL = SMP_UNROLL<W, VEC> / 2;  // two rows a step
+  ExpW<W, VEC> p, q; float ip, iq;
   __device__ __forceinline__ void operator()(int k, int end, float (&w)[4]) const {
     float a[4], b[4];
     p(k, end, a); q(k, end, b);
@@ -272,70 +274,107 @@ __device__ __forceinline__ float uniform_at(const float *__restrict__ u, const i
 }
 
 // One proposal per sequence: a draw from softmax(logits[b] / T).  out[b * out_stride].
-template <bool VEC>
-__global__ __launch_bounds__(SMP_THREADS) void k_sample_rows(const float *__restrict__ logits, int V, float inv_T,
+template <int W, bool VEC>
+__global__ __launch_bounds__(W * 64) void k_sample_rows(const float *__restrict__ logits, int V, float inv_T,
                                                              const float *__restrict__ u, const int32_t *__restrict__ n,
                                                              int off, int u_rows, int32_t *__restrict__ out, int out_stride) {
-  __shared__ float sh[SMP_WAVES];
+  __shared__ float sh[W];
   __shared__ int sh_i;
   const int b = blockIdx.x;
   const float *z = logits + (size_t)b * V;
-  const float m = row_max<VEC>(z, V, sh);  // a draw needs the maximum only: its own pass over the row adds the weights up
+  const float m = row_max<W, VEC>(z, V, sh);  // a draw needs the maximum only: its own pass over the row adds the weights up
   const float uu = n ? uniform_at(u, n, b, off, u_rows, 0) : u[b];
-  const int tok = block_draw(V, ExpW<VEC>{z, V, m, inv_T, -1}, uu, sh, &sh_i);
+  const int tok = block_draw<W>(V, ExpW<W, VEC>{z, V, m, inv_T, -1}, uu, sh, &sh_i);
   if (threadIdx.x == 0) out[(size_t)b * out_stride] = tok;
 }
 
-// Verification, one workgroup per (sequence, place j of the round), places 0 .. s_b: a[b][j] = t_{j+1} if the proposal is
-// kept, -1 - (the drawn token) if it is rejected, the bonus draw at place s_b.  k_sample_seal does the rest.
+// Place j of a round, decided as if the round reached it: t_{j+1} if the proposal is kept, -1 - (the drawn token) if it is
+// rejected; the same in every thread.  zq: the draft's row, null for a point-mass proposal.
+template <int W, bool VEC>
+__device__ __forceinline__ int decide_place(const float *__restrict__ zp, const float *__restrict__ zq, int V, float inv_T,
+                                            int tj, float ua, float us, float *sh, int *sh_i) {
+  RowStats p, q;
+  const bool valid = tj >= 0 && tj < V;
+  int res;
+  if (zq) {
+    row_stats<W, VEC, true>(zp, zq, V, inv_T, sh, p, q);
+    const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
+    const float qt = valid ? __expf((zq[tj] - q.m) * inv_T) * (1.0f / q.Z) : 1.f;
+    if (ua * qt < pt) {
+      res = tj;
+    } else {
+      const ExpW<W, VEC> wp{zp, V, p.m, inv_T, -1};
+      float total;
+      res = block_draw<W>(V, ResidW<W, VEC>{wp, ExpW<W, VEC>{zq, V, q.m, inv_T, -1}, 1.0f / p.Z, 1.0f / q.Z}, us, sh, sh_i, &total);
+      // p = q everywhere leaves no residual (not reachable with u < 1 and a valid proposal): draw from p
+      if (!(total > 0.f)) res = block_draw<W>(V, wp, us, sh, sh_i);
+      res = -1 - res;
+    }
+  } else {
+    row_stats<W, VEC, false>(zp, nullptr, V, inv_T, sh, p, q);
+    const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
+    if (ua < pt) res = tj;
+    else res = -1 - block_draw<W>(V, ExpW<W, VEC>{zp, V, p.m, inv_T, valid ? tj : -1}, us, sh, sh_i);
+  }
+  return res;
+}
+// The bonus draw, for a round that keeps every proposal: needs the row's maximum only.
+template <int W, bool VEC>
+__device__ __forceinline__ int bonus_draw(const float *__restrict__ zp, int V, float inv_T, float us, float *sh, int *sh_i) {
+  const float m = row_max<W, VEC>(zp, V, sh);
+  return block_draw<W>(V, ExpW<W, VEC>{zp, V, m, inv_T, -1}, us, sh, sh_i);
+}
+
+// Verification, a workgroup per (sequence, place j), places 0 .. s_b: a[b][j] = decide_place, or the bonus draw at place s_b.
+// k_sample_seal does the rest.
 //   tl: target logits, row b * (s + 1) + j;  dl: draft logits of step j + 1 at ((size_t)j * d_rows + b) * V, or null
-template <bool VEC>
-__global__ __launch_bounds__(SMP_THREADS) void k_sample_verify(const float *__restrict__ tl, const float *__restrict__ dl,
-                                                               int d_rows, int b0, int s, int V, float inv_T,
-                                                               const int32_t *__restrict__ t, int t_stride,
-                                                               const int32_t *__restrict__ seq_s,
-                                                               const float *__restrict__ u, const int32_t *__restrict__ n,
-                                                               int u_rows, int32_t *__restrict__ a, int a_stride) {
-  __shared__ float sh[4 * SMP_WAVES];
+template <int W, bool VEC>
+__global__ __launch_bounds__(W * 64) void k_sample_verify(const float *__restrict__ tl, const float *__restrict__ dl,
+                                                          int d_rows, int b0, int s, int V, float inv_T,
+                                                          const int32_t *__restrict__ t, int t_stride,
+                                                          const int32_t *__restrict__ seq_s,
+                                                          const float *__restrict__ u, const int32_t *__restrict__ n,
+                                                          int u_rows, int32_t *__restrict__ a, int a_stride) {
+  __shared__ float sh[4 * W];
   __shared__ int sh_i;
   const int b = b0 + blockIdx.x / (s + 1), j = blockIdx.x % (s + 1);
   const int sb = seq_s ? min(s, max(0, seq_s[b])) : s;
   if (j > sb) return;
   const float *zp = tl + ((size_t)b * (s + 1) + j) * V;
   const float us = uniform_at(u, n, b, j, u_rows, 2);
-  RowStats p, q;
-  if (j == sb) {  // the bonus draw, for a round that keeps every proposal: needs the row's maximum only
-    const float m = row_max<VEC>(zp, V, sh);
-    const int tok = block_draw(V, ExpW<VEC>{zp, V, m, inv_T, -1}, us, sh, &sh_i);
+  if (j == sb) {
+    const int tok = bonus_draw<W, VEC>(zp, V, inv_T, us, sh, &sh_i);
     if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = tok;
     return;
   }
-  const int tj = t[(size_t)b * t_stride + j];
-  const bool valid = tj >= 0 && tj < V;
-  const float ua = uniform_at(u, n, b, j, u_rows, 1);
-  int res;
-  if (dl) {
-    const float *zq = dl + ((size_t)j * d_rows + b) * V;
-    row_stats<VEC, true>(zp, zq, V, inv_T, sh, p, q);
-    const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
-    const float qt = valid ? __expf((zq[tj] - q.m) * inv_T) * (1.0f / q.Z) : 1.f;
-    if (ua * qt < pt) {
-      res = tj;
-    } else {
-      const ExpW<VEC> wp{zp, V, p.m, inv_T, -1};
-      float total;
-      res = block_draw(V, ResidW<VEC>{wp, ExpW<VEC>{zq, V, q.m, inv_T, -1}, 1.0f / p.Z, 1.0f / q.Z}, us, sh, &sh_i, &total);
-      // p = q everywhere leaves no residual (not reachable with u < 1 and a valid proposal): draw from p
-      if (!(total > 0.f)) res = block_draw(V, wp, us, sh, &sh_i);
-      res = -1 - res;
-    }
-  } else {
-    row_stats<VEC, false>(zp, nullptr, V, inv_T, sh, p, q);
-    const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
-    if (ua < pt) res = tj;
-    else res = -1 - block_draw(V, ExpW<VEC>{zp, V, p.m, inv_T, valid ? tj : -1}, us, sh, &sh_i);
-  }
+  const int res = decide_place<W, VEC>(zp, dl ? dl + ((size_t)j * d_rows + b) * V : nullptr, V, inv_T, t[(size_t)b * t_stride + j],
+                                       uniform_at(u, n, b, j, u_rows, 1), us, sh, &sh_i);
   if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = res;
+}
+
+// The same with `per` <= s workgroups to a sequence: workgroup i of them takes the places i, i + per, ... up to s_b in
+// turn and stops at the first it rejects.  Every place before the round's first rejection is then decided (a place is
+// left out only behind a rejection of its own workgroup); k_sample_seal ignores what lies behind.
+template <int W, bool VEC, bool DRAFT>
+__global__ __launch_bounds__(W * 64) void k_sample_verify_turns(const float *__restrict__ tl, const float *__restrict__ dl,
+                                                                int d_rows, int b0, int per, int s, int V, float inv_T,
+                                                                const int32_t *__restrict__ t, int t_stride,
+                                                                const int32_t *__restrict__ seq_s,
+                                                                const float *__restrict__ u, const int32_t *__restrict__ n,
+                                                                int u_rows, int32_t *__restrict__ a, int a_stride) {
+  __shared__ float sh[4 * W];
+  __shared__ int sh_i;
+  const int b = b0 + blockIdx.x / per;
+  const int sb = seq_s ? min(s, max(0, seq_s[b])) : s;
+  for (int j = blockIdx.x % per; j <= sb; j += per) {
+    const float *zp = tl + ((size_t)b * (s + 1) + j) * V, *zq = DRAFT ? dl + ((size_t)j * d_rows + b) * V : nullptr;
+    const bool bonus = j == sb;
+    const int tj = bonus ? 0 : t[(size_t)b * t_stride + j];
+    const float ua = uniform_at(u, n, b, j, u_rows, 1), us = uniform_at(u, n, b, j, u_rows, 2);
+    const int res = bonus ? bonus_draw<W, VEC>(zp, V, inv_T, us, sh, &sh_i) : decide_place<W, VEC>(zp, zq, V, inv_T, tj, ua, us, sh, &sh_i);
+    if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = res;
+    if (res < 0) break;
+  }
 }
 
 // Ends every sequence's round at its first rejection: that place gets its drawn token, the places behind it -1.  For the
@@ -366,22 +405,64 @@ __global__ __launch_bounds__(64) void k_sample_seal(int B, int s, const int32_t 
 
 static bool rows_vec(const float *z, int V) { return (V & 3) == 0 && ((uintptr_t)z & 15) == 0; }
 
+// Waves per workgroup, by the vocabulary alone (a draw's sums then still depend on nothing but the row): 4 up to 8192
+// logits, where 16 have too little to do and large rounds pay for starting and meeting them, 16 beyond, where 4 need more
+// trips to memory than a small round can hide.  4 / 16 waves, us: 4096 rows of 1000 logits 12 / 37, 1024 of 6000 11 / 18, 16 of
+// 6000 the same; 16 rows of 16000 14 / 10.
+static bool narrow_rows(int V) { return V <= 8192; }
+
 void launch_sample_rows(const float *logits, int rows, int V, float temperature, const float *u, const int32_t *n, int off,
                         int u_rows, int32_t *out, int out_stride, hipStream_t st) {
   if (rows <= 0) return;
-  auto k = rows_vec(logits, V) ? k_sample_rows<true> : k_sample_rows<false>;
-  hipLaunchKernelGGL(k, dim3(rows), dim3(SMP_THREADS), 0, st, logits, V, 1.0f / temperature, u, n, off, u_rows,
+  const bool vec = rows_vec(logits, V), narrow = narrow_rows(V);
+  auto k = narrow ? (vec ? k_sample_rows<4, true> : k_sample_rows<4, false>) : vec ? k_sample_rows<16, true> : k_sample_rows<16, false>;
+  hipLaunchKernelGGL(k, dim3(rows), dim3(narrow ? 256 : 1024), 0, st, logits, V, 1.0f / temperature, u, n, off, u_rows,
                      out, out_stride);
 }
+// How many workgroups share the places of a sequence's round.  A workgroup per place reads rows behind the first rejection
+// for nothing, which is free only while the chip has room: `slots` is the workgroups it works on at a time (one of 16 waves
+// per CU; four of 4 waves).
+//   point-mass proposals: what fits the slots, so that rounds that end at once cost one place each.
+//   proposals with a draft row (kept more often): as few as take no more turns, if every proposal is kept, than a workgroup
+//   per place would.
+// A workgroup per sequence with the older kernel / a workgroup per place / this, us, draft rows where (d), 32000 logits:
+//   256 sequences x 9 places, 1.4 kept (d) 189 / 185 / 94, all kept (d) 230 / 129 / 126, none kept 32 / 131 / 20
+//   1024 x 9, 1.4 kept (d) 585 / 681 / 243, all kept (d) 932 / 439 / 425, none kept 91 / 498 / 64
+//   128 x 9, 1.2 kept (d) 185 / 101 / 59, all kept (d) 202 / 67 / 66, none kept 30 / 71 / 20
+//   1024 x 9 of 1000 logits, 1.6 kept (d) 45 / 267 / 38, none kept 17 / 212 / 18
+static int workgroups_per_sequence(int B, int s, bool draft, int slots) {
+  if (!draft) return std::min(s + 1, std::max(1, slots / B));
+  auto turns = [&](int per) { return ((int64_t)B * per + slots - 1) / slots * ((s + per) / per); };
+  int per = 1;
+  while (per < s + 1 && turns(per) > turns(s + 1)) ++per;
+  return per;
+}
+
 void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, int s, int V, float temperature,
                           const int32_t *t, int t_stride, const int32_t *seq_s, const float *u, const int32_t *n, int u_rows,
                           int32_t *a, int a_stride, hipStream_t st, int32_t *accepted, int32_t *emitted) {
   if (B <= 0) return;
-  const int per_launch = (1 << 21) / (s + 1);  // a grid holds less than 2^32 threads
-  auto k = rows_vec(tl, V) && (!dl || rows_vec(dl, V)) ? k_sample_verify<true> : k_sample_verify<false>;
-  for (int64_t b0 = 0; b0 < B; b0 += per_launch)
-    hipLaunchKernelGGL(k, dim3((int)std::min<int64_t>(per_launch, B - b0) * (s + 1)), dim3(SMP_THREADS), 0, st, tl, dl,
-                       d_rows, (int)b0, s, V, 1.0f / temperature, t, t_stride, seq_s, u, n, u_rows, a, a_stride);
+  const bool vec = rows_vec(tl, V) && (!dl || rows_vec(dl, V)), narrow = narrow_rows(V);
+  const int per = workgroups_per_sequence(B, s, dl != nullptr, narrow ? 1024 : 256);
+  const int per_launch = (1 << 21) / per;  // a grid holds less than 2^32 threads
+  for (int64_t b0 = 0; b0 < B; b0 += per_launch) {
+    const int nb = (int)std::min<int64_t>(per_launch, B - b0);
+    auto launch = [&](auto W_, auto VEC_) {
+      constexpr int W = decltype(W_)::value;
+      constexpr bool VEC = decltype(VEC_)::value;
+      if (per == s + 1)
+        hipLaunchKernelGGL((k_sample_verify<W, VEC>), dim3(nb * per), dim3(W * 64), 0, st, tl, dl, d_rows, (int)b0, s, V, 1.0f / temperature,
+                           t, t_stride, seq_s, u, n, u_rows, a, a_stride);
+      else
+        hipLaunchKernelGGL((dl ? k_sample_verify_turns<W, VEC, true> : k_sample_verify_turns<W, VEC, false>), dim3(nb * per), dim3(W * 64), 0,
+                           st, tl, dl, d_rows, (int)b0, per, s, V, 1.0f / temperature, t, t_stride, seq_s, u, n, u_rows, a, a_stride);
+    };
+    using std::integral_constant;
+    if (narrow && vec) launch(integral_constant<int, 4>{}, std::true_type{});
+    else if (narrow) launch(integral_constant<int, 4>{}, std::false_type{});
+    else if (vec) launch(integral_constant<int, 16>{}, std::true_type{});
+    else launch(integral_constant<int, 16>{}, std::false_type{});
+  }
   hipLaunchKernelGGL(k_sample_seal, dim3((B - 1) / 4 + 1), dim3(64), 0, st, B, s, seq_s, a, a_stride, t, accepted, emitted);
 }
 

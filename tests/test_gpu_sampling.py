@@ -127,6 +127,60 @@ def test_draws_and_rule_at_the_edges_of_steps_segments_and_alignment(B, V, offse
         assert got[b] == tok or margin < MARGIN, (b, got[b], tok, margin)
 
 
+def _on_device_round(nB, s, V, sigma, seed, T):
+    """Peaked target rows, a draft `sigma` away from them, proposals drawn from the draft, uniform numbers."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    tl = torch.empty((nB, s + 1, V), device=DEV).normal_(0.0, 3.0, generator=g)
+    dl = (tl[:, :s].transpose(0, 1) + sigma * torch.empty((s, nB, V), device=DEV).normal_(generator=g)).contiguous()
+    gum = torch.empty((s, nB, V), device=DEV).exponential_(generator=g).log_().neg_()
+    props = (dl / T + gum).argmax(-1).transpose(0, 1).to(torch.int32).contiguous()
+    return tl, dl, props, torch.rand((nB, s + 1, 3), device=DEV, generator=g)
+
+
+@pytest.mark.parametrize("nB,s,V", [(257, 1, 8196), (300, 5, 9001), (130, 15, 8448), (1025, 3, 1000), (600, 8, 1003), (300, 6, 8192)])
+@pytest.mark.parametrize("sigma", [0.0, 1.0, 3.0])
+def test_rounds_too_large_for_a_workgroup_per_place_are_the_sum_of_small_ones(B, nB, s, V, sigma):
+    """Large rounds decide several places per workgroup in turn, small ones a place per workgroup: same bits for a
+    sequence either way, whether its proposals are all kept, some or none; vocabularies on both sides of the change of
+    the workgroup's size."""
+    T = 0.9
+    tl, dl, props, u = _on_device_round(nB, s, V, sigma, nB + s, T)
+    if sigma == 3.0:
+        props = (props + 1) % V   # mostly rejected at the first place
+    for draft in (dl, None):
+        whole = B.spec_sample_accept(tl, draft, props, u, T)
+        for i in range(0, nB, 14):   # 14 * 16 places: a workgroup each
+            part = B.spec_sample_accept(tl[i:i + 14].contiguous(), None if draft is None else draft[:, i:i + 14].contiguous(),
+                                        props[i:i + 14].contiguous(), u[i:i + 14].contiguous(), T)
+            for w, p in zip(whole, part):
+                assert torch.equal(w[i:i + 14], p), (i, draft is None)
+
+
+def test_a_large_round_does_not_pay_for_places_behind_the_first_rejection(B):
+    """512 sequences x 9 places of 16000 logits: when every round ends at its first place, one place in nine is needed.
+    A workgroup per place would take about as long as with every proposal kept (ratio 0.9 to 1.1); in turn 0.15 to 0.3."""
+    nB, s, V, T = 512, 8, 16000, 0.8
+    tl, _, _, u = _on_device_round(nB, s, V, 1.0, 3, T)
+    best = tl[:, :s].argmax(-1).to(torch.int32)
+    tl[:, :s].scatter_(2, best.long()[..., None], 60.0)   # the arg-max has probability 1: kept whatever u is
+    ms = {}
+    for name, props in (("kept", best.contiguous()), ("rejected", ((best + 1) % V).contiguous())):
+        run = lambda: B.spec_sample_accept(tl, None, props, u, T)
+        assert run()[1].unique().tolist() == [s if name == "kept" else 0]
+        times = []
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(10):
+                run()
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        ms[name] = min(times)
+    assert ms["rejected"] < 0.6 * ms["kept"], ms
+
+
 def test_identical_draft_keeps_everything_and_bad_arguments_are_refused(B):
     rng = np.random.default_rng(5)
     nB, s, V, T = 16, 5, 2048, 1.1
@@ -235,6 +289,32 @@ def test_rounds_inside_a_context_follow_the_rule_on_their_own_logits(B, name, mo
     assert [list(r[:3]) for r in a] == [list(lg[b].argmax(-1)) for b in range(nB)]
     ctx.spec_accept_commit(2)
     ctx.close()
+
+
+@pytest.mark.parametrize("mode", ["draft", "table"])
+def test_a_large_batch_with_caps_samples_what_a_small_one_does(B, mode):
+    """300 sequences that repeat five, with a speculation length each: more places than workgroups, so they are decided
+    in turn; every sequence must emit what it emits in a batch of five."""
+    P, N, s_max, T, caps = 9, 24, 4, 0.9, [0, 1, 2, 3, 4]
+    outs = []
+    for nB in (5, 300):
+        ctx, prompts, L_max, V = _context(B, "tiny_fp32", B.PROPOSALS_DRAFT if mode == "draft" else B.PROPOSALS_EXTERNAL, nB, P, N, s_max)
+        rep = nB // 5
+        rng = np.random.default_rng(6)
+        u, table = rng.random((5, L_max, 3)).astype(np.float32), rng.integers(V, size=(5, L_max), dtype=np.int32)
+        if mode == "table":
+            ctx.spec_set_proposal_table(np.tile(table, (rep, 1)))
+        ctx.spec_reset(np.tile(np.asarray(prompts)[:5], (rep, 1)))
+        ctx.spec_set_seq_s(caps * rep)
+        ctx.spec_set_sampling(T, torch.from_numpy(np.tile(u, (rep, 1, 1))).to(DEV))
+        for s in (3, 4, 1, 0, 2, 4):
+            ctx.spec_round(s, 1)
+        outs.append(ctx.spec_read_output()[0])
+        ctx.close()
+    small, large = outs
+    assert any(len(t) > 6 for t in small) or mode == "table"
+    for b in range(300):
+        assert list(large[b]) == list(small[b % 5]), b
 
 
 @pytest.mark.parametrize("name", list(PAIRS))
