@@ -227,14 +227,18 @@ __device__ __forceinline__ void f32_epilogue(const F32Gemm &a, f32x4 v, int nt, 
   }
 }
 
+// LDS of a workgroup: a finished tile per slice, strip and row tile, and behind them the slices' sums of squares per row.
+// With eight slices of eight tiles that is above the 64 KB a kernel has without asking (fp32_prepare).
+constexpr size_t f32_lds(int KS, int MT, int NB) { return (size_t)KS * (NB * MT * 1024 + MT * 16 * 4); }
+
 // Workgroup = KS waves, one k-slice each, over NB strips of W and MT row tiles of X; the slices meet in LDS.  Bound by the weight stream (few rows) or by the matrix cores (2 x 4 tiles: 256 cycles of MFMA per unit and
 // step against 96 cycles of L2 reads; 4 x 4 spills); operands of the next steps are in flight while the present ones are multiplied.
 template <int MT, int NB, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
-  extern __shared__ float red[];  // [KS][NB * MT][256]
-  __shared__ float ssq_s[8][MT * 16];
+  extern __shared__ float red[];  // [KS][NB * MT][256], then [KS][MT * 16]: f32_lds()
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
   const int KS = a.KS;
+  float *ssq_s = red + (size_t)KS * (NB * MT * 256);
   int G = blockIdx.x, pass = 0;
   if (a.passes > 1) {  // all row passes of a strip group on one XCD: its L2 serves the weights again
     const int rest = (int)blockIdx.x >> 3;
@@ -308,7 +312,7 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
       float t = ssq[mt];
       t += __shfl_xor(t, 16, 64);
       t += __shfl_xor(t, 32, 64);
-      if (g == 0) ssq_s[w][mt * 16 + c] = t;
+      if (g == 0) ssq_s[w * (MT * 16) + mt * 16 + c] = t;
     }
   }
   float rinv[MT];
@@ -317,8 +321,8 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
     for (int mt = 0; mt < MT; ++mt) {
       rinv[mt] = 1.f;
       if (!a.fold) continue;
-      float t = ssq_s[0][mt * 16 + c];
-      for (int s = 1; s < KS; ++s) t += ssq_s[s][mt * 16 + c];
+      float t = ssq_s[mt * 16 + c];
+      for (int s = 1; s < KS; ++s) t += ssq_s[s * (MT * 16) + mt * 16 + c];
       rinv[mt] = 1.0f / sqrtf(t / (float)K + a.eps);
     }
   };
@@ -336,16 +340,47 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
   }
 }
 
+// blocks < 0: preparation pass
+template <int MT, int NB, int EPI>
+static void f32_launch(const F32Gemm &a, int blocks, hipStream_t st) {
+  if (blocks < 0)
+    (void)hipFuncSetAttribute((const void *)k_gemm_f32<MT, NB, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f32_lds(8, MT, NB));
+  else
+    hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI>), dim3(blocks), dim3(a.KS * 64), f32_lds(a.KS, MT, NB), st, a);
+}
+
 template <int MT, int NB>
 static void f32_launch_epi(const F32Gemm &a, int epi, int blocks, hipStream_t st) {
-  const size_t lds = (size_t)a.KS * NB * MT * 1024;
-  const dim3 grid(blocks), block(a.KS * 64);
   switch (epi) {
-    case EPI_RESIDUAL: hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI_RESIDUAL>), grid, block, lds, st, a); break;
-    case EPI_QKV: hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI_QKV>), grid, block, lds, st, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI_SWIGLU>), grid, block, lds, st, a); break;
-    case EPI_RELU: hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI_RELU>), grid, block, lds, st, a); break;
-    default: hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI_LOGITS>), grid, block, lds, st, a); break;
+    case EPI_RESIDUAL: f32_launch<MT, NB, EPI_RESIDUAL>(a, blocks, st); break;
+    case EPI_QKV: f32_launch<MT, NB, EPI_QKV>(a, blocks, st); break;
+    case EPI_SWIGLU: f32_launch<MT, NB, EPI_SWIGLU>(a, blocks, st); break;
+    case EPI_RELU: f32_launch<MT, NB, EPI_RELU>(a, blocks, st); break;
+    default: f32_launch<MT, NB, EPI_LOGITS>(a, blocks, st); break;
+  }
+}
+
+static void f32_launch_shape(const F32Gemm &a, int MT, int NB, int epi, int blocks, hipStream_t st) {
+  switch (MT * 8 + NB) {
+    case 9: f32_launch_epi<1, 1>(a, epi, blocks, st); break;
+    case 10: f32_launch_epi<1, 2>(a, epi, blocks, st); break;
+    case 12: f32_launch_epi<1, 4>(a, epi, blocks, st); break;
+    case 17: f32_launch_epi<2, 1>(a, epi, blocks, st); break;
+    case 18: f32_launch_epi<2, 2>(a, epi, blocks, st); break;
+    case 20: f32_launch_epi<2, 4>(a, epi, blocks, st); break;
+    case 25: f32_launch_epi<3, 1>(a, epi, blocks, st); break;
+    case 26: f32_launch_epi<3, 2>(a, epi, blocks, st); break;
+    case 33: f32_launch_epi<4, 1>(a, epi, blocks, st); break;
+    default: f32_launch_epi<4, 2>(a, epi, blocks, st); break;
+  }
+}
+
+// once per context, with its device current: more than 64 KB of LDS for the shapes with eight tiles
+void fp32_prepare() {
+  const F32Gemm a{};
+  for (int epi : {(int)EPI_RESIDUAL, (int)EPI_QKV, (int)EPI_SWIGLU, (int)EPI_RELU, (int)EPI_LOGITS}) {
+    f32_launch_shape(a, 2, 4, epi, -1, nullptr);
+    f32_launch_shape(a, 4, 2, epi, -1, nullptr);
   }
 }
 
@@ -367,18 +402,7 @@ static void f32_gemm(F32Gemm a, int epi, int n_cu, hipStream_t st) {
   a.passes = (a.M + MT * 16 - 1) / (MT * 16);
   a.groups = (a.NT + NB - 1) / NB;
   const int blocks = a.passes == 1 ? a.groups : (a.groups + 7) / 8 * 8 * a.passes;
-  switch (MT * 8 + NB) {
-    case 9: f32_launch_epi<1, 1>(a, epi, blocks, st); break;
-    case 10: f32_launch_epi<1, 2>(a, epi, blocks, st); break;
-    case 12: f32_launch_epi<1, 4>(a, epi, blocks, st); break;
-    case 17: f32_launch_epi<2, 1>(a, epi, blocks, st); break;
-    case 18: f32_launch_epi<2, 2>(a, epi, blocks, st); break;
-    case 20: f32_launch_epi<2, 4>(a, epi, blocks, st); break;
-    case 25: f32_launch_epi<3, 1>(a, epi, blocks, st); break;
-    case 26: f32_launch_epi<3, 2>(a, epi, blocks, st); break;
-    case 33: f32_launch_epi<4, 1>(a, epi, blocks, st); break;
-    default: f32_launch_epi<4, 2>(a, epi, blocks, st); break;
-  }
+  f32_launch_shape(a, MT, NB, epi, blocks, st);
 }
 
 // ------------------------------------------------------------------------- attention

@@ -254,6 +254,7 @@ extern "C" int spec_init(const spec_model_desc *tgt, const spec_weights *tgt_w, 
       c->n_cu = prop.multiProcessorCount;
     gemm_tile_prepare();
     attention_prepare();
+    fp32_prepare();
   }
   Sizes z = compute_sizes(tgt, drf, run);
   c->M_max = z.M_max;

@@ -223,6 +223,7 @@ void generic_zero(void *dst, size_t bytes, hipStream_t st);
 
 // fp32 matrix-core path (kernels_fp32.hip)
 bool fp32_supported(const spec_model_desc &D, int dtype);
+void fp32_prepare();
 size_t fp32_packed_bytes(const spec_model_desc &D, int L_max);
 void fp32_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);
 void fp32_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, hipStream_t st);
