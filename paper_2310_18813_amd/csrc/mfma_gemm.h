@@ -122,7 +122,7 @@ bool launch_gemm_rowres(int dtype, const GemmArgs &a, int epi, hipStream_t st);
 // bits of GemmArgs::tune
 enum GemmTune {
   TUNE_TILE_MTW_MASK = 0x00f,   // tiled kernel: force MTW (1..4) ...
-  TUNE_TILE_NBW_SHIFT = 4,      // ... and NBW (2..4), both or neither
+  TUNE_TILE_NBW_SHIFT = 4,      // ... and NBW (2, 3, 4 or 6), both or neither
   TUNE_ROWRES_OFF = 0x100,      // never take the row-resident kernel
   TUNE_ROWRES_ALWAYS = 0x200    // take it for every row count it covers (1..16), not only where it was measured faster
 };

@@ -404,8 +404,8 @@ extern "C" int spec_set_eos(spec_ctx *c, int32_t eos_token) {
 extern "C" int spec_set_gemm_tuning(spec_ctx *c, int32_t tile_mtw, int32_t tile_nbw, int32_t flags) {
   if (!c) return fail(nullptr, SPEC_ERR_INVALID_ARG, "spec_set_gemm_tuning: ctx is null");
   const bool tile_auto = tile_mtw == 0 && tile_nbw == 0;
-  if (!tile_auto && (tile_mtw < 1 || tile_mtw > 4 || tile_nbw < 2 || tile_nbw > 4))
-    return fail(c, SPEC_ERR_INVALID_ARG, "spec_set_gemm_tuning: wave tile must be 0,0 (automatic) or 1..4 x 2..4");
+  if (!tile_auto && (tile_mtw < 1 || tile_mtw > 4 || tile_nbw < 2 || tile_nbw > 6 || tile_nbw == 5))
+    return fail(c, SPEC_ERR_INVALID_ARG, "spec_set_gemm_tuning: wave tile must be 0,0 (automatic) or 1..4 x 2, 3, 4 or 6");
   if (flags < 0 || flags > 3) return fail(c, SPEC_ERR_INVALID_ARG, "spec_set_gemm_tuning: unknown flag bits");
   int t = tile_auto ? 0 : (tile_mtw | (tile_nbw << TUNE_TILE_NBW_SHIFT));
   if (flags & 1) t |= TUNE_ROWRES_OFF;

@@ -145,6 +145,28 @@ def test_rows_are_bit_identical_across_batch_and_speculation_length(world):
         ctx.spec_set_gemm_tuning(0, 0, 0)
 
 
+@pytest.mark.parametrize("nbw", [2, 3, 4, 6])
+@pytest.mark.parametrize("mtw", [1, 2, 3, 4])
+def test_every_wave_tile_gives_the_same_bits(world, mtw, nbw):
+    """All shapes of the tiled kernel, over every product of a pass of some hundred rows, against the automatic choice."""
+    wd = world
+    b, s = wd["cfg"]["pair"][1]
+    want, _, _, _ = gpu_cell(wd, b, s)
+    try:
+        wd["ctx"].spec_set_gemm_tuning(mtw, nbw, 0)
+        got, _, _, _ = gpu_cell(wd, b, s)
+    finally:
+        wd["ctx"].spec_set_gemm_tuning(0, 0, 0)
+    assert torch.equal(got, want)
+
+
+def test_wave_tiles_that_are_not_built_are_refused(world):
+    ctx, B = world["ctx"], world["B"]
+    for mtw, nbw in ((0, 2), (5, 2), (1, 0), (1, 1), (2, 5), (2, 7), (4, 8)):
+        with pytest.raises(B.SpecError):
+            ctx.spec_set_gemm_tuning(mtw, nbw, 0)
+
+
 # ------------------------------------------------------------------ full depth
 # End-to-end bounds for the 32-layer 7B shape in bf16 (max |logit error|).  Every branch matrix of the random-initialised
 # stack has gain 0.02 * sqrt(4096) = 1.28, so the stack amplifies what each layer adds, and one thing each layer adds is
