@@ -23,6 +23,10 @@ PAIRS = {
     "tiny_fp32": ("fp32", 1000, si.CONFIGS["tiny_fp32"][2], si.CONFIGS["tiny_fp32"][3]),
     "small_bf16": ("bf16", 77, si.llama_desc(2, 256, 2, 416, 1000, 128), si.llama_desc(1, 128, 2, 160, 1000, 128)),
     "small_fp16_opt": ("fp16", 78, si.opt_desc(2, 256, 4, 384, 777, 128), si.opt_desc(1, 128, 2, 192, 777, 128)),
+    # one of the two on the generic kernels (heads of 96 or 32), the other on the matrix cores, in one workspace
+    "generic_target_bf16": ("bf16", 79, si.llama_desc(2, 192, 2, 416, 1000, 128), si.llama_desc(1, 128, 2, 160, 1000, 128)),
+    "generic_draft_fp16": ("fp16", 80, si.llama_desc(2, 256, 2, 416, 1000, 128), si.llama_desc(1, 96, 3, 100, 1000, 128)),
+    "generic_target_fp32": ("fp32", 81, si.opt_desc(2, 160, 5, 100, 777, 128), si.opt_desc(1, 128, 2, 192, 777, 128)),
 }
 
 
@@ -93,6 +97,8 @@ SCHEDULE = [2, 4, 0, 3, 0, 0, 4, 1, 3] + [0] * 19 + [4, 2]   # s per round; 19 r
     ("tiny_fp32", False, False), ("tiny_fp32", True, False), ("tiny_fp32", False, True),
     ("small_bf16", False, False), ("small_bf16", True, False), ("small_bf16", False, True),
     ("small_fp16_opt", True, False), ("small_fp16_opt", False, True),
+    ("generic_target_bf16", False, True), ("generic_draft_fp16", False, False), ("generic_draft_fp16", False, True),
+    ("generic_target_fp32", False, False), ("generic_target_fp32", True, False),
 ])
 def test_draft_steps_match_oracle_round_by_round(orc, B, name, twin, external):
     """Every draft step of every round: logits and proposal against the oracle's draft forward over the committed
