@@ -44,7 +44,7 @@ extern "C" const char *spec_last_error(const spec_ctx *c) { return c ? c->err.c_
 // ------------------------------------------------------------------ sizing
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 constexpr int PREFILL_CHUNK = 8;
-constexpr int PREFILL_ROWS = 8192;  // most rows of a prefill pass (33B width: 116 KB of activations a row, 0.95 GB)
+constexpr int PREFILL_ROWS = 8192;  // most rows of a prefill pass (33B width: 116 KB of activations a row, 0.95 GB, and 0.44 GB for SPLIT_ROWS)
 constexpr int PREFILL_Q_MIN = 8;    // fewest rows of a prefill row group
 constexpr int SPLIT_ROWS = 2048;    // most rows of a residual GEMM split by k-slice: beyond, its tiles fill the chip unsplit
 constexpr int Q_LIMIT = 16;  // rows per sequence in one pass (attention query tile)
@@ -132,8 +132,9 @@ static Sizes compute_sizes(const spec_model_desc *tgt, const spec_model_desc *dr
   // matrix-core path: split-KV attention partials and per-strip arg-max partials
   const size_t NC = (size_t)attn_chunk_of((int)std::max<size_t>(L, 1) - 1) + 1, NTh = (V + 15) / 16;
   z.act += al256(M * d * NC * 4) + al256(M * (d / 64 + 1) * NC * 2 * 4) + 2 * al256(M * NTh * 4);
-  z.part_rows = Mp > 32 ? std::min<size_t>(Mp, SPLIT_ROWS) : 0;
-  z.act += al256(8 * z.part_rows * d * 4);  // k-slice sums of the split residual GEMMs
+  const bool fast = fast_supported(*tgt, run->dtype) || (drf && fast_supported(*drf, run->dtype));
+  z.part_rows = fast && Mp > 32 ? std::min<size_t>(Mp, SPLIT_ROWS) : 0;
+  z.act += al256(8 * z.part_rows * d * 4);  // k-slice sums of the split residual GEMMs (16-bit matrix-core path only)
   z.act += 2 * al256(Mp * 4);  // 1 / rms (or 1 / std) and mean per row (folded norm)
   z.tgt_w = packed_bytes(*tgt, run->dtype, run->L_max);
   z.kv_area_tgt = B * (size_t)tgt->d_model * z.L_pad;

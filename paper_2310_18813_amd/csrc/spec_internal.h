@@ -77,17 +77,17 @@ enum PassKind {
 
 struct Workspace {
   // activations (shared by both models; sized for the larger)
-  float *h = nullptr;       // [M_max][d]   fp32 residual stream
-  void *x = nullptr;        // [M_max][d]   normed rows, model dtype (MFMA path: fp16 operands, as attn and act)
-  void *q = nullptr;        // [M_max][d]   queries, pair-interleaved per head: fp32 (matrix-core path) or model dtype (generic)
-  void *attn = nullptr;     // [M_max][d]   attention output, model dtype
-  void *act = nullptr;      // [M_max][f]   FFN activation, model dtype
-  float *y32 = nullptr;     // [M_max][max(3d, 2f)] fp32 GEMM output (generic path)
-  float *logits = nullptr;  // [M_max][vocab] fp32 (generic path / debug)
+  float *h = nullptr;       // [M_pf][d]    fp32 residual stream
+  void *x = nullptr;        // [M_pf][d]    normed rows, model dtype (MFMA path: fp16 operands, as attn and act)
+  void *q = nullptr;        // [M_pf][d]    queries, pair-interleaved per head: fp32 (matrix-core path) or model dtype (generic)
+  void *attn = nullptr;     // [M_pf][d]    attention output, model dtype
+  void *act = nullptr;      // [M_pf][f]    FFN activation, model dtype
+  float *y32 = nullptr;     // [M_pf][max(3d, 2f)] fp32 GEMM output (a generic model in the context; else empty)
+  float *logits = nullptr;  // [M_max][vocab] fp32 (the same)
   float *attn_part = nullptr, *attn_ml = nullptr;  // split-KV partials (MFMA path)
-  float *row_mean = nullptr;                       // [M_max] their means (folded LayerNorm)
-  float *row_inv = nullptr;                        // [M_max] 1 / rms of the rows of h (folded norm, tiled GEMM with large wave tiles)
-  float *gemm_part = nullptr;                      // k-slice sums of the split residual GEMMs (M_max > 32)
+  float *row_mean = nullptr;                       // [M_pf] their means (folded LayerNorm)
+  float *row_inv = nullptr;                        // [M_pf] 1 / rms of the rows of h (folded norm, tiled GEMM with large wave tiles)
+  float *gemm_part = nullptr;                      // k-slice sums of the split residual GEMMs, [8][part_rows][d] (16-bit matrix-core models)
   float *head_part = nullptr;                      // per-strip arg-max partials (MFMA path)
   int32_t *head_part_idx = nullptr;
   int32_t *row_tok = nullptr, *row_pos = nullptr;  // [M_pf]

@@ -130,3 +130,23 @@ def test_sampling_entry_points_validate_before_any_device_call(B):
     assert B.lib.spec_sample_accept(None, fake, None, fake, fake, 2, 3, 100, -2.0, fake, fake, fake) == B.ERR_INVALID_ARG
     assert B.lib.spec_sample_accept(None, fake, None, fake, fake, 0, 3, 100, 1.0, fake, fake, fake) == B.OK
     assert B.lib.spec_set_sampling(None, 1.0, fake, fake, fake) == B.ERR_INVALID_ARG                # no context
+
+
+def test_only_16_bit_matrix_core_models_carry_the_scratch_of_the_split_products(B):
+    """[8][up to 2048 rows][d_model] floats, read by no other path: 64 MB here."""
+    desc = si.llama_desc(1, 1024, 16, 4096, 32000, 512)
+    run = dict(B_max=8, s_max=4, L_max=512, gen_max=16)
+    d, f, V, rows, decode_rows, split = 1024, 4096, 32000, 8 * 512, 8 * 8, 8 * 2048 * 1024 * 4
+
+    def expected(esz, generic):
+        weights = esz * (2 * V * d + 4 * d * d + 3 * d * f + 512 * d)
+        cache = 2 * 8 * 512 * d * esz
+        acts = rows * (8 * d + 2 * d * esz + f * esz) + generic * (rows * 2 * f * 4 + decode_rows * V * 4)
+        return weights + cache + acts
+
+    few = 8 << 20  # partials of attention and arg-max, tables, alignment
+    assert expected(4, 0) < B.spec_workspace_bytes(desc, None, run_desc(B, dtype=B.DTYPE_F32, **run)) < expected(4, 0) + few
+    thin = dict(desc, n_heads=32)  # heads of 32: the generic kernels
+    assert B.spec_workspace_bytes(thin, None, run_desc(B, dtype=B.DTYPE_F32, **run)) < expected(4, 1) + few
+    assert B.spec_workspace_bytes(thin, None, run_desc(B, dtype=B.DTYPE_BF16, **run)) < expected(2, 1) + few
+    assert B.spec_workspace_bytes(desc, None, run_desc(B, dtype=B.DTYPE_BF16, **run)) > expected(2, 0) - 2 * d * 512 + split
