@@ -29,12 +29,12 @@ namespace spec {
 // Written out because the compiler, which would have to assume that every LDS read depends on such a load, waits for
 // all of them in front of each read; here the waits are placed by hand (vmcnt before the barrier that publishes a slot).
 __device__ __forceinline__ void load_frag_to_lds(const unsigned char *base, unsigned lane_off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
 }
 // the same for all lanes (mask -1, uniform) or for none (0); counted by vmcnt either way
 __device__ __forceinline__ void load_frag_to_lds_masked(const unsigned char *base, unsigned lane_off, unsigned lds, int mask) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"s"(lds),
-               "v"(lane_off), "s"(base), "s"(mask) : "memory", "m0");
+  asm volatile("s_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"{m0}"(lds),
+               "v"(lane_off), "s"(base), "s"(mask) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {
