@@ -42,6 +42,12 @@ __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+template <int N, int R>
+__device__ __forceinline__ void wait_loads_and_reads() {
+  static_assert(N >= 0 && N < 64 && R >= 0 && R < 16, "wait count fields");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)" ::"n"(N), "n"(R) : "memory");
+}
+
 // Fragments of one 32-k step of a workgroup, and the ring of LDS slots that hold one step each: as deep as LDS allows,
 // since the loads in flight are what the small tiles, which stream weights for few rows, are bound by.
 template <int MTW, int NBW> struct TileShape {
@@ -200,16 +206,20 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
     pin_step<MTW, NBW>();
   };
   // A bare barrier, not __syncthreads(): the fence of the latter would wait for the loads in flight.
-  auto publish = [&](auto left) {  // this wave's loads are done but for those of the last `left` steps; then meet
+  // `left`: this wave's loads are done but for those of the last `left` steps; its LDS reads but for the READS of the
+  // step it has just issued (LDS reads return in order).  The earlier ones, from the position that is fetched into behind
+  // the barrier, have then arrived wherever the scheduler has put the multiplies that use them.
+  constexpr int READS = NBW + MTW;
+  auto publish = [&](auto left) {
     constexpr int L = decltype(left)::value;
-    wait_loads<L * LPW>();
+    wait_loads_and_reads<L * LPW, READS>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
 
   // Step kt lives at ring position kt % RING.  At the top of step kt the registers hold (or await) its fragments, and
-  // the barrier there says that step kt + 1 is in LDS.  Behind it every wave is done with step kt - 1 (its multiplies
-  // are under way), whose position takes step kt + RING - 1.
+  // the barrier there says that step kt + 1 is in LDS.  Behind it every wave has the fragments of step kt - 1 in its
+  // registers, whose position takes step kt + RING - 1.
   int at = 0, kt = 0;
   auto turn = [&](auto first, const u32x4_v (&x)[MTW], u32x4_v (&xn)[MTW]) {
     publish(std::integral_constant<int, RING - 3>{});
