@@ -161,7 +161,9 @@ __global__ __launch_bounds__(576) void k_gemm_rowres(GemmArgs a) {
     wg_barrier();
     wp = wp_next;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the over-fetched tail
+  // the over-fetched tail: every slot tied to a wait, so that no register of the ring is given away with a load in flight
+#pragma unroll
+  for (int r = 0; r < R; ++r) stream_wait<0>(ring[r]);
 }
 
 template <class T, int MT, int KTP, int R>
