@@ -141,9 +141,10 @@ int spec_reset(spec_ctx *ctx, int32_t B, const int32_t *d_prompt, int32_t P);
 
 /* As spec_reset for prompts of different lengths: row b of d_prompt ([B][P_stride], int32, device) holds the
    h_len[b] prompt tokens of sequence b (h_len: host, B entries, 1 <= h_len[b] <= P_stride; the rest of a row
-   is ignored).  One batch prefill over the longest prompt, rows beyond a sequence's own prompt being dead
-   rows of the pass; the capacity rules of spec_reset apply to the longest prompt.  Every sequence emits up to
-   gen_max tokens after its own prompt.  Synchronises the stream once (the lengths go to the device).       */
+   is ignored).  The prompts are prefilled together: each is cut into groups of 16 (or 8) consecutive positions, and
+   passes of up to 8192 rows take groups of any sequences; the capacity rules of spec_reset apply to the longest
+   prompt.  Every sequence emits up to gen_max tokens after its own prompt.  Synchronises the stream once (the lengths
+   go to the device).                                                                                       */
 int spec_reset_ragged(spec_ctx *ctx, int32_t B, const int32_t *d_prompt, int32_t P_stride, const int32_t *h_len);
 
 /* As spec_reset but without touching the KV caches: the caller provides positions

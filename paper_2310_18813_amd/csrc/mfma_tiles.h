@@ -21,11 +21,6 @@ struct Mfma16 {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_v, a), __builtin_bit_cast(f16x8_v, b), c,
                                                   0, 0, 0);
   }
-  // d = A * B, in d's own registers: written out so that the chain's registers stay in place across the two kinds of
-  // step (as a builtin with a zero operand it got registers of its own, and the largest wave tile spilled)
-  static __device__ __forceinline__ void run_from_zero(u32x4_v a, u32x4_v b, f32x4_v &d) {
-    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "+v"(d) : "v"(a), "v"(b));
-  }
 };
 
 // Folded norm, consumer side: the sum of squares of a row of activations is taken from the fp16 operand
