@@ -443,12 +443,19 @@ static void launch_epi(const GemmArgs &a, int epi, dim3 grid, dim3 block, size_t
 // times as dear as one that hits L2 (measured).  Against doubling NB up to MT: QKV at d_model 4096 with 17..64
 // rows 27..36 -> 23..31 us (three strips per workgroup: one workgroup per unit).  Small matrices (a draft model's)
 // come out with two row tiles per workgroup and more row passes: their few strips then spread over more units.
-// Returns the estimate in us: 4 us and 12.8 ns (more with more row passes) per step and thousand cost units (within 10 %
-// from 36 to 256 rows on the matrices of the 7B, 13B and 33B widths).
+// Returns the time of the launch as stream_us estimates it.
+//
+// stream_us: per step and thousand cost units of the compute unit with the most workgroups, and per tile
+// of that unit's workgroups for the meeting of the slices and the epilogue (the LM head's: the arg-max).  Fitted to 369 launches
+// of 33 to 512 rows over the five products of nine models, widths 512 to 6656 (rms error 12 %; without the share per tile,
+// which is most of a short k, 29 %, and up to twice too low).
+static double stream_us(long per_cu, long cost, int tiles, int passes, int KT, double tile_us) {
+  return 2.0 + 1e-6 * cost * KT * (10.5 + 1.4 * std::min(passes - 1, 3)) + tile_us * per_cu * tiles;
+}
 static double choose_stream(const GemmArgs &a, int &MT, int &NB) {
   const int n_cu = a.n_cu > 0 ? a.n_cu : 256, mt_max = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 4;
   static const int cand[] = {1, 2, 3, 4, 6, 8};
-  long best = -1;
+  long best = -1, best_per_cu = 0;
   MT = mt_max; NB = 1;
   for (int mt = mt_max; mt >= 1; mt >>= 1) {
     const int passes = (a.M + mt * 16 - 1) / (mt * 16);
@@ -458,19 +465,33 @@ static double choose_stream(const GemmArgs &a, int &MT, int &NB) {
       const long per_cu = (wgs + n_cu - 1) / n_cu;
       const long w_cost = (3000 + 1000 * (passes - 1)) / passes;  // per strip and step, averaged over the row passes
       const long cost = per_cu * (nb * w_cost + mt * 1000);
-      if (best < 0 || cost < best) { best = cost; NB = nb; MT = mt; }
+      if (best < 0 || cost < best) { best = cost; best_per_cu = per_cu; NB = nb; MT = mt; }
     }
   }
-  const int passes = (a.M + MT * 16 - 1) / (MT * 16);
-  return 4.0 + 1e-6 * best * a.KT * (12.8 + 1.4 * std::min(passes - 1, 3));
+  return stream_us(best_per_cu, best, NB * MT, (a.M + MT * 16 - 1) / (MT * 16), a.KT, 0.54);
+}
+
+// The LM head's streaming launch.  Up to 16 rows as above; beyond, with its arg-max epilogue per strip, it measured better
+// with fewer strips per workgroup than that estimate picks: as many as row tiles while 160 workgroups remain.
+static double choose_stream_head(const GemmArgs &a, int &MT, int &NB) {
+  if (a.M <= 16) return choose_stream(a, MT, NB);
+  MT = a.M <= 32 ? 2 : 4; NB = 1;
+  const int passes = (a.M + MT * 16 - 1) / (MT * 16), n_cu = a.n_cu > 0 ? a.n_cu : 256;
+  while (NB < MT && (a.NT / (NB * 2)) * passes >= 160) NB *= 2;
+  if (MT == 4 && NB == 4 && (a.NT / 8) * passes >= 160) NB = 8;
+  const long per_cu = ((long)((a.NT + NB - 1) / NB) * passes + n_cu - 1) / n_cu;
+  const long w_cost = (3000 + 1000 * (passes - 1)) / passes;
+  return stream_us(per_cu, per_cu * (NB * w_cost + MT * 1000), NB * MT, passes, a.KT, 0.7);
 }
 
 // Which kernel: the streaming one up to 32 rows, beyond whichever the estimates say is faster (all give the same bits).
 // The tiled kernel shares the activations of a workgroup through LDS and reads a weight once per up to 256 rows; narrow
 // outputs leave it too few workgroups unless each takes one k-slice and a second kernel adds the slices.  Measured
 // (us; streaming / tiled / split): 15360 x 5120 at 64 rows 40 / 35 / -, 12288 x 4096 at 64 rows 27 / 29 / -; 4096 x 4096
-// at 128, 256 and 512 rows 17 / 22 / -, 25 / 23 / - and - / 33 / 50; 4096 x 11008 at 64, 256 and 1024 rows - / 52 / 27,
-// - / 52 / 43 and - / 105 / 142.
+// at 128, 256 and 512 rows 17 / 22 / -, 25 / 23 / - and - / 33 / 50; LM heads of 32000 x 768, 2048 and 4096 at 48 rows
+// 32 / 18 / -, 44 / 33 / - and 64 / 56 / -, 8192 x 4096 at 48 and 96 rows 23 / 27 / - and 36 / 28 / -; gate-up 8192 x 1024 at
+// 96 and 256 rows 17 / 13 / - and 27 / 17 / -; 4096 x 11008 at 64, 256 and 1024 rows - / 52 / 27, - / 52 / 43 and
+// - / 105 / 142.  Over 540 launches (33 to 512 rows) the choice takes 0.5 % more than the best of the three.
 enum GemmRoute { ROUTE_STREAM, ROUTE_TILE, ROUTE_SPLIT };
 static GemmRoute route(const GemmArgs &a, int epi) {
   if (a.M <= 32 || a.NT < 16) return ROUTE_STREAM;
@@ -478,9 +499,10 @@ static GemmRoute route(const GemmArgs &a, int epi) {
   const bool split_ok = epi == EPI_RESIDUAL && a.part && a.KS > 1 && (a.KT / a.KS >= 32 || (a.M > 256 && a.KT / a.KS >= 2));
   if (a.tune & 0xff) return split_ok ? ROUTE_SPLIT : ROUTE_TILE;  // a pinned wave tile (test / tuning aid)
   int MT, NB;
-  const double stream = choose_stream(a, MT, NB), tile = gemm_tile_us(a, false);
-  if (split_ok && gemm_tile_us(a, true) < std::min(stream, tile)) return ROUTE_SPLIT;
-  return tile < 0.95 * stream ? ROUTE_TILE : ROUTE_STREAM;
+  const double stream = epi == EPI_LOGITS ? choose_stream_head(a, MT, NB) : choose_stream(a, MT, NB), tile = gemm_tile_us(a, false);
+  // (the split launch's estimate is about 15 % high at up to 256 rows, where one row pass reads the weights)
+  if (split_ok && (a.M <= 256 ? 0.85 : 1.0) * gemm_tile_us(a, true) < std::min(stream, tile)) return ROUTE_SPLIT;
+  return tile < stream ? ROUTE_TILE : ROUTE_STREAM;
 }
 bool gemm_can_leave_ssq(const GemmArgs &a) {  // the row-wise reduction keeps the fp16 row in LDS: rows of up to 8192
   return a.x_out && a.M > 64 && (a.N & 31) == 0 && a.N <= 8192 && route(a, EPI_RESIDUAL) == ROUTE_SPLIT;
@@ -503,15 +525,8 @@ static void launch_gemm_t(GemmArgs a, int epi, hipStream_t st) {
   if (launch_gemm_rowres(std::is_same<T, bf16_t>::value ? SPEC_DTYPE_BF16 : SPEC_DTYPE_F16, a, epi, st)) return;
   const int KS = a.KS;
   int MT, NB;
-  choose_stream(a, MT, NB);
-  if (epi == EPI_LOGITS && a.M > 16) {
-    // the LM head, with its arg-max epilogue per strip, measured better with fewer strips per workgroup than that
-    // estimate picks: as many as row tiles while 160 workgroups remain
-    MT = a.M <= 32 ? 2 : 4; NB = 1;
-    const int passes = (a.M + MT * 16 - 1) / (MT * 16);
-    while (NB < MT && (a.NT / (NB * 2)) * passes >= 160) NB *= 2;
-    if (MT == 4 && NB == 4 && (a.NT / 8) * passes >= 160) NB = 8;
-  }
+  if (epi == EPI_LOGITS) choose_stream_head(a, MT, NB);
+  else choose_stream(a, MT, NB);
   a.passes = (a.M + MT * 16 - 1) / (MT * 16);
   a.groups = (a.NT + NB - 1) / NB;
   const int blocks = a.passes == 1 ? a.groups : ((a.groups + 7) / 8) * 8 * a.passes;

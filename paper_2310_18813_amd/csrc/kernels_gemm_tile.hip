@@ -473,7 +473,11 @@ static void launch_shape(int dtype, const GemmArgs &a, int MTW, int NBW, int epi
 constexpr int TILE_MT[4] = {1, 2, 3, 4}, TILE_NB[4] = {2, 3, 4, 6};
 static double tile_us(int mt, int nb, int M, int NT, int n_cu, int steps, int wg_mult, double w_bytes) {
   const int passes = (M + 64 * mt - 1) / (64 * mt);
-  const int wgs = passes * ((NT + 2 * nb - 1) / (2 * nb)) * wg_mult;
+  int groups = (NT + 2 * nb - 1) / (2 * nb);
+  // all workgroups of a strip group of a split launch of two or four k-slices share an XCD: the XCDs with one group more
+  // set the time (2048 x 5504 at 320 rows, 11 groups x 20 workgroups: 42 us, where 32 groups x 8 take 25)
+  if (wg_mult > 1 && wg_mult < 8) groups = (groups + 7) / 8 * 8;
+  const int wgs = passes * groups * wg_mult;
   const int rounds = (wgs + n_cu - 1) / n_cu;
   const double mul = 0.0113 * mt * nb, load = 0.0087 * (2 * nb + 4 * mt);
   const double raw = rounds * (1.35 + 0.396 * mt * nb + steps * (0.066 + std::sqrt(mul * mul + load * load)));
