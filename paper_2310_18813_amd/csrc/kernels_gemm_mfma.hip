@@ -447,7 +447,7 @@ static void launch_epi(const GemmArgs &a, int epi, dim3 grid, dim3 block, size_t
 //
 // stream_us: per step and thousand cost units of the compute unit with the most workgroups, and per tile
 // of that unit's workgroups for the meeting of the slices and the epilogue (the LM head's: the arg-max).  Fitted to 369 launches
-// of 33 to 512 rows over the five products of nine models, widths 512 to 6656 (rms error 12 %; without the share per tile,
+// of 33 to 512 rows over the five products of nine models, widths 512 to 6656 (rms error 15 %; without the share per tile,
 // which is most of a short k, 29 %, and up to twice too low).
 static double stream_us(long per_cu, long cost, int tiles, int passes, int KT, double tile_us) {
   return 2.0 + 1e-6 * cost * KT * (10.5 + 1.4 * std::min(passes - 1, 3)) + tile_us * per_cu * tiles;
