@@ -28,13 +28,22 @@ namespace spec {
 // One fragment of 1 KB from `base` (uniform) straight to LDS byte offset `lds` (uniform), lane l's 16 bytes at 16 l.
 // Written out because the compiler, which would have to assume that every LDS read depends on such a load, waits for
 // all of them in front of each read; here the waits are placed by hand (vmcnt before the barrier that publishes a slot).
+// NT: non-temporally
+template <bool NT>
 __device__ __forceinline__ void load_frag_to_lds(const unsigned char *base, unsigned lane_off, unsigned lds) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
+  if (NT) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
+  else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
 }
 // the same for all lanes (mask -1, uniform) or for none (0); counted by vmcnt either way
 __device__ __forceinline__ void load_frag_to_lds_masked(const unsigned char *base, unsigned lane_off, unsigned lds, int mask) {
   asm volatile("s_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" ::"{m0}"(lds),
                "v"(lane_off), "s"(base), "s"(mask) : "memory");
+}
+// -1 if x is negative, else 0, in a scalar register (written out: the compiler may make a per-lane select of a mask)
+__device__ __forceinline__ int sign_mask(int x) {
+  int m;
+  asm("s_ashr_i32 %0, %1, 31" : "=s"(m) : "s"(x) : "scc");
+  return m;
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {
@@ -76,12 +85,23 @@ __device__ __forceinline__ void pin_step() {
 }
 
 // NORM: what is folded in front (0 nothing, 1 RMS norm, 2 LayerNorm).  T: the cache's type (EPI_QKV only).
-template <class T, int MTW, int NBW, int EPI, int NORM>
+// ONCE: a single row pass, so that no other workgroup reads a weight: they are loaded non-temporally.  (With several row passes
+// that takes them out of the L2 for the next workgroup: loads alone, 22016 x 4096 at 6592 rows 632 -> 711 us.)
+template <class T, int MTW, int NBW, int EPI, int NORM, bool ONCE>
 __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using S = TileShape<MTW, NBW>;
   constexpr int NBG = S::NBG, MTG = S::MTG, FRAGS = S::FRAGS, SLOT = S::SLOT, RING = S::RING;
-  constexpr int LPW = (FRAGS + 7) / 8;  // fragments each wave fetches per step (the last one: only some waves)
+  // Fragments a wave fetches per step, between its multiplies.  ONCE: LW strips and LX row tiles, and of the W_REST strips and
+  // X_REST tiles left over the first and the last waves one each.  Else strips and tiles in one row, w, w + 8, ..., and in the
+  // last place the waves without a fragment issue a load without lanes, so that all waves count alike.  Such a load takes a
+  // place among the loads a CU keeps in flight like any other, and those are what a launch of few rows is bound by (10
+  // fragments of 36 rows were 16 loads: gate-up 22016 x 4096 40.0 -> 35.1 us; 12 of 64 rows 16: 46.0 -> 40.3); with several
+  // row passes the branches around the rest cost more than it gains (776 rows, 5120 wide, a layer +4 %).  The rest goes out in
+  // front of a step's multiplies, with one row tile per wave behind them (80 rows of 20480 x 5120 50.6 and 52.7, 36 rows of
+  // 22016 x 4096 38.1 and 35.1).
+  constexpr int LW = ONCE ? NBG / 8 : 0, W_REST = ONCE ? NBG % 8 : 0, LX = MTG / 8, X_REST = ONCE ? MTG % 8 : 0;
+  constexpr int LPW = ONCE ? LW + LX : (FRAGS + 7) / 8;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wn = w & 1, wm = w >> 1;
   const int c = lane & 15, g = lane >> 4;
@@ -110,6 +130,9 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
     pass = blk * 8 + rest % in_blk;
     G = (rest / in_blk) * 8 + (id & 7);
   }
+  G = __builtin_amdgcn_readfirstlane(G);
+  pass = __builtin_amdgcn_readfirstlane(pass);
+  slice_id = __builtin_amdgcn_readfirstlane(slice_id);
   if (G >= a.groups) return;
   const int kt_per = a.KT / a.KS;
   const int KTL = PARTIAL ? kt_per : a.KT;          // steps of this workgroup
@@ -118,25 +141,37 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   const int mtile0 = pass * MTG;
   const int m_tiles = (a.M + 15) >> 4;
 
-  // Fragment f of a step: f < NBG weight strip nt0 + f; else activation tile f - NBG.  Wave w fetches f = w, w + 8, ...
-  const unsigned char *src[LPW];
+  // Fragment f of a step (and its place in the slot): f < NBG weight strip nt0 + f; else activation tile f - NBG.
+  const bool w_rest = W_REST > 0 && w < W_REST, x_rest = X_REST > 0 && w >= 8 - X_REST;
+  auto frag_of = [&](int i) {
+    if (!ONCE) return min(w + 8 * i, FRAGS - 1);
+    if (i < LPW) return i < LW ? w + 8 * i : NBG + w + 8 * (i - LW);
+    return i == LPW ? min(w + 8 * LW, NBG - 1) : NBG + min(8 * LX + max(w - (8 - X_REST), 0), MTG - 1);
+  };
+  const unsigned char *src[LPW + 2];
 #pragma unroll
-  for (int i = 0; i < LPW; ++i) {
-    const int f = min(w + 8 * i, FRAGS - 1);
+  for (int i = 0; i < LPW + 2; ++i) {
+    const int f = frag_of(i);
     const size_t row = f < NBG ? (size_t)min(nt0 + f, a.NT - 1) : (size_t)min(mtile0 + f - NBG, m_tiles - 1);
     src[i] = (const unsigned char *)(f < NBG ? a.W : a.X) + (row * a.KT + kt_lo) * 1024;
   }
   const unsigned lane_off = lane * 16;
-  // not every wave has an LPW-th fragment: those without issue its load with no lane, so that all count alike
-  const int last_mask = __builtin_amdgcn_readfirstlane(w < FRAGS - 8 * (LPW - 1) ? -1 : 0);
+  const int last_mask = sign_mask(w - (FRAGS - 8 * (LPW - 1)));  // !ONCE: the waves with an LPW-th fragment
+  // this wave's fragments at byte k of their rows into the slot at `lds`
   auto fetch1 = [&](int i, size_t k, unsigned lds) {
-    if (i < LPW - 1 || FRAGS % 8 == 0) load_frag_to_lds(src[i] + k, lane_off, lds + i * 8 * 1024);
-    else load_frag_to_lds_masked(src[i] + k, lane_off, lds + i * 8 * 1024, last_mask);
+    if (ONCE && i < LW) load_frag_to_lds<true>(src[i] + k, lane_off, lds + (w + 8 * i) * 1024);
+    else if (ONCE) load_frag_to_lds<false>(src[i] + k, lane_off, lds + (NBG + w + 8 * (i - LW)) * 1024);
+    else if (i < LPW - 1 || FRAGS % 8 == 0) load_frag_to_lds<false>(src[i] + k, lane_off, lds + (w + 8 * i) * 1024);
+    else load_frag_to_lds_masked(src[i] + k, lane_off, lds + (w + 8 * i) * 1024, last_mask);
+  };
+  auto fetch_rest = [&](size_t k, unsigned lds) {
+    if (w_rest) load_frag_to_lds<true>(src[LPW] + k, lane_off, lds + (8 * LW + w) * 1024);
+    if (x_rest) load_frag_to_lds<false>(src[LPW + 1] + k, lane_off, lds + (NBG + 8 * LX + w - (8 - X_REST)) * 1024);
   };
   // step kt of this wave's fragments into ring position `at`; beyond the end the last step is fetched again: nobody
   // reads it, and no wait count depends on where the end lies
   auto fetch_k = [&](int kt) { return (size_t)min(kt, KTL - 1) * 1024; };
-  auto fetch_lds = [&](int at) { return (unsigned)(at * SLOT + w * 1024); };
+  auto fetch_lds = [&](int at) { return (unsigned)(at * SLOT); };
 
   f32x4_v cur[NBW][MTW], tot[NBW][MTW];
 #pragma unroll
@@ -183,6 +218,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   auto step = [&](auto first, const u32x4_v (&x)[MTW], u32x4_v (&xn)[MTW], int at, size_t fk, unsigned flds) {
     constexpr bool FIRST = decltype(first)::value;
     const unsigned char *wp = w_base + at * SLOT, *xp = x_base + at * SLOT;
+    if (MTW > 1) fetch_rest(fk, flds);
     if (INLOOP) {
 #pragma unroll
       for (int mt = 0; mt < MTW; ++mt) {
@@ -204,6 +240,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
       for (int i = nb * LPW / NBW; i < (nb + 1) * LPW / NBW; ++i) fetch1(i, fk, flds);
     }
     pin_step<MTW, NBW>();
+    if (MTW == 1) fetch_rest(fk, flds);
   };
   // A bare barrier, not __syncthreads(): the fence of the latter would wait for the loads in flight.
   // `left`: this wave's loads are done but for those of the last `left` steps; its LDS reads but for the READS of the
@@ -212,7 +249,9 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   constexpr int READS = NBW + MTW;
   auto publish = [&](auto left) {
     constexpr int L = decltype(left)::value;
-    wait_loads_and_reads<L * LPW, READS>();
+    if (w_rest && x_rest) wait_loads_and_reads<L * (LPW + 2), READS>();
+    else if (w_rest || x_rest) wait_loads_and_reads<L * (LPW + 1), READS>();
+    else wait_loads_and_reads<L * LPW, READS>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
@@ -229,9 +268,11 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
     ++kt;
   };
 #pragma unroll
-  for (int s = 0; s < RING - 1; ++s)
+  for (int s = 0; s < RING - 1; ++s) {
 #pragma unroll
     for (int i = 0; i < LPW; ++i) fetch1(i, fetch_k(s), fetch_lds(s));
+    fetch_rest(fetch_k(s), fetch_lds(s));
+  }
   publish(std::integral_constant<int, RING - 2>{});
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): with no scalar load left under way the waits on LDS reads in the loop are exact counts
 #pragma unroll
@@ -422,10 +463,14 @@ __global__ __launch_bounds__(512) void k_row_inv_x(const void *__restrict__ X, i
 template <class T, int MTW, int NBW, int EPI, int NORM>
 static void launch_one(const GemmArgs &a, int blocks, hipStream_t st) {
   constexpr size_t lds = TileShape<MTW, NBW>::LDS;
-  if (blocks < 0)
-    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  else
-    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM>), dim3(blocks), dim3(512), lds, st, a);
+  if (blocks < 0) {
+    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  } else if (a.passes == 1) {
+    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM, true>), dim3(blocks), dim3(512), lds, st, a);
+  } else {
+    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM, false>), dim3(blocks), dim3(512), lds, st, a);
+  }
 }
 
 template <class T, int MTW, int NBW, int EPI>
