@@ -492,8 +492,9 @@ static double choose_stream_head(const GemmArgs &a, int &MT, int &NB) {
 // 32 / 18 / -, 44 / 33 / - and 64 / 56 / -, 8192 x 4096 at 48 and 96 rows 23 / 27 / - and 36 / 28 / -; gate-up 8192 x 1024 at
 // 96 and 256 rows 17 / 13 / - and 27 / 17 / -; 4096 x 11008 at 64, 256 and 1024 rows - / 52 / 27, - / 52 / 43 and
 // - / 105 / 142.  Over 540 launches (33 to 512 rows) the choice takes 0.5 % more than the best of the three.
-enum GemmRoute { ROUTE_STREAM, ROUTE_TILE, ROUTE_SPLIT };
+enum GemmRoute { ROUTE_STREAM, ROUTE_TILE, ROUTE_SPLIT, ROUTE_STRIPS };
 static GemmRoute route(const GemmArgs &a, int epi) {
+  if (epi == EPI_LOGITS && gemm_takes_strips(a)) return ROUTE_STRIPS;
   if (a.M <= 32 || a.NT < 16) return ROUTE_STREAM;
   // the slices of a split launch are at least 32 steps long (shorter ones at up to 256 rows: no faster than streaming)
   const bool split_ok = epi == EPI_RESIDUAL && a.part && a.KS > 1 && (a.KT / a.KS >= 32 || (a.M > 256 && a.KT / a.KS >= 2));
@@ -511,12 +512,16 @@ bool gemm_wants_row_inv(const GemmArgs &a, int epi) {
   return a.M > 0 && route(a, epi) == ROUTE_TILE && gemm_tile_wants_row_inv(a, epi);
 }
 
-int gemm_head_partials(const GemmArgs &a) { return route(a, EPI_LOGITS) == ROUTE_TILE ? gemm_tile_head_partials(a) : a.NT; }
+int gemm_head_partials(const GemmArgs &a) {
+  const GemmRoute r = route(a, EPI_LOGITS);
+  return r == ROUTE_STRIPS ? gemm_strips_partials(a) : r == ROUTE_TILE ? gemm_tile_head_partials(a) : a.NT;
+}
 
 template <class T>
 static void launch_gemm_t(GemmArgs a, int epi, hipStream_t st) {
   if (a.M <= 0) return;
   const GemmRoute r = route(a, epi);
+  if (r == ROUTE_STRIPS) { launch_gemm_strips(a, st); return; }
   if (r != ROUTE_STREAM) {
     launch_gemm_tile(std::is_same<T, bf16_t>::value ? SPEC_DTYPE_BF16 : SPEC_DTYPE_F16, a, epi, r == ROUTE_SPLIT, st);
     return;

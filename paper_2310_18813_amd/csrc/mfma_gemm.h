@@ -119,6 +119,11 @@ void attention_prepare();
 // walks several weight strips (kernels_gemm_rowres.hip).  launch_gemm_rowres returns false when the shape is not
 // covered (the caller then takes the streaming kernel).
 bool launch_gemm_rowres(int dtype, const GemmArgs &a, int epi, hipStream_t st);
+// LM head of up to 32 rows over a short k: a wave per strip (kernels_gemm_strips.hip)
+bool gemm_takes_strips(const GemmArgs &a);
+int gemm_strips_partials(const GemmArgs &a);
+void launch_gemm_strips(GemmArgs a, hipStream_t st);
+void gemm_strips_prepare();
 // bits of GemmArgs::tune
 enum GemmTune {
   TUNE_TILE_MTW_MASK = 0x00f,   // tiled kernel: force MTW (1..4) ...

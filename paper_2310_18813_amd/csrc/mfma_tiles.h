@@ -111,6 +111,16 @@ __device__ __forceinline__ float *logits_row(const GemmArgs &a, int m) {
   if (a.logit_step <= 1) return a.logits + (size_t)m * a.N;
   return m % a.logit_step == a.logit_step - 1 ? a.logits + (size_t)(m / a.logit_step) * a.N : nullptr;
 }
+// ... and four consecutive outputs v of column n on (a multiple of four) into it, in one store where all rows allow it
+__device__ __forceinline__ void dump_logits(const GemmArgs &a, float *row, int n, f32x4_v v) {
+  if ((a.N & 3) == 0 && ((uintptr_t)a.logits & 15) == 0) {
+    if (n < a.N) *(f32x4_v *)(row + n) = v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (n + i < a.N) row[n + i] = v[i];
+  }
+}
 // EPI_LOGITS: the four lane groups' candidates for row m -> partial p of the row (lowest index wins ties)
 __device__ __forceinline__ void row_argmax_out(const GemmArgs &a, float bv, int bi, int m, int p, bool live, int g) {
 #pragma unroll
@@ -218,10 +228,8 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int 
     float *dump = live ? logits_row(a, m) : nullptr;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (n + i < a.N) {
-        if (dump) dump[n + i] = v[i];
-        argmax_combine(bv, bi, v[i], n + i);
-      }
+      if (n + i < a.N) argmax_combine(bv, bi, v[i], n + i);
+    if (dump) dump_logits(a, dump, n, v);
     row_argmax_out(a, bv, bi, m, nt, live, g);
   }
 }
@@ -290,10 +298,8 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
         const int n = (nt0 + nb) * 16 + 4 * g;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (n + i < a.N) {
-            if (dump) dump[n + i] = v[i];
-            argmax_combine(bv, bi, v[i], n + i);
-          }
+          if (n + i < a.N) argmax_combine(bv, bi, v[i], n + i);
+        if (dump) dump_logits(a, dump, n, v);
       }
       row_argmax_out(a, bv, bi, m, nt0 / NBW, live[mt], g);
     }

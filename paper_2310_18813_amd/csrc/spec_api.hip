@@ -254,6 +254,7 @@ extern "C" int spec_init(const spec_model_desc *tgt, const spec_weights *tgt_w, 
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
       c->n_cu = prop.multiProcessorCount;
     gemm_tile_prepare();
+    gemm_strips_prepare();
     attention_prepare();
     fp32_prepare();
   }
