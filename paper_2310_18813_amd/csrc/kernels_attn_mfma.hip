@@ -19,7 +19,7 @@
 // the partials are merged pairwise in ascending chunk order.  Masked keys contribute exact
 // zeros and leave the running maximum unchanged, and merging an all-masked partial is an
 // exact no-op, so neither the other rows of a pass nor the launch shape change a row's
-// bits.  Two launch shapes compute exactly that: one wave per (sequence, head, chunk) with
+// bits.  The launch shapes compute exactly that: one wave per (sequence, head, chunk) with
 // the partials merged by a second kernel (few sequences: parallelism over chunks), or one
 // wave per (sequence, head) walking its chunks and merging in registers (many sequences:
 // no partial traffic).
@@ -418,12 +418,162 @@ __global__ __launch_bounds__(512) void k_attn_group(AttnArgs a) {
   }
 }
 
+// Launch shape 4, prefills: a workgroup takes four row groups of one head, a wave each, and the waves read the cache rows of
+// the groups' sequence (mostly one: its groups follow each other) through LDS, every step once for all of them.  One wave
+// per (group, head) asks for 16 KB of cache rows per 16 query rows and 32 keys, and what a CU keeps in flight on that way
+// bounds a long prompt (5 prompts of up to
+// 2011 tokens x 52 heads of 128: 1.42 ms a layer, the whole prefill 23.1 -> 21.7 ms with this).  The steps and merges of a wave are those of the other shapes; steps beyond its own
+// last position it sits out.
+constexpr int PREFILL_WAVES = 4, PREFILL_RING = 4;
+constexpr size_t attn_prefill_lds(int HD) { return (size_t)PREFILL_RING * (HD / 8) * 1024 + 2 * PREFILL_WAVES * sizeof(int); }
+
+// 16 bytes per lane from the lane's own address to LDS byte offset `lds` + 16 lane
+__device__ __forceinline__ void load_lanes_to_lds(const void *p, unsigned lds) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(lds), "v"(p) : "memory");
+}
+
+template <class T, int HD>
+__global__ __launch_bounds__(256, 2) void k_attn_prefill(AttnArgs a) {
+  constexpr int HT = HD / 16, KK = HD / 32, FRAGS = HD / 8, FPW = FRAGS / PREFILL_WAVES, STEP_BYTES = 32 * HD * 2;
+  // [PREFILL_RING][FRAGS][64] 16-byte units, behind them the groups' sequences and last positions (no static LDS: the loads
+  // straight to LDS count from its start)
+  extern __shared__ __attribute__((aligned(16))) unsigned char attn_smem[];
+  int *sh_seq = (int *)(attn_smem + PREFILL_RING * FRAGS * 1024), *sh_pmax = sh_seq + PREFILL_WAVES;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // last first: the groups of a sequence are in ascending order of position, and the short ones fill the end
+  const int id = (int)gridDim.x - 1 - (int)blockIdx.x, hh = id % a.H, b = id / a.H * PREFILL_WAVES + wv;
+  const bool on = b < a.B;
+  WaveSetup w = wave_setup(a, on ? b : a.B - 1, lane);
+  if (!on) { w.pos_j = -1; w.pmax = -1; }
+  w.pmax = __builtin_amdgcn_readfirstlane(w.pmax);  // the same for the whole wave
+  const int d = a.H * HD;
+  const float scale = rsqrtf((float)HD) * LOG2E;  // score scale in base-2 exponent units
+  QFrags<T, HD> qf;
+  load_q<T, HD>(qf, (const float *)a.q + (size_t)w.m_row * d + (size_t)hh * HD, w.g);
+  if (lane == 0) { sh_seq[wv] = on ? a.grp_seq[b] : -1; sh_pmax[wv] = w.pmax; }
+  __syncthreads();
+
+  float mr = NEG_BIG, lr = 0.f, mc = NEG_BIG, lc = 0.f;
+  f32x4_v ar[HT], ac[HT];
+#pragma unroll
+  for (int ht = 0; ht < HT; ++ht) ar[ht] = ac[ht] = (f32x4_v){0.f, 0.f, 0.f, 0.f};
+  // this wave's fragments of a step: FPW consecutive ones of k0, k1, v
+  const int f0 = wv * FPW, r = w.j, g = w.g;
+  const u32x4_v *frags = (const u32x4_v *)attn_smem;
+
+  for (int first = 0; first < PREFILL_WAVES;) {  // the sequences of the four groups, one after the other
+    const int seq = __builtin_amdgcn_readfirstlane(sh_seq[first]);
+    int end = first, last = -1;  // this sequence's groups, and the last position any of them reads
+    while (end < PREFILL_WAVES && __builtin_amdgcn_readfirstlane(sh_seq[end]) == seq) {
+      last = max(last, __builtin_amdgcn_readfirstlane(sh_pmax[end]));
+      ++end;
+    }
+    const bool mine = wv >= first && wv < end;
+    first = end;
+    if (last < 0) continue;
+    const int steps = last / 32 + 1;
+    const size_t cbh = (size_t)seq * a.H + hh;
+    const unsigned char *kbase = (const unsigned char *)a.kc + cbh * a.L_pad * HD * 2, *vbase = (const unsigned char *)a.vc + cbh * a.L_pad * HD * 2;
+    const unsigned char *src[FPW];
+#pragma unroll
+    for (int i = 0; i < FPW; ++i) {
+      const int f = f0 + i;
+      if (f < 2 * KK) src[i] = kbase + ((size_t)(8 * (r >> 2) + (r & 3) + (f >= KK ? 4 : 0)) * HD + 8 * g + (f >= KK ? f - KK : f) * 32) * 2;
+      else src[i] = vbase + (((size_t)g * HD + r) * KV_VBLOCK + (size_t)(f - 2 * KK) * 16 * KV_VBLOCK) * 2;
+    }
+    auto fetch = [&](int step, int slot) {  // beyond the end the last step again: no wait count depends on where it lies
+#pragma unroll
+      for (int i = 0; i < FPW; ++i)
+        load_lanes_to_lds(src[i] + (size_t)min(step, steps - 1) * STEP_BYTES, (unsigned)((slot * FRAGS + f0 + i) * 1024));
+    };
+#pragma unroll
+    for (int s = 0; s < PREFILL_RING - 1; ++s) fetch(s, s);
+    int slot = 0, chunk_end = 0;
+    for (int step = 0; step < steps; ++step) {
+      // this wave's part of the step is in LDS and its reads of the slot that is fetched into are done; behind the barrier
+      // everyone's
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((PREFILL_RING - 2) * FPW) : "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      fetch(step + PREFILL_RING - 1, slot == 0 ? PREFILL_RING - 1 : slot - 1);
+      const int ks = step * 32;
+      if (mine && ks <= w.pmax) {
+        if (ks == chunk_end) {  // a chunk starts: the last one joins the total
+          const int c = attn_chunk_of(ks);
+          chunk_end = attn_chunk_begin(c + 1);
+          if (c == 1) {
+            mr = mc; lr = lc;
+#pragma unroll
+            for (int ht = 0; ht < HT; ++ht) ar[ht] = ac[ht];
+          } else if (c > 1) {
+            float mn, wa, wb;
+            merge_weights(mr, mc, scale, mn, wa, wb);
+            lr = merge_value(lr, wa, lc, wb);
+#pragma unroll
+            for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) ar[ht][i] = merge_value(ar[ht][i], wa, ac[ht][i], wb);
+            mr = mn;
+          }
+          mc = NEG_BIG; lc = 0.f;
+#pragma unroll
+          for (int ht = 0; ht < HT; ++ht) ac[ht] = (f32x4_v){0.f, 0.f, 0.f, 0.f};
+        }
+        Frags<HD> f;
+        const u32x4_v *fp = frags + slot * (FRAGS * 64) + lane;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) { f.k0[kk] = fp[kk * 64]; f.k1[kk] = fp[(KK + kk) * 64]; }
+#pragma unroll
+        for (int ht = 0; ht < HT; ++ht) f.v[ht] = fp[(2 * KK + ht) * 64];
+        compute_step<T, HD>(f, qf, ks, w.g, w.pos_j, scale, mc, lc, ac);
+      }
+      slot = slot + 1 == PREFILL_RING ? 0 : slot + 1;
+    }
+    // the next sequence's fetches, and the end of the workgroup, find LDS idle
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
+  // the last chunk
+  if (w.pmax >= 0) {
+    if (attn_chunk_of(w.pmax) == 0) {
+      lr = lc;
+#pragma unroll
+      for (int ht = 0; ht < HT; ++ht) ar[ht] = ac[ht];
+    } else {
+      float mn, wa, wb;
+      merge_weights(mr, mc, scale, mn, wa, wb);
+      lr = merge_value(lr, wa, lc, wb);
+#pragma unroll
+      for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ar[ht][i] = merge_value(ar[ht][i], wa, ac[ht][i], wb);
+    }
+  }
+  if (on && w.j < a.q_rows) {
+    const int m = b * a.q_rows + w.j;
+    const float inv = (w.pos_j >= 0) ? 1.0f / lr : 0.f;
+#pragma unroll
+    for (int ht = 0; ht < HT; ++ht) {
+      op_t o4[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o4[i] = to_op(w.pos_j >= 0 ? ar[ht][i] * inv : 0.f);
+      const size_t at = xpack_index(m, hh * HD + ht * 16 + 4 * w.g, d >> 5);
+      *(uint2 *)((op_t *)a.out + at) = *(const uint2 *)o4;
+    }
+  }
+}
+
 constexpr size_t attn_group_lds(int HD, int NC) { return (size_t)NC * ((HD / 16) * 64 * 16 + 64 * 8); }
 
 template <class T, int HD, bool STREAM>
 static void launch_attn_group(const AttnArgs &a, int pairs, hipStream_t st) {
   const int waves = a.NC < ATTN_GROUP_MAX_WAVES ? a.NC : ATTN_GROUP_MAX_WAVES;
   hipLaunchKernelGGL((k_attn_group<T, HD, STREAM>), dim3(pairs), dim3(64 * waves), attn_group_lds(HD, a.NC), st, a);
+}
+template <class T, int HD>
+static void prepare_attn_prefill() {
+  (void)hipFuncSetAttribute((const void *)k_attn_prefill<T, HD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_prefill_lds(HD));
 }
 template <class T, int HD>
 static void prepare_attn_group() {  // more than the default 64 KB of LDS has to be asked for
@@ -434,6 +584,8 @@ static void prepare_attn_group() {  // more than the default 64 KB of LDS has to
 void attention_prepare() {
   prepare_attn_group<bf16_t, 128>(); prepare_attn_group<bf16_t, 64>();
   prepare_attn_group<f16_t, 128>(); prepare_attn_group<f16_t, 64>();
+  prepare_attn_prefill<bf16_t, 128>(); prepare_attn_prefill<bf16_t, 64>();
+  prepare_attn_prefill<f16_t, 128>(); prepare_attn_prefill<f16_t, 64>();
 }
 
 template <class T, int HD>
@@ -463,7 +615,12 @@ static void launch_attn_hd(const AttnArgs &a, hipStream_t st) {
     // workgroups of one wave: few pairs then spread over all compute units (measured, us per layer at 32 heads: 4
     // sequences x 100 positions 15.1 -> 11.8, 24 x 250 29.6 -> 26.6), and many pairs drain evenly (64 sequences x 300
     // positions 72.5 -> 71.4 against workgroups of four waves; 32 sequences x 52 heads x 2048 positions: the same)
-    if (a.grp_seq) hipLaunchKernelGGL((k_attn_seq<T, HD, false>), dim3(pairs), dim3(64), 0, st, a);  // several groups read one cache
+    // a prefill, several groups of which read one cache: through LDS, but for prompts within the first chunk, where there is
+    // little to share (64 prompts of up to 128 tokens: a prefill of 4 layers 11.71 ms, through LDS 11.73)
+    if (a.grp_seq && a.shape == 0 && a.NC > 1)
+      hipLaunchKernelGGL((k_attn_prefill<T, HD>), dim3((a.B + PREFILL_WAVES - 1) / PREFILL_WAVES * a.H), dim3(64 * PREFILL_WAVES),
+                         attn_prefill_lds(HD), st, a);
+    else if (a.grp_seq) hipLaunchKernelGGL((k_attn_seq<T, HD, false>), dim3(pairs), dim3(64), 0, st, a);
     else hipLaunchKernelGGL((k_attn_seq<T, HD, true>), dim3(pairs), dim3(64), 0, st, a);
   } else if (group) {
     if (pairs * a.NC >= ATTN_STREAM_MIN_WAVES) launch_attn_group<T, HD, true>(a, pairs, st);
