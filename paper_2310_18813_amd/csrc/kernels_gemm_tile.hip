@@ -557,6 +557,53 @@ static double tile_for(const GemmArgs &a, bool split, int &MTW, int &NBW) {
   MTW = 2; NBW = 2;
   return second + choose_tile(a.M, a.NT, n_cu, steps, wg_mult, w_bytes, MTW, NBW);
 }
+
+// A launch of several rounds of workgroups ends in one that is partly empty, and a round of large wave tiles is long: the
+// rows of that round can go to a second launch, whose wave tile suits what is left.  Returns how many of a.M rows the first
+// launch takes (all of them unless two are estimated to save 3 %), and the second launch's wave tile.  One launch / two, us:
+// 4096 x 11008 at 6592 and 4848 rows 628 / 583 and 426 / 409, 4096 x 4096 263 / 248 and 181 / 174, gate-up 22016 x 4096 at 6592
+// and 776 rows 1078 / 1062 and 171 / 158, 15360 x 5120 at 784 rows 161 / 152, 6656 x 17920 at 4848 rows 1064 / 1035.
+static int rows_of_first_launch(const GemmArgs &a, int epi, int MTW, int NBW, int &MTW2, int &NBW2) {
+  const int n_cu = a.n_cu > 0 ? a.n_cu : 256, pass_rows = 64 * MTW;
+  const int groups = (a.NT + 2 * NBW - 1) / (2 * NBW), passes = (a.M + pass_rows - 1) / pass_rows;
+  // (not the LM head, whose partials are counted by strip group; nor where the rows' sums of squares are taken in the loop,
+  // since the second launch's wave tile may want them from k_row_inv_x)
+  if ((a.tune & 0xff) || epi == EPI_LOGITS || passes * groups <= n_cu || (a.fold_x && tile_takes_row_sums(MTW))) return a.M;
+  const double w_bytes = 1024.0 * a.NT * a.KT;
+  double best = 0.97 * tile_us(MTW, NBW, a.M, a.NT, n_cu, a.KT, 1, w_bytes);
+  const int rounds = (passes * groups + n_cu - 1) / n_cu;
+  int first = a.M;
+  for (int r = rounds - 1; r >= 1 && r >= rounds - 2; --r) {
+    const int rows = r * n_cu / groups * pass_rows;
+    if (rows <= 0 || rows >= a.M || (epi == EPI_QKV && rows % a.q_rows != 0)) continue;
+    int mt = 2, nb = 2;
+    const double rest = choose_tile(a.M - rows, a.NT, n_cu, a.KT, 1, w_bytes, mt, nb);
+    const double us = tile_us(MTW, NBW, rows, a.NT, n_cu, a.KT, 1, w_bytes) + rest;
+    if (us < best) { best = us; first = rows; MTW2 = mt; NBW2 = nb; }
+  }
+  return first;
+}
+// the arguments of the same product for the rows from m0 on (a multiple of 16, and of q_rows where the epilogue is EPI_QKV)
+static GemmArgs rows_from(GemmArgs a, int m0) {
+  const size_t r = (size_t)m0;
+  a.M -= m0;
+  a.X = (const op_t *)a.X + r * a.KT * 32;
+  if (a.h) a.h += r * a.N;
+  if (a.x_out) a.x_out = (op_t *)a.x_out + r * a.N;
+  if (a.act) a.act = (op_t *)a.act + r * (a.f > 0 ? a.f : a.N);
+  if (a.rinv_ws) a.rinv_ws += r;
+  if (a.mean_ws) a.mean_ws += r;
+  if (a.row_pos) {
+    a.row_pos += r;
+    a.q = (float *)a.q + r * a.d;
+    const size_t seqs = r / a.q_rows, elems = a.grp_seq ? 0 : seqs * a.H * a.L_pad * a.hd;
+    if (a.grp_seq) a.grp_seq += seqs;
+    a.kc = (char *)a.kc + 2 * elems;  // 16-bit caches
+    a.vc = (char *)a.vc + 2 * elems;
+  }
+  return a;
+}
+
 double gemm_tile_us(const GemmArgs &a, bool split) {
   int MTW, NBW;
   return tile_for(a, split, MTW, NBW);
@@ -594,16 +641,27 @@ int gemm_tile_head_partials(const GemmArgs &a) {
   return 2 * ((a.NT + 2 * NBW - 1) / (2 * NBW));
 }
 
-void launch_gemm_tile(int dtype, GemmArgs a, int epi, bool split, hipStream_t st) {
-  int MTW, NBW;
-  tile_for(a, split, MTW, NBW);
+static void launch_rows(int dtype, GemmArgs a, int epi, bool split, int MTW, int NBW, hipStream_t st) {
   a.n_part = 2 * ((a.NT + 2 * NBW - 1) / (2 * NBW));
-  if (split) epi = EPI_PARTIAL;
   a.passes = (a.M + 64 * MTW - 1) / (64 * MTW);
   a.groups = (a.NT + 2 * NBW - 1) / (2 * NBW);
   const int blocks = split ? (a.KS == 8 ? a.groups * a.passes * 8 : ((a.groups + 7) / 8) * 8 * a.passes * a.KS)
                            : a.passes == 1 ? a.groups : (a.groups * a.passes + 7) / 8 * 8;
-  launch_shape(dtype, a, MTW, NBW, epi, blocks, st);
+  launch_shape(dtype, a, MTW, NBW, split ? (int)EPI_PARTIAL : epi, blocks, st);
+}
+
+void launch_gemm_tile(int dtype, GemmArgs a, int epi, bool split, hipStream_t st) {
+  int MTW, NBW, MTW2, NBW2;
+  tile_for(a, split, MTW, NBW);
+  const int first = split ? a.M : rows_of_first_launch(a, epi, MTW, NBW, MTW2, NBW2);
+  if (first < a.M) {
+    GemmArgs f = a;
+    f.M = first;
+    launch_rows(dtype, f, epi, false, MTW, NBW, st);
+    launch_rows(dtype, rows_from(a, first), epi, false, MTW2, NBW2, st);
+    return;
+  }
+  launch_rows(dtype, a, epi, split, MTW, NBW, st);
   if (split && a.ssq_ks > 0 && a.x_out) {
     const int rr_threads = std::min(1024, ((a.N >> 2) + 63) / 64 * 64);  // one float4 of outputs per thread where that fits
     hipLaunchKernelGGL(k_partial_reduce_rows, dim3(a.M), dim3(rr_threads), (size_t)a.N * sizeof(op_t), st, a);
