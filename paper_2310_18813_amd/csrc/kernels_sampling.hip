@@ -22,7 +22,8 @@
 // after the other through B; a row is read once for maximum and sum together, and once more (from L2) where a token is
 // drawn from it.  A thread with a contiguous chunk of its own (loads 512 bytes apart across a wave), a pass for each of
 // maximum and sum, and a sequence's places in turn took 87 us for 64 sequences x 4 places of 32000 logits with draft rows;
-// this takes 30 us.  Larger rounds take places in turn (workgroups_per_sequence).
+// this takes 26 us (30 with a test for -inf
+// and for the end beside every exponential: what is left of a place is about equal parts loads and exponentials).  Larger rounds take places in turn (workgroups_per_sequence).
 #include "spec_internal.h"
 #include "device_utils.h"
 #include <algorithm>
@@ -61,6 +62,20 @@ __device__ __forceinline__ void load4z(const float *__restrict__ z, int k, int V
     }
   }
 }
+// U steps of z[k ..]: as load4z, without its clamps and selects where all of them lie before `end`
+template <bool VEC, int U>
+__device__ __forceinline__ void load_steps(const float *__restrict__ z, int k, int lane4, int V, int end, float (&v)[U][4]) {
+  if (VEC && k + U * SMP_STEP <= end) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const float4 t = *(const float4 *)(z + k + i * SMP_STEP + lane4);
+      v[i][0] = t.x; v[i][1] = t.y; v[i][2] = t.z; v[i][3] = t.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < U; ++i) load4z<VEC>(z, k + i * SMP_STEP + lane4, V, end, v[i]);
+  }
+}
 // steps whose loads are in flight together (single loads need four addresses a step; a segment of a short row has few steps)
 template <int W, bool VEC> constexpr int SMP_UNROLL = !VEC ? 2 : W == 4 ? 4 : 8;
 
@@ -92,8 +107,7 @@ __device__ __forceinline__ float row_max(const float *__restrict__ z, int V, flo
 #pragma unroll 1
   for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
     float v[U][4];
-#pragma unroll
-    for (int i = 0; i < U; ++i) load4z<VEC>(z, k + i * SMP_STEP + lane4, V, g.end, v[i]);
+    load_steps<VEC, U>(z, k, lane4, V, g.end, v);
 #pragma unroll
     for (int i = 0; i < U; ++i) lm = fmaxf(fmaxf(lm, v[i][0]), fmaxf(fmaxf(v[i][1], v[i][2]), v[i][3]));
   }
@@ -116,11 +130,13 @@ __device__ __forceinline__ void stats_step(const float (&v)[U][4], float inv_T, 
   float mn = m;
 #pragma unroll
   for (int i = 0; i < U; ++i) mn = fmaxf(fmaxf(mn, v[i][0]), fmaxf(fmaxf(v[i][1], v[i][2]), v[i][3]));
+  // the exponential of -inf is 0 by itself, but for a maximum that is -inf too
+  const float base = mn == -INFINITY ? 0.f : mn;
   float ls = 0.f;
 #pragma unroll
   for (int i = 0; i < U; ++i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) ls += v[i][e] == -INFINITY ? 0.f : __expf((v[i][e] - mn) * inv_T);
+    for (int e = 0; e < 4; ++e) ls += __expf((v[i][e] - base) * inv_T);
   Z = rescaled(Z, m, mn, inv_T) + ls;
   m = mn;
 }
@@ -138,12 +154,8 @@ __device__ __forceinline__ void row_stats(const float *__restrict__ zp, const fl
 #pragma unroll 1
   for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
     float v[U][4], w[U][4];
-#pragma unroll
-    for (int i = 0; i < U; ++i) load4z<VEC>(zp, k + i * SMP_STEP + lane4, V, g.end, v[i]);
-    if (PAIR) {
-#pragma unroll
-      for (int i = 0; i < U; ++i) load4z<VEC>(zq, k + i * SMP_STEP + lane4, V, g.end, w[i]);
-    }
+    load_steps<VEC, U>(zp, k, lane4, V, g.end, v);
+    if (PAIR) load_steps<VEC, U>(zq, k, lane4, V, g.end, w);
     stats_step<U>(v, inv_T, mp, Zp);
     if (PAIR) stats_step<U>(w, inv_T, mq, Zq);
   }
@@ -169,7 +181,8 @@ __device__ __forceinline__ void row_stats(const float *__restrict__ zp, const fl
   if (PAIR) q = combine(sh + 2 * W);
 }
 
-// Draw with u from the weights w4(k, end, out) -> weights of k .. k+3 (zero from `end` on), k a multiple of four:
+// Draw with u from the weights w4(k, lane4, end, out) -> weights of the lane's four tokens of W4::UNROLL steps from k on (zero
+// from `end` on):
 // every thread returns the same index.  *total_out: the sum of all weights.
 template <int W, class W4>
 __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int *sh_i, float *total_out = nullptr) {
@@ -180,8 +193,7 @@ __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int 
 #pragma unroll 1
   for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
     float w[U][4];
-#pragma unroll
-    for (int i = 0; i < U; ++i) w4(k + i * SMP_STEP + lane4, g.end, w[i]);
+    w4(k, lane4, g.end, w);
 #pragma unroll
     for (int i = 0; i < U; ++i) local += (w[i][0] + w[i][1]) + (w[i][2] + w[i][3]);
   }
@@ -202,33 +214,40 @@ __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int 
   if (wv == owner) {
     float run = excl;
     int pick = -1, last = -1;  // wave-wide pick; this lane's last token with weight
+    constexpr int UW = U > 4 ? 4 : U;
+    // as in the sum, the loads of several steps are in flight together: one step after the other, each waiting for its rows, the
+    // walk took half a microsecond more (64 sequences x 4 places 26.7 -> 26.2)
 #pragma unroll 1
-    for (int k = g.k0; k < g.end && pick < 0; k += SMP_STEP) {
-      const int kl = k + lane4;
-      float w[4];
-      w4(kl, g.end, w);
-      const float mine = (w[0] + w[1]) + (w[2] + w[3]);
-      float inc = mine;  // inclusive prefix over the lanes, added pairwise by doubling distances
+    for (int k = g.k0; k < g.end && pick < 0; k += UW * SMP_STEP) {
+      float w[UW][4];
+      w4(k, lane4, g.end, w);
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const float up = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += up;
-      }
-      int own = -1;  // the first of this lane's tokens whose cumulative weight exceeds x, or the nearest one with weight
-      float c = run + (inc - mine);
-      bool past = false;
+      for (int s = 0; s < UW; ++s) {
+        if (pick >= 0) break;
+        const int kl = k + s * SMP_STEP + lane4;
+        const float mine = (w[s][0] + w[s][1]) + (w[s][2] + w[s][3]);
+        float inc = mine;  // inclusive prefix over the lanes, added pairwise by doubling distances
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        c += w[i];
-        if (w[i] > 0.f) {
-          last = kl + i;
-          if (!past || own < 0) own = kl + i;
+        for (int o = 1; o < 64; o <<= 1) {
+          const float up = __shfl_up(inc, o, 64);
+          if (lane >= o) inc += up;
         }
-        past |= c > x;
+        int own = -1;  // the first of this lane's tokens whose cumulative weight exceeds x, or the nearest one with weight
+        float c = run + (inc - mine);
+        bool past = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          c += w[s][i];
+          if (w[s][i] > 0.f) {
+            last = kl + i;
+            if (!past || own < 0) own = kl + i;
+          }
+          past |= c > x;
+        }
+        const unsigned long long hit = __ballot(mine > 0.f && run + inc > x);
+        if (hit) pick = __shfl(own, __ffsll(hit) - 1, 64);
+        run += __shfl(inc, 63, 64);
       }
-      const unsigned long long hit = __ballot(mine > 0.f && run + inc > x);
-      if (hit) pick = __shfl(own, __ffsll(hit) - 1, 64);
-      run += __shfl(inc, 63, 64);
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
@@ -240,16 +259,25 @@ __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int 
   return *sh_i;
 }
 
-// weights exp((z - m) * inv_T) of a row, optionally with one token removed
+// weights exp((z - m) * inv_T) of a row, optionally with one token removed; -inf behind the end makes the zeros there
 template <int W, bool VEC>
 struct ExpW {
   static constexpr int UNROLL = SMP_UNROLL<W, VEC>;
   const float *z; int V; float m, inv_T; int drop;
-  __device__ __forceinline__ void operator()(int k, int end, float (&w)[4]) const {
-    float v[4];
-    load4z<VEC>(z, k, V, end, v);
+  template <int U>
+  __device__ __forceinline__ void operator()(int k, int lane4, int end, float (&w)[U][4]) const {
+    load_steps<VEC, U>(z, k, lane4, V, end, w);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = (k + i == drop || k + i >= end) ? 0.f : __expf((v[i] - m) * inv_T);
+    for (int s = 0; s < U; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[s][i] = __expf((w[s][i] - m) * inv_T);
+    if ((unsigned)(drop - k) < (unsigned)(U * SMP_STEP)) {
+#pragma unroll
+      for (int s = 0; s < U; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (k + s * SMP_STEP + lane4 + i == drop) w[s][i] = 0.f;
+    }
   }
 };
 // residual weights max(0, p - q) of a target and a draft row
@@ -257,11 +285,14 @@ template <int W, bool VEC>
 struct ResidW {
   static constexpr int UNROLL = SMP_UNROLL<W, VEC> / 2;  // two rows a step
   ExpW<W, VEC> p, q; float ip, iq;
-  __device__ __forceinline__ void operator()(int k, int end, float (&w)[4]) const {
-    float a[4], b[4];
-    p(k, end, a); q(k, end, b);
+  template <int U>
+  __device__ __forceinline__ void operator()(int k, int lane4, int end, float (&w)[U][4]) const {
+    float b[U][4];
+    p(k, lane4, end, w); q(k, lane4, end, b);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { const float r = a[i] * ip - b[i] * iq; w[i] = r > 0.f ? r : 0.f; }
+    for (int s = 0; s < U; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { const float r = w[s][i] * ip - b[s][i] * iq; w[s][i] = r > 0.f ? r : 0.f; }
   }
 };
 
