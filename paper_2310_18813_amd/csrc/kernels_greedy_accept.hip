@@ -27,7 +27,13 @@ __global__ __launch_bounds__(256) void k_ga_partials(const float *__restrict__ l
   const int c0 = chunk * GA_CHUNK, c1 = min(c0 + GA_CHUNK, V);
   float bv = -INFINITY;
   int bi = 0x7fffffff;
-  for (int c = c0 + threadIdx.x; c < c1; c += 256) argmax_combine(bv, bi, src[c], c);
+  // the chunk's loads all in flight together, the ones behind its end repeating the last logit (24 rows of 50272 logits 5.6 ->
+  // 4.1 us)
+  float v[GA_CHUNK / 256];
+#pragma unroll
+  for (int k = 0; k < GA_CHUNK / 256; ++k) v[k] = src[min(c0 + (int)threadIdx.x + 256 * k, c1 - 1)];
+#pragma unroll
+  for (int k = 0; k < GA_CHUNK / 256; ++k) argmax_combine(bv, bi, v[k], min(c0 + (int)threadIdx.x + 256 * k, c1 - 1));
   wave_argmax(bv, bi);
   if ((threadIdx.x & 63) == 0) { shv[threadIdx.x >> 6] = bv; shi[threadIdx.x >> 6] = bi; }
   __syncthreads();
@@ -37,22 +43,21 @@ __global__ __launch_bounds__(256) void k_ga_partials(const float *__restrict__ l
   }
 }
 
-// One wave per sequence.  emitted: t_1..t_l, a_l, then -1 up to s + 1 entries.
-__global__ __launch_bounds__(64) void k_ga_accept(const GaPartial *__restrict__ part, int n_chunks, int V, int s,
+// One workgroup per sequence, a wave per row (s + 1 of them: one wave that takes the rows in turn waits for memory once a row:
+// 4 sequences x 6 rows 7.3 -> 3.0 us).  emitted: t_1..t_l, a_l, then -1 up to s + 1 entries.
+__global__ __launch_bounds__(1024) void k_ga_accept(const GaPartial *__restrict__ part, int n_chunks, int V, int s,
                                                   const int32_t *__restrict__ proposals, int32_t *__restrict__ accepted,
                                                   int32_t *__restrict__ emitted) {
   __shared__ int a_sh[16];
-  const int b = blockIdx.x, lane = threadIdx.x;
-  for (int i = 0; i <= s; ++i) {
-    const GaPartial *p = part + (size_t)(b * (s + 1) + i) * n_chunks;
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int c = lane; c < n_chunks; c += 64) argmax_combine(bv, bi, p[c].v, p[c].i);
-    wave_argmax(bv, bi);
-    if (lane == 0) a_sh[i] = (bi < 0 || bi >= V) ? 0 : bi;
-  }
+  const int b = blockIdx.x, lane = threadIdx.x & 63, i = threadIdx.x >> 6;
+  const GaPartial *p = part + (size_t)(b * (s + 1) + i) * n_chunks;
+  float bv = -INFINITY;
+  int bi = 0x7fffffff;
+  for (int c = lane; c < n_chunks; c += 64) argmax_combine(bv, bi, p[c].v, p[c].i);
+  wave_argmax(bv, bi);
+  if (lane == 0) a_sh[i] = (bi < 0 || bi >= V) ? 0 : bi;
   __syncthreads();
-  if (lane == 0) {
+  if (threadIdx.x == 0) {
     const int32_t *t = proposals + (size_t)b * s;
     int l = 0;
     while (l < s && t[l] == a_sh[l]) ++l;
@@ -79,7 +84,7 @@ static int ga_launch(hipStream_t st, const float *d_logits, const int32_t *d_pro
                      int32_t *d_accepted, int32_t *d_emitted) {
   const int n_chunks = (vocab + GA_CHUNK - 1) / GA_CHUNK;
   hipLaunchKernelGGL(k_ga_partials, dim3(B * (s + 1), n_chunks), dim3(256), 0, st, d_logits, vocab, n_chunks, (GaPartial *)scratch);
-  hipLaunchKernelGGL(k_ga_accept, dim3(B), dim3(64), 0, st, (const GaPartial *)scratch, n_chunks, vocab, s, d_proposals,
+  hipLaunchKernelGGL(k_ga_accept, dim3(B), dim3(64 * (s + 1)), 0, st, (const GaPartial *)scratch, n_chunks, vocab, s, d_proposals,
                      d_accepted, d_emitted);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? SPEC_OK : fail_noctx(SPEC_ERR_HIP, "greedy accept launch: %s", hipGetErrorString(e));
