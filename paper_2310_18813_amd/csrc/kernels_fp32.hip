@@ -370,6 +370,7 @@ static void f32_launch_shape(const F32Gemm &a, int MT, int NB, int epi, int bloc
     case 20: f32_launch_epi<2, 4>(a, epi, blocks, st); break;
     case 25: f32_launch_epi<3, 1>(a, epi, blocks, st); break;
     case 26: f32_launch_epi<3, 2>(a, epi, blocks, st); break;
+    case 28: f32_launch_epi<3, 4>(a, epi, blocks, st); break;
     case 33: f32_launch_epi<4, 1>(a, epi, blocks, st); break;
     default: f32_launch_epi<4, 2>(a, epi, blocks, st); break;
   }
@@ -380,12 +381,15 @@ void fp32_prepare() {
   const F32Gemm a{};
   for (int epi : {(int)EPI_RESIDUAL, (int)EPI_QKV, (int)EPI_SWIGLU, (int)EPI_RELU, (int)EPI_LOGITS}) {
     f32_launch_shape(a, 2, 4, epi, -1, nullptr);
+    f32_launch_shape(a, 3, 4, epi, -1, nullptr);
     f32_launch_shape(a, 4, 2, epi, -1, nullptr);
   }
 }
 
 // Strips and row tiles per workgroup (neither changes a result): the compute unit with the most workgroups sets the
-// time (gate-up of d_model 1024 at 1328 rows: 585 us as 1 x 1, 370 us as 4 strips x 2 tiles).  Cycles per 16-k step of a workgroup: 16 per 1 KB fragment from L2, about three times that for weights the first
+// time (gate-up of d_model 1024 at 1328 rows: 585 us as 1 x 1, 370 us as 4 strips x 2 tiles).  (4 strips x 3 tiles: the LM
+// head 32000 x 1024 at 40 rows, whose activations are then fetched half as often as at 2 x 3: a verification of 8 sequences x 5
+// rows 304 -> 299 us.)  Cycles per 16-k step of a workgroup: 16 per 1 KB fragment from L2, about three times that for weights the first
 // time they are read (HBM), against 32 of the matrix cores per tile.
 static void f32_gemm(F32Gemm a, int epi, int n_cu, hipStream_t st) {
   if (a.M <= 0) return;
@@ -393,7 +397,7 @@ static void f32_gemm(F32Gemm a, int epi, int n_cu, hipStream_t st) {
   long best = -1;
   for (int mt = 1; mt <= 4; ++mt) {
     const long passes = (a.M + mt * 16 - 1) / (mt * 16);
-    for (int nb = 1; nb * mt <= 8 && nb <= 4; nb *= 2) {
+    for (int nb = 1; nb * mt <= 12 && nb <= 4; nb *= 2) {
       const long per_cu = ((a.NT + nb - 1) / nb * passes + n_cu - 1) / n_cu;
       const long cost = per_cu * (16 * nb * (2 + passes) / passes + 16 * mt + 32 * nb * mt);
       if (best < 0 || cost < best) { best = cost; MT = mt; NB = nb; }
