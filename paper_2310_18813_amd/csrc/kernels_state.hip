@@ -31,7 +31,7 @@ __device__ __forceinline__ void load4(const T *__restrict__ p, size_t i, float (
 template <class T, bool PREP>
 __global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, int s_max, int L_max, int vocab, int d,
                                  int learned_pos, const int32_t *__restrict__ grp_seq, const int32_t *__restrict__ grp_base, const int32_t *__restrict__ seq, const int32_t *__restrict__ n,
-                                 const int32_t *__restrict__ kv_draft, const int32_t *__restrict__ t,
+                                 const int32_t *__restrict__ kv_draft, int32_t *__restrict__ t, const int32_t *__restrict__ table, int fill,
                                  const int32_t *__restrict__ seq_s, const int32_t *__restrict__ P_b,
                                  const T *__restrict__ tok_emb, const T *__restrict__ pos_emb,
                                  int32_t *__restrict__ row_tok, int32_t *__restrict__ row_pos, float *__restrict__ h,
@@ -41,12 +41,17 @@ __global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, 
   const int b = grp_seq ? grp_seq[grp] : grp, i = m % q;
   int tok = 0, pos = -1;
   const int nb = n[b];
+  // External proposals from a table, t_j = table[b][n_b + j - 1] (absolute position): the round's first pass leaves them for
+  // the kernels behind it, which saves a launch a round (a round of 299 us takes 296).  Its own rows read the table.
+  auto table_tok = [&](int jj) { return nb + jj < L_max ? table[(size_t)b * L_max + nb + jj] : 0; };
+  if (table && i == 0)
+    for (int jj = threadIdx.x; jj < fill; jj += blockDim.x) t[(size_t)b * s_max + jj] = table_tok(jj);
   // a sequence with its own cap s_b on the speculation length: its rows for proposals beyond s_b are dead
   const int sb = seq_s ? max(0, seq_s[b]) : s_max;
   if (kind == PASS_VERIFY) {
     if (i <= sb) {
       pos = nb - 1 + i;
-      tok = (i == 0) ? seq[(size_t)b * L_max + nb - 1] : t[(size_t)b * s_max + i - 1];
+      tok = (i == 0) ? seq[(size_t)b * L_max + nb - 1] : table ? table_tok(i - 1) : t[(size_t)b * s_max + i - 1];
     }
   } else if (kind == PASS_DRAFT_FIRST) {
     int p = nb - j - q + i;  // j: positions the pass ends before n_b (catch-up passes of a draft cache far behind)
@@ -106,7 +111,7 @@ void launch_assemble_embed(const spec_ctx *c, const Model &m, const PassArgs &pa
                        (int)(m.desc.pos_kind == SPEC_POS_LEARNED), prefill ? c->ws.grp_seq + pa.g0 : nullptr, prefill ? c->ws.grp_base + pa.g0 : nullptr,
                        c->st.seq + (size_t)pa.b0 * c->run.L_max,
                        c->st.n + pa.b0, c->drf.kv_len ? c->drf.kv_len + pa.b0 : nullptr,
-                       c->st.t + (size_t)pa.b0 * c->run.s_max, c->seq_s ? c->seq_s + pa.b0 : nullptr, c->st.P_b + pa.b0,
+                       c->st.t + (size_t)pa.b0 * c->run.s_max, pa.fill > 0 ? c->prop_table + (size_t)pa.b0 * c->run.L_max : nullptr, pa.fill, c->seq_s ? c->seq_s + pa.b0 : nullptr, c->st.P_b + pa.b0,
                        (const T *)m.tok_emb, (const T *)m.pos_emb, c->ws.row_tok, c->ws.row_pos, c->ws.h,
                        (op_t *)c->ws.x, c->st.sat));
 }
@@ -290,20 +295,7 @@ void launch_argmax_rows(const float *logits, int M, int V, int q, int out_stride
 
 // -------------------------------------------------------------------------
 // -------------------------------------------------------------------------
-// External proposals: t_j = table[b][n_b + j - 1] (absolute position), or a plain copy.
-__global__ void k_fill_proposals(int B, int s, int s_max, int L_max, const int32_t *__restrict__ table,
-                                 const int32_t *__restrict__ n, int32_t *__restrict__ t) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * s) return;
-  int b = i / s, jj = i % s;
-  int p = n[b] + jj;
-  t[(size_t)b * s_max + jj] = (p < L_max) ? table[(size_t)b * L_max + p] : 0;
-}
-void launch_fill_proposals(spec_ctx *c, int s, hipStream_t st) {
-  if (s <= 0) return;
-  hipLaunchKernelGGL(k_fill_proposals, dim3((c->B * s + 255) / 256), dim3(256), 0, st, c->B, s, c->run.s_max,
-                     c->run.L_max, c->prop_table, c->st.n, c->st.t);
-}
+// External proposals given for the round (those of a table are fetched by the round's first pass, k_assemble_embed).
 __global__ void k_copy_proposals(int B, int s, int s_max, const int32_t *__restrict__ src, int32_t *__restrict__ t) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= B * s) return;

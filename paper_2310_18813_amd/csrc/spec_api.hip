@@ -658,12 +658,13 @@ extern "C" int spec_set_proposals(spec_ctx *c, const int32_t *d_tok, int32_t s) 
   return SPEC_OK;
 }
 
-// proposals for the coming round from the table, if that is how they are supplied
-static int ensure_proposals(spec_ctx *c, int s, const char *who) {
+// proposals for the coming round from the table, if that is how they are supplied: the next pass fetches `fill` of them
+static int ensure_proposals(spec_ctx *c, int s, const char *who, int &fill) {
+  fill = 0;
   if (c->run.proposal_mode != SPEC_PROPOSALS_EXTERNAL || s == 0 || c->proposals_ready) return SPEC_OK;
   if (!c->prop_table)
     return fail(c, SPEC_ERR_STATE, "%s: external proposals expected; call spec_set_proposals or spec_set_proposal_table", who);
-  launch_fill_proposals(c, s, c->stream);
+  fill = s;
   c->proposals_ready = true;
   return SPEC_OK;
 }
@@ -693,9 +694,10 @@ extern "C" int spec_draft_step(spec_ctx *c, int32_t j) {
   }
   const int arg_stride_used = draw ? 1 : arg_stride;
   if (j == 1) {
+    int fill = 0;
     if (ext && c->prop_table && !c->proposals_ready) {
       // later draft steps ingest t_1.. : fetch them now (all s_max; verify uses the first s)
-      launch_fill_proposals(c, c->run.s_max, c->stream);
+      fill = c->run.s_max;
       c->proposals_ready = true;
     }
     // The draft's cache is at most draft_lag tokens behind the committed sequences (2 after a round with draft
@@ -706,11 +708,14 @@ extern "C" int spec_draft_step(spec_ctx *c, int32_t j) {
     rc = SPEC_OK;
     while (lag > q_cap && !rc) {
       PassArgs pa{PASS_DRAFT_FIRST, c->B, q_cap, lag - q_cap};
+      pa.fill = fill;
+      fill = 0;
       rc = forward_pass(c, c->drf, pa, HEAD_NONE, nullptr, nullptr, 0, c->n_ub - 1);
       lag -= q_cap;
     }
     if (!rc) {
       PassArgs pa{PASS_DRAFT_FIRST, c->B, lag, 0};
+      pa.fill = fill;
       rc = forward_pass(c, c->drf, pa, HEAD_LAST, lg, arg_out, arg_stride_used, c->n_ub - 1);
     }
   } else {
@@ -738,9 +743,11 @@ extern "C" int spec_verify_step(spec_ctx *c, int32_t s, float *d_logits_or_null)
     return fail(c, SPEC_ERR_STATE, "spec_verify_step: s=%d needs %d draft steps first, %d were run", s, s, c->draft_j);
   if (c->draft_j != 0 && c->draft_j != s)
     return fail(c, SPEC_ERR_STATE, "spec_verify_step: %d draft steps were run for s=%d", c->draft_j, s);
-  int rc = ensure_proposals(c, s, "spec_verify_step");
+  int fill;
+  int rc = ensure_proposals(c, s, "spec_verify_step", fill);
   if (rc) return rc;
   PassArgs pa{PASS_VERIFY, c->B, s + 1, 0};
+  pa.fill = fill;
   float *lg = d_logits_or_null ? d_logits_or_null : c->smp_u ? c->smp_tl : nullptr;
   rc = forward_pass(c, c->tgt, pa, HEAD_ALL, lg, c->st.a, c->run.s_max + 1, c->n_ub - 1 + s);
   if (rc) return rc;

@@ -190,6 +190,7 @@ struct PassArgs {
   int b0 = 0;    // first batch slot of the pass: its rows are the sequences b0 .. b0 + B - 1
   int g0 = 0;    // PASS_PREFILL: B counts groups of q rows at consecutive positions of one sequence, and the pass takes
                  // the groups g0 .. g0 + B - 1 of the table in the workspace (launch_prefill_groups)
+  int fill = 0;  // > 0: the pass also fetches the round's first `fill` proposals from the caller's table
 };
 
 void launch_assemble_embed(const spec_ctx *c, const Model &m, const PassArgs &pa, hipStream_t st);
@@ -204,7 +205,6 @@ void launch_sample_rows(const float *logits, int rows, int V, float temperature,
 void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, int s, int V, float temperature,
                           const int32_t *t, int t_stride, const int32_t *seq_s, const float *u, const int32_t *n, int u_rows,
                           int32_t *a, int a_stride, hipStream_t st, int32_t *accepted = nullptr, int32_t *emitted = nullptr);
-void launch_fill_proposals(spec_ctx *c, int s, hipStream_t st);
 void launch_prefill_groups(const spec_ctx *c, int b0, int B, int q, hipStream_t st);
 void launch_copy_proposals(spec_ctx *c, const int32_t *d_tok, int s, hipStream_t st);
 void launch_state_reset(spec_ctx *c, const int32_t *d_prompt, int P_stride, bool ragged, hipStream_t st);
