@@ -425,12 +425,13 @@ __global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int L_p
 // The export of 16-bit rows to buffers aligned to 16 bytes: a thread takes eight channels at eight consecutive positions,
 // where the cache has the values of a channel side by side, and the keys of eight pairs (two runs of four channels) of a
 // row.  Element by element the scattered loads and stores were most of the time: 64 x 128 rows of 4096
-// 120 -> 74 us.
-__global__ __launch_bounds__(256) void k_kv_export16(int B, int len, int H, int hd, int L_pad, const uint16_t *__restrict__ kc,
+// 120 -> 74 us.  Workgroups of one wave, keys (blockIdx.y 0) and values (1) apart, so that a short export spreads over the CUs:
+// 16 rows of 6656 10.7 us with four waves and both in a thread, 6.0 so (5.0 element by element).
+__global__ __launch_bounds__(64) void k_kv_export16(int B, int len, int H, int hd, int L_pad, const uint16_t *__restrict__ kc,
                                                      const uint16_t *__restrict__ vc, uint16_t *__restrict__ k_user,
                                                      uint16_t *__restrict__ v_user) {
   const int d = H * hd, nb = (len + KV_VBLOCK - 1) / KV_VBLOCK, n8 = d >> 3;
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
   if (i >= (size_t)B * nb * n8) return;
   const int c0 = (int)(i % n8) * 8;
   const size_t r = i / n8;
@@ -438,12 +439,24 @@ __global__ __launch_bounds__(256) void k_kv_export16(int B, int len, int H, int 
   const int rows = min(KV_VBLOCK, len - p0);
   struct alignas(16) Eight { uint16_t v[8]; };
   struct alignas(8) Four { uint16_t v[4]; };
-  uint16_t val[8][8];  // [channel][position]
+  const size_t row0 = ((size_t)b * len + p0) * d + (size_t)hh * hd;
+  if (blockIdx.y) {
+    uint16_t val[8][8];  // [channel][position]
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const Eight t = *(const Eight *)(vc + kv_v_index(L_pad, H, hd, b, hh, p0, e0 + e));
+    for (int e = 0; e < 8; ++e) {
+      const Eight t = *(const Eight *)(vc + kv_v_index(L_pad, H, hd, b, hh, p0, e0 + e));
 #pragma unroll
-    for (int p = 0; p < 8; ++p) val[e][p] = t.v[p];
+      for (int p = 0; p < 8; ++p) val[e][p] = t.v[p];
+    }
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      if (p >= rows) break;
+      Eight o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o.v[e] = val[e][p];
+      *(Eight *)(v_user + row0 + (size_t)p * d + e0) = o;
+    }
+    return;
   }
   Eight key[8];  // stored elements e0 .. e0 + 7 of a row: the pairs of channels e0 / 2 .. e0 / 2 + 3 and their partners
 #pragma unroll
@@ -451,14 +464,10 @@ __global__ __launch_bounds__(256) void k_kv_export16(int B, int len, int H, int 
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
     if (p >= rows) break;
-    const size_t row = ((size_t)b * len + p0 + p) * d + (size_t)hh * hd;
-    Eight o;
     Four lo, hi;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o.v[e] = val[e][p];
-#pragma unroll
     for (int e = 0; e < 4; ++e) { lo.v[e] = key[p].v[2 * e]; hi.v[e] = key[p].v[2 * e + 1]; }
-    *(Eight *)(v_user + row + e0) = o;
+    const size_t row = row0 + (size_t)p * d;
     *(Four *)(k_user + row + (e0 >> 1)) = lo;
     *(Four *)(k_user + row + half + (e0 >> 1)) = hi;
   }
@@ -472,7 +481,7 @@ void launch_kv_convert(spec_ctx *c, const Model &m, int layer, int B, int len, v
   char *vc = (char *)m.vcache + (size_t)layer * m.kv_area_elems * esz;
   if (!import_ && esz == 2 && m.hd % 16 == 0 && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
     const size_t threads = (size_t)B * ((len + KV_VBLOCK - 1) / KV_VBLOCK) * (m.desc.d_model / 8);
-    hipLaunchKernelGGL(k_kv_export16, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, B, len, m.desc.n_heads, m.hd, m.L_pad,
+    hipLaunchKernelGGL(k_kv_export16, dim3((unsigned)((threads + 63) / 64), 2), dim3(64), 0, st, B, len, m.desc.n_heads, m.hd, m.L_pad,
                        (const uint16_t *)kc, (const uint16_t *)vc, (uint16_t *)k, (uint16_t *)v);
     return;
   }
