@@ -319,7 +319,8 @@ int spec_greedy_accept_noalloc(void *hip_stream, const float *d_logits, const in
      ([.][j][0] is not read); out: d_chosen [B][s+1] (the token chosen at each place up to the one that ended the
      round, -1 behind it), d_accepted [B] = l_b, d_emitted [B][s+1] = the l_b kept proposals, the drawn token, -1.
    Both enqueue on hip_stream (NULL = the default stream), need no context and no workspace, and do not wait.
-   temperature > 0, s <= 15 (SPEC_ERR_INVALID_ARG, SPEC_ERR_CAPACITY).  All device pointers, all the caller's.
+   temperature > 0 (infinite: every token but those at -inf alike), s <= 15 (SPEC_ERR_INVALID_ARG, SPEC_ERR_CAPACITY).
+   All device pointers, all the caller's.
 
    spec_set_sampling: the same rule inside a context, for every following round (spec_draft_step draws t_j, the
    verify step applies the rule; commit, roll-back, end token, budgets and per-sequence s work as in the greedy

@@ -27,6 +27,7 @@
 #include "spec_internal.h"
 #include "device_utils.h"
 #include <algorithm>
+#include <limits>
 #include <type_traits>
 
 namespace spec {
@@ -434,6 +435,11 @@ __global__ __launch_bounds__(64) void k_sample_seal(int B, int s, const int32_t 
   emitted[(size_t)b * (s + 1) + j] = j <= l ? v : -1;
 }
 
+// 1 / T as the kernels take it, never 0: the zero weight of a masked token, and of what lies behind a row's end, is the
+// exponential of -inf * inv_T, and T = inf (every token alike) would make that the one of -inf * 0.  The smallest positive
+// float leaves finite logits their weight of 1 there (3.4e38 * 1.4e-45 = 5e-7).
+static float inverse_temperature(float T) { return std::max(1.0f / T, std::numeric_limits<float>::denorm_min()); }
+
 static bool rows_vec(const float *z, int V) { return (V & 3) == 0 && ((uintptr_t)z & 15) == 0; }
 
 // Waves per workgroup, by the vocabulary alone (a draw's sums then still depend on nothing but the row): 4 up to 8192
@@ -447,7 +453,7 @@ void launch_sample_rows(const float *logits, int rows, int V, float temperature,
   if (rows <= 0) return;
   const bool vec = rows_vec(logits, V), narrow = narrow_rows(V);
   auto k = narrow ? (vec ? k_sample_rows<4, true> : k_sample_rows<4, false>) : vec ? k_sample_rows<16, true> : k_sample_rows<16, false>;
-  hipLaunchKernelGGL(k, dim3(rows), dim3(narrow ? 256 : 1024), 0, st, logits, V, 1.0f / temperature, u, n, off, u_rows,
+  hipLaunchKernelGGL(k, dim3(rows), dim3(narrow ? 256 : 1024), 0, st, logits, V, inverse_temperature(temperature), u, n, off, u_rows,
                      out, out_stride);
 }
 // How many workgroups share the places of a sequence's round.  A workgroup per place reads rows behind the first rejection
@@ -474,6 +480,7 @@ void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, i
                           int32_t *a, int a_stride, hipStream_t st, int32_t *accepted, int32_t *emitted) {
   if (B <= 0) return;
   const bool vec = rows_vec(tl, V) && (!dl || rows_vec(dl, V)), narrow = narrow_rows(V);
+  const float inv_T = inverse_temperature(temperature);
   const int per = workgroups_per_sequence(B, s, dl != nullptr, narrow ? 1024 : 256);
   const int per_launch = (1 << 21) / per;  // a grid holds less than 2^32 threads
   for (int64_t b0 = 0; b0 < B; b0 += per_launch) {
@@ -482,11 +489,11 @@ void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, i
       constexpr int W = decltype(W_)::value;
       constexpr bool VEC = decltype(VEC_)::value;
       if (per == s + 1)
-        hipLaunchKernelGGL((k_sample_verify<W, VEC>), dim3(nb * per), dim3(W * 64), 0, st, tl, dl, d_rows, (int)b0, s, V, 1.0f / temperature,
+        hipLaunchKernelGGL((k_sample_verify<W, VEC>), dim3(nb * per), dim3(W * 64), 0, st, tl, dl, d_rows, (int)b0, s, V, inv_T,
                            t, t_stride, seq_s, u, n, u_rows, a, a_stride);
       else
         hipLaunchKernelGGL((dl ? k_sample_verify_turns<W, VEC, true> : k_sample_verify_turns<W, VEC, false>), dim3(nb * per), dim3(W * 64), 0,
-                           st, tl, dl, d_rows, (int)b0, per, s, V, 1.0f / temperature, t, t_stride, seq_s, u, n, u_rows, a, a_stride);
+                           st, tl, dl, d_rows, (int)b0, per, s, V, inv_T, t, t_stride, seq_s, u, n, u_rows, a, a_stride);
     };
     using std::integral_constant;
     if (narrow && vec) launch(integral_constant<int, 4>{}, std::true_type{});

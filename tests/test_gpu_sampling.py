@@ -127,6 +127,42 @@ def test_draws_and_rule_at_the_edges_of_steps_segments_and_alignment(B, V, offse
         assert got[b] == tok or margin < MARGIN, (b, got[b], tok, margin)
 
 
+@pytest.mark.parametrize("V", [5, 1003, 4100, 8192, 8200, 32000, 50272, 70001])
+@pytest.mark.parametrize("T", [1e30, float(np.finfo(np.float32).max), float("inf")])
+def test_very_large_and_infinite_temperatures_draw_uniformly(B, V, T):
+    """1 / T so small that every finite logit has a weight of 1 in fp32 (sums of ones are exact), masked tokens none; rows that do
+    not fill their last step group.  The uniform numbers lie in the middle of a token's share, half a share from either
+    boundary: several thousand times what rounding u * V moves it by."""
+    rng = np.random.default_rng(V)
+    rows, lo = 16, V // 3
+    z = (rng.normal(size=(rows, V)) * 4.0).astype(np.float32)
+    z[1::2, :lo] = -np.inf                                        # odd rows: a masked prefix
+    first = np.where(np.arange(rows) % 2, lo, 0)
+    want = np.concatenate([first[:2], np.full(2, V - 1), rng.integers(first[4:], V)])
+    u = ((want - first + 0.5) / (V - first)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    assert B.spec_sample_tokens(dev(z), dev(u), T).cpu().tolist() == want.tolist()
+    # the rule, a round of one proposal per row: a point mass is kept below 1 / V and replaced otherwise
+    zz = np.stack([z, z], axis=1)                                 # [rows][2][V]
+    props = np.full((rows, 1), V - 1, dtype=np.int32)
+    un = np.zeros((rows, 2, 3), dtype=np.float32)
+    un[:, 0, 1], un[:, 1, 2] = 0.5 / V, u                         # kept, then the bonus draw
+    _, acc, em = (x.cpu().numpy() for x in B.spec_sample_accept(dev(zz), None, dev(props), dev(un), T))
+    assert acc.tolist() == [1] * rows and em[:, 0].tolist() == [V - 1] * rows and em[:, 1].tolist() == want.tolist()
+    props[:, 0] = first                                           # the residual is every live token but the first
+    un[:, 0, 1] = 2.0 / (V - first)
+    got = np.maximum(want, first + 1)
+    un[:, 0, 2] = (got - first - 1 + 0.5) / (V - first - 1)
+    _, acc, em = (x.cpu().numpy() for x in B.spec_sample_accept(dev(zz), None, dev(props), dev(un), T))
+    assert acc.tolist() == [0] * rows and em[:, 0].tolist() == got.tolist()
+    # a draft without the mask: its masked proposals are rejected, and the residual is uniform over the live tokens
+    odd = np.arange(1, rows, 2)
+    q = np.where(np.isinf(z[odd]), np.float32(0.0), z[odd])
+    un[odd, 0, 1], un[odd, 0, 2] = 0.5, u[odd]
+    _, acc, em = (x.cpu().numpy() for x in B.spec_sample_accept(dev(zz[odd]), dev(q[None]), dev(np.zeros((len(odd), 1), np.int32)), dev(un[odd]), T))
+    assert acc.tolist() == [0] * len(odd) and em[:, 0].tolist() == want[odd].tolist()
+
+
 def _on_device_round(nB, s, V, sigma, seed, T):
     """Peaked target rows, a draft `sigma` away from them, proposals drawn from the draft, uniform numbers."""
     g = torch.Generator(device=DEV)
