@@ -424,9 +424,9 @@ __global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int L_p
 }
 // The export of 16-bit rows to buffers aligned to 16 bytes: a thread takes eight channels at eight consecutive positions,
 // where the cache has the values of a channel side by side, and the keys of eight pairs (two runs of four channels) of a
-// row.  Element by element the scattered loads and stores were most of the time: 64 x 128 rows of 4096
-// 120 -> 74 us.  Workgroups of one wave, keys (blockIdx.y 0) and values (1) apart, so that a short export spreads over the CUs:
-// 16 rows of 6656 10.7 us with four waves and both in a thread, 6.0 so (5.0 element by element).
+// row.  Element by element the scattered loads and stores were most of the time: 64 x 128 rows of 4096 116 -> 67 us (33 MB
+// read at the rate they are written).  Workgroups of one wave, keys (blockIdx.y 0) and values (1) apart, so that a
+// small export spreads over the CUs.
 __global__ __launch_bounds__(64) void k_kv_export16(int B, int len, int H, int hd, int L_pad, const uint16_t *__restrict__ kc,
                                                      const uint16_t *__restrict__ vc, uint16_t *__restrict__ k_user,
                                                      uint16_t *__restrict__ v_user) {
@@ -479,7 +479,10 @@ void launch_kv_convert(spec_ctx *c, const Model &m, int layer, int B, int len, v
   size_t esz = dtype_bytes(c->run.dtype);
   char *kc = (char *)m.kcache + (size_t)layer * m.kv_area_elems * esz;
   char *vc = (char *)m.vcache + (size_t)layer * m.kv_area_elems * esz;
-  if (!import_ && esz == 2 && m.hd % 16 == 0 && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
+  // From 3 * 2^18 elements on: a thread's eight rows in turn take a microsecond longer than a launch of single elements, until
+  // those are several to a lane of the chip.  Elements / blocks, us: 16 rows of 4096 2.4 / 3.4, 64 rows of 6656 3.4 / 3.6, 128
+  // rows of 5120 4.1 / 4.3, 64 x 16 rows of 768 4.6 / 4.4, 256 rows of 4096 5.4 / 4.5, 777 rows of 5120 14.3 / 9.7.
+  if (!import_ && esz == 2 && total >= ((size_t)3 << 18) && m.hd % 16 == 0 && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
     const size_t threads = (size_t)B * ((len + KV_VBLOCK - 1) / KV_VBLOCK) * (m.desc.d_model / 8);
     hipLaunchKernelGGL(k_kv_export16, dim3((unsigned)((threads + 63) / 64), 2), dim3(64), 0, st, B, len, m.desc.n_heads, m.hd, m.L_pad,
                        (const uint16_t *)kc, (const uint16_t *)vc, (uint16_t *)k, (uint16_t *)v);
