@@ -2,8 +2,8 @@
 // target model itself and wants only a_i = argmax o_i, the accepted count l_b and the emitted tokens.
 //
 // Two kernels.  k_ga_partials: one workgroup per (row, 4096-logit chunk) leaves the chunk's (value, index)
-// arg-max in scratch.  k_ga_accept: one wave per sequence reduces the chunks of its s + 1 rows (lowest index wins
-// ties, at every stage) and applies the first-mismatch rule.  Every partial the second kernel reads was written by
+// arg-max in scratch.  k_ga_accept: one workgroup per sequence, a wave for each of its s + 1 rows, reduces the rows' chunks
+// (lowest index wins ties, at every stage) and applies the first-mismatch rule.  Every partial the second kernel reads was written by
 // the first in the same call, so the scratch needs no clearing.
 //
 // The scratch is the caller's workspace (spec_greedy_accept) or a file-scope device array
@@ -18,6 +18,17 @@ constexpr int GA_CHUNK = 4096;                      // logits per first-stage wo
 
 struct GaPartial { float v; int32_t i; };
 
+// The thread's candidates of the logits c0 .. c1 - 1, at most 256 N of them: all loads in flight together, the ones behind the end
+// repeating the last logit (24 rows of 50272 logits 5.6 -> 4.1 us).
+template <int N>
+__device__ __forceinline__ void chunk_argmax(const float *__restrict__ src, int c0, int c1, float &bv, int &bi) {
+  float v[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = src[min(c0 + (int)threadIdx.x + 256 * k, c1 - 1)];
+#pragma unroll
+  for (int k = 0; k < N; ++k) argmax_combine(bv, bi, v[k], min(c0 + (int)threadIdx.x + 256 * k, c1 - 1));
+}
+
 __global__ __launch_bounds__(256) void k_ga_partials(const float *__restrict__ logits, int V, int n_chunks,
                                                      GaPartial *__restrict__ part) {
   __shared__ float shv[4];
@@ -27,13 +38,13 @@ __global__ __launch_bounds__(256) void k_ga_partials(const float *__restrict__ l
   const int c0 = chunk * GA_CHUNK, c1 = min(c0 + GA_CHUNK, V);
   float bv = -INFINITY;
   int bi = 0x7fffffff;
-  // the chunk's loads all in flight together, the ones behind its end repeating the last logit (24 rows of 50272 logits 5.6 ->
-  // 4.1 us)
-  float v[GA_CHUNK / 256];
-#pragma unroll
-  for (int k = 0; k < GA_CHUNK / 256; ++k) v[k] = src[min(c0 + (int)threadIdx.x + 256 * k, c1 - 1)];
-#pragma unroll
-  for (int k = 0; k < GA_CHUNK / 256; ++k) argmax_combine(bv, bi, v[k], min(c0 + (int)threadIdx.x + 256 * k, c1 - 1));
+  // A thread's loads, the same for the workgroup.  A short row that repeats its last logit up to sixteen loads pays for them:
+  // 32768 rows of 37 logits, both kernels, 61 us with sixteen, 38 with one; of 1000 62 and 46.  Few variants, the longest one first:
+  // five of them in ascending order took 1 us of 20 more at 2100 logits.
+  const int loads = (c1 - c0 + 255) >> 8;
+  if (loads > 4) chunk_argmax<GA_CHUNK / 256>(src, c0, c1, bv, bi);
+  else if (loads > 1) chunk_argmax<4>(src, c0, c1, bv, bi);
+  else chunk_argmax<1>(src, c0, c1, bv, bi);
   wave_argmax(bv, bi);
   if ((threadIdx.x & 63) == 0) { shv[threadIdx.x >> 6] = bv; shi[threadIdx.x >> 6] = bi; }
   __syncthreads();

@@ -32,7 +32,7 @@ def make_case(nB, s, V, seed, alpha=0.7):
 
 
 @pytest.mark.parametrize("nB,s,V", [(1, 0, 17), (3, 4, 1000), (64, 8, 32000), (5, 15, 50272), (2, 3, 4096), (2, 2, 4097),
-                                     (7, 1, 151936)])
+                                     (7, 1, 151936), (3, 1, 256), (3, 1, 257), (2, 2, 1024), (2, 2, 1025), (2, 1, 5120)])
 def test_greedy_accept_matches_numpy_argmax_and_oracle_rule(nB, s, V):
     from oracle import oracle as om
     from paper_2310_18813_amd import binding as B
@@ -44,6 +44,27 @@ def test_greedy_accept_matches_numpy_argmax_and_oracle_rule(nB, s, V):
         l, out = orc.accept([int(x) for x in t[b]], [int(x) for x in a[b]])
         assert acc[b] == l, (b, acc[b], l)
         assert list(em[b, :l + 1]) == out and all(x == -1 for x in em[b, l + 1:]), (b, em[b], out)
+
+
+def test_short_rows_do_not_pay_for_the_loads_of_a_full_chunk():
+    """32768 rows of 37 logits against as many of 2048: 0.55 of the time; 0.97 when both make a thread issue sixteen loads."""
+    from paper_2310_18813_amd import binding as B
+    nB, s, us = 2048, 15, {}
+    props = torch.zeros((nB, s), dtype=torch.int32, device=DEV)
+    for V in (37, 2048):
+        lg = torch.randn((nB, s + 1, V), device=DEV)
+        B.spec_greedy_accept(lg, props)
+        times = []
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(50):
+                B.spec_greedy_accept(lg, props)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1) * 20)
+        us[V] = min(times)
+    assert us[37] < 0.8 * us[2048], us
 
 
 def test_greedy_accept_rejects_bad_arguments():
