@@ -387,21 +387,34 @@ void fp32_prepare() {
 }
 
 // Strips and row tiles per workgroup (neither changes a result): the compute unit with the most workgroups sets the
-// time (gate-up of d_model 1024 at 1328 rows: 585 us as 1 x 1, 370 us as 4 strips x 2 tiles).  (4 strips x 3 tiles: the LM
-// head 32000 x 1024 at 40 rows, whose activations are then fetched half as often as at 2 x 3: a verification of 8 sequences x 5
-// rows 304 -> 299 us.)  Cycles per 16-k step of a workgroup: 16 per 1 KB fragment from L2, about three times that for weights the first
-// time they are read (HBM), against 32 of the matrix cores per tile.
+// time (gate-up of d_model 1024 at 1328 rows: 585 us as 1 x 1, 370 us as 4 strips x 2 tiles).  Cycles per 16-k step of a workgroup:
+// 16 per 1 KB fragment from L2, about three times that for weights the first time they are read (HBM), against 32 of the
+// matrix cores per tile.
+static long f32_cost(int M, int NT, int mt, int nb, int n_cu, bool by_xcd) {
+  const long passes = (M + mt * 16 - 1) / (mt * 16), groups = (NT + nb - 1) / nb;
+  // by_xcd: as the launch deals them, whole strip groups to an XCD when there are several row passes
+  const long xcd_cu = std::max(1, n_cu / 8), per_cu = by_xcd && passes > 1 ? ((groups + 7) / 8 * passes + xcd_cu - 1) / xcd_cu : (groups * passes + n_cu - 1) / n_cu;
+  return per_cu * (16 * nb * (2 + passes) / passes + 16 * mt + 32 * nb * mt);
+}
 static void f32_gemm(F32Gemm a, int epi, int n_cu, hipStream_t st) {
   if (a.M <= 0) return;
   int MT = 1, NB = 1;
   long best = -1;
-  for (int mt = 1; mt <= 4; ++mt) {
-    const long passes = (a.M + mt * 16 - 1) / (mt * 16);
-    for (int nb = 1; nb * mt <= 12 && nb <= 4; nb *= 2) {
-      const long per_cu = ((a.NT + nb - 1) / nb * passes + n_cu - 1) / n_cu;
-      const long cost = per_cu * (16 * nb * (2 + passes) / passes + 16 * mt + 32 * nb * mt);
+  for (int mt = 1; mt <= 4; ++mt)
+    for (int nb = 1; nb * mt <= 8 && nb <= 4; nb *= 2) {
+      const long cost = f32_cost(a.M, a.NT, mt, nb, n_cu, false);
       if (best < 0 || cost < best) { best = cost; MT = mt; NB = nb; }
     }
+  // Twelve tiles (one workgroup a CU, by its LDS) where that is estimated faster: one row pass (LM head 32000 x 1024 at 40 rows, whose
+  // activations are fetched half as often as at 3 x 2: a verification of 8 sequences x 5 rows 304 -> 299 us); several, where
+  // a look at the XCDs confirms it and it replaces 3 x 2 or 4 x 2 (qkv of d_model 1024 at 704 rows 86 -> 73 us, gate-up of 768 at
+  // 848 rows 152 -> 128), or 2 x 4 with a share to save (over the products of d_model 512 to 1024 with k of up to 1024
+  // 4 % faster, with longer k or less to save up to 3 % slower).  Elsewhere it loses: down of 768 at 784 rows, 12 groups on 8 XCDs, 64 -> 108 us as 3 x 4; the head at 72 rows, 1 x 4
+  // keeps four workgroups a CU, 78 -> 103.
+  if (MT == 3 || MT == 4 || NB == 4) {
+    const bool once = a.M <= 48;
+    const long twelve = f32_cost(a.M, a.NT, 3, 4, n_cu, !once), other = f32_cost(a.M, a.NT, MT, NB, n_cu, !once);
+    if (once || MT >= 3 ? twelve < other : MT == 2 && 100 * twelve <= (a.KT <= 64 ? 98 : 93) * other) { MT = 3; NB = 4; }
   }
   a.passes = (a.M + MT * 16 - 1) / (MT * 16);
   a.groups = (a.NT + NB - 1) / NB;
