@@ -126,15 +126,16 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   } else {
     // The tiles in blocks of up to 8 row passes, strip group by strip group, one eighth of that row to each XCD (workgroups are
     // dealt round-robin to the 8 XCDs): the 32 workgroups an XCD runs at a time are 8 passes x 4 groups and share both
-    // operands in its L2, and no XCD has more than one tile more than another.  (Strip groups dealt to the XCDs whole, with all
+    // operands in its L2, and none has more than an eighth of all tiles, rounded up.  (Strip groups dealt to the XCDs whole, with all
     // their passes, left XCDs with a group more than others: 4096 x 11008 at 1328 rows, 11 groups, 218 -> 138 us, 20480 x 5120
-    // at 784 rows 221 -> 195, 6592 rows of the 7B width's four products -1.5 to -2.6 %.)
-    const int id = blockIdx.x, total = a.groups * a.passes, per = (total + 7) >> 3, at = id >> 3;
-    const int tile = (id & 7) * per + at;
+    // at 784 rows 221 -> 195, 6592 rows of the 7B width's four products -1.5 to -2.6 %.)  a.whole_groups: dealt whole after all.
+    const bool whole = EPI == EPI_QKV && a.whole_groups;
+    const int id = blockIdx.x, row = whole ? (a.groups + 7) >> 3 : a.groups, total = row * a.passes, per = whole ? total : (total + 7) >> 3, at = id >> 3;
+    const int tile = whole ? at : (id & 7) * per + at;
     if (at >= per || tile >= total) return;
-    const int blk = tile / (a.groups * 8), rest = tile - blk * a.groups * 8, in_blk = min(8, a.passes - blk * 8);
+    const int blk = tile / (row * 8), rest = tile - blk * row * 8, in_blk = min(8, a.passes - blk * 8);
     pass = blk * 8 + rest % in_blk;
-    G = rest / in_blk;
+    G = whole ? rest / in_blk * 8 + (id & 7) : rest / in_blk;
   }
   G = __builtin_amdgcn_readfirstlane(G);
   pass = __builtin_amdgcn_readfirstlane(pass);
@@ -645,12 +646,24 @@ int gemm_tile_head_partials(const GemmArgs &a) {
   return 2 * ((a.NT + 2 * NBW - 1) / (2 * NBW));
 }
 
+// The value strips of a decoding round's QKV product scatter a few rows over the cache, one channel at a time.  Dealt by eighths they
+// end on two or three XCDs, which then finish last: as long as whole strip groups take no more rounds they go to the XCDs
+// in turn (12288 x 4096 at 640 rows 89 us by eighths, 84 in turn, 19968 x 6656 at 1280 rows 327 and 309).  A prefill's values are
+// written eight positions at a time: 19968 x 6656 at 8192 rows 1754 us by eighths, 1820 in turn.
+static bool deal_whole_groups(const GemmArgs &a, int epi) {
+  if (epi != EPI_QKV || a.grp_seq) return false;
+  const int n_cu = a.n_cu > 0 ? a.n_cu : 256, xcd_cu = std::max(1, n_cu / 8);
+  const int whole = (a.groups + 7) / 8 * a.passes, even = (a.groups * a.passes + 7) / 8;
+  return (whole + xcd_cu - 1) / xcd_cu == (even + xcd_cu - 1) / xcd_cu;
+}
+
 static void launch_rows(int dtype, GemmArgs a, int epi, bool split, int MTW, int NBW, hipStream_t st) {
   a.n_part = 2 * ((a.NT + 2 * NBW - 1) / (2 * NBW));
   a.passes = (a.M + 64 * MTW - 1) / (64 * MTW);
   a.groups = (a.NT + 2 * NBW - 1) / (2 * NBW);
+  a.whole_groups = !split && a.passes > 1 && deal_whole_groups(a, epi);
   const int blocks = split ? (a.KS == 8 ? a.groups * a.passes * 8 : ((a.groups + 7) / 8) * 8 * a.passes * a.KS)
-                           : a.passes == 1 ? a.groups : (a.groups * a.passes + 7) / 8 * 8;
+                           : a.passes == 1 ? a.groups : a.whole_groups ? (a.groups + 7) / 8 * 8 * a.passes : (a.groups * a.passes + 7) / 8 * 8;
   launch_shape(dtype, a, MTW, NBW, split ? (int)EPI_PARTIAL : epi, blocks, st);
 }
 

@@ -29,7 +29,7 @@ struct GemmArgs {
   const void *X;      // fp16 activations in fragment order (xpack_index), ceil(M/16) x KT tiles
   float out_scale;    // 1 / (power of two the packed weights were multiplied by)
   int M, N, NT, KT, KS, K_pad;
-  int passes, groups;  // filled by the launcher
+  int passes, groups, whole_groups;  // filled by the launcher
   unsigned int *sat;   // counts activations clamped to the fp16 range on their way to a GEMM operand (or null)
   int n_cu;            // compute units of the device (0: 256)
   int tune;            // launch-shape overrides of spec_set_gemm_tuning (0: none); never change a result
