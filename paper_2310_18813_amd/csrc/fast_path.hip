@@ -215,7 +215,7 @@ void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
   // the norms are folded: ws.x holds fp16(h), left by the producer of h, and the consumer takes 1 / rms (LayerNorm:
   // mean and 1 / std) of its rows from it
   auto consume_norm = [&](GemmArgs &a, const float *wsum) {
-    a.fold_x = 1; a.ss_d = d; a.ss_eps = D.norm_eps; a.rinv_ws = ws.row_inv;
+    a.fold_x = 1; a.stats_left = c->x_ssq; a.ss_d = d; a.ss_eps = D.norm_eps; a.rinv_ws = ws.row_inv;
     if (m.fold_ln) { a.wsum = wsum; a.mean_ws = ws.row_mean; }
   };
   // the tiled kernel's larger wave tiles read 1 / rms per row from scratch: a small kernel fills it first, unless
@@ -294,7 +294,7 @@ void fast_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits
   a.logit_step = last_of_q;  // the head runs over every row of the pass: dump the wanted ones only
   a.part_val = c->ws.head_part;
   a.part_idx = c->ws.head_part_idx;
-  a.fold_x = 1; a.ss_d = m.desc.d_model; a.ss_eps = m.desc.norm_eps; a.rinv_ws = c->ws.row_inv;
+  a.fold_x = 1; a.stats_left = c->x_ssq; a.ss_d = m.desc.d_model; a.ss_eps = m.desc.norm_eps; a.rinv_ws = c->ws.row_inv;
   if (m.fold_ln) { a.wsum = m.wsum_head; a.mean_ws = c->ws.row_mean; }
   // the row statistics, unless the last layer's down projection has left them
   if (!c->x_ssq && gemm_wants_row_inv(a, EPI_LOGITS)) { KScope k(c, tgt ? SPEC_KCLASS_NORM : -1); launch_row_inv_x(a, st); }

@@ -521,13 +521,17 @@ static void launch_shape(int dtype, const GemmArgs &a, int MTW, int NBW, int epi
 // matrices of the 7B, 13B and 33B widths, whole and split by k-slice (1300 launches; rms error 11 %): per step a
 // constant for the meeting of the waves and the multiplies (us per tile) beside the fetches (us per KB), which overlap
 // in part; per round the pipeline's filling and the epilogue; and no launch is faster than its weights stream from HBM.
-// Over the sweep's 117 (matrix, row count) cells the shape it picks is 0.6 % slower than the best one, 11 % at worst.
-// Two terms came later, from a sweep of 36 .. 512 rows (14 matrices, 1412 launches): weights that several row passes read stream
+// Over the sweep's 117 (matrix, row count) cells the shape it picked was 0.6 % slower than the best one, 11 % at worst.
+// Three terms came later.  From a sweep of 36 .. 512 rows (14 matrices, 1412 launches): weights that several row passes read stream
 // more slowly than those a single pass loads non-temporally, and the row sums of a folded norm, taken in the loop with one row
-// tile per wave, cost a step 0.04 us.  Over its 162 cells the pick is 0.8 % slower than the best (1.5 % before); 15360 x 5120 at
-// 80 and 128 rows 50 -> 41 and 53 -> 46 us, 22016 x 4096 at 256 rows 63 -> 59, 12288 x 4096 at 80 rows 38 -> 33.
+// tile per wave, cost a step 0.04 us; over its 162 cells the pick was then 0.8 % slower than the best (1.5 % before), 15360 x 5120 at
+// 80 and 128 rows 50 -> 41 and 53 -> 46 us, 22016 x 4096 at 256 rows 63 -> 59, 12288 x 4096 at 80 rows 38 -> 33.  And larger wave
+// tiles need k_row_inv_x in front, unless the producer has left the statistics: 3.5 us with its launch (without that term
+// narrow products took it: 8192 x 1024 at 224 rows 12 -> 15 us).
+enum Fold { FOLD_NONE, FOLD_WANTED, FOLD_LEFT };  // no norm folded in; its row statistics still to be taken; left by the producer
+static Fold fold_of(const GemmArgs &a) { return !a.fold_x ? FOLD_NONE : a.stats_left ? FOLD_LEFT : FOLD_WANTED; }
 constexpr int TILE_MT[4] = {1, 2, 3, 4}, TILE_NB[4] = {2, 3, 4, 6};
-static double tile_us(int mt, int nb, int M, int NT, int n_cu, int steps, int wg_mult, double w_bytes, bool fold) {
+static double tile_us(int mt, int nb, int M, int NT, int n_cu, int steps, int wg_mult, double w_bytes, Fold fold) {
   const int passes = (M + 64 * mt - 1) / (64 * mt);
   int groups = (NT + 2 * nb - 1) / (2 * nb);
   // all workgroups of a strip group of a split launch of two or four k-slices share an XCD: the XCDs with one group more
@@ -535,11 +539,12 @@ static double tile_us(int mt, int nb, int M, int NT, int n_cu, int steps, int wg
   if (wg_mult > 1 && wg_mult < 8) groups = (groups + 7) / 8 * 8;
   const int wgs = passes * groups * wg_mult;
   const int rounds = (wgs + n_cu - 1) / n_cu;
-  const double mul = 0.0113 * mt * nb + (fold && tile_takes_row_sums(mt) ? 0.04 : 0.0), load = 0.0087 * (2 * nb + 4 * mt);
+  const double mul = 0.0113 * mt * nb + (fold != FOLD_NONE && tile_takes_row_sums(mt) ? 0.04 : 0.0), load = 0.0087 * (2 * nb + 4 * mt);
   const double raw = rounds * (1.35 + 0.396 * mt * nb + steps * (0.066 + std::sqrt(mul * mul + load * load)));
-  return 3.0 + std::max(raw, w_bytes / (passes == 1 || wg_mult > 1 ? 5.3e6 : 3.5e6)) + 0.1 * raw;
+  const double stats = fold == FOLD_WANTED && !tile_takes_row_sums(mt) ? 3.5 : 0.0;  // k_row_inv_x in front
+  return 3.0 + stats + std::max(raw, w_bytes / (passes == 1 || wg_mult > 1 ? 5.3e6 : 3.5e6)) + 0.1 * raw;
 }
-static double choose_tile(int M, int NT, int n_cu, int steps, int wg_mult, double w_bytes, bool fold, int &MTW, int &NBW) {
+static double choose_tile(int M, int NT, int n_cu, int steps, int wg_mult, double w_bytes, Fold fold, int &MTW, int &NBW) {
   double best = 0.0;
   for (int mt : TILE_MT)
     for (int nb : TILE_NB) {
@@ -557,10 +562,10 @@ static double tile_for(const GemmArgs &a, bool split, int &MTW, int &NBW) {
   const int f_mt = a.tune & TUNE_TILE_MTW_MASK, f_nb = (a.tune >> TUNE_TILE_NBW_SHIFT) & 0xf;
   if (f_mt >= 1 && f_mt <= 4 && f_nb >= 2 && f_nb <= 6 && f_nb != 5) {  // test / tuning aid
     MTW = f_mt; NBW = f_nb;
-    return second + tile_us(MTW, NBW, a.M, a.NT, n_cu, steps, wg_mult, w_bytes, a.fold_x);
+    return second + tile_us(MTW, NBW, a.M, a.NT, n_cu, steps, wg_mult, w_bytes, fold_of(a));
   }
   MTW = 2; NBW = 2;
-  return second + choose_tile(a.M, a.NT, n_cu, steps, wg_mult, w_bytes, a.fold_x, MTW, NBW);
+  return second + choose_tile(a.M, a.NT, n_cu, steps, wg_mult, w_bytes, fold_of(a), MTW, NBW);
 }
 
 // A launch of several rounds of workgroups ends in one that is partly empty, and a round of large wave tiles is long: the
@@ -575,15 +580,15 @@ static int rows_of_first_launch(const GemmArgs &a, int epi, int MTW, int NBW, in
   // since the second launch's wave tile may want them from k_row_inv_x)
   if ((a.tune & 0xff) || epi == EPI_LOGITS || passes * groups <= n_cu || (a.fold_x && tile_takes_row_sums(MTW))) return a.M;
   const double w_bytes = 1024.0 * a.NT * a.KT;
-  double best = 0.97 * tile_us(MTW, NBW, a.M, a.NT, n_cu, a.KT, 1, w_bytes, a.fold_x);
+  double best = 0.97 * tile_us(MTW, NBW, a.M, a.NT, n_cu, a.KT, 1, w_bytes, fold_of(a));
   const int rounds = (passes * groups + n_cu - 1) / n_cu;
   int first = a.M;
   for (int r = rounds - 1; r >= 1 && r >= rounds - 2; --r) {
     const int rows = r * n_cu / groups * pass_rows;
     if (rows <= 0 || rows >= a.M || (epi == EPI_QKV && rows % a.q_rows != 0)) continue;
     int mt = 2, nb = 2;
-    const double rest = choose_tile(a.M - rows, a.NT, n_cu, a.KT, 1, w_bytes, a.fold_x, mt, nb);
-    const double us = tile_us(MTW, NBW, rows, a.NT, n_cu, a.KT, 1, w_bytes, a.fold_x) + rest;
+    const double rest = choose_tile(a.M - rows, a.NT, n_cu, a.KT, 1, w_bytes, a.fold_x ? FOLD_LEFT : FOLD_NONE, mt, nb);
+    const double us = tile_us(MTW, NBW, rows, a.NT, n_cu, a.KT, 1, w_bytes, fold_of(a)) + rest;
     if (us < best) { best = us; first = rows; MTW2 = mt; NBW2 = nb; }
   }
   return first;
@@ -609,8 +614,12 @@ static GemmArgs rows_from(GemmArgs a, int m0) {
   return a;
 }
 
-double gemm_tile_us(const GemmArgs &a, bool split) {
+// For the choice between the kernels: with the share of the row sums only for k beyond 2048.  (Streaming / tiled, us: 12288 x 4096 at
+// 40 rows 24 / 27, but 6144 x 2048 at 80 rows 18 / 15, 2048 x 512 at 192 rows 10 / 7: over a short k the share outweighs what it
+// costs, and the streaming kernel's estimate has none.)
+double gemm_tile_us(GemmArgs a, bool split) {
   int MTW, NBW;
+  if (a.KT <= 64) a.fold_x = 0;
   return tile_for(a, split, MTW, NBW);
 }
 

@@ -39,6 +39,7 @@ struct GemmArgs {
   // activations are the fp16-rounded rows of h themselves, written by the producer of h; the consumer's
   // epilogue multiplies by 1 / rms of the row, which it takes from the operand fragments it reads anyway.
   int fold_x;                // consumer: norm folded in (row length ss_d, epsilon ss_eps)
+  int stats_left;            // consumer: the producer of the rows has left their statistics in rinv_ws (and mean_ws)
   int ss_d;
   float ss_eps;
   int ssq_ks;                // producer (below): the k-slices of the GEMM that will consume x_out, gemm_ks_for(N / 32); else 0
@@ -96,7 +97,7 @@ void launch_rope_table(int L, int hd, float theta, float2 *tab, hipStream_t st);
 void launch_gemm_mfma(int dtype, const GemmArgs &a, int epi, hipStream_t st);
 // more than 32 rows; split (EPI_RESIDUAL with a.part): one k-slice per workgroup, added up by a second kernel
 void launch_gemm_tile(int dtype, GemmArgs a, int epi, bool split, hipStream_t st);
-double gemm_tile_us(const GemmArgs &a, bool split);  // its estimated time
+double gemm_tile_us(GemmArgs a, bool split);  // its estimated time
 // EPI_LOGITS: arg-max partials per row the launch for these arguments leaves
 int gemm_head_partials(const GemmArgs &a);
 int gemm_tile_head_partials(const GemmArgs &a);
