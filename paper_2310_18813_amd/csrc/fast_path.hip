@@ -200,7 +200,7 @@ static GemmArgs base_args(const spec_ctx *c, const PackedDims &p, const void *W,
 
 // One pre-norm decoder layer over the M rows of the pass; max_pos is an upper bound of the
 // largest row position (sizes the attention grid; chunks past a sequence's end exit at once).
-void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, int max_pos, hipStream_t st) {
+void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, double reuse, int max_pos, hipStream_t st) {
   const spec_model_desc &D = m.desc;
   const int dt = c->run.dtype, M = B * q_rows, d = D.d_model;
   const LayerW &L = m.layers[layer];
@@ -249,6 +249,7 @@ void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
     t.part_acc = ws.attn_part; t.part_ml = ws.attn_ml;
     t.B = B; t.q_rows = q_rows; t.H = D.n_heads; t.hd = m.hd; t.L_pad = m.L_pad;
     t.grp_seq = grp_seq;
+    t.reuse = reuse;
     t.part_rows = c->M_max;
     t.shape = c->attn_shape;
     t.n_cu = c->n_cu;

@@ -26,6 +26,7 @@
 #include "spec_internal.h"
 #include "device_utils.h"
 #include "mfma_gemm.h"
+#include <cmath>
 
 // No implicit fusing of multiplies and adds: which product a compiler folds into an FMA can
 // differ between two instantiations of the same source, and results here must be bit-identical
@@ -424,7 +425,7 @@ __global__ __launch_bounds__(512) void k_attn_group(AttnArgs a) {
 // bounds a long prompt (5 prompts of up to
 // 2011 tokens x 52 heads of 128: 1.42 ms a layer, the whole prefill 23.1 -> 21.7 ms with this).  The steps and merges of a wave are those of the other shapes; steps beyond its own
 // last position it sits out.
-constexpr int PREFILL_WAVES = 4, PREFILL_RING = 4;
+constexpr int PREFILL_RING = 4;
 constexpr size_t attn_prefill_lds(int HD) { return (size_t)PREFILL_RING * (HD / 8) * 1024 + 2 * PREFILL_WAVES * sizeof(int); }
 
 // 16 bytes per lane from the lane's own address to LDS byte offset `lds` + 16 lane
@@ -615,9 +616,16 @@ static void launch_attn_hd(const AttnArgs &a, hipStream_t st) {
     // workgroups of one wave: few pairs then spread over all compute units (measured, us per layer at 32 heads: 4
     // sequences x 100 positions 15.1 -> 11.8, 24 x 250 29.6 -> 26.6), and many pairs drain evenly (64 sequences x 300
     // positions 72.5 -> 71.4 against workgroups of four waves; 32 sequences x 52 heads x 2048 positions: the same)
-    // a prefill, several groups of which read one cache: through LDS, but for prompts within the first chunk, where there is
-    // little to share (64 prompts of up to 128 tokens: a prefill of 4 layers 11.71 ms, through LDS 11.73)
-    if (a.grp_seq && a.shape == 0 && a.NC > 1)
+    // Where this shape is taken for a prefill, several groups of which may read one cache: through LDS as far as they do
+    // (prefill_reuse).  The waves of a workgroup work on one sequence at a time, so that groups of different short
+    // prompts wait for each other.  One wave per group / through LDS, us, heads of 128: reuse 3.55 (5 prompts of up to 2011 tokens x
+    // 32 heads) 657 / 393, 2.0 (24 of up to 300 x 32) 90 / 74, 1.56 (64 of 130 x 40) 169 / 156, but 1.3 (150 of 9 and one of
+    // 600 x 16) 38 / 41, 0.96 (240 of 17 and one of 800 x 32) 82 / 95, 0.45 (200 of 9 and one of 200 x 32) 43 / 64.
+    // Heads of 64, half the bytes a step: 2.6 (16 of 250 x 32) 41 / 36, 2.1 (one of 900 and 30 of 100 x 32) 51 / 53.  Up to one round
+    // of waves, where a step's latency counts and no stream: heads of 128 with a reuse of 3 (one of 900 x 16) 37 / 34,
+    // 2.6 (4 of 400 x 8) 20 / 22; heads of 64 (one of 500 x 32) 18 / 20.
+    const double enough = HD == 128 ? (rounds > 1 ? 1.5 : 3.0) : rounds > 1 ? 2.5 : INFINITY;
+    if (a.grp_seq && a.shape == 0 && a.NC > 1 && a.reuse >= enough)
       hipLaunchKernelGGL((k_attn_prefill<T, HD>), dim3((a.B + PREFILL_WAVES - 1) / PREFILL_WAVES * a.H), dim3(64 * PREFILL_WAVES),
                          attn_prefill_lds(HD), st, a);
     else if (a.grp_seq) hipLaunchKernelGGL((k_attn_seq<T, HD, false>), dim3(pairs), dim3(64), 0, st, a);

@@ -143,6 +143,7 @@ struct AttnArgs {
   int shape;                // 0 auto, 1 split + merge, 2 one wave per (sequence, head), 3 one workgroup per (sequence, head)
   int B, q_rows, H, hd, L_pad, NC;  // NC = chunks launched (upper bound over the batch)
   const int32_t *grp_seq;   // prefill: the sequence whose cache each group of q_rows rows reads (several groups share one); null: group b is sequence b
+  double reuse;             // prefill: prefill_reuse of the pass's groups
   int part_rows;            // rows that part_acc and part_ml have room for
   int n_cu;                 // compute units of the device (0: 256)
 };
@@ -160,6 +161,20 @@ constexpr int ATTN_STREAM_MIN_WAVES = 2048;  // (sequence, head, chunk) waves fr
 constexpr int ATTN_SEQ_MIN_PAIRS = 768;   // (sequence, head) pairs from which one wave walks all chunks (measured: 24 sequences x 32 heads 55 -> 45 us)
 constexpr int ATTN_GROUP_MAX_WAVES = 8;  // waves of the one-workgroup-per-(sequence, head) shape, a chunk each (four waves with the register budget of the split kernel were measured no faster, and slower at 16 sequences)
 constexpr int ATTN_GROUP_MAX_CHUNKS = 16;  // ... or every eighth chunk each when there are more: 139 KB of partials at head_dim 128 (2560 positions)
+// What the prefill kernel saves on the groups of a pass, in steps of 32 keys: group by group over workgroup by workgroup, which take
+// PREFILL_WAVES groups in turn and every sequence among them once, with two steps' time for its start.  last(k): the
+// last position of group k; first_of(k): whether it is the first of its sequence.
+constexpr int PREFILL_WAVES = 4;
+template <class Last, class First>
+double prefill_reuse(int groups, Last last, First first_of) {
+  long own = 0, shared = 0;
+  for (int k = 0; k < groups; ++k) {
+    const int steps = last(k) / 32 + 1;
+    own += steps;
+    if (k + 1 == groups || (k + 1) % PREFILL_WAVES == 0 || first_of(k + 1)) shared += steps + 2;  // ascending within a sequence
+  }
+  return shared > 0 ? (double)own / shared : 0.0;
+}
 void launch_attention_mfma(int dtype, const AttnArgs &a, hipStream_t st);
 
 }  // namespace spec

@@ -470,7 +470,7 @@ static int forward_pass(spec_ctx *c, Model &m, const PassArgs &pa, HeadMode head
   c->x_ssq = false;  // the rows in ws.x come from the embedding
   const int32_t *grp_seq = pa.kind == PASS_PREFILL ? c->ws.grp_seq + pa.g0 : nullptr;
   for (int l = 0; l < m.desc.n_layers; ++l) {
-    if (m.fast) fast_layer(c, m, l, pa.B, pa.q, pa.b0, grp_seq, max_pos, st);
+    if (m.fast) fast_layer(c, m, l, pa.B, pa.q, pa.b0, grp_seq, pa.reuse, max_pos, st);
     else if (m.f32) fp32_layer(c, m, l, pa.B, pa.q, pa.b0, grp_seq, st);
     else generic_layer(c, m, l, M, pa.q, pa.b0, grp_seq, st);
     if (dump) generic_copy(c->ws.h, (char *)dump + (size_t)(l + 1) * hbytes, hbytes, st);
@@ -516,18 +516,22 @@ static int prefill(spec_ctx *c, int b0, int B) {
   const int per = (int)std::min<long long>(fit, ((rows + passes - 1) / passes + 255) / 256 * 256) / q;  // groups per pass
   launch_prefill_groups(c, b0, B, q, c->stream);
   const int groups = (int)(rows / q);
+  std::vector<int> ends;  // the last position of every group of the pass
   int b = 0, start = 0;  // the sequence the pass's first group belongs to, and that sequence's first group
   for (int g0 = 0; g0 < groups; g0 += per) {
     const int n = std::min(per, groups - g0);
     int max_pos = 0;  // the largest position of the pass
+    ends.clear();
     while (start < g0 + n) {
       const int own = (P[b] - 1 + q - 1) / q;
       max_pos = std::max(max_pos, std::min(P[b] - 2, (g0 + n - start) * q - 1));
+      for (int k = std::max(start, g0); k < std::min(start + own, g0 + n); ++k) ends.push_back(std::min(P[b] - 2, (k - start + 1) * q - 1));
       if (start + own > g0 + n) break;
       start += own;
       ++b;
     }
     PassArgs pa{PASS_PREFILL, n, q, 0, b0, g0};
+    pa.reuse = prefill_reuse(n, [&](int k) { return ends[k]; }, [&](int k) { return ends[k] < q; });
     int rc = forward_pass(c, c->tgt, pa, HEAD_NONE, nullptr, nullptr, 0, max_pos);
     if (!rc && c->drf.present) rc = forward_pass(c, c->drf, pa, HEAD_NONE, nullptr, nullptr, 0, max_pos);
     if (rc) return rc;

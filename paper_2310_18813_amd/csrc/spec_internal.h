@@ -190,6 +190,7 @@ struct PassArgs {
   int b0 = 0;    // first batch slot of the pass: its rows are the sequences b0 .. b0 + B - 1
   int g0 = 0;    // PASS_PREFILL: B counts groups of q rows at consecutive positions of one sequence, and the pass takes
                  // the groups g0 .. g0 + B - 1 of the table in the workspace (launch_prefill_groups)
+  double reuse = 0.0;  // PASS_PREFILL: prefill_reuse of its groups
   int fill = 0;  // > 0: the pass also fetches the round's first `fill` proposals from the caller's table
 };
 
@@ -237,7 +238,7 @@ int fail_noctx(int code, const char *fmt, ...);  // records the message spec_las
 bool fast_supported(const spec_model_desc &D, int dtype);
 size_t fast_packed_bytes(const spec_model_desc &D, int dtype, int L_max);
 bool fast_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);  // false: HIP error
-void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, int max_pos, hipStream_t st);
+void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, double reuse, int max_pos, hipStream_t st);
 void fast_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits_or_null, int q, int arg_stride,
                int32_t *arg_out, hipStream_t st);
 
