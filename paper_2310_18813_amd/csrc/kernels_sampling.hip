@@ -22,8 +22,8 @@
 // after the other through B; a row is read once for maximum and sum together, and once more (from L2) where a token is
 // drawn from it.  A thread with a contiguous chunk of its own (loads 512 bytes apart across a wave), a pass for each of
 // maximum and sum, and a sequence's places in turn took 87 us for 64 sequences x 4 places of 32000 logits with draft rows;
-// this takes 26 us (30 with a test for -inf
-// and for the end beside every exponential: what is left of a place is about equal parts loads and exponentials).  Larger rounds take places in turn (workgroups_per_sequence).
+// this takes 26 us (30 with a test for -inf and for the end beside every exponential: what is left of a place is about
+// equal parts loads and exponentials).  Larger rounds take places in turn (workgroups_per_sequence).
 #include "spec_internal.h"
 #include "device_utils.h"
 #include <algorithm>
@@ -77,8 +77,10 @@ __device__ __forceinline__ void load_steps(const float *__restrict__ z, int k, i
     for (int i = 0; i < U; ++i) load4z<VEC>(z, k + i * SMP_STEP + lane4, V, end, v[i]);
   }
 }
-// steps whose loads are in flight together (single loads need four addresses a step; a segment of a short row has few steps)
-template <int W, bool VEC> constexpr int SMP_UNROLL = !VEC ? 2 : W == 4 ? 4 : 8;
+// How a kernel loads its rows, LD: bit 0 for 16-byte loads, above it the steps whose loads are in flight together (single loads
+// need four addresses a step).  with_loads chooses.
+constexpr bool ld_vec(int LD) { return LD & 1; }
+constexpr int ld_steps(int LD) { return LD >> 1; }
 
 // Exclusive prefix over the waves of one value per wave, *total = the sum over the workgroup: added in wave order, the
 // same bits in every thread.  sh: W floats.
@@ -99,16 +101,16 @@ __device__ __forceinline__ float waves_prefix(float v, float *sh, float *total) 
 }
 
 // maximum of a row, the same in every thread
-template <int W, bool VEC>
+template <int W, int LD>
 __device__ __forceinline__ float row_max(const float *__restrict__ z, int V, float *sh) {
   const Seg g = my_seg<W>(V);
   const int lane4 = (threadIdx.x & 63) * 4;
-  constexpr int U = SMP_UNROLL<W, VEC>;
+  constexpr int U = ld_steps(LD);
   float lm = -INFINITY;
 #pragma unroll 1
   for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
     float v[U][4];
-    load_steps<VEC, U>(z, k, lane4, V, g.end, v);
+    load_steps<ld_vec(LD), U>(z, k, lane4, V, g.end, v);
 #pragma unroll
     for (int i = 0; i < U; ++i) lm = fmaxf(fmaxf(lm, v[i][0]), fmaxf(fmaxf(v[i][1], v[i][2]), v[i][3]));
   }
@@ -145,18 +147,18 @@ __device__ __forceinline__ void stats_step(const float (&v)[U][4], float inv_T, 
 // Maximum and sum of exp((z - max) * inv_T) of a target row and, PAIR, of a draft row, the same bits in every thread
 // (a row of -inf alone has no distribution: its sum is NaN).  sh: 4 * W floats.
 struct RowStats { float m, Z; };
-template <int W, bool VEC, bool PAIR>
+template <int W, int LD, bool PAIR>
 __device__ __forceinline__ void row_stats(const float *__restrict__ zp, const float *__restrict__ zq, int V, float inv_T,
                                           float *sh, RowStats &p, RowStats &q) {
   const Seg g = my_seg<W>(V);
   const int lane4 = (threadIdx.x & 63) * 4, wv = threadIdx.x >> 6;
-  constexpr int U = SMP_UNROLL<W, VEC>;
+  constexpr int U = ld_steps(LD);
   float mp = -INFINITY, Zp = 0.f, mq = -INFINITY, Zq = 0.f;
 #pragma unroll 1
   for (int k = g.k0; k < g.end; k += U * SMP_STEP) {
     float v[U][4], w[U][4];
-    load_steps<VEC, U>(zp, k, lane4, V, g.end, v);
-    if (PAIR) load_steps<VEC, U>(zq, k, lane4, V, g.end, w);
+    load_steps<ld_vec(LD), U>(zp, k, lane4, V, g.end, v);
+    if (PAIR) load_steps<ld_vec(LD), U>(zq, k, lane4, V, g.end, w);
     stats_step<U>(v, inv_T, mp, Zp);
     if (PAIR) stats_step<U>(w, inv_T, mq, Zq);
   }
@@ -183,8 +185,7 @@ __device__ __forceinline__ void row_stats(const float *__restrict__ zp, const fl
 }
 
 // Draw with u from the weights w4(k, lane4, end, out) -> weights of the lane's four tokens of W4::UNROLL steps from k on (zero
-// from `end` on):
-// every thread returns the same index.  *total_out: the sum of all weights.
+// from `end` on): every thread returns the same index.  *total_out: the sum of all weights.
 template <int W, class W4>
 __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int *sh_i, float *total_out = nullptr) {
   const Seg g = my_seg<W>(V);
@@ -261,13 +262,13 @@ __device__ __forceinline__ int block_draw(int V, W4 w4, float u, float *sh, int 
 }
 
 // weights exp((z - m) * inv_T) of a row, optionally with one token removed; -inf behind the end makes the zeros there
-template <int W, bool VEC>
+template <int W, int LD>
 struct ExpW {
-  static constexpr int UNROLL = SMP_UNROLL<W, VEC>;
+  static constexpr int UNROLL = ld_steps(LD);
   const float *z; int V; float m, inv_T; int drop;
   template <int U>
   __device__ __forceinline__ void operator()(int k, int lane4, int end, float (&w)[U][4]) const {
-    load_steps<VEC, U>(z, k, lane4, V, end, w);
+    load_steps<ld_vec(LD), U>(z, k, lane4, V, end, w);
 #pragma unroll
     for (int s = 0; s < U; ++s)
 #pragma unroll
@@ -282,10 +283,10 @@ struct ExpW {
   }
 };
 // residual weights max(0, p - q) of a target and a draft row
-template <int W, bool VEC>
+template <int W, int LD>
 struct ResidW {
-  static constexpr int UNROLL = SMP_UNROLL<W, VEC> / 2;  // two rows a step
-  ExpW<W, VEC> p, q; float ip, iq;
+  static constexpr int UNROLL = ld_steps(LD) > 1 ? ld_steps(LD) / 2 : 1;  // two rows a step
+  ExpW<W, LD> p, q; float ip, iq;
   template <int U>
   __device__ __forceinline__ void operator()(int k, int lane4, int end, float (&w)[U][4]) const {
     float b[U][4];
@@ -306,7 +307,7 @@ __device__ __forceinline__ float uniform_at(const float *__restrict__ u, const i
 }
 
 // One proposal per sequence: a draw from softmax(logits[b] / T).  out[b * out_stride].
-template <int W, bool VEC>
+template <int W, int LD>
 __global__ __launch_bounds__(W * 64) void k_sample_rows(const float *__restrict__ logits, int V, float inv_T,
                                                              const float *__restrict__ u, const int32_t *__restrict__ n,
                                                              int off, int u_rows, int32_t *__restrict__ out, int out_stride) {
@@ -314,53 +315,53 @@ __global__ __launch_bounds__(W * 64) void k_sample_rows(const float *__restrict_
   __shared__ int sh_i;
   const int b = blockIdx.x;
   const float *z = logits + (size_t)b * V;
-  const float m = row_max<W, VEC>(z, V, sh);  // a draw needs the maximum only: its own pass over the row adds the weights up
+  const float m = row_max<W, LD>(z, V, sh);  // a draw needs the maximum only: its own pass over the row adds the weights up
   const float uu = n ? uniform_at(u, n, b, off, u_rows, 0) : u[b];
-  const int tok = block_draw<W>(V, ExpW<W, VEC>{z, V, m, inv_T, -1}, uu, sh, &sh_i);
+  const int tok = block_draw<W>(V, ExpW<W, LD>{z, V, m, inv_T, -1}, uu, sh, &sh_i);
   if (threadIdx.x == 0) out[(size_t)b * out_stride] = tok;
 }
 
 // Place j of a round, decided as if the round reached it: t_{j+1} if the proposal is kept, -1 - (the drawn token) if it is
 // rejected; the same in every thread.  zq: the draft's row, null for a point-mass proposal.
-template <int W, bool VEC>
+template <int W, int LD>
 __device__ __forceinline__ int decide_place(const float *__restrict__ zp, const float *__restrict__ zq, int V, float inv_T,
                                             int tj, float ua, float us, float *sh, int *sh_i) {
   RowStats p, q;
   const bool valid = tj >= 0 && tj < V;
   int res;
   if (zq) {
-    row_stats<W, VEC, true>(zp, zq, V, inv_T, sh, p, q);
+    row_stats<W, LD, true>(zp, zq, V, inv_T, sh, p, q);
     const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
     const float qt = valid ? __expf((zq[tj] - q.m) * inv_T) * (1.0f / q.Z) : 1.f;
     if (ua * qt < pt) {
       res = tj;
     } else {
-      const ExpW<W, VEC> wp{zp, V, p.m, inv_T, -1};
+      const ExpW<W, LD> wp{zp, V, p.m, inv_T, -1};
       float total;
-      res = block_draw<W>(V, ResidW<W, VEC>{wp, ExpW<W, VEC>{zq, V, q.m, inv_T, -1}, 1.0f / p.Z, 1.0f / q.Z}, us, sh, sh_i, &total);
+      res = block_draw<W>(V, ResidW<W, LD>{wp, ExpW<W, LD>{zq, V, q.m, inv_T, -1}, 1.0f / p.Z, 1.0f / q.Z}, us, sh, sh_i, &total);
       // p = q everywhere leaves no residual (not reachable with u < 1 and a valid proposal): draw from p
       if (!(total > 0.f)) res = block_draw<W>(V, wp, us, sh, sh_i);
       res = -1 - res;
     }
   } else {
-    row_stats<W, VEC, false>(zp, nullptr, V, inv_T, sh, p, q);
+    row_stats<W, LD, false>(zp, nullptr, V, inv_T, sh, p, q);
     const float pt = valid ? __expf((zp[tj] - p.m) * inv_T) * (1.0f / p.Z) : 0.f;
     if (ua < pt) res = tj;
-    else res = -1 - block_draw<W>(V, ExpW<W, VEC>{zp, V, p.m, inv_T, valid ? tj : -1}, us, sh, sh_i);
+    else res = -1 - block_draw<W>(V, ExpW<W, LD>{zp, V, p.m, inv_T, valid ? tj : -1}, us, sh, sh_i);
   }
   return res;
 }
 // The bonus draw, for a round that keeps every proposal: needs the row's maximum only.
-template <int W, bool VEC>
+template <int W, int LD>
 __device__ __forceinline__ int bonus_draw(const float *__restrict__ zp, int V, float inv_T, float us, float *sh, int *sh_i) {
-  const float m = row_max<W, VEC>(zp, V, sh);
-  return block_draw<W>(V, ExpW<W, VEC>{zp, V, m, inv_T, -1}, us, sh, sh_i);
+  const float m = row_max<W, LD>(zp, V, sh);
+  return block_draw<W>(V, ExpW<W, LD>{zp, V, m, inv_T, -1}, us, sh, sh_i);
 }
 
 // Verification, a workgroup per (sequence, place j), places 0 .. s_b: a[b][j] = decide_place, or the bonus draw at place s_b.
 // k_sample_seal does the rest.
 //   tl: target logits, row b * (s + 1) + j;  dl: draft logits of step j + 1 at ((size_t)j * d_rows + b) * V, or null
-template <int W, bool VEC>
+template <int W, int LD>
 __global__ __launch_bounds__(W * 64) void k_sample_verify(const float *__restrict__ tl, const float *__restrict__ dl,
                                                           int d_rows, int b0, int s, int V, float inv_T,
                                                           const int32_t *__restrict__ t, int t_stride,
@@ -375,11 +376,11 @@ __global__ __launch_bounds__(W * 64) void k_sample_verify(const float *__restric
   const float *zp = tl + ((size_t)b * (s + 1) + j) * V;
   const float us = uniform_at(u, n, b, j, u_rows, 2);
   if (j == sb) {
-    const int tok = bonus_draw<W, VEC>(zp, V, inv_T, us, sh, &sh_i);
+    const int tok = bonus_draw<W, LD>(zp, V, inv_T, us, sh, &sh_i);
     if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = tok;
     return;
   }
-  const int res = decide_place<W, VEC>(zp, dl ? dl + ((size_t)j * d_rows + b) * V : nullptr, V, inv_T, t[(size_t)b * t_stride + j],
+  const int res = decide_place<W, LD>(zp, dl ? dl + ((size_t)j * d_rows + b) * V : nullptr, V, inv_T, t[(size_t)b * t_stride + j],
                                        uniform_at(u, n, b, j, u_rows, 1), us, sh, &sh_i);
   if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = res;
 }
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(W * 64) void k_sample_verify(const float *__restric
 // The same with `per` <= s workgroups to a sequence: workgroup i of them takes the places i, i + per, ... up to s_b in
 // turn and stops at the first it rejects.  Every place before the round's first rejection is then decided (a place is
 // left out only behind a rejection of its own workgroup); k_sample_seal ignores what lies behind.
-template <int W, bool VEC, bool DRAFT>
+template <int W, int LD, bool DRAFT>
 __global__ __launch_bounds__(W * 64) void k_sample_verify_turns(const float *__restrict__ tl, const float *__restrict__ dl,
                                                                 int d_rows, int b0, int per, int s, int V, float inv_T,
                                                                 const int32_t *__restrict__ t, int t_stride,
@@ -403,7 +404,7 @@ __global__ __launch_bounds__(W * 64) void k_sample_verify_turns(const float *__r
     const bool bonus = j == sb;
     const int tj = bonus ? 0 : t[(size_t)b * t_stride + j];
     const float ua = uniform_at(u, n, b, j, u_rows, 1), us = uniform_at(u, n, b, j, u_rows, 2);
-    const int res = bonus ? bonus_draw<W, VEC>(zp, V, inv_T, us, sh, &sh_i) : decide_place<W, VEC>(zp, zq, V, inv_T, tj, ua, us, sh, &sh_i);
+    const int res = bonus ? bonus_draw<W, LD>(zp, V, inv_T, us, sh, &sh_i) : decide_place<W, LD>(zp, zq, V, inv_T, tj, ua, us, sh, &sh_i);
     if (threadIdx.x == 0) a[(size_t)b * a_stride + j] = res;
     if (res < 0) break;
   }
@@ -448,13 +449,28 @@ static bool rows_vec(const float *z, int V) { return (V & 3) == 0 && ((uintptr_t
 // 6000 the same; 16 rows of 16000 14 / 10.
 static bool narrow_rows(int V) { return V <= 8192; }
 
+// f(waves per workgroup, LD) for rows of V logits.  Four steps in flight a wave of a narrow workgroup, eight of a wide one, but no more
+// than a wave's segment has: steps behind its end cost their exponentials (64 draws from 1000 logits 4.8 us with four, 4.1 with
+// one; from 2000 5.1, 4.5 with two; sums and draws stay the same bits).
+template <class F>
+static void with_loads(int V, bool vec, F f) {
+  auto go = [&](auto W, auto vec_ld, auto single_ld) { vec ? f(W, vec_ld) : f(W, single_ld); };
+  using std::integral_constant;
+  constexpr integral_constant<int, 4> four{};
+  if (!narrow_rows(V)) go(integral_constant<int, 16>{}, integral_constant<int, 8 * 2 + 1>{}, integral_constant<int, 2 * 2>{});
+  else if (V <= 4 * SMP_STEP) go(four, integral_constant<int, 1 * 2 + 1>{}, integral_constant<int, 1 * 2>{});
+  else if (V <= 8 * SMP_STEP) go(four, integral_constant<int, 2 * 2 + 1>{}, integral_constant<int, 2 * 2>{});
+  else go(four, integral_constant<int, 4 * 2 + 1>{}, integral_constant<int, 2 * 2>{});
+}
+
 void launch_sample_rows(const float *logits, int rows, int V, float temperature, const float *u, const int32_t *n, int off,
                         int u_rows, int32_t *out, int out_stride, hipStream_t st) {
   if (rows <= 0) return;
-  const bool vec = rows_vec(logits, V), narrow = narrow_rows(V);
-  auto k = narrow ? (vec ? k_sample_rows<4, true> : k_sample_rows<4, false>) : vec ? k_sample_rows<16, true> : k_sample_rows<16, false>;
-  hipLaunchKernelGGL(k, dim3(rows), dim3(narrow ? 256 : 1024), 0, st, logits, V, inverse_temperature(temperature), u, n, off, u_rows,
-                     out, out_stride);
+  with_loads(V, rows_vec(logits, V), [&](auto W_, auto LD_) {
+    constexpr int W = decltype(W_)::value, LD = decltype(LD_)::value;
+    hipLaunchKernelGGL((k_sample_rows<W, LD>), dim3(rows), dim3(W * 64), 0, st, logits, V, inverse_temperature(temperature), u, n, off, u_rows,
+                       out, out_stride);
+  });
 }
 // How many workgroups share the places of a sequence's round.  A workgroup per place reads rows behind the first rejection
 // for nothing, which is free only while the chip has room: `slots` is the workgroups it works on at a time (one of 16 waves
@@ -485,21 +501,15 @@ void launch_sample_verify(const float *tl, const float *dl, int d_rows, int B, i
   const int per_launch = (1 << 21) / per;  // a grid holds less than 2^32 threads
   for (int64_t b0 = 0; b0 < B; b0 += per_launch) {
     const int nb = (int)std::min<int64_t>(per_launch, B - b0);
-    auto launch = [&](auto W_, auto VEC_) {
-      constexpr int W = decltype(W_)::value;
-      constexpr bool VEC = decltype(VEC_)::value;
+    with_loads(V, vec, [&](auto W_, auto LD_) {
+      constexpr int W = decltype(W_)::value, LD = decltype(LD_)::value;
       if (per == s + 1)
-        hipLaunchKernelGGL((k_sample_verify<W, VEC>), dim3(nb * per), dim3(W * 64), 0, st, tl, dl, d_rows, (int)b0, s, V, inv_T,
+        hipLaunchKernelGGL((k_sample_verify<W, LD>), dim3(nb * per), dim3(W * 64), 0, st, tl, dl, d_rows, (int)b0, s, V, inv_T,
                            t, t_stride, seq_s, u, n, u_rows, a, a_stride);
       else
-        hipLaunchKernelGGL((dl ? k_sample_verify_turns<W, VEC, true> : k_sample_verify_turns<W, VEC, false>), dim3(nb * per), dim3(W * 64), 0,
+        hipLaunchKernelGGL((dl ? k_sample_verify_turns<W, LD, true> : k_sample_verify_turns<W, LD, false>), dim3(nb * per), dim3(W * 64), 0,
                            st, tl, dl, d_rows, (int)b0, per, s, V, inv_T, t, t_stride, seq_s, u, n, u_rows, a, a_stride);
-    };
-    using std::integral_constant;
-    if (narrow && vec) launch(integral_constant<int, 4>{}, std::true_type{});
-    else if (narrow) launch(integral_constant<int, 4>{}, std::false_type{});
-    else if (vec) launch(integral_constant<int, 16>{}, std::true_type{});
-    else launch(integral_constant<int, 16>{}, std::false_type{});
+    });
   }
   hipLaunchKernelGGL(k_sample_seal, dim3((B - 1) / 4 + 1), dim3(64), 0, st, B, s, seq_s, a, a_stride, t, accepted, emitted);
 }

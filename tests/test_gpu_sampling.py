@@ -5,12 +5,15 @@ The GPU decides in fp32, the oracle in fp64, and a decision is an integer: where
 number fell within MARGIN of a decision boundary, either outcome is legitimate and that row or sequence is left out
 of the comparison (and counted: the share must stay tiny).  Everything else must agree exactly.
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 import synth_inputs as si
 from helpers import build_pair, truth_table
+from launches import launched_kernels, template_ints
 from oracle import sampling as osm
 
 pytestmark = pytest.mark.gpu
@@ -89,7 +92,7 @@ def test_acceptance_rule_matches_the_oracle(B, V, s, point_mass):
         assert 0 < np.mean(ls) < s, "the inputs should exercise both keeping and rejecting"
 
 
-@pytest.mark.parametrize("V", [1, 5, 256, 260, 4095, 4100, 32772, 70001])
+@pytest.mark.parametrize("V", [1, 5, 256, 260, 1024, 1028, 2048, 2052, 4095, 4100, 32772, 70001])
 @pytest.mark.parametrize("offset", [0, 1])
 def test_draws_and_rule_at_the_edges_of_steps_segments_and_alignment(B, V, offset):
     """Vocabularies around a wave's step (256), a segment per wave (4096), a register tile (32768) and beyond, rows that
@@ -161,6 +164,18 @@ def test_very_large_and_infinite_temperatures_draw_uniformly(B, V, T):
     un[odd, 0, 1], un[odd, 0, 2] = 0.5, u[odd]
     _, acc, em = (x.cpu().numpy() for x in B.spec_sample_accept(dev(zz[odd]), dev(q[None]), dev(np.zeros((len(odd), 1), np.int32)), dev(un[odd]), T))
     assert acc.tolist() == [0] * len(odd) and em[:, 0].tolist() == want[odd].tolist()
+
+
+@pytest.mark.parametrize("V,steps", [(256, 1), (1024, 1), (1028, 2), (2048, 2), (2052, 4), (8192, 4), (8196, 8), (1003, 1), (2047, 2), (8191, 2)])
+def test_a_wave_loads_no_more_steps_than_its_segment_has(B, V, steps):
+    """Rows of up to 1024 logits are one step a wave: with four in flight a draw took 1.08 of the time of the loop before it."""
+    z, u, out = torch.zeros((3, V), device=DEV), torch.zeros(3, device=DEV), torch.zeros(3, dtype=torch.int32, device=DEV)
+    torch.cuda.synchronize()
+    stream, p = torch.cuda.Stream(), lambda x: C.c_void_p(x.data_ptr())
+    kernels = launched_kernels(B.lib, stream, lambda: B.lib.spec_sample_tokens(C.c_void_p(stream.cuda_stream), p(z), 3, V, C.c_float(1.0), p(u), p(out)))
+    (name, _, threads), = kernels
+    waves, loads = template_ints(name)[:2]
+    assert threads == 64 * waves == (256 if V <= 8192 else 1024) and loads >> 1 == steps and (loads & 1) == (V % 4 == 0), name
 
 
 def _on_device_round(nB, s, V, sigma, seed, T):
