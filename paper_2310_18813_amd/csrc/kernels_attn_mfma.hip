@@ -13,16 +13,18 @@
 // lane and tile) is already the B-operand layout of the second once the key rows fed to
 // the first product are permuted: tile t, row 4g'+i carries key ks + 8g' + 4t + i.
 //
-// Numerics depend on (sequence, absolute positions) only.  The cache is cut into chunks of
-// 256 positions starting at multiples of 256.  Each chunk yields a fresh partial (running
+// Numerics depend on (sequence, absolute positions) only.  The cache is cut into chunks at
+// fixed positions (attn_chunk_begin: 128 positions each up to 512, 256 beyond).  Each chunk yields a fresh partial (running
 // maximum, sum, un-normalised output) from an online softmax over ascending 32-key steps;
 // the partials are merged pairwise in ascending chunk order.  Masked keys contribute exact
 // zeros and leave the running maximum unchanged, and merging an all-masked partial is an
 // exact no-op, so neither the other rows of a pass nor the launch shape change a row's
-// bits.  The launch shapes compute exactly that: one wave per (sequence, head, chunk) with
-// the partials merged by a second kernel (few sequences: parallelism over chunks), or one
-// wave per (sequence, head) walking its chunks and merging in registers (many sequences:
-// no partial traffic).
+// bits.  Four launch shapes compute exactly that: (1) one wave per (sequence, head, chunk) with
+// the partials merged by a second kernel (few sequences and many chunks); (2) one wave per
+// (sequence, head) walking its chunks and merging in registers (many sequences: no partial
+// traffic); (3) one workgroup per (sequence, head) with a wave per chunk, merged in LDS (few
+// sequences); (4) for prefills, four row groups to a workgroup that share their sequence's
+// cache rows through LDS.  launch_attn_hd chooses.
 #include "spec_internal.h"
 #include "device_utils.h"
 #include "mfma_gemm.h"
@@ -76,7 +78,7 @@ __device__ __forceinline__ float exp_diff(float a, float b, float sl2) {
   return __builtin_amdgcn_exp2f((a - b) * sl2);
 }
 
-// (m, l, acc) <- (m, l, acc) (+) (mc, lc, accc): the one merge rule, used by both launch shapes.
+// (m, l, acc) <- (m, l, acc) (+) (mc, lc, accc): the one merge rule, used by every launch shape.
 __device__ __forceinline__ void merge_weights(float m, float mc, float scale, float &m_new, float &wa, float &wb) {
   m_new = fmaxf(m, mc);
   wa = exp_diff(m, m_new, scale);
@@ -422,9 +424,8 @@ __global__ __launch_bounds__(512) void k_attn_group(AttnArgs a) {
 // Launch shape 4, prefills: a workgroup takes four row groups of one head, a wave each, and the waves read the cache rows of
 // the groups' sequence (mostly one: its groups follow each other) through LDS, every step once for all of them.  One wave
 // per (group, head) asks for 16 KB of cache rows per 16 query rows and 32 keys, and what a CU keeps in flight on that way
-// bounds a long prompt (5 prompts of up to
-// 2011 tokens x 52 heads of 128: 1.42 ms a layer, the whole prefill 23.1 -> 21.7 ms with this).  The steps and merges of a wave are those of the other shapes; steps beyond its own
-// last position it sits out.
+// bounds a long prompt (5 prompts of up to 2011 tokens x 52 heads of 128: 1.42 ms a layer, the whole prefill 23.1 -> 21.7 ms
+// with this).  The steps and merges of a wave are those of the other shapes; steps beyond its own last position it sits out.
 constexpr int PREFILL_RING = 4;
 constexpr size_t attn_prefill_lds(int HD) { return (size_t)PREFILL_RING * (HD / 8) * 1024 + 2 * PREFILL_WAVES * sizeof(int); }
 

@@ -491,7 +491,9 @@ static double choose_stream_head(const GemmArgs &a, int &MT, int &NB) {
 // at 128, 256 and 512 rows 17 / 22 / -, 25 / 23 / - and - / 33 / 50; LM heads of 32000 x 768, 2048 and 4096 at 48 rows
 // 32 / 18 / -, 44 / 33 / - and 64 / 56 / -, 8192 x 4096 at 48 and 96 rows 23 / 27 / - and 36 / 28 / -; gate-up 8192 x 1024 at
 // 96 and 256 rows 17 / 13 / - and 27 / 17 / -; 4096 x 11008 at 64, 256 and 1024 rows - / 52 / 27, - / 52 / 43 and
-// - / 105 / 142.  Over 540 launches (33 to 512 rows) the choice takes 0.5 % more than the best of the three.
+// - / 105 / 142.  Over 540 launches (33 to 512 rows) the choice took 0.5 % more than the best of the three, by the tiled kernel's
+// estimate as it was before its later terms (tile_us).  The estimate is that of one tiled launch: where rows_of_first_launch
+// makes two of it, they are faster than what is compared here.
 enum GemmRoute { ROUTE_STREAM, ROUTE_TILE, ROUTE_SPLIT, ROUTE_STRIPS };
 static GemmRoute route(const GemmArgs &a, int epi) {
   if (epi == EPI_LOGITS && gemm_takes_strips(a)) return ROUTE_STRIPS;
