@@ -502,9 +502,9 @@ static GemmRoute route(const GemmArgs &a, int epi) {
   const bool split_ok = epi == EPI_RESIDUAL && a.part && a.KS > 1 && (a.KT / a.KS >= 32 || (a.M > 256 && a.KT / a.KS >= 2));
   if (a.tune & 0xff) return split_ok ? ROUTE_SPLIT : ROUTE_TILE;  // a pinned wave tile (test / tuning aid)
   int MT, NB;
-  const double stream = epi == EPI_LOGITS ? choose_stream_head(a, MT, NB) : choose_stream(a, MT, NB), tile = gemm_tile_us(a, false);
+  const double stream = epi == EPI_LOGITS ? choose_stream_head(a, MT, NB) : choose_stream(a, MT, NB), tile = gemm_tile_us(a, epi, false);
   // (the split launch's estimate is about 15 % high at up to 256 rows, where one row pass reads the weights)
-  if (split_ok && (a.M <= 256 ? 0.85 : 1.0) * gemm_tile_us(a, true) < std::min(stream, tile)) return ROUTE_SPLIT;
+  if (split_ok && (a.M <= 256 ? 0.85 : 1.0) * gemm_tile_us(a, epi, true) < std::min(stream, tile)) return ROUTE_SPLIT;
   return tile < stream ? ROUTE_TILE : ROUTE_STREAM;
 }
 bool gemm_can_leave_ssq(const GemmArgs &a) {  // the row-wise reduction keeps the fp16 row in LDS: rows of up to 8192

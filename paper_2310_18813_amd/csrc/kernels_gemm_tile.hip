@@ -614,12 +614,13 @@ static GemmArgs rows_from(GemmArgs a, int m0) {
   return a;
 }
 
-// For the choice between the kernels: with the share of the row sums only for k beyond 2048.  (Streaming / tiled, us: 12288 x 4096 at
-// 40 rows 24 / 27, but 6144 x 2048 at 80 rows 18 / 15, 2048 x 512 at 192 rows 10 / 7: over a short k the share outweighs what it
-// costs, and the streaming kernel's estimate has none.)
-double gemm_tile_us(GemmArgs a, bool split) {
+// For the choice between the kernels: without the share of the row sums, which the streaming kernel's estimate has none of, but for
+// QKV products over k beyond 3072, where it stands for the scattered stores behind a long k.  Streaming / tiled, us: QKV 12288 x 4096
+// at 40 and 64 rows 28 / 30 and 30 / 33, but 9216 x 3072 at 64 27 / 25, 6144 x 2048 at 80 18 / 15; others 10240 x 2560 at 40 and 64
+// rows 21 / 20 and 24 / 21, 12288 x 3072 at 64 27 / 24, 10240 x 5120 at 40 and 64 32 / 33 and 36 / 34, 2048 x 512 at 192 10 / 7.
+double gemm_tile_us(GemmArgs a, int epi, bool split) {
   int MTW, NBW;
-  if (a.KT <= 64) a.fold_x = 0;
+  if (epi != EPI_QKV || a.KT <= 96) a.fold_x = 0;
   return tile_for(a, split, MTW, NBW);
 }
 

@@ -97,7 +97,7 @@ void launch_rope_table(int L, int hd, float theta, float2 *tab, hipStream_t st);
 void launch_gemm_mfma(int dtype, const GemmArgs &a, int epi, hipStream_t st);
 // more than 32 rows; split (EPI_RESIDUAL with a.part): one k-slice per workgroup, added up by a second kernel
 void launch_gemm_tile(int dtype, GemmArgs a, int epi, bool split, hipStream_t st);
-double gemm_tile_us(GemmArgs a, bool split);  // its estimated time
+double gemm_tile_us(GemmArgs a, int epi, bool split);  // its estimated time
 // EPI_LOGITS: arg-max partials per row the launch for these arguments leaves
 int gemm_head_partials(const GemmArgs &a);
 int gemm_tile_head_partials(const GemmArgs &a);
