@@ -31,6 +31,22 @@ static FastDims fast_dims(const spec_model_desc &D) {
   return f;
 }
 
+// Whether a pass finds weights of the one before in the memory-side cache.  It holds 256 MB, and of half as much again there is still
+// a part.  Rounds against loads that were plain throughout, plain / non-temporal: 211 MB (two layers of d_model 1536) 0.99 / 1.03 at
+// 65 to 128 rows; 314 MB (two of 2560 x 10240) 152 / 160 us at 42 rows; 337 MB (two of 2048) 1.00 / 1.02 at 33 to 64; 374 MB (two of
+// 2560 x 5120) 192 / 200 us at 72 rows; 484 MB (two of 2560 x 7040) and more are faster non-temporally, and so is a draft of 99 MB
+// beside a target of 13 GB, whose passes come in between (64 sequences, three draft steps a round: 7285 / 7250 us).
+bool fast_weights_kept(const spec_model_desc &tgt, const spec_model_desc *drf, int dtype) {
+  size_t bytes = 0;
+  for (const spec_model_desc *D : {&tgt, drf}) {
+    if (!D) continue;
+    const FastDims f = fast_dims(*D);
+    const size_t e = dtype_bytes(dtype);
+    bytes += (f.qkv.bytes(e) + f.o.bytes(e) + f.w13.bytes(e) + f.w2.bytes(e)) * (size_t)D->n_layers + f.head.bytes(e);
+  }
+  return bytes <= (size_t)384 << 20;
+}
+
 size_t fast_packed_bytes(const spec_model_desc &D, int dtype, int L_max) {
   const size_t e = dtype_bytes(dtype), d = D.d_model;
   FastDims f = fast_dims(D);
@@ -192,7 +208,7 @@ bool fast_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&curso
 
 static GemmArgs base_args(const spec_ctx *c, const PackedDims &p, const void *W, float inv_scale, const void *bias, const void *X, int M) {
   GemmArgs a{};
-  a.n_cu = c->n_cu; a.tune = c->gemm_tune; a.sat = c->st.sat;
+  a.n_cu = c->n_cu; a.tune = c->gemm_tune; a.sat = c->st.sat; a.w_kept = c->w_kept;
   a.W = W; a.bias = (const float *)bias; a.X = X; a.out_scale = inv_scale;
   a.M = M; a.N = p.N; a.NT = p.NT; a.KT = p.KT; a.KS = p.KS; a.K_pad = p.K_pad;
   return a;

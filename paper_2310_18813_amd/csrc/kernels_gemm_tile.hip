@@ -85,13 +85,18 @@ __device__ __forceinline__ void pin_step() {
 }
 
 // NORM: what is folded in front (0 nothing, 1 RMS norm, 2 LayerNorm).  T: the cache's type (EPI_QKV only).
-// ONCE: a single row pass, so that no other workgroup reads a weight: they are loaded non-temporally.  (With several row passes
-// that takes them out of the L2 for the next workgroup: loads alone, 22016 x 4096 at 6592 rows 632 -> 711 us.)
-template <class T, int MTW, int NBW, int EPI, int NORM, bool ONCE>
+// LOADS: LOADS_PASSES several row passes; else a single one, so that no other workgroup reads a weight: LOADS_NT loads them
+// non-temporally.  (With several row passes that takes them out of the L2 for the next workgroup: loads alone, 22016 x 4096 at 6592
+// rows 632 -> 711 us.)  LOADS_KEPT does not: weights that fit the memory-side cache are there from the last pass (two layers
+// of d_model 1536 with an LM head of 32000, 211 MB: the head at 72 rows 22.9 us, non-temporally 24.7; 14 layers of it 25.7 and
+// 24.3).  fast_weights_kept says which.
+enum TileLoads { LOADS_PASSES, LOADS_NT, LOADS_KEPT };
+template <class T, int MTW, int NBW, int EPI, int NORM, int LOADS>
 __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using S = TileShape<MTW, NBW>;
   constexpr int NBG = S::NBG, MTG = S::MTG, FRAGS = S::FRAGS, SLOT = S::SLOT, RING = S::RING;
+  constexpr bool ONCE = LOADS != LOADS_PASSES, NT = LOADS == LOADS_NT;
   // Fragments a wave fetches per step, between its multiplies.  ONCE: LW strips and LX row tiles, and of the W_REST strips and
   // X_REST tiles left over the first and the last waves one each.  Else strips and tiles in one row, w, w + 8, ..., and in the
   // last place the waves without a fragment issue a load without lanes, so that all waves count alike.  Such a load takes a
@@ -166,13 +171,13 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(GemmArgs a) {
   const int last_mask = sign_mask(w - (FRAGS - 8 * (LPW - 1)));  // !ONCE: the waves with an LPW-th fragment
   // this wave's fragments at byte k of their rows into the slot at `lds`
   auto fetch1 = [&](int i, size_t k, unsigned lds) {
-    if (ONCE && i < LW) load_frag_to_lds<true>(src[i] + k, lane_off, lds + (w + 8 * i) * 1024);
+    if (ONCE && i < LW) load_frag_to_lds<NT>(src[i] + k, lane_off, lds + (w + 8 * i) * 1024);
     else if (ONCE) load_frag_to_lds<false>(src[i] + k, lane_off, lds + (NBG + w + 8 * (i - LW)) * 1024);
     else if (i < LPW - 1 || FRAGS % 8 == 0) load_frag_to_lds<false>(src[i] + k, lane_off, lds + (w + 8 * i) * 1024);
     else load_frag_to_lds_masked(src[i] + k, lane_off, lds + (w + 8 * i) * 1024, last_mask);
   };
   auto fetch_rest = [&](size_t k, unsigned lds) {
-    if (w_rest) load_frag_to_lds<true>(src[LPW] + k, lane_off, lds + (8 * LW + w) * 1024);
+    if (w_rest) load_frag_to_lds<NT>(src[LPW] + k, lane_off, lds + (8 * LW + w) * 1024);
     if (x_rest) load_frag_to_lds<false>(src[LPW + 1] + k, lane_off, lds + (NBG + 8 * LX + w - (8 - X_REST)) * 1024);
   };
   // step kt of this wave's fragments into ring position `at`; beyond the end the last step is fetched again: nobody
@@ -471,12 +476,15 @@ template <class T, int MTW, int NBW, int EPI, int NORM>
 static void launch_one(const GemmArgs &a, int blocks, hipStream_t st) {
   constexpr size_t lds = TileShape<MTW, NBW>::LDS;
   if (blocks < 0) {
-    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  } else if (a.passes == 1) {
-    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM, true>), dim3(blocks), dim3(512), lds, st, a);
+    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM, LOADS_PASSES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM, LOADS_NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute((const void *)k_gemm_tile<T, MTW, NBW, EPI, NORM, LOADS_KEPT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  } else if (a.passes > 1) {
+    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM, LOADS_PASSES>), dim3(blocks), dim3(512), lds, st, a);
+  } else if (a.w_kept) {
+    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM, LOADS_KEPT>), dim3(blocks), dim3(512), lds, st, a);
   } else {
-    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM, false>), dim3(blocks), dim3(512), lds, st, a);
+    hipLaunchKernelGGL((k_gemm_tile<T, MTW, NBW, EPI, NORM, LOADS_NT>), dim3(blocks), dim3(512), lds, st, a);
   }
 }
 

@@ -39,7 +39,8 @@ struct GemmArgs {
   // activations are the fp16-rounded rows of h themselves, written by the producer of h; the consumer's
   // epilogue multiplies by 1 / rms of the row, which it takes from the operand fragments it reads anyway.
   int fold_x;                // consumer: norm folded in (row length ss_d, epsilon ss_eps)
-  int stats_left;            // consumer: the producer of the rows has left their statistics in rinv_ws (and mean_ws)
+  short stats_left;          // consumer: the producer of the rows has left their statistics in rinv_ws (and mean_ws)
+  short w_kept;              // fast_weights_kept: the tiled kernel's LOADS_KEPT
   int ss_d;
   float ss_eps;
   int ssq_ks;                // producer (below): the k-slices of the GEMM that will consume x_out, gemm_ks_for(N / 32); else 0

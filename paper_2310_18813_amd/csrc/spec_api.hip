@@ -258,6 +258,7 @@ extern "C" int spec_init(const spec_model_desc *tgt, const spec_weights *tgt_w, 
     attention_prepare();
     fp32_prepare();
   }
+  c->w_kept = fast_weights_kept(*tgt, drf, run->dtype);
   Sizes z = compute_sizes(tgt, drf, run);
   c->M_max = z.M_max;
   c->M_pf = z.M_pf;

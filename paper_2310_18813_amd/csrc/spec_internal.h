@@ -144,6 +144,7 @@ struct spec_ctx {
   int attn_shape = 0;
   int gemm_tune = 0;      // GemmTune bits (spec_set_gemm_tuning)
   int n_cu = 256;         // compute units of the context's device
+  bool w_kept = false;    // fast_weights_kept of the models
   std::vector<int32_t> lut_B, lut_s;
   std::string err;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -236,6 +237,7 @@ int fail_noctx(int code, const char *fmt, ...);  // records the message spec_las
 
 // matrix-core path (16-bit dtypes)
 bool fast_supported(const spec_model_desc &D, int dtype);
+bool fast_weights_kept(const spec_model_desc &tgt, const spec_model_desc *drf, int dtype);  // drf: null without a draft
 size_t fast_packed_bytes(const spec_model_desc &D, int dtype, int L_max);
 bool fast_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);  // false: HIP error
 void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, double reuse, int max_pos, hipStream_t st);
