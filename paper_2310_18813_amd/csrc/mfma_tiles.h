@@ -86,6 +86,34 @@ __device__ __forceinline__ void to_op_group(const float (&x)[N], op_t (&o)[N], u
   }
 }
 
+// The same for the MT row tiles of a strip (rows that do not exist are left out), one test for all of them, the same for the
+// wave: the clamping and counting then stay off the path that the others take (tile by tile the branches were most of an epilogue:
+// with this, the products' own code per kind of model and the rows of h ahead, a prefill of 64 prompts at the 7B width 11.24 -> 11.03 ms).
+template <int MT, int N>
+__device__ __forceinline__ void to_op_strip(const float (&x)[MT][N], const bool (&live)[MT], op_t (&o)[MT][N], unsigned int *sat) {
+  float big = 0.f;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    float b = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) b = fmaxf(b, fabsf(x[mt][i]));
+    big = fmaxf(big, live[mt] ? b : 0.f);
+  }
+  if (__builtin_expect(__any(big > 65504.f), 0)) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (live[mt]) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) o[mt][i] = to_op_counted(x[mt][i], sat);
+      }
+  } else {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int i = 0; i < N; ++i) o[mt][i] = (op_t)x[mt][i];
+  }
+}
+
 // h[m][n..n+3] += v (scaled, biased): the residual update of one lane's four outputs; o4 = the updated values
 // rounded to the next GEMM's operand type (also written to x_out in fragment order when that is set).
 __device__ __forceinline__ void residual_update(const GemmArgs &a, f32x4_v v, int n, int m, op_t (&o4)[4]) {
@@ -135,7 +163,12 @@ __device__ __forceinline__ void row_argmax_out(const GemmArgs &a, float bv, int 
   }
 }
 
-__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.0f + __expf(-gate)) * up; }
+// gate / (1 + exp(-gate)) * up.  The quotient from the reciprocal and one correction by its exact remainder instead of the
+// compiler's division, which scales its operands against overflow first (the divisor is at least 1): five instructions for ten.
+__device__ __forceinline__ float swiglu(float gate, float up) {
+  const float den = 1.0f + __expf(-gate), r = __builtin_amdgcn_rcpf(den), q = gate * r;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-den, q, gate), r, q), den, gate) * up;  // (the fix-up: infinities and NaN)
+}
 
 // The sequence (row group) m / q_rows of row m without an integer division: a float product, made exact by one step
 // either way.
@@ -269,14 +302,22 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
   for (int mt = 0; mt < MTW; ++mt) live[mt] = (mtile0 + mt) * 16 + c < a.M;
   const bool lnx = a.wsum != nullptr;
   // (acc - mean * wsum) * scale * rinv + bias of the four outputs of a tile
-  auto finish = [&](f32x4_v v, int mt, const float4 &b4, const float4 &w4) {
+  auto finish = [&](f32x4_v v, int mt, const float4 &b4, const float4 &w4, auto lnx, auto bias) {
     if (EPI != EPI_RESIDUAL && lnx) {
       v[0] -= mean[mt] * w4.x; v[1] -= mean[mt] * w4.y; v[2] -= mean[mt] * w4.z; v[3] -= mean[mt] * w4.w;
     }
     v[0] *= a.out_scale; v[1] *= a.out_scale; v[2] *= a.out_scale; v[3] *= a.out_scale;  // exact: a power of two
     if (EPI != EPI_RESIDUAL) { v[0] *= rinv[mt]; v[1] *= rinv[mt]; v[2] *= rinv[mt]; v[3] *= rinv[mt]; }
-    if (a.bias) { v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w; }
+    if (bias) { v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w; }
     return v;
+  };
+  // What a model has is the same for the launch: the usual combinations get code of their own (tile by tile the tests, or the
+  // additions behind a select, are as many instructions as the rest of `finish`).
+  auto with_kind = [&](auto body) {
+    if (!a.bias && (EPI == EPI_RESIDUAL || !lnx)) body(std::false_type{}, std::false_type{});
+    else if (EPI == EPI_RESIDUAL) body(std::false_type{}, std::true_type{});
+    else if (a.bias && lnx) body(std::true_type{}, std::true_type{});
+    else body(lnx, a.bias != nullptr);
   };
   float4 b4[NBW], w4[NBW];
 #pragma unroll
@@ -294,7 +335,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
       int bi = 0x7fffffff;
 #pragma unroll
       for (int nb = 0; nb < NBW; ++nb) {
-        const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
+        const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], lnx, a.bias != nullptr);
         const int n = (nt0 + nb) * 16 + 4 * g;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -311,57 +352,69 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
     for (int mt = 0; mt < MTW; ++mt)
       row[mt] = (unsigned char *)a.act + (size_t)(mtile0 + mt) * tile_bytes + c * 16 +
                 (EPI == EPI_SWIGLU ? g * 4 : (g >> 1) * 256 + (g & 1) * 8);
+    with_kind([&](auto ln, auto bias) {
 #pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      if (nt0 + nb >= a.NT) break;
+      for (int nb = 0; nb < NBW; ++nb) {
+        if (nt0 + nb >= a.NT) break;
+        constexpr int N = EPI == EPI_SWIGLU ? 2 : 4;
+        float r[MTW][N];
+        op_t o[MTW][N];
 #pragma unroll
-      for (int mt = 0; mt < MTW; ++mt) {
-        const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
-        if (EPI == EPI_SWIGLU) {
-          const float r2[2] = {swiglu(v[0], v[1]), swiglu(v[2], v[3])};
-          op_t o2[2];
-          if (live[mt]) {
-            to_op_group(r2, o2, a.sat);
-            *(uint32_t *)(row[mt] + (size_t)(nt0 + nb) * 256) = *(const uint32_t *)o2;
-          }
-        } else {
-          float r4[4];
-          op_t o4[4];
+        for (int mt = 0; mt < MTW; ++mt) {
+          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], ln, bias);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) r4[i] = v[i] > 0.f ? v[i] : 0.f;
-          if (live[mt]) {
-            to_op_group(r4, o4, a.sat);
-            *(uint2 *)(row[mt] + (size_t)(nt0 + nb) * 512) = *(const uint2 *)o4;
+          for (int i = 0; i < N; ++i) {
+            if constexpr (EPI == EPI_SWIGLU) r[mt][i] = swiglu(v[2 * i], v[2 * i + 1]);
+            else r[mt][i] = v[i] > 0.f ? v[i] : 0.f;
           }
         }
+        to_op_strip(r, live, o, a.sat);
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt)
+          if (live[mt]) {
+            if constexpr (EPI == EPI_SWIGLU) *(uint32_t *)(row[mt] + (size_t)(nt0 + nb) * 256) = *(const uint32_t *)o[mt];
+            else *(uint2 *)(row[mt] + (size_t)(nt0 + nb) * 512) = *(const uint2 *)o[mt];
+          }
       }
-    }
+    });
   } else if (EPI == EPI_RESIDUAL) {
-    float4 o[MTW];
+    // DEPTH strips' rows of h in flight: one strip at a time is a memory latency per strip (256 x 192 outputs took 16 us, beside 78 for the
+    // steps of a k of 4096; 4096 x 4096 at 6592 rows 299 -> 290 us)
+    constexpr int DEPTH = NBW < 3 ? NBW : 3;
+    float4 o[DEPTH][MTW];
+    // a row tile's place is the same for the wave, a lane's in it the same for all row tiles: few registers for addresses
+    const unsigned h_lane = (unsigned)(c * a.N + 4 * g) * 4, x_lane = c * 16 + (g >> 1) * 256 + (g & 1) * 8;
+    auto h_at = [&](int nb, int mt) { return (float4 *)((unsigned char *)a.h + ((size_t)(mtile0 + mt) * 16 * a.N + (size_t)(nt0 + nb) * 16) * 4 + h_lane); };
     auto load_h = [&](int nb) {
 #pragma unroll
       for (int mt = 0; mt < MTW; ++mt)
-        if (live[mt]) o[mt] = *(const float4 *)(a.h + (size_t)((mtile0 + mt) * 16 + c) * a.N + (nt0 + nb) * 16 + 4 * g);
+        if (live[mt] && nt0 + nb < a.NT) o[nb % DEPTH][mt] = *h_at(nb, mt);
     };
 #pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      if (nt0 + nb >= a.NT) break;
-      load_h(nb);
+    for (int nb = 0; nb < DEPTH; ++nb) load_h(nb);
+    with_kind([&](auto ln, auto bias) {
 #pragma unroll
-      for (int mt = 0; mt < MTW; ++mt) {
-        const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
-        const float x4[4] = {o[mt].x + v[0], o[mt].y + v[1], o[mt].z + v[2], o[mt].w + v[3]};
-        op_t o4[4];
-        if (live[mt]) {
-          *(float4 *)(a.h + (size_t)((mtile0 + mt) * 16 + c) * a.N + (nt0 + nb) * 16 + 4 * g) = make_float4(x4[0], x4[1], x4[2], x4[3]);
-          if (a.x_out) {
-            to_op_group(x4, o4, a.sat);
-            *(uint2 *)((unsigned char *)a.x_out + (size_t)(mtile0 + mt) * a.N * 32 + (size_t)(nt0 + nb) * 512 + c * 16 +
-                       (g >> 1) * 256 + (g & 1) * 8) = *(const uint2 *)o4;
-          }
+      for (int nb = 0; nb < NBW; ++nb) {
+        if (nt0 + nb >= a.NT) break;
+        float x4[MTW][4];
+        op_t o4[MTW][4];
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt) {
+          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], ln, bias);
+          const float4 h4 = o[nb % DEPTH][mt];
+          x4[mt][0] = h4.x + v[0]; x4[mt][1] = h4.y + v[1]; x4[mt][2] = h4.z + v[2]; x4[mt][3] = h4.w + v[3];
+          if (live[mt]) *h_at(nb, mt) = make_float4(x4[mt][0], x4[mt][1], x4[mt][2], x4[mt][3]);
+        }
+        if (nb + DEPTH < NBW) load_h(nb + DEPTH);
+        if (a.x_out) {
+          to_op_strip(x4, live, o4, a.sat);
+#pragma unroll
+          for (int mt = 0; mt < MTW; ++mt)
+            if (live[mt])
+              *(uint2 *)((unsigned char *)a.x_out + ((size_t)(mtile0 + mt) * a.N * 32 + (size_t)(nt0 + nb) * 512) + x_lane) = *(const uint2 *)o4[mt];
         }
       }
-    }
+    });
   } else {  // EPI_QKV
     // A strip of 16 stored rows lies inside one head of one of q, k, v: its place is scalar arithmetic.  What depends on
     // the row (cache rows of its sequence and position) is worked out once per row tile.
@@ -392,49 +445,51 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
       for (int mt = 0; mt < MTW; ++mt) cs[nb & 1][mt] = *(const float4 *)(tab + (size_t)max(pos[mt], 0) * half);
     };
     if (a.rope && region < 2) load_cs(0, cc0);
+    with_kind([&](auto ln, auto bias) {
 #pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      if (nt0 + nb >= a.NT) break;
-      const int next_cc0 = cc0 + 16 == a.d ? 0 : cc0 + 16, next_region = cc0 + 16 == a.d ? region + 1 : region;
-      if (nb + 1 < NBW && a.rope && next_region < 2) load_cs(nb + 1, next_cc0);
-      const int hh = cc0 >> hd_shift, e = (cc0 & (a.hd - 1)) + 4 * g;
-      const size_t head = (size_t)hh * a.L_pad * a.hd;
-      if (region < 2) {
+      for (int nb = 0; nb < NBW; ++nb) {
+        if (nt0 + nb >= a.NT) break;
+        const int next_cc0 = cc0 + 16 == a.d ? 0 : cc0 + 16, next_region = cc0 + 16 == a.d ? region + 1 : region;
+        if (nb + 1 < NBW && a.rope && next_region < 2) load_cs(nb + 1, next_cc0);
+        const int hh = cc0 >> hd_shift, e = (cc0 & (a.hd - 1)) + 4 * g;
+        const size_t head = (size_t)hh * a.L_pad * a.hd;
+        if (region < 2) {
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
-          float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
-          if (a.rope && pos[mt] >= 0) {
-            const float4 t = cs[nb & 1][mt];
-            r0 = v[0] * t.x - v[1] * t.y; r1 = v[1] * t.x + v[0] * t.y;
-            r2 = v[2] * t.z - v[3] * t.w; r3 = v[3] * t.z + v[2] * t.w;
+          for (int mt = 0; mt < MTW; ++mt) {
+            const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], ln, bias);
+            float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
+            if (a.rope && pos[mt] >= 0) {
+              const float4 t = cs[nb & 1][mt];
+              r0 = v[0] * t.x - v[1] * t.y; r1 = v[1] * t.x + v[0] * t.y;
+              r2 = v[2] * t.z - v[3] * t.w; r3 = v[3] * t.z + v[2] * t.w;
+            }
+            if (region == 0) {  // queries stay fp32 (see tile_epilogue)
+              if (live[mt]) *(float4 *)((float *)a.q + (size_t)((mtile0 + mt) * 16 + c) * a.d + cc0 + 4 * g) = make_float4(r0, r1, r2, r3);
+            } else {
+              T o4[4];
+              Conv<T>::st(o4, 0, r0); Conv<T>::st(o4, 1, r1); Conv<T>::st(o4, 2, r2); Conv<T>::st(o4, 3, r3);
+              if (pos[mt] >= 0) *(uint2 *)(krow[mt] + head + e) = *(const uint2 *)o4;
+            }
           }
-          if (region == 0) {  // queries stay fp32 (see tile_epilogue)
-            if (live[mt]) *(float4 *)((float *)a.q + (size_t)((mtile0 + mt) * 16 + c) * a.d + cc0 + 4 * g) = make_float4(r0, r1, r2, r3);
-          } else {
+        } else {
+#pragma unroll
+          for (int mt = 0; mt < MTW; ++mt) {
+            const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], ln, bias);
             T o4[4];
-            Conv<T>::st(o4, 0, r0); Conv<T>::st(o4, 1, r1); Conv<T>::st(o4, 2, r2); Conv<T>::st(o4, 3, r3);
-            if (pos[mt] >= 0) *(uint2 *)(krow[mt] + head + e) = *(const uint2 *)o4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Conv<T>::st(o4, i, v[i]);
+            if (quads[mt]) {  // four rows of one element per lane: their positions are neighbours in the cache
+              const uint2 o = quad_transpose(*(const uint2 *)o4, lane);
+              *(uint2 *)(vrow[mt] - (lane & 3) + head + (size_t)(e + (lane & 3)) * KV_VBLOCK) = o;
+            } else if (pos[mt] >= 0) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) vrow[mt][head + (size_t)(e + i) * KV_VBLOCK] = o4[i];
+            }
           }
         }
-      } else {
-#pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb]);
-          T o4[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) Conv<T>::st(o4, i, v[i]);
-          if (quads[mt]) {  // four rows of one element per lane: their positions are neighbours in the cache
-            const uint2 o = quad_transpose(*(const uint2 *)o4, lane);
-            *(uint2 *)(vrow[mt] - (lane & 3) + head + (size_t)(e + (lane & 3)) * KV_VBLOCK) = o;
-          } else if (pos[mt] >= 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) vrow[mt][head + (size_t)(e + i) * KV_VBLOCK] = o4[i];
-          }
-        }
+        region = next_region; cc0 = next_cc0;
       }
-      region = next_region; cc0 = next_cc0;
-    }
+    });
   }
 }
 
