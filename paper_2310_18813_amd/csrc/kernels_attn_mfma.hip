@@ -2,7 +2,7 @@
 // sequence against that sequence's KV cache, causal among the new rows.
 //
 // HBM-bound on the cache (a handful of flops per cached byte), so the layout is built
-// around the loads: keys stream in as full rows (256 bytes at head_dim 128), values as
+// around the loads: keys stream in as runs of 256 bytes (four positions x 32 elements, kv_k_index), values as
 // 16-byte runs of 8 consecutive positions, and the next 32-key step is in flight while
 // the current one is computed.
 //
@@ -121,12 +121,13 @@ template <int HD> struct Frags {
 template <class T, int HD, bool STREAM>
 __device__ __forceinline__ void load_step(Frags<HD> &f, const T *kbase, const T *vbase, int ks, int r, int g) {
   auto ld = [](const u32x4_v *p) { return STREAM ? __builtin_nontemporal_load(p) : *p; };
-  const T *kr0 = kbase + (size_t)(ks + 8 * (r >> 2) + (r & 3)) * HD + 8 * g;
-  const T *kr1 = kr0 + 4 * HD;
+  // keys ks + 8 (r / 4) + r % 4 (and 4 on), units 4 kk + g of their elements
+  const T *kr0 = kbase + (size_t)(ks + 8 * (r >> 2)) * HD + (g * KV_KBLOCK + (r & 3)) * KV_KUNIT16;
+  const T *kr1 = kr0 + KV_KBLOCK * HD;
 #pragma unroll
   for (int kk = 0; kk < HD / 32; ++kk) {
-    f.k0[kk] = ld((const u32x4_v *)(kr0 + kk * 32));
-    f.k1[kk] = ld((const u32x4_v *)(kr1 + kk * 32));
+    f.k0[kk] = ld((const u32x4_v *)(kr0 + kk * 4 * KV_KBLOCK * KV_KUNIT16));
+    f.k1[kk] = ld((const u32x4_v *)(kr1 + kk * 4 * KV_KBLOCK * KV_KUNIT16));
   }
   const T *vr = vbase + ((size_t)(ks / KV_VBLOCK + g) * HD + r) * KV_VBLOCK;
 #pragma unroll
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < FPW; ++i) {
       const int f = f0 + i;
-      if (f < 2 * KK) src[i] = kbase + ((size_t)(8 * (r >> 2) + (r & 3) + (f >= KK ? 4 : 0)) * HD + 8 * g + (f >= KK ? f - KK : f) * 32) * 2;
+      if (f < 2 * KK) src[i] = kbase + ((size_t)(8 * (r >> 2) + (f >= KK ? KV_KBLOCK : 0)) * HD + ((4 * (f >= KK ? f - KK : f) + g) * KV_KBLOCK + (r & 3)) * KV_KUNIT16) * 2;
       else src[i] = vbase + (((size_t)g * HD + r) * KV_VBLOCK + (size_t)(f - 2 * KK) * 16 * KV_VBLOCK) * 2;
     }
     auto fetch = [&](int step, int slot) {  // beyond the end the last step again: no wait count depends on where it lies

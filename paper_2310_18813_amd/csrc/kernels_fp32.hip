@@ -219,7 +219,7 @@ __device__ __forceinline__ void f32_epilogue(const F32Gemm &a, f32x4 v, int nt, 
     }
     if (pos < 0) return;
     const int grp = m / a.q_rows, b = a.grp_seq ? a.grp_seq[grp] : grp;
-    if (region == 1) *(f32x4 *)(a.kc + kv_k_index(a.L_pad, a.H, a.hd, b, hh, pos, e0)) = v;
+    if (region == 1) *(f32x4 *)(a.kc + kv_k_index(a.L_pad, a.H, a.hd, KV_KUNIT32, b, hh, pos, e0)) = v;
     else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) a.vc[kv_v_index(a.L_pad, a.H, a.hd, b, hh, pos, e0 + e)] = v[e];
@@ -453,10 +453,10 @@ __global__ __launch_bounds__(512) void k_attn_f32(int q_rows, int chunks, const 
   float mx = -INFINITY, sum = 0.f;
   for (int k0 = w * 16; k0 <= last; k0 += 128) {
     f32x4 kf[NI], vf[NI];
-    const f32x4 *kp = (const f32x4 *)(kc + head + (size_t)(k0 + c) * HD) + g;
+    const f32x4 *kp = (const f32x4 *)(kc + head) + (size_t)((k0 + c) / KV_KBLOCK) * HD + 4 * g + c % KV_KBLOCK;
     const f32x4 *vp = (const f32x4 *)(vc + head + ((size_t)((k0 >> 3) + (g >> 1)) * HD + c) * 8 + (g & 1) * 4);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) kf[i] = kp[4 * i];
+    for (int i = 0; i < NI; ++i) kf[i] = kp[16 * i];
 #pragma unroll
     for (int i = 0; i < NI; ++i) vf[i] = vp[32 * i];
     f32x4 s0 = zero, s1 = zero;

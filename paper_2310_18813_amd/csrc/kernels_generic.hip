@@ -133,7 +133,7 @@ __global__ void k_rope_append(int q_rows, const int32_t *__restrict__ grp_seq, i
     Conv<T>::st(qr, 2 * i, rq0);
     Conv<T>::st(qr, 2 * i + 1, rq1);
     if (pos >= 0) {
-      size_t ki = kv_k_index(L_pad, H, hd, b, hh, pos, 2 * i);
+      size_t ki = kv_k_index(L_pad, H, hd, hd, b, hh, pos, 2 * i);
       Conv<T>::st(kc, ki, rk0);
       Conv<T>::st(kc, ki + 1, rk1);
       Conv<T>::st(vc, kv_v_index(L_pad, H, hd, b, hh, pos, i), yv[i]);
@@ -166,7 +166,7 @@ __global__ void k_attn_generic(int q_rows, const int32_t *__restrict__ grp_seq, 
   const float scale = 1.0f / sqrtf((float)hd);
   float mx = -INFINITY;
   for (int j = lane; j < nk; j += 64) {
-    const T *kr = kc + kv_k_index(L_pad, H, hd, b, hh, j, 0);
+    const T *kr = kc + kv_k_index(L_pad, H, hd, hd, b, hh, j, 0);
     float dot = 0.f;
     for (int i = 0; i < hd; ++i) dot = fmaf(Conv<T>::ld(qr, i), Conv<T>::ld(kr, i), dot);
     dot *= scale;

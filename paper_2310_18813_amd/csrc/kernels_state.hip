@@ -408,7 +408,7 @@ void launch_state_reset(spec_ctx *c, const int32_t *d_prompt, int P_stride, bool
 // KV import / export between the caller's [B][len][d_model] layout and the cache layout
 // (keys pair-interleaved inside each head, values blocked by 8 positions).
 template <class T>
-__global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int L_pad, T *__restrict__ kc,
+__global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int k_unit, int L_pad, T *__restrict__ kc,
                              T *__restrict__ vc, T *__restrict__ k_user, T *__restrict__ v_user) {
   const int d = H * hd;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -417,7 +417,7 @@ __global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int L_p
   size_t r = i / d;
   int pos = (int)(r % len), b = (int)(r / len);
   int hh = c / hd, e = c % hd;
-  size_t ki = kv_k_index(L_pad, H, hd, b, hh, pos, hd_interleave(e, hd));
+  size_t ki = kv_k_index(L_pad, H, hd, k_unit, b, hh, pos, hd_interleave(e, hd));
   size_t vi = kv_v_index(L_pad, H, hd, b, hh, pos, e);
   if (import_) { kc[ki] = k_user[i]; vc[vi] = v_user[i]; }
   else { k_user[i] = kc[ki]; v_user[i] = vc[vi]; }
@@ -427,7 +427,7 @@ __global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int L_p
 // row.  Element by element the scattered loads and stores were most of the time: 64 x 128 rows of 4096 116 -> 67 us (33 MB
 // read at the rate they are written).  Workgroups of one wave, keys (blockIdx.y 0) and values (1) apart, so that a
 // small export spreads over the CUs.
-__global__ __launch_bounds__(64) void k_kv_export16(int B, int len, int H, int hd, int L_pad, const uint16_t *__restrict__ kc,
+__global__ __launch_bounds__(64) void k_kv_export16(int B, int len, int H, int hd, int k_unit, int L_pad, const uint16_t *__restrict__ kc,
                                                      const uint16_t *__restrict__ vc, uint16_t *__restrict__ k_user,
                                                      uint16_t *__restrict__ v_user) {
   const int d = H * hd, nb = (len + KV_VBLOCK - 1) / KV_VBLOCK, n8 = d >> 3;
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(64) void k_kv_export16(int B, int len, int H, int h
   }
   Eight key[8];  // stored elements e0 .. e0 + 7 of a row: the pairs of channels e0 / 2 .. e0 / 2 + 3 and their partners
 #pragma unroll
-  for (int p = 0; p < 8; ++p) key[p] = *(const Eight *)(kc + kv_k_index(L_pad, H, hd, b, hh, p0 + p, e0));
+  for (int p = 0; p < 8; ++p) key[p] = *(const Eight *)(kc + kv_k_index(L_pad, H, hd, k_unit, b, hh, p0 + p, e0));
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
     if (p >= rows) break;
@@ -484,13 +484,13 @@ void launch_kv_convert(spec_ctx *c, const Model &m, int layer, int B, int len, v
   // rows of 5120 4.1 / 4.3, 64 x 16 rows of 768 4.6 / 4.4, 256 rows of 4096 5.4 / 4.5, 777 rows of 5120 14.3 / 9.7.
   if (!import_ && esz == 2 && total >= ((size_t)3 << 18) && m.hd % 16 == 0 && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
     const size_t threads = (size_t)B * ((len + KV_VBLOCK - 1) / KV_VBLOCK) * (m.desc.d_model / 8);
-    hipLaunchKernelGGL(k_kv_export16, dim3((unsigned)((threads + 63) / 64), 2), dim3(64), 0, st, B, len, m.desc.n_heads, m.hd, m.L_pad,
+    hipLaunchKernelGGL(k_kv_export16, dim3((unsigned)((threads + 63) / 64), 2), dim3(64), 0, st, B, len, m.desc.n_heads, m.hd, m.k_unit, m.L_pad,
                        (const uint16_t *)kc, (const uint16_t *)vc, (uint16_t *)k, (uint16_t *)v);
     return;
   }
   SPEC_DISPATCH_DTYPE(c->run.dtype, T,
     hipLaunchKernelGGL(k_kv_convert<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (int)import_, B, len,
-                       m.desc.n_heads, m.hd, m.L_pad, (T *)kc, (T *)vc, (T *)k, (T *)v));
+                       m.desc.n_heads, m.hd, m.k_unit, m.L_pad, (T *)kc, (T *)vc, (T *)k, (T *)v));
 }
 
 }  // namespace spec

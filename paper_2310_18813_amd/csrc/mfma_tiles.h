@@ -228,7 +228,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int 
         } else if (pos >= 0) {
           T o4[4];
           Conv<T>::st(o4, 0, r0); Conv<T>::st(o4, 1, r1); Conv<T>::st(o4, 2, r2); Conv<T>::st(o4, 3, r3);
-          *(uint2 *)((T *)a.kc + kv_k_index(a.L_pad, a.H, a.hd, b, hh, pos, e)) = *(const uint2 *)o4;
+          *(uint2 *)((T *)a.kc + kv_k_index(a.L_pad, a.H, a.hd, KV_KUNIT16, b, hh, pos, e)) = *(const uint2 *)o4;
         }
       } else if (pos >= 0) {
         T *vc = (T *)a.vc;
@@ -434,7 +434,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
       if (a.grp_seq && live[mt]) b = a.grp_seq[b];
       const size_t seq0 = (size_t)b * a.H * a.L_pad * a.hd;
       const int p0 = max(pos[mt], 0);
-      krow[mt] = (T *)a.kc + seq0 + (size_t)p0 * a.hd;
+      krow[mt] = (T *)a.kc + kv_k_index(a.L_pad, a.H, a.hd, KV_KUNIT16, b, 0, p0, 0);
       vrow[mt] = (T *)a.vc + seq0 + (size_t)(p0 / KV_VBLOCK) * a.hd * KV_VBLOCK + p0 % KV_VBLOCK;
       quads[mt] = (a.q_rows & 3) == 0 && __all(pos[mt] >= 0 && (pos[mt] & 3) == (lane & 3) && pos[mt] == __shfl(pos[mt], lane & ~3, 64) + (lane & 3));
     }
@@ -468,7 +468,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
             } else {
               T o4[4];
               Conv<T>::st(o4, 0, r0); Conv<T>::st(o4, 1, r1); Conv<T>::st(o4, 2, r2); Conv<T>::st(o4, 3, r3);
-              if (pos[mt] >= 0) *(uint2 *)(krow[mt] + head + e) = *(const uint2 *)o4;
+              if (pos[mt] >= 0) *(uint2 *)(krow[mt] + head + (e >> 3) * (8 * KV_KBLOCK) + (e & 7)) = *(const uint2 *)o4;
             }
           }
         } else {

@@ -199,6 +199,7 @@ static int setup_model(spec_ctx *c, Model &m, const spec_model_desc *d, const sp
   m.L_pad = L_pad;
   m.fast = fast_supported(*d, c->run.dtype);
   m.f32 = fp32_supported(*d, c->run.dtype);
+  m.k_unit = m.fast ? KV_KUNIT16 : m.f32 ? KV_KUNIT32 : m.hd;
   m.layers.resize(d->n_layers);
   void *cursor = p;
   if (m.fast) {

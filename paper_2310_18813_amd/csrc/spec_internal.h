@@ -14,22 +14,29 @@ namespace spec {
 
 constexpr int WAVE = 64;
 constexpr int KV_VBLOCK = 8;  // values of 8 consecutive positions are stored together (see kv_v_index)
+constexpr int KV_KBLOCK = 4;  // positions of a block of keys (see kv_k_index)
+constexpr int KV_KUNIT16 = 8, KV_KUNIT32 = 4;  // elements of 16 bytes
 constexpr int KV_LPAD = 32;   // cache rows per sequence are padded to the attention kernel's 32-key step
 
 // ---------------------------------------------------------------- layouts
 // KV cache of one model: for each layer a K area and a V area, each
 // [B_max][H][L_pad][hd] elements, L_pad = L_max rounded up to KV_LPAD.
-//   K: row-major over positions; inside a row the head's elements are stored
-//      pair-interleaved: canonical element i (i < hd/2) sits at 2i, its rotary
-//      partner i + hd/2 at 2i+1.  Q is produced in the same order, so q.k is unchanged.
+//   K: the head's elements of a position are pair-interleaved: canonical element i (i < hd/2) is number 2i, its
+//      rotary partner i + hd/2 number 2i+1.  Q is produced in the same order, so q.k is unchanged.  They are stored in blocks
+//      of KV_KBLOCK positions, [pos / 4][hd / u][pos % 4][u], u elements being the 16 bytes a lane loads at once (8 of 16 bits,
+//      4 of fp32): the 16 positions x 4 units that a load of an attention kernel takes are then runs of 256 bytes.  In plain rows they
+//      were runs of 64, half a cache line, and half a line takes a place among the requests of a CU like a whole one: 24
+//      sequences of up to 2048 positions x 52 heads 188 -> 167 us, 64 of up to 224 x 32 heads 37 -> 34.8.  Models on the
+//      generic kernels, whose hd can be anything, have u = hd, which is plain rows.
 //   V: blocked by KV_VBLOCK positions: [pos / 8][hd][pos % 8], canonical element order,
 //      so that 8 consecutive positions of one element are one 16-byte load.
 __host__ __device__ inline int hd_interleave(int i, int hd) {
   int half = hd >> 1;
   return i < half ? 2 * i : 2 * (i - half) + 1;
 }
-__host__ __device__ inline size_t kv_k_index(int L_pad, int H, int hd, int b, int h, int pos, int i_stored) {
-  return (((size_t)b * H + h) * L_pad + pos) * hd + i_stored;
+__host__ __device__ inline size_t kv_k_index(int L_pad, int H, int hd, int u, int b, int h, int pos, int i_stored) {
+  const int blk = pos / KV_KBLOCK * KV_KBLOCK;
+  return (((size_t)b * H + h) * L_pad + blk) * hd + (i_stored / u * KV_KBLOCK + (pos - blk)) * u + i_stored % u;
 }
 __host__ __device__ inline size_t kv_v_index(int L_pad, int H, int hd, int b, int h, int pos, int i) {
   return ((((size_t)b * H + h) * (L_pad / KV_VBLOCK) + pos / KV_VBLOCK) * hd + i) * KV_VBLOCK + pos % KV_VBLOCK;
@@ -64,6 +71,7 @@ struct Model {
   const float2 *rope = nullptr;                        // MFMA path: (cos, sin) table [L_max][hd/2]
   void *kcache = nullptr, *vcache = nullptr;  // [n_layers] x area
   size_t kv_area_elems = 0;                   // elements per layer per K (or V) area
+  int k_unit = 0;                             // kv_k_index's u
   int32_t *kv_len = nullptr;                  // draft only: device [B_max] valid cache length
 };
 
