@@ -346,12 +346,11 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
     }
   } else if (EPI == EPI_SWIGLU || EPI == EPI_RELU) {
     // fragment order: a strip of 16 outputs (8 after SwiGLU) is 512 (256) consecutive bytes of its row tile
-    unsigned char *row[MTW];
     const size_t tile_bytes = (size_t)(EPI == EPI_SWIGLU ? a.f : a.N) * 32;
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt)
-      row[mt] = (unsigned char *)a.act + (size_t)(mtile0 + mt) * tile_bytes + c * 16 +
-                (EPI == EPI_SWIGLU ? g * 4 : (g >> 1) * 256 + (g & 1) * 8);
+    const unsigned in_row = c * 16 + (EPI == EPI_SWIGLU ? g * 4 : (g >> 1) * 256 + (g & 1) * 8);
+    auto row = [&](int nb, int mt) {  // a row tile's place is the same for the wave
+      return (unsigned char *)a.act + ((size_t)(mtile0 + mt) * tile_bytes + (size_t)(nt0 + nb) * (EPI == EPI_SWIGLU ? 256 : 512)) + in_row;
+    };
     with_kind([&](auto ln, auto bias) {
 #pragma unroll
       for (int nb = 0; nb < NBW; ++nb) {
@@ -372,8 +371,8 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
 #pragma unroll
         for (int mt = 0; mt < MTW; ++mt)
           if (live[mt]) {
-            if constexpr (EPI == EPI_SWIGLU) *(uint32_t *)(row[mt] + (size_t)(nt0 + nb) * 256) = *(const uint32_t *)o[mt];
-            else *(uint2 *)(row[mt] + (size_t)(nt0 + nb) * 512) = *(const uint2 *)o[mt];
+            if constexpr (EPI == EPI_SWIGLU) *(uint32_t *)row(nb, mt) = *(const uint32_t *)o[mt];
+            else *(uint2 *)row(nb, mt) = *(const uint2 *)o[mt];
           }
       }
     });
@@ -445,51 +444,49 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, f32x4_v (&acc)[
       for (int mt = 0; mt < MTW; ++mt) cs[nb & 1][mt] = *(const float4 *)(tab + (size_t)max(pos[mt], 0) * half);
     };
     if (a.rope && region < 2) load_cs(0, cc0);
-    with_kind([&](auto ln, auto bias) {
 #pragma unroll
-      for (int nb = 0; nb < NBW; ++nb) {
-        if (nt0 + nb >= a.NT) break;
-        const int next_cc0 = cc0 + 16 == a.d ? 0 : cc0 + 16, next_region = cc0 + 16 == a.d ? region + 1 : region;
-        if (nb + 1 < NBW && a.rope && next_region < 2) load_cs(nb + 1, next_cc0);
-        const int hh = cc0 >> hd_shift, e = (cc0 & (a.hd - 1)) + 4 * g;
-        const size_t head = (size_t)hh * a.L_pad * a.hd;
-        if (region < 2) {
+    for (int nb = 0; nb < NBW; ++nb) {
+      if (nt0 + nb >= a.NT) break;
+      const int next_cc0 = cc0 + 16 == a.d ? 0 : cc0 + 16, next_region = cc0 + 16 == a.d ? region + 1 : region;
+      if (nb + 1 < NBW && a.rope && next_region < 2) load_cs(nb + 1, next_cc0);
+      const int hh = cc0 >> hd_shift, e = (cc0 & (a.hd - 1)) + 4 * g;
+      const size_t head = (size_t)hh * a.L_pad * a.hd;
+      if (region < 2) {
 #pragma unroll
-          for (int mt = 0; mt < MTW; ++mt) {
-            const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], ln, bias);
-            float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
-            if (a.rope && pos[mt] >= 0) {
-              const float4 t = cs[nb & 1][mt];
-              r0 = v[0] * t.x - v[1] * t.y; r1 = v[1] * t.x + v[0] * t.y;
-              r2 = v[2] * t.z - v[3] * t.w; r3 = v[3] * t.z + v[2] * t.w;
-            }
-            if (region == 0) {  // queries stay fp32 (see tile_epilogue)
-              if (live[mt]) *(float4 *)((float *)a.q + (size_t)((mtile0 + mt) * 16 + c) * a.d + cc0 + 4 * g) = make_float4(r0, r1, r2, r3);
-            } else {
-              T o4[4];
-              Conv<T>::st(o4, 0, r0); Conv<T>::st(o4, 1, r1); Conv<T>::st(o4, 2, r2); Conv<T>::st(o4, 3, r3);
-              if (pos[mt] >= 0) *(uint2 *)(krow[mt] + head + (e >> 3) * (8 * KV_KBLOCK) + (e & 7)) = *(const uint2 *)o4;
-            }
+        for (int mt = 0; mt < MTW; ++mt) {
+          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], lnx, a.bias != nullptr);
+          float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
+          if (a.rope && pos[mt] >= 0) {
+            const float4 t = cs[nb & 1][mt];
+            r0 = v[0] * t.x - v[1] * t.y; r1 = v[1] * t.x + v[0] * t.y;
+            r2 = v[2] * t.z - v[3] * t.w; r3 = v[3] * t.z + v[2] * t.w;
           }
-        } else {
-#pragma unroll
-          for (int mt = 0; mt < MTW; ++mt) {
-            const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], ln, bias);
+          if (region == 0) {  // queries stay fp32 (see tile_epilogue)
+            if (live[mt]) *(float4 *)((float *)a.q + (size_t)((mtile0 + mt) * 16 + c) * a.d + cc0 + 4 * g) = make_float4(r0, r1, r2, r3);
+          } else {
             T o4[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Conv<T>::st(o4, i, v[i]);
-            if (quads[mt]) {  // four rows of one element per lane: their positions are neighbours in the cache
-              const uint2 o = quad_transpose(*(const uint2 *)o4, lane);
-              *(uint2 *)(vrow[mt] - (lane & 3) + head + (size_t)(e + (lane & 3)) * KV_VBLOCK) = o;
-            } else if (pos[mt] >= 0) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) vrow[mt][head + (size_t)(e + i) * KV_VBLOCK] = o4[i];
-            }
+            Conv<T>::st(o4, 0, r0); Conv<T>::st(o4, 1, r1); Conv<T>::st(o4, 2, r2); Conv<T>::st(o4, 3, r3);
+            if (pos[mt] >= 0) *(uint2 *)(krow[mt] + head + (e >> 3) * (8 * KV_KBLOCK) + (e & 7)) = *(const uint2 *)o4;
           }
         }
-        region = next_region; cc0 = next_cc0;
+      } else {
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt) {
+          const f32x4_v v = finish(acc[nb][mt], mt, b4[nb], w4[nb], lnx, a.bias != nullptr);
+          T o4[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) Conv<T>::st(o4, i, v[i]);
+          if (quads[mt]) {  // four rows of one element per lane: their positions are neighbours in the cache
+            const uint2 o = quad_transpose(*(const uint2 *)o4, lane);
+            *(uint2 *)(vrow[mt] - (lane & 3) + head + (size_t)(e + (lane & 3)) * KV_VBLOCK) = o;
+          } else if (pos[mt] >= 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) vrow[mt][head + (size_t)(e + i) * KV_VBLOCK] = o4[i];
+          }
+        }
       }
-    });
+      region = next_region; cc0 = next_cc0;
+    }
   }
 }
 
