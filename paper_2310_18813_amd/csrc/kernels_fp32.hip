@@ -14,7 +14,7 @@
 //
 // Against the generic kernels (norm, product, rotary + append, attention, activation as nine launches a layer; one wave
 // per output and four rows): verification of 8 sequences x 5 rows at d_model 1024, 4 layers 2679 -> 307 us, logits'
-// error against 64 bits 7.2e-7 -> 6.7e-7; a d_model 256 target with its 128 draft, 12 rounds 4.7 -> 2.5 ms, 2.4e-7 both.
+// error against 64 bits 7.2e-7 -> 6.7e-7 (266 us since); a d_model 256 target with its 128 draft, 12 rounds 4.7 -> 2.5 ms, 2.4e-7 both.
 #include "spec_internal.h"
 #include "device_utils.h"
 #include <algorithm>
@@ -231,12 +231,15 @@ __device__ __forceinline__ void f32_epilogue(const F32Gemm &a, f32x4 v, int nt, 
 // With eight slices of eight tiles that is above the 64 KB a kernel has without asking (fp32_prepare).
 constexpr size_t f32_lds(int KS, int MT, int NB) { return (size_t)KS * (NB * MT * 1024 + MT * 16 * 4); }
 
-// Workgroup = KS waves, one k-slice each, over NB strips of W and MT row tiles of X; the slices meet in LDS.  Bound by the weight stream (few rows) or by the matrix cores (2 x 4 tiles: 256 cycles of MFMA per unit and
-// step against 96 cycles of L2 reads; 4 x 4 spills); operands of the next steps are in flight while the present ones are multiplied.
-template <int MT, int NB, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
+// Workgroup = KS waves, one k-slice each, over NB strips of W and MT row tiles of X; the slices meet in LDS.  Bound by the latencies of a
+// wave's loads (few rows: a slice is 2 to 32 steps) or by the matrix cores (2 x 4 tiles: 256 cycles of MFMA per unit and step
+// against 96 cycles of L2 reads; 4 x 4 spills); operands of the next steps are in flight while the present ones are multiplied.
+// (A wave per strip over all of k, the rows through LDS, was slower everywhere but for the head at 1 to 5 rows: 8192 x 1024 at 40 rows 44
+// us against 15.6, 32000 x 1024 55 and 53.)
+template <int MT, int NB, int EPI, bool DEEP>
+__global__ __launch_bounds__(512, 2) void k_gemm_f32(F32Gemm a) {
   extern __shared__ float red[];  // [KS][NB * MT][256], then [KS][MT * 16]: f32_lds()
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, g = lane >> 4;
   const int KS = a.KS;
   float *ssq_s = red + (size_t)KS * (NB * MT * 256);
   int G = blockIdx.x, pass = 0;
@@ -249,12 +252,18 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
   const int nt0 = G * NB, m_base = pass * (MT * 16), K = a.KT * 16;
   const int kt_per = a.KT / KS, kt0 = w * kt_per, kt1 = kt0 + kt_per;
 
-  const f32x4 *Wp[NB], *Xp[MT];
+  // Addresses: what is the same for the wave in scalars, a lane's part in 32 bits (no registers for addresses beside the batches).
+  const unsigned char *Wp[NB], *Xp[MT];
+  unsigned x_off[MT];
+  const unsigned w_off = lane * 16;
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) Wp[nb] = a.W + (size_t)min(nt0 + nb, a.NT - 1) * a.KT * 64 + lane;
+  for (int nb = 0; nb < NB; ++nb) Wp[nb] = (const unsigned char *)a.W + (size_t)min(nt0 + nb, a.NT - 1) * a.KT * 1024;
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-    Xp[mt] = (const f32x4 *)(a.X + ((size_t)min(m_base + mt * 16 + c, a.M - 1) * a.x_mul + a.x_off) * K) + g;
+  for (int mt = 0; mt < MT; ++mt) {
+    const int row0 = min(m_base + mt * 16, a.M - 1), row = min(row0 + c, a.M - 1);
+    Xp[mt] = (const unsigned char *)a.X + ((size_t)row0 * a.x_mul + a.x_off) * K * 4;
+    x_off[mt] = (unsigned)((row - row0) * a.x_mul * K + 4 * g) * 4;
+  }
 
   f32x4 acc[NB][MT];
   float ssq[MT];
@@ -265,31 +274,36 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb][mt] = zero;
   }
-  constexpr int U = NB + MT >= 5 ? 1 : NB + MT >= 3 ? 2 : 4;
+  // Steps in two batches of U, the loads of one in flight while the other is multiplied.  DEEP: inside the loop every load is
+  // unconditional (behind a branch the compiler waits, where it joins, for all loads under way), and the multiplies stay
+  // in order, so that few of their intermediate sums take registers beside the batches.
+  constexpr int U = DEEP ? (NB + MT <= 5 ? 4 : 2) : NB + MT >= 5 ? 1 : NB + MT >= 3 ? 2 : 4;
   f32x4 wf[2][U][NB], xf[2][U][MT];
   auto load = [&](f32x4 (&wd)[U][NB], f32x4 (&xd)[U][MT], int kt) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = min(kt + u, kt1 - 1);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) wd[u][nb] = __builtin_nontemporal_load(Wp[nb] + (size_t)k * 64);
+      for (int nb = 0; nb < NB; ++nb) wd[u][nb] = __builtin_nontemporal_load((const f32x4 *)(Wp[nb] + (size_t)k * 1024 + w_off));
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) xd[u][mt] = Xp[mt][(size_t)k * 4];
+      for (int mt = 0; mt < MT; ++mt) xd[u][mt] = *(const f32x4 *)(Xp[mt] + (size_t)k * 64 + x_off[mt]);
     }
   };
-  auto mul = [&](const f32x4 (&wd)[U][NB], const f32x4 (&xd)[U][MT], int kt) {
+  auto mul = [&](const f32x4 (&wd)[U][NB], const f32x4 (&xd)[U][MT], int steps) {  // the first `steps` of a batch, the same for the wave
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (kt + u >= kt1) break;
+      if (u >= steps) break;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+      for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
           const f32x4 lo = mfma4(wd[u][nb][1], xd[u][mt][1], mfma4(wd[u][nb][0], xd[u][mt][0], zero));
           const f32x4 hi = mfma4(wd[u][nb][3], xd[u][mt][3], mfma4(wd[u][nb][2], xd[u][mt][2], zero));
           acc[nb][mt] += lo + hi;
         }
-      if (a.fold) {
+        if (DEEP) __builtin_amdgcn_sched_barrier(0);
+      }
+      if (EPI != EPI_RESIDUAL) {  // (without a test: used or not, a.fold says; a branch here costs the batches their registers)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -298,12 +312,32 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
     }
   };
   load(wf[0], xf[0], kt0);
-  for (int kt = kt0; kt < kt1; kt += 2 * U) {
-    if (kt + U < kt1) load(wf[1], xf[1], kt + U);
-    mul(wf[0], xf[0], kt);
-    if (kt + U >= kt1) break;
-    if (kt + 2 * U < kt1) load(wf[0], xf[0], kt + 2 * U);
-    mul(wf[1], xf[1], kt + U);
+  if (DEEP) {
+    int left = __builtin_amdgcn_readfirstlane(kt_per), kt = kt0;
+    for (; left > 2 * U; left -= 2 * U, kt += 2 * U) {
+      load(wf[1], xf[1], kt + U);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(wf[0], xf[0], U);
+      load(wf[0], xf[0], kt + 2 * U);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(wf[1], xf[1], U);
+    }
+    if (left > U) {
+      load(wf[1], xf[1], kt + U);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(wf[0], xf[0], U);
+      mul(wf[1], xf[1], left - U);
+    } else {
+      mul(wf[0], xf[0], left);
+    }
+  } else {
+    for (int kt = kt0; kt < kt1; kt += 2 * U) {
+      if (kt + U < kt1) load(wf[1], xf[1], kt + U);
+      mul(wf[0], xf[0], kt1 - kt);
+      if (kt + U >= kt1) break;
+      if (kt + 2 * U < kt1) load(wf[0], xf[0], kt + 2 * U);
+      mul(wf[1], xf[1], kt1 - kt - U);
+    }
   }
 
   if (a.fold) {  // the row's sum of squares: the four k-quarters of a slice here, the slices in order behind the barrier
@@ -321,8 +355,17 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
     for (int mt = 0; mt < MT; ++mt) {
       rinv[mt] = 1.f;
       if (!a.fold) continue;
-      float t = ssq_s[mt * 16 + c];
-      for (int s = 1; s < KS; ++s) t += ssq_s[s * (MT * 16) + mt * 16 + c];
+      const float *p = ssq_s + mt * 16 + c;
+      float t = p[0];
+      if (KS == 8) {  // (all reads ahead of the additions)
+        float q[8];
+#pragma unroll
+        for (int s = 1; s < 8; ++s) q[s] = p[s * (MT * 16)];
+#pragma unroll
+        for (int s = 1; s < 8; ++s) t += q[s];
+      } else {
+        for (int s = 1; s < KS; ++s) t += p[s * (MT * 16)];
+      }
       rinv[mt] = 1.0f / sqrtf(t / (float)K + a.eps);
     }
   };
@@ -334,45 +377,60 @@ __global__ __launch_bounds__(512) void k_gemm_f32(F32Gemm a) {
 #pragma unroll
   for (int t = 0; t < TILES; ++t) {
     if (t % KS != w) continue;
-    f32x4 v = *(const f32x4 *)&red[((size_t)t * 64 + lane) * 4];
-    for (int s = 1; s < KS; ++s) v += *(const f32x4 *)&red[((size_t)(s * TILES + t) * 64 + lane) * 4];
+    const f32x4 *p = (const f32x4 *)red + t * 64 + lane;
+    f32x4 v = p[0];
+    if (KS == 8) {
+      f32x4 q[8];
+#pragma unroll
+      for (int s = 1; s < 8; ++s) q[s] = p[s * TILES * 64];
+#pragma unroll
+      for (int s = 1; s < 8; ++s) v += q[s];
+    } else {
+      for (int s = 1; s < KS; ++s) v += p[s * TILES * 64];
+    }
     f32_epilogue<EPI>(a, v, nt0 + t / MT, m_base + (t % MT) * 16 + c, g, rinv[t % MT]);
   }
 }
 
-// blocks < 0: preparation pass
+// blocks < 0: preparation pass.  DEEP where the workgroups leave a CU to one or two and a wave's chain of memory latencies is what
+// counts: no more than two of one tile to a CU, one of two or three tiles (us without / with: 8192 x 1024 at 1 row 9.5 / 8.4, 1024 x
+// 4096 11.2 / 9.3, 3072 x 1024 at 40 rows as 3 x 1 11.8 / 11.2; but 32000 x 1024 at 1 row 30.5 / 32.3, 8192 x 1024 at 40 as 3 x 2 15.6 / 16.3).
 template <int MT, int NB, int EPI>
-static void f32_launch(const F32Gemm &a, int blocks, hipStream_t st) {
+static void f32_launch(const F32Gemm &a, int blocks, int n_cu, hipStream_t st) {
+  constexpr bool CAN = MT * NB <= 3;
+  const size_t lds = f32_lds(a.KS, MT, NB);
   if (blocks < 0)
-    (void)hipFuncSetAttribute((const void *)k_gemm_f32<MT, NB, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f32_lds(8, MT, NB));
+    (void)hipFuncSetAttribute((const void *)k_gemm_f32<MT, NB, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f32_lds(8, MT, NB));
+  else if (CAN && blocks <= (MT * NB == 1 ? 2 : 1) * n_cu)
+    hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI, CAN>), dim3(blocks), dim3(a.KS * 64), lds, st, a);
   else
-    hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI>), dim3(blocks), dim3(a.KS * 64), f32_lds(a.KS, MT, NB), st, a);
+    hipLaunchKernelGGL((k_gemm_f32<MT, NB, EPI, false>), dim3(blocks), dim3(a.KS * 64), lds, st, a);
 }
 
 template <int MT, int NB>
-static void f32_launch_epi(const F32Gemm &a, int epi, int blocks, hipStream_t st) {
+static void f32_launch_epi(const F32Gemm &a, int epi, int blocks, int n_cu, hipStream_t st) {
   switch (epi) {
-    case EPI_RESIDUAL: f32_launch<MT, NB, EPI_RESIDUAL>(a, blocks, st); break;
-    case EPI_QKV: f32_launch<MT, NB, EPI_QKV>(a, blocks, st); break;
-    case EPI_SWIGLU: f32_launch<MT, NB, EPI_SWIGLU>(a, blocks, st); break;
-    case EPI_RELU: f32_launch<MT, NB, EPI_RELU>(a, blocks, st); break;
-    default: f32_launch<MT, NB, EPI_LOGITS>(a, blocks, st); break;
+    case EPI_RESIDUAL: f32_launch<MT, NB, EPI_RESIDUAL>(a, blocks, n_cu, st); break;
+    case EPI_QKV: f32_launch<MT, NB, EPI_QKV>(a, blocks, n_cu, st); break;
+    case EPI_SWIGLU: f32_launch<MT, NB, EPI_SWIGLU>(a, blocks, n_cu, st); break;
+    case EPI_RELU: f32_launch<MT, NB, EPI_RELU>(a, blocks, n_cu, st); break;
+    default: f32_launch<MT, NB, EPI_LOGITS>(a, blocks, n_cu, st); break;
   }
 }
 
-static void f32_launch_shape(const F32Gemm &a, int MT, int NB, int epi, int blocks, hipStream_t st) {
+static void f32_launch_shape(const F32Gemm &a, int MT, int NB, int epi, int blocks, int n_cu, hipStream_t st) {
   switch (MT * 8 + NB) {
-    case 9: f32_launch_epi<1, 1>(a, epi, blocks, st); break;
-    case 10: f32_launch_epi<1, 2>(a, epi, blocks, st); break;
-    case 12: f32_launch_epi<1, 4>(a, epi, blocks, st); break;
-    case 17: f32_launch_epi<2, 1>(a, epi, blocks, st); break;
-    case 18: f32_launch_epi<2, 2>(a, epi, blocks, st); break;
-    case 20: f32_launch_epi<2, 4>(a, epi, blocks, st); break;
-    case 25: f32_launch_epi<3, 1>(a, epi, blocks, st); break;
-    case 26: f32_launch_epi<3, 2>(a, epi, blocks, st); break;
-    case 28: f32_launch_epi<3, 4>(a, epi, blocks, st); break;
-    case 33: f32_launch_epi<4, 1>(a, epi, blocks, st); break;
-    default: f32_launch_epi<4, 2>(a, epi, blocks, st); break;
+    case 9: f32_launch_epi<1, 1>(a, epi, blocks, n_cu, st); break;
+    case 10: f32_launch_epi<1, 2>(a, epi, blocks, n_cu, st); break;
+    case 12: f32_launch_epi<1, 4>(a, epi, blocks, n_cu, st); break;
+    case 17: f32_launch_epi<2, 1>(a, epi, blocks, n_cu, st); break;
+    case 18: f32_launch_epi<2, 2>(a, epi, blocks, n_cu, st); break;
+    case 20: f32_launch_epi<2, 4>(a, epi, blocks, n_cu, st); break;
+    case 25: f32_launch_epi<3, 1>(a, epi, blocks, n_cu, st); break;
+    case 26: f32_launch_epi<3, 2>(a, epi, blocks, n_cu, st); break;
+    case 28: f32_launch_epi<3, 4>(a, epi, blocks, n_cu, st); break;
+    case 33: f32_launch_epi<4, 1>(a, epi, blocks, n_cu, st); break;
+    default: f32_launch_epi<4, 2>(a, epi, blocks, n_cu, st); break;
   }
 }
 
@@ -380,9 +438,9 @@ static void f32_launch_shape(const F32Gemm &a, int MT, int NB, int epi, int bloc
 void fp32_prepare() {
   const F32Gemm a{};
   for (int epi : {(int)EPI_RESIDUAL, (int)EPI_QKV, (int)EPI_SWIGLU, (int)EPI_RELU, (int)EPI_LOGITS}) {
-    f32_launch_shape(a, 2, 4, epi, -1, nullptr);
-    f32_launch_shape(a, 3, 4, epi, -1, nullptr);
-    f32_launch_shape(a, 4, 2, epi, -1, nullptr);
+    f32_launch_shape(a, 2, 4, epi, -1, 0, nullptr);
+    f32_launch_shape(a, 3, 4, epi, -1, 0, nullptr);
+    f32_launch_shape(a, 4, 2, epi, -1, 0, nullptr);
   }
 }
 
@@ -419,7 +477,7 @@ static void f32_gemm(F32Gemm a, int epi, int n_cu, hipStream_t st) {
   a.passes = (a.M + MT * 16 - 1) / (MT * 16);
   a.groups = (a.NT + NB - 1) / NB;
   const int blocks = a.passes == 1 ? a.groups : (a.groups + 7) / 8 * 8 * a.passes;
-  f32_launch_shape(a, MT, NB, epi, blocks, st);
+  f32_launch_shape(a, MT, NB, epi, blocks, n_cu, st);
 }
 
 // ------------------------------------------------------------------------- attention
@@ -440,9 +498,6 @@ __global__ __launch_bounds__(512) void k_attn_f32(int q_rows, int chunks, const 
   const int b = grp_seq ? grp_seq[grp] : grp;
   const size_t m = (size_t)grp * q_rows + r0 + min(c, nr - 1);
   const int pos = c < nr ? row_pos[m] : -1;
-  int last = pos;
-#pragma unroll
-  for (int o = 8; o >= 1; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   const f32x4 *qp = (const f32x4 *)(q + m * d + (size_t)hh * HD) + g;
   f32x4 qf[NI], acc[NI];
@@ -451,14 +506,22 @@ __global__ __launch_bounds__(512) void k_attn_f32(int q_rows, int chunks, const 
   const size_t head = ((size_t)b * H + hh) * L_pad * HD;
   const float scale = 1.0f / sqrtf((float)HD);
   float mx = -INFINITY, sum = 0.f;
-  for (int k0 = w * 16; k0 <= last; k0 += 128) {
-    f32x4 kf[NI], vf[NI];
+  f32x4 kf[NI], vf[NI];
+  auto fetch = [&](int k0) {
     const f32x4 *kp = (const f32x4 *)(kc + head) + (size_t)((k0 + c) / KV_KBLOCK) * HD + 4 * g + c % KV_KBLOCK;
     const f32x4 *vp = (const f32x4 *)(vc + head + ((size_t)((k0 >> 3) + (g >> 1)) * HD + c) * 8 + (g & 1) * 4);
 #pragma unroll
     for (int i = 0; i < NI; ++i) kf[i] = kp[16 * i];
 #pragma unroll
     for (int i = 0; i < NI; ++i) vf[i] = vp[32 * i];
+  };
+  // the first tile is asked for before the rows' positions are here (inside the cache, if behind the last key)
+  fetch(min(w * 16, L_pad - 16));
+  int last = pos;
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
+  for (int k0 = w * 16; k0 <= last; k0 += 128) {
+    if (k0 >= 128) fetch(k0);
     f32x4 s0 = zero, s1 = zero;
 #pragma unroll
     for (int i = 0; i < NI; i += 2)

@@ -62,3 +62,21 @@ def test_a_later_row_that_is_not_finite_leaves_the_rows_before_it_alone():
         rows.append(ctx.spec_verify_step(3, want_logits=True)[0].cpu().numpy().copy())
     assert np.array_equal(rows[0][:3], rows[1][:3])
     assert np.isfinite(rows[0]).all() and not np.isfinite(rows[1][3]).any()
+
+
+@pytest.mark.parametrize("d,heads,ffn", [(128, 2, 416), (320, 5, 1232), (640, 10, 1024), (1024, 16, 4096)])
+def test_a_row_alone_has_the_bits_of_the_row_among_many(d, heads, ffn):
+    """One row's products keep more steps of a k-slice under way than those of many rows do (slices of 4 to 77 steps here, odd
+    ones among them): the same sums, for batches on either side of the row counts where that changes."""
+    from paper_2310_18813_amd import binding as B
+    desc = si.llama_desc(2, d, heads, ffn, 700, 128)
+    w = si.make_weights(desc, "fp32", 5, device=DEV, tag="tgt.")
+    prompt = si.make_prompts(1, 21, 700, 7)
+    got = {}
+    for n in (1, 5, 17, 40, 130):
+        ctx = B.Context(desc, w, None, None, "fp32", n, 0, 64, 8, B.PROPOSALS_EXTERNAL, DEV)
+        ctx.spec_reset(np.repeat(prompt, n, 0))
+        got[n] = ctx.spec_verify_step(0, want_logits=True).reshape(n, 700).cpu()
+        ctx.close()
+    for n, rows in got.items():
+        assert torch.equal(rows, got[1].expand(n, 700)), n
