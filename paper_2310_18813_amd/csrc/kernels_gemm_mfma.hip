@@ -234,13 +234,26 @@ void launch_rope_table(int L, int hd, float theta, float2 *tab, hipStream_t st) 
 // group) and MT 16-row tiles of X (a pass).  Weights and activations are both read in
 // fragment order, 1 KB per wave per load.  After the k loop the KS partial tiles meet in
 // LDS, eight tiles at a time, and are added in slice order.
+// Behind the k loop a launch is a chain of latencies, most of the time of a draft model's products: the slices of a tile and of the rows' sums are
+// read from LDS together, and what a wave's tile needs from memory (rows of h, positions and rotary entries, bias) is asked for before
+// the waves meet.  Products of a 768-wide model at 8 rows, us: QKV 4.9 -> 4.3, O 3.9 -> 3.3, fc1 5.2 -> 4.3, down 5.4 -> 4.8; QKV 12288 x 4096
+// 19.9 -> 18.8, at 36 rows 25.7 -> 23.8; 7B round of one sequence with seven draft steps 704 -> 668.
 // With more than one pass the linear workgroup id is decoded so that all passes of a strip
 // group run on the same XCD (workgroups are dealt round-robin to the 8 XCDs): the group's
 // weights are fetched from HBM once and hit that XCD's L2 for the other passes.
+// f(0), f(1), ... f(N - 1), each number a constant
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void for_each_int(F f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    for_each_int<N, I + 1>(f);
+  }
+}
+
 template <class T, int MT, int NB, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_stream(GemmArgs a) {
   extern __shared__ float red[];  // [KS][min(NB*MT, 8)][256]
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int KS = blockDim.x >> 6;
   int G, pass;
@@ -279,6 +292,12 @@ __global__ __launch_bounds__(512) void k_gemm_stream(GemmArgs a) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[nb][mt] = (f32x4_v){0.f, 0.f, 0.f, 0.f};
 
+  // the tile this wave finishes first (eight slices: tile 8 r + w in round r), and its rows' positions, asked for ahead (32 tiles
+  // leave no registers for that)
+  constexpr bool AHEAD = NB * MT < 32;
+  auto row_of = [&](int t) { return m_base + (t % MT) * 16 + c; };
+  int pos0 = -1;
+  if (AHEAD && EPI == EPI_QKV && KS == 8 && w < NB * MT && row_of(w) < a.M) pos0 = a.row_pos[row_of(w)];
   constexpr bool FOLDX = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_RELU || EPI == EPI_LOGITS;  // the GEMMs behind a norm
   const bool foldx = FOLDX && a.fold_x;
   const bool lnx = foldx && a.wsum;  // the folded norm is a LayerNorm: the plain sums as well
@@ -370,22 +389,23 @@ __global__ __launch_bounds__(512) void k_gemm_stream(GemmArgs a) {
     if (!foldx) return;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      float t = ssq[mt];
-      if (KS > 1) {
-        t = ssq_s[0][mt * 64 + lane];
-        for (int s = 1; s < KS; ++s) t += ssq_s[s][mt * 64 + lane];
-      }
-      mean_x[mt] = 0.f;
-      if (lnx) {
-        float ts = sm[mt];
-        if (KS > 1) {
-          ts = sum_s[0][mt * 64 + lane];
-          for (int s = 1; s < KS; ++s) ts += sum_s[s][mt * 64 + lane];
+      auto slices = [&](float (*p)[FOLDX ? MT * 64 : 1]) {  // in slice order; with eight, all reads ahead of the additions
+        float t = p[0][mt * 64 + lane];
+        if (KS == 8) {
+          float q[8];
+#pragma unroll
+          for (int s = 1; s < 8; ++s) q[s] = p[s][mt * 64 + lane];
+#pragma unroll
+          for (int s = 1; s < 8; ++s) t += q[s];
+        } else {
+          for (int s = 1; s < KS; ++s) t += p[s][mt * 64 + lane];
         }
-        row_ln_from_lane(t, ts, a.ss_d, a.ss_eps, rinv_x[mt], mean_x[mt]);
-      } else {
-        rinv_x[mt] = row_inv_from_lane_ssq(t, a.ss_d, a.ss_eps);
-      }
+        return t;
+      };
+      const float t = KS > 1 ? slices(ssq_s) : ssq[mt];
+      mean_x[mt] = 0.f;
+      if (lnx) row_ln_from_lane(t, KS > 1 ? slices(sum_s) : sm[mt], a.ss_d, a.ss_eps, rinv_x[mt], mean_x[mt]);
+      else rinv_x[mt] = row_inv_from_lane_ssq(t, a.ss_d, a.ss_eps);
     }
   };
   auto rinv_of = [&](int mt) { return foldx ? rinv_x[mt] : 1.0f; };
@@ -399,13 +419,34 @@ __global__ __launch_bounds__(512) void k_gemm_stream(GemmArgs a) {
   }
   constexpr int ROUNDS = (TILES + 7) / 8;
   constexpr int SLOTS = TILES < 8 ? TILES : 8;
-#pragma unroll
-  for (int r = 0; r < ROUNDS; ++r) {
+  for_each_int<ROUNDS>([&](auto round) {  // (unrolled whatever its size: the tiles are in registers)
+    constexpr int r = decltype(round)::value;
     if (r > 0) __syncthreads();
 #pragma unroll
     for (int slot = 0; slot < 8; ++slot) {
       const int t = r * 8 + slot;
       if (t < TILES) *(f32x4_v *)&red[((size_t)(w * SLOTS + slot) * 64 + lane) * 4] = acc[t / MT][t % MT];
+    }
+    if (AHEAD && KS == 8) {  // a tile per wave; what its epilogue reads is under way while the waves meet
+      const int t = r * 8 + w, nt = nt0 + t / MT, m = row_of(t);
+      TileOperands ops;
+      if (t < TILES) ops = fetch_tile_operands<EPI>(a, nt, m, g, EPI == EPI_QKV && r == 0 ? &pos0 : nullptr);
+      __syncthreads();
+      if (r == 0) finish_rinv();
+      if (t < TILES) {
+        const f32x4_v *p = (const f32x4_v *)red + w * 64 + lane;
+        f32x4_v v = p[0], q[8];
+#pragma unroll
+        for (int s = 1; s < 8; ++s) q[s] = p[s * SLOTS * 64];
+#pragma unroll
+        for (int s = 1; s < 8; ++s) { v[0] += q[s][0]; v[1] += q[s][1]; v[2] += q[s][2]; v[3] += q[s][3]; }
+        float rinv = 1.0f, mean = 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          if (t % MT == mt) { rinv = rinv_of(mt); mean = mean_of(mt); }
+        tile_epilogue<T, EPI>(a, v, nt, m, g, rinv, mean, ops);
+      }
+      return;
     }
     __syncthreads();
     if (r == 0) finish_rinv();
@@ -421,7 +462,7 @@ __global__ __launch_bounds__(512) void k_gemm_stream(GemmArgs a) {
       }
       tile_epilogue<T, EPI>(a, v, nt0 + t / MT, m_base + (t % MT) * 16 + c, g, rinv_of(t % MT), mean_of(t % MT));
     }
-  }
+  });
 }
 
 template <class T, int MT, int NB>

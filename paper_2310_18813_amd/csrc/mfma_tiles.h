@@ -116,14 +116,11 @@ __device__ __forceinline__ void to_op_strip(const float (&x)[MT][N], const bool 
 
 // h[m][n..n+3] += v (scaled, biased): the residual update of one lane's four outputs; o4 = the updated values
 // rounded to the next GEMM's operand type (also written to x_out in fragment order when that is set).
-__device__ __forceinline__ void residual_update(const GemmArgs &a, f32x4_v v, int n, int m, op_t (&o4)[4]) {
+// o: the values of h, b4: the bias (if there is one)
+__device__ __forceinline__ void residual_update(const GemmArgs &a, f32x4_v v, int n, int m, op_t (&o4)[4], float4 o, const float4 &b4) {
   v[0] *= a.out_scale; v[1] *= a.out_scale; v[2] *= a.out_scale; v[3] *= a.out_scale;  // exact: a power of two
-  if (a.bias) {
-    const float4 b4 = *(const float4 *)(a.bias + n);
-    v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w;
-  }
+  if (a.bias) { v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w; }
   float4 *p = (float4 *)(a.h + (size_t)m * a.N + n);
-  float4 o = *p;
   o.x += v[0]; o.y += v[1]; o.z += v[2]; o.w += v[3];
   *p = o;
   if (a.x_out) {  // the next GEMM's activations: the updated row, rounded to fp16
@@ -131,6 +128,12 @@ __device__ __forceinline__ void residual_update(const GemmArgs &a, f32x4_v v, in
     to_op_group(x4, o4, a.sat);
     *(uint2 *)((op_t *)a.x_out + xpack_index(m, n, a.N >> 5)) = *(const uint2 *)o4;
   }
+}
+
+__device__ __forceinline__ void residual_update(const GemmArgs &a, f32x4_v v, int n, int m, op_t (&o4)[4]) {
+  float4 b4;
+  if (a.bias) b4 = *(const float4 *)(a.bias + n);
+  residual_update(a, v, n, m, o4, *(const float4 *)(a.h + (size_t)m * a.N + n), b4);
 }
 
 // EPI_LOGITS: where row m of the logits is dumped, if it is
@@ -183,45 +186,69 @@ __device__ __forceinline__ int row_group(int m, int q_rows, float inv_q) {
 // One finished 16x16 tile: this lane holds stored rows n .. n+3 (n = 16*nt + 4g) of
 // activation row m.  The element-wise work of the layer happens here, on fp32 sums.
 // rinv: 1 / rms of row m when the norm in front of this GEMM is folded into it, else 1.
+// What it reads from memory can be asked for ahead (fetch_tile_operands), while the sums are still on their way.
+struct TileOperands {
+  float4 b4, w4;  // bias; row sums of the weights (folded LayerNorm)
+  float4 h;       // EPI_RESIDUAL
+  float4 cs;      // EPI_QKV: (cos, sin) of the two rotary pairs
+  int pos, seq;   // EPI_QKV: the row's position and sequence
+  int region, cc, hh;  // EPI_QKV: 0 q, 1 k, 2 v; the strip's first column there, and its head
+};
+// EPI_QKV, pos: the row's position, if it is here already
+template <int EPI>
+__device__ __forceinline__ TileOperands fetch_tile_operands(const GemmArgs &a, int nt, int m, int g, const int *pos = nullptr) {
+  TileOperands t;
+  t.b4 = t.w4 = t.h = t.cs = make_float4(0.f, 0.f, 0.f, 0.f);
+  t.pos = -1; t.seq = t.region = t.cc = t.hh = 0;
+  const int n = nt * 16 + 4 * g;
+  if (nt >= a.NT) return t;
+  if (a.bias) t.b4 = *(const float4 *)(a.bias + n);
+  if (EPI == EPI_RESIDUAL) {
+    if (m < a.M && n < a.N) t.h = *(const float4 *)(a.h + (size_t)m * a.N + n);
+    return t;
+  }
+  if (a.wsum) t.w4 = *(const float4 *)(a.wsum + n);
+  if (EPI == EPI_QKV && m < a.M && n < a.N) {
+    t.pos = pos ? *pos : a.row_pos[m];
+    t.seq = row_group(m, a.q_rows, 1.0f / (float)a.q_rows);
+    if (a.grp_seq) t.seq = a.grp_seq[t.seq];  // prefill passes only
+    // No per-lane integer division (it would be most of this epilogue).  A strip of 16 stored rows lies
+    // inside one head of one of q, k, v (d and hd are multiples of 16), and the strip number is the same for
+    // the whole wave: its place is scalar arithmetic.
+    const int base = __builtin_amdgcn_readfirstlane(nt) * 16;
+    t.region = base / a.d; t.cc = base - t.region * a.d; t.hh = t.cc / a.hd;
+    const int e = t.cc - t.hh * a.hd + 4 * g;
+    if (t.region < 2 && a.rope && t.pos >= 0) t.cs = *(const float4 *)(a.rope + (size_t)t.pos * (a.hd >> 1) + (e >> 1));
+  }
+  return t;
+}
 template <class T, int EPI>
-__device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int nt, int m, int g, float rinv = 1.0f, float mean = 0.f) {
+__device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int nt, int m, int g, float rinv, float mean, const TileOperands &t) {
   if (nt >= a.NT) return;
   const int n = nt * 16 + 4 * g;
   if (EPI == EPI_RESIDUAL) {
     op_t o4[4];
-    if (m < a.M && n < a.N) residual_update(a, v, n, m, o4);
+    if (m < a.M && n < a.N) residual_update(a, v, n, m, o4, t.h, t.b4);
     return;
   }
   if (a.wsum) {  // folded LayerNorm: take the mean's share out, in the packed weights' units
-    const float4 ws = *(const float4 *)(a.wsum + n);
+    const float4 ws = t.w4;
     v[0] -= mean * ws.x; v[1] -= mean * ws.y; v[2] -= mean * ws.z; v[3] -= mean * ws.w;
   }
   v[0] *= a.out_scale; v[1] *= a.out_scale; v[2] *= a.out_scale; v[3] *= a.out_scale;  // exact: a power of two
   v[0] *= rinv; v[1] *= rinv; v[2] *= rinv; v[3] *= rinv;
-  if (a.bias) {
-    const float4 b4 = *(const float4 *)(a.bias + n);
-    v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w;
-  }
+  if (a.bias) { v[0] += t.b4.x; v[1] += t.b4.y; v[2] += t.b4.z; v[3] += t.b4.w; }
   const bool live = m < a.M;
 
   if (EPI == EPI_QKV) {
     if (live && n < a.N) {
-      // No per-lane integer division (it would be most of this epilogue).  A strip of 16 stored rows lies
-      // inside one head of one of q, k, v (d and hd are multiples of 16), and the strip number is the same for
-      // the whole wave: its place is scalar arithmetic.
-      const int base = __builtin_amdgcn_readfirstlane(nt) * 16;
-      const int region = base / a.d, cc0 = base - region * a.d, hh = cc0 / a.hd;
-      const int cc = cc0 + 4 * g, e = cc - hh * a.hd;
-      const int pos = a.row_pos[m];
-      int b = row_group(m, a.q_rows, 1.0f / (float)a.q_rows);
-      if (a.grp_seq) b = a.grp_seq[b];  // prefill passes only
+      const int region = t.region, hh = t.hh, cc = t.cc + 4 * g, e = cc - hh * a.hd;
+      const int pos = t.pos, b = t.seq;
       if (region < 2) {
         float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
         if (a.rope && pos >= 0) {
-          const float2 cs0 = a.rope[(size_t)pos * (a.hd >> 1) + (e >> 1)];
-          const float2 cs1 = a.rope[(size_t)pos * (a.hd >> 1) + (e >> 1) + 1];
-          r0 = v[0] * cs0.x - v[1] * cs0.y; r1 = v[1] * cs0.x + v[0] * cs0.y;
-          r2 = v[2] * cs1.x - v[3] * cs1.y; r3 = v[3] * cs1.x + v[2] * cs1.y;
+          r0 = v[0] * t.cs.x - v[1] * t.cs.y; r1 = v[1] * t.cs.x + v[0] * t.cs.y;
+          r2 = v[2] * t.cs.z - v[3] * t.cs.w; r3 = v[3] * t.cs.z + v[2] * t.cs.w;
         }
         if (region == 0) {  // queries stay fp32: they are never cached, and the attention kernel feeds them at full width
           *(float4 *)((float *)a.q + (size_t)m * a.d + cc) = make_float4(r0, r1, r2, r3);
@@ -265,6 +292,10 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int 
     if (dump) dump_logits(a, dump, n, v);
     row_argmax_out(a, bv, bi, m, nt, live, g);
   }
+}
+template <class T, int EPI>
+__device__ __forceinline__ void tile_epilogue(const GemmArgs &a, f32x4_v v, int nt, int m, int g, float rinv = 1.0f, float mean = 0.f) {
+  tile_epilogue<T, EPI>(a, v, nt, m, g, rinv, mean, fetch_tile_operands<EPI>(a, nt, m, g));
 }
 
 // Four lanes 4k .. 4k+3 hold four 16-bit values each: lane 4k+i returns value i of all four lanes, in lane order.
