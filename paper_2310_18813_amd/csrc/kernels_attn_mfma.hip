@@ -611,7 +611,14 @@ static void launch_attn_hd(const AttnArgs &a, hipStream_t st) {
   const bool fills = rounds == 1 || (double)pairs >= full * (double)rounds * slots;
   // (a prefill's rows are more than the partials' scratch holds: the split shape is for passes that fit)
   const bool no_split = M > a.part_rows;
-  const bool seq = a.shape == 2 || (a.shape == 0 && ((pairs >= ATTN_SEQ_MIN_PAIRS && fills) || a.NC == 1)) || (no_split && !(group_fits && a.shape != 1));
+  // Decoding, three or four chunks, at most one round of waves.  Heads of 128: two workgroups of three waves fit a CU, and more pairs than that are
+  // a second round of them (us, workgroups / waves: 640 pairs of up to 350 positions 23.5 / 20.5, of 350 27.2 / 22.7, 544 of 350 28.3 /
+  // 24.9, but 512 of 350 22.5 / 22.8; with four chunks, two workgroups of four waves to a CU, no difference).  Heads of 64 need half the
+  // registers, and a workgroup of them is ahead throughout (768 pairs of up to 500 positions 16.5 / 19.9, of 350 14.0 / 14.5).
+  const bool waves_ahead = !a.grp_seq && HD == 128 && a.NC == 3 && pairs > slots / 2 && rounds == 1;
+  const bool groups_ahead = !a.grp_seq && HD == 64 && (a.NC == 3 || a.NC == 4) && rounds == 1;
+  const bool many = waves_ahead || (pairs >= ATTN_SEQ_MIN_PAIRS && fills && !groups_ahead);
+  const bool seq = a.shape == 2 || (a.shape == 0 && (many || a.NC == 1)) || (no_split && !(group_fits && a.shape != 1));
   // few sequences: a workgroup per (sequence, head), as long as its partials fit into LDS with a wave per chunk
   const bool group = !seq && (a.shape == 3 || a.shape == 0) && group_fits;
   if (seq) {
