@@ -116,6 +116,21 @@ def _dp(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+# The current stream of a device as the integer the entry points take (torch.cuda.current_stream builds an object around it, 2 us of
+# a call of 16 on a small batch's logits).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
+def _call(dev, fn, *args):
+    """fn(the current stream of dev, *args) with dev current; without the switch (1 us) where it is current already."""
+    st = _raw_stream(dev.index)
+    if torch.cuda.current_device() == dev.index:
+        _check(fn(st, *args))
+    else:
+        with torch.cuda.device(dev):
+            _check(fn(st, *args))
+
+
 def make_desc(d):
     return ModelDesc(**{k: d[k] for k, _ in ModelDesc._fields_})
 
@@ -155,24 +170,21 @@ def spec_greedy_accept(logits, proposals, accepted=None, emitted=None, workspace
     if s:
         assert proposals.dtype == torch.int32 and proposals.shape == (nB, s) and proposals.is_contiguous()
     dev = logits.device
-    st = C.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    props = proposals.data_ptr() if s else None
     if noalloc:
         assert accepted is not None and emitted is not None
-        with torch.cuda.device(dev):
-            _check(lib.spec_greedy_accept_noalloc(st, _dp(logits), _dp(proposals) if s else None, nB, s, V, _dp(accepted),
-                                                  _dp(emitted)))
+        _call(dev, lib.spec_greedy_accept_noalloc, logits.data_ptr(), props, nB, s, V, accepted.data_ptr(), emitted.data_ptr())
         return accepted, emitted
     if accepted is None:
         accepted = torch.empty(nB, dtype=torch.int32, device=dev)
     if emitted is None:
         emitted = torch.empty((nB, q), dtype=torch.int32, device=dev)
-    n = C.c_size_t(0)
-    _check(lib.spec_greedy_accept_workspace_bytes(nB, s, V, C.byref(n)))
     if workspace is None:
+        n = C.c_size_t(0)
+        _check(lib.spec_greedy_accept_workspace_bytes(nB, s, V, C.byref(n)))
         workspace = torch.empty(max(8, n.value), dtype=torch.uint8, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib.spec_greedy_accept(st, _dp(logits), _dp(proposals) if s else None, nB, s, V, _dp(workspace),
-                                      workspace.numel(), _dp(accepted), _dp(emitted)))
+    _call(dev, lib.spec_greedy_accept, logits.data_ptr(), props, nB, s, V, workspace.data_ptr(), workspace.numel(), accepted.data_ptr(),
+          emitted.data_ptr())
     return accepted, emitted
 
 
@@ -182,10 +194,8 @@ def spec_sample_tokens(logits, uniforms, temperature):
     assert uniforms.dtype == torch.float32 and uniforms.shape == (logits.shape[0],) and uniforms.is_contiguous()
     dev = logits.device
     out = torch.empty(logits.shape[0], dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
-        st = C.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
-        _check(lib.spec_sample_tokens(st, _dp(logits), logits.shape[0], logits.shape[1], float(temperature), _dp(uniforms),
-                                      _dp(out)))
+    _call(dev, lib.spec_sample_tokens, logits.data_ptr(), logits.shape[0], logits.shape[1], float(temperature), uniforms.data_ptr(),
+          out.data_ptr())
     return out
 
 
@@ -204,11 +214,9 @@ def spec_sample_accept(target_logits, draft_logits, proposals, uniforms, tempera
     chosen = torch.empty((nB, q), dtype=torch.int32, device=dev)
     accepted = torch.empty(nB, dtype=torch.int32, device=dev)
     emitted = torch.empty((nB, q), dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
-        st = C.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
-        _check(lib.spec_sample_accept(st, _dp(target_logits), _dp(draft_logits) if draft_logits is not None and s else None,
-                                      _dp(proposals) if s else None, _dp(uniforms), nB, s, V, float(temperature),
-                                      _dp(chosen), _dp(accepted), _dp(emitted)))
+    _call(dev, lib.spec_sample_accept, target_logits.data_ptr(), draft_logits.data_ptr() if draft_logits is not None and s else None,
+          proposals.data_ptr() if s else None, uniforms.data_ptr(), nB, s, V, float(temperature), chosen.data_ptr(), accepted.data_ptr(),
+          emitted.data_ptr())
     return chosen, accepted, emitted
 
 
