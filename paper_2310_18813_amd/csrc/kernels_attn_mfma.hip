@@ -137,7 +137,7 @@ __device__ __forceinline__ void load_step(Frags<HD> &f, const T *kbase, const T 
 // One 32-key step of the online softmax for the 16 query columns of the wave.
 template <class T, int HD>
 __device__ __forceinline__ void compute_step(const Frags<HD> &f, const QFrags<T, HD> &qf, int ks, int g,
-                                             int pos_j, float scale, float &m_run, float &l_run,
+                                             int pos_j, int pmin, float scale, float &m_run, float &l_run,
                                              f32x4_v (&acc)[HD / 16]) {
   f32x4_v s0 = (f32x4_v){0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
@@ -154,11 +154,17 @@ __device__ __forceinline__ void compute_step(const Frags<HD> &f, const QFrags<T,
   }
   // lane (query j, group g): s0[i] <-> key ks + 8g + i, s1[i] <-> key ks + 8g + 4 + i
   float sv[8];
-  const int kfirst = ks + 8 * g;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    sv[i] = (kfirst + i <= pos_j) ? s0[i] : NEG_BIG;
-    sv[4 + i] = (kfirst + 4 + i <= pos_j) ? s1[i] : NEG_BIG;
+  for (int i = 0; i < 4; ++i) { sv[i] = s0[i]; sv[4 + i] = s1[i]; }
+  // What most steps do not need is left out by tests that are the same for the wave: the mask (no key of the step lies behind a row) and
+  // the rescaling (the maximum stays).  Not for bf16 heads of 128, where the stream is the bound and the workgroup shape has no
+  // registers left (with it: 24 sequences of up to 2048 positions x 52 heads 166 -> 207 us).  Heads of 64, 24 x 16 of up to 2048 33.0 -> 31.0
+  // us; fp16 heads of 128, 16 x 40 of up to 350 21.0 -> 20.3.
+  constexpr bool LEAN = HD == 64 || !MfmaA<T>::HILO;
+  if (!LEAN || ks + 31 > pmin) {
+    const int kfirst = ks + 8 * g;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sv[i] = kfirst + i <= pos_j ? sv[i] : NEG_BIG;
   }
   float smax = sv[0];
 #pragma unroll
@@ -193,9 +199,12 @@ __device__ __forceinline__ void compute_step(const Frags<HD> &f, const QFrags<T,
 #pragma unroll
     for (int i = 0; i < 4; ++i) pfl[i] = MfmaA<T>::pack2(plo[2 * i], plo[2 * i + 1]);
   }
+  if (!LEAN || !__all(corr == 1.0f)) {
+#pragma unroll
+    for (int ht = 0; ht < HD / 16; ++ht) { acc[ht][0] *= corr; acc[ht][1] *= corr; acc[ht][2] *= corr; acc[ht][3] *= corr; }
+  }
 #pragma unroll
   for (int ht = 0; ht < HD / 16; ++ht) {
-    acc[ht][0] *= corr; acc[ht][1] *= corr; acc[ht][2] *= corr; acc[ht][3] *= corr;
     acc[ht] = MfmaA<T>::run(f.v[ht], pf, acc[ht]);
     if (MfmaA<T>::HILO) acc[ht] = MfmaA<T>::run(f.v[ht], pfl, acc[ht]);
   }
@@ -204,7 +213,7 @@ __device__ __forceinline__ void compute_step(const Frags<HD> &f, const QFrags<T,
 // Fresh partial of the chunk [k0, kend): steps of 32 keys, next step's loads in flight.
 template <class T, int HD, bool STREAM>
 __device__ __forceinline__ void chunk_partial(const T *kbase, const T *vbase, const QFrags<T, HD> &qf, int k0,
-                                              int kend, int r, int g, int pos_j, float scale, float &m_run,
+                                              int kend, int r, int g, int pos_j, int pmin, float scale, float &m_run,
                                               float &l_run, f32x4_v (&acc)[HD / 16]) {
   m_run = NEG_BIG;
   l_run = 0.f;
@@ -218,22 +227,22 @@ __device__ __forceinline__ void chunk_partial(const T *kbase, const T *vbase, co
   int ks = k0;
   while (ks + 64 <= klast) {  // steps ks and ks + 32, and a step behind them to prefetch
     load_step<T, HD, STREAM>(fb, kbase, vbase, ks + 32, r, g);
-    compute_step<T, HD>(fa, qf, ks, g, pos_j, scale, m_run, l_run, acc);
+    compute_step<T, HD>(fa, qf, ks, g, pos_j, pmin, scale, m_run, l_run, acc);
     load_step<T, HD, STREAM>(fa, kbase, vbase, ks + 64, r, g);
-    compute_step<T, HD>(fb, qf, ks + 32, g, pos_j, scale, m_run, l_run, acc);
+    compute_step<T, HD>(fb, qf, ks + 32, g, pos_j, pmin, scale, m_run, l_run, acc);
     ks += 64;
   }
   if (ks + 32 <= klast) {  // two steps left
     load_step<T, HD, STREAM>(fb, kbase, vbase, ks + 32, r, g);
-    compute_step<T, HD>(fa, qf, ks, g, pos_j, scale, m_run, l_run, acc);
-    compute_step<T, HD>(fb, qf, ks + 32, g, pos_j, scale, m_run, l_run, acc);
+    compute_step<T, HD>(fa, qf, ks, g, pos_j, pmin, scale, m_run, l_run, acc);
+    compute_step<T, HD>(fb, qf, ks + 32, g, pos_j, pmin, scale, m_run, l_run, acc);
   } else {                 // one
-    compute_step<T, HD>(fa, qf, ks, g, pos_j, scale, m_run, l_run, acc);
+    compute_step<T, HD>(fa, qf, ks, g, pos_j, pmin, scale, m_run, l_run, acc);
   }
 }
 
 struct WaveSetup {
-  int j, g, pos_j, pmax, m_row;
+  int j, g, pos_j, pmax, pmin, m_row;  // pmin: the first of the rows' positions, rows that are dead or do not exist left out
 };
 __device__ __forceinline__ WaveSetup wave_setup(const AttnArgs &a, int b, int lane) {
   WaveSetup w;
@@ -241,10 +250,14 @@ __device__ __forceinline__ WaveSetup wave_setup(const AttnArgs &a, int b, int la
   w.g = lane >> 4;
   w.m_row = b * a.q_rows + min(w.j, a.q_rows - 1);
   w.pos_j = (w.j < a.q_rows) ? a.row_pos[b * a.q_rows + w.j] : -1;
-  int pmax = w.pos_j;
+  int pmax = w.pos_j, pmin = w.pos_j >= 0 ? w.pos_j : 0x7fffffff;
 #pragma unroll
-  for (int o = 1; o <= 8; o <<= 1) pmax = max(pmax, __shfl_xor(pmax, o, 64));
+  for (int o = 1; o <= 8; o <<= 1) {
+    pmax = max(pmax, __shfl_xor(pmax, o, 64));
+    pmin = min(pmin, __shfl_xor(pmin, o, 64));
+  }
   w.pmax = pmax;
+  w.pmin = __builtin_amdgcn_readfirstlane(pmin);
   return w;
 }
 
@@ -269,7 +282,7 @@ __global__ __launch_bounds__(256) void k_attn_split(AttnArgs a) {
   const T *vbase = (const T *)a.vc + cbh * (a.L_pad / KV_VBLOCK) * HD * KV_VBLOCK;
   float m_run, l_run;
   f32x4_v acc[HT];
-  chunk_partial<T, HD, STREAM>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, scale, m_run, l_run, acc);
+  chunk_partial<T, HD, STREAM>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, w.pmin, scale, m_run, l_run, acc);
   if (w.j < a.q_rows && w.pos_j >= k0) {
     const size_t slot = ((size_t)(b * a.q_rows + w.j) * a.H + hh) * a.NC + c;
     if (w.g == 0) { a.part_ml[slot * 2] = m_run; a.part_ml[slot * 2 + 1] = l_run; }
@@ -329,7 +342,7 @@ __global__ __launch_bounds__(256) void k_attn_seq(AttnArgs a) {  // launched wit
     const int kend = min(attn_chunk_begin(c + 1), w.pmax + 1);
     float mc, lc;
     f32x4_v ac[HT];
-    chunk_partial<T, HD, STREAM>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, scale, mc, lc, ac);
+    chunk_partial<T, HD, STREAM>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, w.pmin, scale, mc, lc, ac);
     if (k0 == 0) {
       mr = mc; lr = lc;
 #pragma unroll
@@ -385,7 +398,7 @@ __global__ __launch_bounds__(512) void k_attn_group(AttnArgs a) {
     const int kend = min(attn_chunk_begin(c + 1), w.pmax + 1);
     float mc, lc;
     f32x4_v ac[HT];
-    chunk_partial<T, HD, STREAM>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, scale, mc, lc, ac);
+    chunk_partial<T, HD, STREAM>(kbase, vbase, qf, k0, kend, w.j, w.g, w.pos_j, w.pmin, scale, mc, lc, ac);
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht) pacc[(c * HT + ht) * 64 + lane] = ac[ht];
     pml[c * 64 + lane] = make_float2(mc, lc);
@@ -528,7 +541,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(AttnArgs a) {
         for (int kk = 0; kk < KK; ++kk) { f.k0[kk] = fp[kk * 64]; f.k1[kk] = fp[(KK + kk) * 64]; }
 #pragma unroll
         for (int ht = 0; ht < HT; ++ht) f.v[ht] = fp[(2 * KK + ht) * 64];
-        compute_step<T, HD>(f, qf, ks, w.g, w.pos_j, scale, mc, lc, ac);
+        compute_step<T, HD>(f, qf, ks, w.g, w.pos_j, w.pmin, scale, mc, lc, ac);
       }
       slot = slot + 1 == PREFILL_RING ? 0 : slot + 1;
     }
