@@ -303,7 +303,7 @@ void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
 // taken by the GEMM from the fp16 rows the last layer left); the GEMM runs over every row of the pass and the second
 // arg-max stage picks the rows that are wanted.
 void fast_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits_or_null, int q, int arg_stride, int32_t *arg_out,
-               hipStream_t st) {
+               HeadPartials *leave, hipStream_t st) {
   const bool tgt = &m == &c->tgt;
   const int rows = last_of_q > 0 ? Mh * last_of_q : Mh;
   GemmArgs a = base_args(c, m.p_head, m.lm_head, m.s_head, m.fold_ln ? m.b_head : nullptr, c->ws.x, rows);
@@ -316,8 +316,11 @@ void fast_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits
   // the row statistics, unless the last layer's down projection has left them
   if (!c->x_ssq && gemm_wants_row_inv(a, EPI_LOGITS)) { KScope k(c, tgt ? SPEC_KCLASS_NORM : -1); launch_row_inv_x(a, st); }
   { KScope k(c, tgt ? SPEC_KCLASS_GEMM_HEAD : -1); launch_gemm_mfma(c->run.dtype, a, EPI_LOGITS, st); }
-  { KScope k(c, tgt ? SPEC_KCLASS_OTHER : -1);
-    launch_argmax_partials(a.part_val, a.part_idx, Mh, last_of_q, gemm_head_partials(a), m.desc.vocab, q, arg_stride, arg_out, st); }
+  if (leave) *leave = {a.part_val, a.part_idx, last_of_q, gemm_head_partials(a), m.desc.vocab, arg_out, arg_stride};
+  else {
+    KScope k(c, tgt ? SPEC_KCLASS_OTHER : -1);
+    launch_argmax_partials(a.part_val, a.part_idx, Mh, last_of_q, gemm_head_partials(a), m.desc.vocab, q, arg_stride, arg_out, st);
+  }
 }
 
 }  // namespace spec

@@ -14,7 +14,7 @@
 //
 // Against the generic kernels (norm, product, rotary + append, attention, activation as nine launches a layer; one wave
 // per output and four rows): verification of 8 sequences x 5 rows at d_model 1024, 4 layers 2679 -> 307 us, logits'
-// error against 64 bits 7.2e-7 -> 6.7e-7 (266 us since); a d_model 256 target with its 128 draft, 12 rounds 4.7 -> 2.5 ms, 2.4e-7 both.
+// error against 64 bits 7.2e-7 -> 6.7e-7 (266 us since); a d_model 256 target with its 128 draft, 12 rounds 4.7 -> 2.2 ms, 2.4e-7 both.
 #include "spec_internal.h"
 #include "device_utils.h"
 #include <algorithm>
@@ -661,7 +661,7 @@ void fp32_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b
 
 // Final norm and LM head: all Mh rows of the pass, or (last_of_q > 0) the last row of each of Mh groups.
 void fp32_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits_or_null, int q, int arg_stride, int32_t *arg_out,
-               hipStream_t st) {
+               HeadPartials *leave, hipStream_t st) {
   const spec_model_desc &D = m.desc;
   const bool ln = D.norm_kind == SPEC_NORM_LAYER;
   if (ln) launch_norm(c, m, c->ws.h, m.final_norm_w, m.final_norm_b, c->ws.x, Mh, last_of_q, st);
@@ -670,7 +670,8 @@ void fp32_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits
   if (!ln && last_of_q > 0) { a.x_mul = last_of_q; a.x_off = last_of_q - 1; }
   a.out = logits_or_null; a.ldo = D.vocab; a.part_val = c->ws.head_part; a.part_idx = c->ws.head_part_idx;
   f32_gemm(a, EPI_LOGITS, c->n_cu, st);
-  launch_argmax_partials(a.part_val, a.part_idx, Mh, 0, a.NT, D.vocab, q, arg_stride, arg_out, st);
+  if (leave) *leave = {a.part_val, a.part_idx, 0, a.NT, D.vocab, arg_out, arg_stride};
+  else launch_argmax_partials(a.part_val, a.part_idx, Mh, 0, a.NT, D.vocab, q, arg_stride, arg_out, st);
 }
 
 }  // namespace spec

@@ -614,36 +614,11 @@ void launch_gemm_mfma(int dtype, const GemmArgs &a, int epi, hipStream_t st) {
 
 // Second stage of the fused arg-max: one block per row over the per-strip partials.
 // row_step > 0: output row m takes the partials of GEMM row m * row_step + row_step - 1 (the last row of its group).
-__global__ void k_argmax_partials(const float *__restrict__ pv, const int32_t *__restrict__ pi, int row_step, int n_part, int V,
-                                  int q, int out_stride, int32_t *__restrict__ out) {
-  __shared__ float shv[4];
-  __shared__ int shi[4];
+__global__ __launch_bounds__(256) void k_argmax_partials(const float *__restrict__ pv, const int32_t *__restrict__ pi, int row_step, int n_part, int V,
+                                                         int q, int out_stride, int32_t *__restrict__ out) {
   const int m = blockIdx.x;
-  float bv = -INFINITY;
-  int bi = 0x7fffffff;
-  const size_t src = row_step > 0 ? (size_t)m * row_step + row_step - 1 : (size_t)m;
-  // Trips to memory are what this costs (2000 partials of a 32000-token head): eight partials a thread in flight, the
-  // clamped ones repeating the last, instead of one after the other.  7B width, 4 layers, one sequence, seven draft
-  // steps and a verification: 765 -> 748 us a round; six sequences, five draft steps: 863 -> 847.
-  for (int t0 = threadIdx.x; t0 < n_part; t0 += 2048) {
-    float v[8];
-    int id[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const size_t at = src * n_part + min(t0 + 256 * i, n_part - 1);
-      v[i] = pv[at]; id[i] = pi[at];
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) argmax_combine(bv, bi, v[i], id[i]);
-  }
-  wave_argmax(bv, bi);
-  if ((threadIdx.x & 63) == 0) { shv[threadIdx.x >> 6] = bv; shi[threadIdx.x >> 6] = bi; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) argmax_combine(bv, bi, shv[w], shi[w]);
-    if (bi < 0 || bi >= V) bi = 0;
-    out[(size_t)(m / q) * out_stride + m % q] = bi;
-  }
+  const int best = block_argmax_partials(pv, pi, row_step > 0 ? (size_t)m * row_step + row_step - 1 : (size_t)m, n_part, V);
+  if (threadIdx.x == 0) out[(size_t)(m / q) * out_stride + m % q] = best;
 }
 void launch_argmax_partials(const float *pv, const int32_t *pi, int M, int row_step, int n_part, int V, int q, int out_stride,
                             int32_t *out, hipStream_t st) {

@@ -26,12 +26,15 @@ __device__ __forceinline__ void load4(const T *__restrict__ p, size_t i, float (
 // no attention, logits ignored), then gathers the embedding (plus the learned position
 // row for OPT-shape models) into the fp32 residual stream.
 // Verification rows follow Alg. 1's call LLM(S, t_1..t_s): pending token, then proposals.
+// last: a draft head's arg-max whose second stage this kernel is, a launch less a draft step (a whole round of spec_round; a step
+// called by itself has to leave its token).  Rounds, us: 7B width, one sequence, seven draft steps 663 -> 658, six sequences, five steps
+// 718 -> 708, 13B width, 16 sequences 1157 -> 1145; twelve rounds of a d_model 256 target with its 128 draft 2278 -> 2212.
 // PREP (models whose RMS norm is folded into the GEMMs): the kernel also leaves what the first layer's QKV GEMM
 // consumes, the fp16 copy of the row in fragment order (the GEMM takes 1 / rms of the row from those values).
 template <class T, bool PREP>
 __global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, int s_max, int L_max, int vocab, int d,
                                  int learned_pos, const int32_t *__restrict__ grp_seq, const int32_t *__restrict__ grp_base, const int32_t *__restrict__ seq, const int32_t *__restrict__ n,
-                                 const int32_t *__restrict__ kv_draft, int32_t *__restrict__ t, const int32_t *__restrict__ table, int fill,
+                                 const int32_t *__restrict__ kv_draft, int32_t *__restrict__ t, HeadPartials last, const int32_t *__restrict__ table, int fill,
                                  const int32_t *__restrict__ seq_s, const int32_t *__restrict__ P_b,
                                  const T *__restrict__ tok_emb, const T *__restrict__ pos_emb,
                                  int32_t *__restrict__ row_tok, int32_t *__restrict__ row_pos, float *__restrict__ h,
@@ -46,12 +49,19 @@ __global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, 
   auto table_tok = [&](int jj) { return nb + jj < L_max ? table[(size_t)b * L_max + nb + jj] : 0; };
   if (table && i == 0)
     for (int jj = threadIdx.x; jj < fill; jj += blockDim.x) t[(size_t)b * s_max + jj] = table_tok(jj);
+  // live or not, every sequence's token is written: t is what a draft step by itself leaves
+  const bool take = last.val && i == q - 1;  // q is 1 in a draft step
+  int newest = 0;
+  if (take) {
+    newest = block_argmax_partials(last.val, last.idx, last.row_step > 0 ? (size_t)b * last.row_step + last.row_step - 1 : (size_t)b, last.n_part, last.vocab);
+    if (threadIdx.x == 0) last.out[(size_t)b * last.stride] = newest;
+  }
   // a sequence with its own cap s_b on the speculation length: its rows for proposals beyond s_b are dead
   const int sb = seq_s ? max(0, seq_s[b]) : s_max;
   if (kind == PASS_VERIFY) {
     if (i <= sb) {
       pos = nb - 1 + i;
-      tok = (i == 0) ? seq[(size_t)b * L_max + nb - 1] : table ? table_tok(i - 1) : t[(size_t)b * s_max + i - 1];
+      tok = (i == 0) ? seq[(size_t)b * L_max + nb - 1] : take && last.proposes ? newest : table ? table_tok(i - 1) : t[(size_t)b * s_max + i - 1];
     }
   } else if (kind == PASS_DRAFT_FIRST) {
     int p = nb - j - q + i;  // j: positions the pass ends before n_b (catch-up passes of a draft cache far behind)
@@ -59,7 +69,7 @@ __global__ __launch_bounds__(256) void k_assemble_embed(int kind, int q, int j, 
   } else if (kind == PASS_DRAFT_NEXT) {  // draft step j >= 2 yields t_j: wanted only up to s_b
     if (j <= sb) {
       pos = nb + j - 2;
-      tok = t[(size_t)b * s_max + j - 2];
+      tok = take && last.proposes ? newest : t[(size_t)b * s_max + j - 2];
     }
   } else {  // PASS_PREFILL
     const int p = grp_base[grp] + i;
@@ -111,7 +121,7 @@ void launch_assemble_embed(const spec_ctx *c, const Model &m, const PassArgs &pa
                        (int)(m.desc.pos_kind == SPEC_POS_LEARNED), prefill ? c->ws.grp_seq + pa.g0 : nullptr, prefill ? c->ws.grp_base + pa.g0 : nullptr,
                        c->st.seq + (size_t)pa.b0 * c->run.L_max,
                        c->st.n + pa.b0, c->drf.kv_len ? c->drf.kv_len + pa.b0 : nullptr,
-                       c->st.t + (size_t)pa.b0 * c->run.s_max, pa.fill > 0 ? c->prop_table + (size_t)pa.b0 * c->run.L_max : nullptr, pa.fill, c->seq_s ? c->seq_s + pa.b0 : nullptr, c->st.P_b + pa.b0,
+                       c->st.t + (size_t)pa.b0 * c->run.s_max, pa.last, pa.fill > 0 ? c->prop_table + (size_t)pa.b0 * c->run.L_max : nullptr, pa.fill, c->seq_s ? c->seq_s + pa.b0 : nullptr, c->st.P_b + pa.b0,
                        (const T *)m.tok_emb, (const T *)m.pos_emb, c->ws.row_tok, c->ws.row_pos, c->ws.h,
                        (op_t *)c->ws.x, c->st.sat));
 }

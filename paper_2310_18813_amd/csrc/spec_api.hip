@@ -460,7 +460,7 @@ enum HeadMode { HEAD_NONE = 0, HEAD_ALL = 1, HEAD_LAST = 2 };
 // One forward pass of a model over B*q rows: embed -> layers -> (final norm, LM head,
 // arg-max for the rows that need a token).
 static int forward_pass(spec_ctx *c, Model &m, const PassArgs &pa, HeadMode head, float *logits_out,
-                        int32_t *arg_out, int arg_stride, int max_pos) {
+                        int32_t *arg_out, int arg_stride, int max_pos, HeadPartials *leave = nullptr) {
   const int M = pa.B * pa.q;
   hipStream_t st = c->stream;
   max_pos = std::max(0, std::min(max_pos, c->run.L_max - 1));
@@ -482,9 +482,9 @@ static int forward_pass(spec_ctx *c, Model &m, const PassArgs &pa, HeadMode head
     const int Mh = last ? pa.B : M;
     const int last_of_q = last ? pa.q : 0;  // the final norm gathers the rows that need a token
     if (m.fast) {
-      fast_head(c, m, Mh, last_of_q, logits_out, last ? 1 : pa.q, arg_stride, arg_out, st);
+      fast_head(c, m, Mh, last_of_q, logits_out, last ? 1 : pa.q, arg_stride, arg_out, leave, st);
     } else if (m.f32) {
-      fp32_head(c, m, Mh, last_of_q, logits_out, last ? 1 : pa.q, arg_stride, arg_out, st);
+      fp32_head(c, m, Mh, last_of_q, logits_out, last ? 1 : pa.q, arg_stride, arg_out, leave, st);
     } else {
       float *lg = logits_out ? logits_out : c->ws.logits;
       generic_head(c, m, Mh, last_of_q, lg, st);
@@ -676,7 +676,9 @@ static int ensure_proposals(spec_ctx *c, int s, const char *who, int &fill) {
 }
 
 // ------------------------------------------------------------------ draft step
-extern "C" int spec_draft_step(spec_ctx *c, int32_t j) {
+// carry: null, or the rounds' own: the step takes the partials of the step before from it and leaves its own arg-max's there,
+// for the next step or the verification of the same call.
+static int draft_step(spec_ctx *c, int32_t j, HeadPartials *carry) {
   if (!c) return fail(nullptr, SPEC_ERR_INVALID_ARG, "spec_draft_step: ctx is null");
   if (!c->active) return fail(c, SPEC_ERR_STATE, "spec_draft_step: no batch; call spec_reset first");
   if (!c->drf.present) return fail(c, SPEC_ERR_STATE, "spec_draft_step: no draft model");
@@ -699,6 +701,9 @@ extern "C" int spec_draft_step(spec_ctx *c, int32_t j) {
     arg_out = c->st.draft_arg;
   }
   const int arg_stride_used = draw ? 1 : arg_stride;
+  HeadPartials before;
+  if (carry) std::swap(before, *carry);
+  HeadPartials *leave = carry && !draw && (c->drf.fast || c->drf.f32) ? carry : nullptr;
   if (j == 1) {
     int fill = 0;
     if (ext && c->prop_table && !c->proposals_ready) {
@@ -722,13 +727,15 @@ extern "C" int spec_draft_step(spec_ctx *c, int32_t j) {
     if (!rc) {
       PassArgs pa{PASS_DRAFT_FIRST, c->B, lag, 0};
       pa.fill = fill;
-      rc = forward_pass(c, c->drf, pa, HEAD_LAST, lg, arg_out, arg_stride_used, c->n_ub - 1);
+      rc = forward_pass(c, c->drf, pa, HEAD_LAST, lg, arg_out, arg_stride_used, c->n_ub - 1, leave);
     }
   } else {
     PassArgs pa{PASS_DRAFT_NEXT, c->B, 1, j};
-    rc = forward_pass(c, c->drf, pa, HEAD_LAST, lg, arg_out, arg_stride_used, c->n_ub + j - 2);
+    pa.last = before;
+    rc = forward_pass(c, c->drf, pa, HEAD_LAST, lg, arg_out, arg_stride_used, c->n_ub + j - 2, leave);
   }
   if (rc) return rc;
+  if (leave) leave->proposes = !ext;
   if (draw) {  // t_j decides the token at position n_b + j - 1
     const int V = c->drf.desc.vocab;
     launch_sample_rows(lg, c->B, V, c->smp_T, c->smp_u, c->st.n, j - 1, c->run.L_max, c->st.t + (j - 1), c->run.s_max, c->stream);
@@ -739,8 +746,10 @@ extern "C" int spec_draft_step(spec_ctx *c, int32_t j) {
   return SPEC_OK;
 }
 
+extern "C" int spec_draft_step(spec_ctx *c, int32_t j) { return draft_step(c, j, nullptr); }
+
 // ------------------------------------------------------------------ verify
-extern "C" int spec_verify_step(spec_ctx *c, int32_t s, float *d_logits_or_null) {
+static int verify_step(spec_ctx *c, int32_t s, float *d_logits_or_null, const HeadPartials &last) {
   if (!c) return fail(nullptr, SPEC_ERR_INVALID_ARG, "spec_verify_step: ctx is null");
   if (!c->active) return fail(c, SPEC_ERR_STATE, "spec_verify_step: no batch; call spec_reset first");
   if (s < 0 || s > c->run.s_max) return fail(c, SPEC_ERR_CAPACITY, "spec_verify_step: s=%d outside 0..s_max=%d", s, c->run.s_max);
@@ -754,6 +763,7 @@ extern "C" int spec_verify_step(spec_ctx *c, int32_t s, float *d_logits_or_null)
   if (rc) return rc;
   PassArgs pa{PASS_VERIFY, c->B, s + 1, 0};
   pa.fill = fill;
+  pa.last = last;
   float *lg = d_logits_or_null ? d_logits_or_null : c->smp_u ? c->smp_tl : nullptr;
   rc = forward_pass(c, c->tgt, pa, HEAD_ALL, lg, c->st.a, c->run.s_max + 1, c->n_ub - 1 + s);
   if (rc) return rc;
@@ -766,6 +776,8 @@ extern "C" int spec_verify_step(spec_ctx *c, int32_t s, float *d_logits_or_null)
   c->verified_s = s;
   return SPEC_OK;
 }
+
+extern "C" int spec_verify_step(spec_ctx *c, int32_t s, float *d_logits_or_null) { return verify_step(c, s, d_logits_or_null, {}); }
 
 // ------------------------------------------------------------------ accept / commit
 extern "C" int spec_accept_commit(spec_ctx *c, int32_t s) {
@@ -795,9 +807,10 @@ extern "C" int spec_round(spec_ctx *c, int32_t s, int32_t n_rounds) {
   if (!ext && s > 0 && !c->drf.present) return fail(c, SPEC_ERR_STATE, "spec_round: no draft model");
   for (int r = 0; r < n_rounds; ++r) {
     int rc = SPEC_OK;
+    HeadPartials carry;
     if (c->drf.present)
-      for (int j = 1; j <= s && !rc; ++j) rc = spec_draft_step(c, j);
-    if (!rc) rc = spec_verify_step(c, s, nullptr);
+      for (int j = 1; j <= s && !rc; ++j) rc = draft_step(c, j, &carry);
+    if (!rc) rc = verify_step(c, s, nullptr, carry);
     if (!rc) rc = spec_accept_commit(c, s);
     if (rc) return rc;
   }

@@ -191,6 +191,16 @@ struct KScope {
 namespace spec {
 
 // ---- launchers implemented in the kernel files (all asynchronous on `st`) ----
+// An LM head's arg-max partials whose second stage is left to the kernel that consumes the token (row_step: see
+// launch_argmax_partials).
+struct HeadPartials {
+  const float *val = nullptr;
+  const int32_t *idx = nullptr;
+  int row_step = 0, n_part = 0, vocab = 0;
+  int32_t *out = nullptr;  // [sequence * stride]: where the token goes
+  int stride = 0;
+  bool proposes = false;   // the token is the newest proposal (with external proposals it is computed, and not used)
+};
 struct PassArgs {
   PassKind kind;
   int B, q;      // rows M = B*q
@@ -201,6 +211,7 @@ struct PassArgs {
                  // the groups g0 .. g0 + B - 1 of the table in the workspace (launch_prefill_groups)
   double reuse = 0.0;  // PASS_PREFILL: prefill_reuse of its groups
   int fill = 0;  // > 0: the pass also fetches the round's first `fill` proposals from the caller's table
+  HeadPartials last = {};  // val set: the draft step before has left its arg-max's second stage to the pass
 };
 
 void launch_assemble_embed(const spec_ctx *c, const Model &m, const PassArgs &pa, hipStream_t st);
@@ -237,8 +248,9 @@ void fp32_prepare();
 size_t fp32_packed_bytes(const spec_model_desc &D, int L_max);
 void fp32_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);
 void fp32_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, hipStream_t st);
+// leave: null, or where the partials of an arg-max are put whose second stage another kernel takes (arg_out is not written then)
 void fp32_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits_or_null, int q, int arg_stride,
-               int32_t *arg_out, hipStream_t st);
+               int32_t *arg_out, HeadPartials *leave, hipStream_t st);
 
 size_t dtype_bytes(int dtype);
 int fail_noctx(int code, const char *fmt, ...);  // records the message spec_last_error(NULL) returns; returns code
@@ -250,6 +262,6 @@ size_t fast_packed_bytes(const spec_model_desc &D, int dtype, int L_max);
 bool fast_setup_model(spec_ctx *c, Model &m, const spec_weights *w, void *&cursor, hipStream_t st);  // false: HIP error
 void fast_layer(spec_ctx *c, const Model &m, int layer, int B, int q_rows, int b0, const int32_t *grp_seq, double reuse, int max_pos, hipStream_t st);
 void fast_head(spec_ctx *c, const Model &m, int Mh, int last_of_q, float *logits_or_null, int q, int arg_stride,
-               int32_t *arg_out, hipStream_t st);
+               int32_t *arg_out, HeadPartials *leave, hipStream_t st);
 
 }  // namespace spec
