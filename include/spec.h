@@ -370,9 +370,11 @@ int spec_set_gemm_tuning(spec_ctx *ctx, int32_t tile_mtw, int32_t tile_nbw, int3
 
 /* Per-kernel timing for benchmarks.  While enabled, every launch of the target model's
    kernels is bracketed by a HIP event pair on the context's stream (this adds a few
-   microseconds per launch: leave it off in production).  spec_read_kernel_timing
-   synchronises, adds up the elapsed time per kernel class since the last read and clears
-   the record.  h_count, h_ms: [SPEC_KCLASS_COUNT].                                        */
+   microseconds per launch: leave it off in production), and every draft pass inside
+   spec_round takes its arg-max to the end in a launch of its own (otherwise the next pass's
+   embedding kernel does), so that its record covers all of its work and no other pass's does.
+   spec_read_kernel_timing synchronises, adds up the elapsed time per kernel class since the
+   last read and clears the record.  h_count, h_ms: [SPEC_KCLASS_COUNT].                   */
 enum {
   SPEC_KCLASS_GEMM_QKV = 0,   /* QKV projection + rotary + KV append            */
   SPEC_KCLASS_GEMM_O,         /* attention output projection + residual         */
@@ -383,7 +385,8 @@ enum {
   SPEC_KCLASS_NORM,           /* norm kernels (fp32 path); 16-bit path: the row
                                  statistics kernel of the norms folded into GEMMs */
   SPEC_KCLASS_OTHER,          /* embedding, arg-max merge, accept/commit        */
-  SPEC_KCLASS_DRAFT_PASS,     /* one whole forward pass of the draft model      */
+  SPEC_KCLASS_DRAFT_PASS,     /* one whole forward pass of the draft model, its
+                                 arg-max included                               */
   SPEC_KCLASS_COUNT
 };
 int spec_kernel_timing(spec_ctx *ctx, int32_t enable);

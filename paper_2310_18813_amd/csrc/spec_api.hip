@@ -703,7 +703,8 @@ static int draft_step(spec_ctx *c, int32_t j, HeadPartials *carry) {
   const int arg_stride_used = draw ? 1 : arg_stride;
   HeadPartials before;
   if (carry) std::swap(before, *carry);
-  HeadPartials *leave = carry && !draw && (c->drf.fast || c->drf.f32) ? carry : nullptr;
+  // (not while launches are timed: a draft pass's record covers the whole pass, its arg-max to the end)
+  HeadPartials *leave = carry && !draw && !c->kt_on && (c->drf.fast || c->drf.f32) ? carry : nullptr;
   if (j == 1) {
     int fill = 0;
     if (ext && c->prop_table && !c->proposals_ready) {

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import synth_inputs as si
+from launches import launched_kernels
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -46,4 +47,39 @@ def test_round_equals_its_steps(dtype, tgt, drf, n, caps, table):
 
     steps = run(False)
     assert run(True) == steps
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype,tgt,drf", [
+    ("fp32", si.llama_desc(1, 128, 2, 352, 333, 64), si.llama_desc(1, 64, 1, 96, 333, 64)),
+    ("bf16", si.llama_desc(1, 256, 2, 416, 1000, 64), si.llama_desc(1, 128, 2, 160, 1000, 64))])
+def test_timed_draft_passes_are_whole(dtype, tgt, drf):
+    """While launches are timed, a draft pass (SPEC_KCLASS_DRAFT_PASS) takes its own arg-max to the end: a round of three draft steps
+    launches four second stages (one of them the verification's), as its steps by themselves do, and emits the same tokens."""
+    from paper_2310_18813_amd import binding as B
+    wt = si.make_weights(tgt, dtype, 5, device=DEV, emb_std=1.0, tag="tgt.")
+    wd = si.make_weights(drf, dtype, 5, device=DEV, emb_std=1.0, tag="drf.")
+    stream = torch.cuda.Stream()
+    ctx = B.Context(tgt, wt, drf, wd, dtype, 2, 3, 40, 20, B.PROPOSALS_DRAFT, DEV, stream)
+    prompts = torch.from_numpy(si.make_prompts(2, 6, tgt["vocab"], 5)).to(DEV)
+    torch.cuda.synchronize()
+
+    def second_stages(timed):
+        ctx.spec_reset(prompts)
+        ctx.spec_kernel_timing(timed)
+        names = [k for k, _, _ in launched_kernels(B.lib, stream, lambda: B._check(B.lib.spec_round(ctx.h, 3, 1), ctx.h))]
+        ctx.spec_kernel_timing(False)
+        return sum("k_argmax_partials" in k for k in names)
+
+    assert second_stages(False) == 1
+    assert second_stages(True) == 4
+
+    def tokens(timed):
+        ctx.spec_reset(prompts)
+        ctx.spec_kernel_timing(timed)
+        ctx.spec_round(3, 3)
+        ctx.spec_kernel_timing(False)
+        return ctx.spec_read_output()
+
+    assert tokens(True) == tokens(False)
     ctx.close()
