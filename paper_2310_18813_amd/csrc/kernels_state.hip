@@ -417,8 +417,9 @@ void launch_state_reset(spec_ctx *c, const int32_t *d_prompt, int P_stride, bool
 // -------------------------------------------------------------------------
 // KV import / export between the caller's [B][len][d_model] layout and the cache layout
 // (keys pair-interleaved inside each head, values blocked by 8 positions).
-template <class T>
-__global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int k_unit, int L_pad, T *__restrict__ kc,
+// BLOCKED: keys in units of 16 bytes (else plain rows, kv_k_index's u = hd).
+template <class T, bool BLOCKED>
+__global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int L_pad, T *__restrict__ kc,
                              T *__restrict__ vc, T *__restrict__ k_user, T *__restrict__ v_user) {
   const int d = H * hd;
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -427,7 +428,7 @@ __global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int k_u
   size_t r = i / d;
   int pos = (int)(r % len), b = (int)(r / len);
   int hh = c / hd, e = c % hd;
-  size_t ki = kv_k_index(L_pad, H, hd, k_unit, b, hh, pos, hd_interleave(e, hd));
+  size_t ki = kv_k_index(L_pad, H, hd, BLOCKED ? (int)(16 / sizeof(T)) : hd, b, hh, pos, hd_interleave(e, hd));
   size_t vi = kv_v_index(L_pad, H, hd, b, hh, pos, e);
   if (import_) { kc[ki] = k_user[i]; vc[vi] = v_user[i]; }
   else { k_user[i] = kc[ki]; v_user[i] = vc[vi]; }
@@ -437,18 +438,20 @@ __global__ void k_kv_convert(int import_, int B, int len, int H, int hd, int k_u
 // row.  Element by element the scattered loads and stores were most of the time: 64 x 128 rows of 4096 116 -> 67 us (33 MB
 // read at the rate they are written).  Workgroups of one wave, keys (blockIdx.y 0) and values (1) apart, so that a
 // small export spreads over the CUs.
+// Of a row of keys, neighbouring threads' units lie 64 bytes apart (kv_k_index).  So the wave loads them as they lie, a lane the positions lane % 4 and
+// 4 + lane % 4 of every fourth unit (1 KB side by side at heads of 128), and the units change hands in LDS: 64 x 128 rows of 4096 75 -> 67.5 us, 5 x
+// 2011 of 6656 146 -> 137, 777 of 5120 from memory 15.5 -> 13.7.  (Four positions at a time in half the LDS, that is more waves to a CU: 143 us.)
 __global__ __launch_bounds__(64) void k_kv_export16(int B, int len, int H, int hd, int k_unit, int L_pad, const uint16_t *__restrict__ kc,
                                                      const uint16_t *__restrict__ vc, uint16_t *__restrict__ k_user,
                                                      uint16_t *__restrict__ v_user) {
-  const int d = H * hd, nb = (len + KV_VBLOCK - 1) / KV_VBLOCK, n8 = d >> 3;
-  const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
-  if (i >= (size_t)B * nb * n8) return;
-  const int c0 = (int)(i % n8) * 8;
-  const size_t r = i / n8;
-  const int p0 = (int)(r % nb) * KV_VBLOCK, b = (int)(r / nb), hh = c0 / hd, e0 = c0 - hh * hd, half = hd >> 1;
-  const int rows = min(KV_VBLOCK, len - p0);
   struct alignas(16) Eight { uint16_t v[8]; };
-  struct alignas(8) Four { uint16_t v[4]; };
+  __shared__ u32x4_v rows_s[8][66];  // [position][unit of the wave]; two more: the rows of a block are written without a bank conflict
+  const int d = H * hd, nb = (len + KV_VBLOCK - 1) / KV_VBLOCK, n8 = d >> 3, lane = threadIdx.x;
+  const size_t i = (size_t)blockIdx.x * 64 + lane, last = (size_t)B * nb * n8 - 1, at = min(i, last);
+  const int c0 = (int)(at % n8) * 8;
+  const size_t r = at / n8;
+  const int p0 = (int)(r % nb) * KV_VBLOCK, b = (int)(r / nb), hh = c0 / hd, e0 = c0 - hh * hd, half = hd >> 1;
+  const int rows = i <= last ? min(KV_VBLOCK, len - p0) : 0;
   const size_t row0 = ((size_t)b * len + p0) * d + (size_t)hh * hd;
   if (blockIdx.y) {
     uint16_t val[8][8];  // [channel][position]
@@ -460,26 +463,34 @@ __global__ __launch_bounds__(64) void k_kv_export16(int B, int len, int H, int h
     }
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
-      if (p >= rows) break;
       Eight o;
 #pragma unroll
       for (int e = 0; e < 8; ++e) o.v[e] = val[e][p];
-      *(Eight *)(v_user + row0 + (size_t)p * d + e0) = o;
+      if (p < rows) *(Eight *)(v_user + row0 + (size_t)p * d + e0) = o;
     }
     return;
   }
-  Eight key[8];  // stored elements e0 .. e0 + 7 of a row: the pairs of channels e0 / 2 .. e0 / 2 + 3 and their partners
+  // stored elements e0 .. e0 + 7 of a row: the pairs of channels e0 / 2 .. e0 / 2 + 3 and their partners
+  const unsigned long long mine = kv_k_index(L_pad, H, hd, k_unit, b, hh, p0, e0);
+  u32x4_v key[8];
 #pragma unroll
-  for (int p = 0; p < 8; ++p) key[p] = *(const Eight *)(kc + kv_k_index(L_pad, H, hd, k_unit, b, hh, p0 + p, e0));
+  for (int k = 0; k < 4; ++k) {
+    const uint16_t *p = kc + __shfl(mine, 16 * k + (lane >> 2), 64) + (lane & 3) * k_unit;
+    key[2 * k] = *(const u32x4_v *)p;
+    key[2 * k + 1] = *(const u32x4_v *)(p + KV_KBLOCK * hd);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) rows_s[KV_KBLOCK * j + (lane & 3)][16 * k + (lane >> 2)] = key[2 * k + j];
+  __syncthreads();
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
-    if (p >= rows) break;
-    Four lo, hi;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { lo.v[e] = key[p].v[2 * e]; hi.v[e] = key[p].v[2 * e + 1]; }
-    const size_t row = row0 + (size_t)p * d;
-    *(Four *)(k_user + row + (e0 >> 1)) = lo;
-    *(Four *)(k_user + row + half + (e0 >> 1)) = hi;
+    if (p >= rows) continue;
+    const u32x4_v t = rows_s[p][lane];  // a word: a channel and its partner
+    const size_t row = row0 + (size_t)p * d + (e0 >> 1);
+    *(uint2 *)(k_user + row) = make_uint2((t[0] & 0xffff) | t[1] << 16, (t[2] & 0xffff) | t[3] << 16);
+    *(uint2 *)(k_user + row + half) = make_uint2(t[0] >> 16 | (t[1] & 0xffff0000u), t[2] >> 16 | (t[3] & 0xffff0000u));
   }
 }
 void launch_kv_convert(spec_ctx *c, const Model &m, int layer, int B, int len, void *k, void *v, bool import_,
@@ -489,9 +500,9 @@ void launch_kv_convert(spec_ctx *c, const Model &m, int layer, int B, int len, v
   size_t esz = dtype_bytes(c->run.dtype);
   char *kc = (char *)m.kcache + (size_t)layer * m.kv_area_elems * esz;
   char *vc = (char *)m.vcache + (size_t)layer * m.kv_area_elems * esz;
-  // From 3 * 2^18 elements on: a thread's eight rows in turn take a microsecond longer than a launch of single elements, until
-  // those are several to a lane of the chip.  Elements / blocks, us: 16 rows of 4096 2.4 / 3.4, 64 rows of 6656 3.4 / 3.6, 128
-  // rows of 5120 4.1 / 4.3, 64 x 16 rows of 768 4.6 / 4.4, 256 rows of 4096 5.4 / 4.5, 777 rows of 5120 14.3 / 9.7.
+  // From 3 * 2^18 elements on: a thread's eight rows in turn take a microsecond or two longer than a launch of single elements, until
+  // those are several to a lane of the chip; around the line there is little between them.  Elements / blocks, us: 16 rows of 4096 2.9 / 4.8, 64
+  // rows of 6656 4.6 / 4.6, 128 rows of 5120 5.0 / 4.7, 64 x 16 rows of 768 5.4 / 4.9, 256 rows of 4096 6.5 / 4.9, 777 rows of 5120 17.3 / 9.6.
   if (!import_ && esz == 2 && total >= ((size_t)3 << 18) && m.hd % 16 == 0 && (((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
     const size_t threads = (size_t)B * ((len + KV_VBLOCK - 1) / KV_VBLOCK) * (m.desc.d_model / 8);
     hipLaunchKernelGGL(k_kv_export16, dim3((unsigned)((threads + 63) / 64), 2), dim3(64), 0, st, B, len, m.desc.n_heads, m.hd, m.k_unit, m.L_pad,
@@ -499,8 +510,8 @@ void launch_kv_convert(spec_ctx *c, const Model &m, int layer, int B, int len, v
     return;
   }
   SPEC_DISPATCH_DTYPE(c->run.dtype, T,
-    hipLaunchKernelGGL(k_kv_convert<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (int)import_, B, len,
-                       m.desc.n_heads, m.hd, m.k_unit, m.L_pad, (T *)kc, (T *)vc, (T *)k, (T *)v));
+    hipLaunchKernelGGL((m.k_unit == m.hd ? k_kv_convert<T, false> : k_kv_convert<T, true>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
+                       (int)import_, B, len, m.desc.n_heads, m.hd, m.L_pad, (T *)kc, (T *)vc, (T *)k, (T *)v));
 }
 
 }  // namespace spec
