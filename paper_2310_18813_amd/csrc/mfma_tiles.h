@@ -166,8 +166,10 @@ __device__ __forceinline__ void row_argmax_out(const GemmArgs &a, float bv, int 
   }
 }
 
-// gate / (1 + exp(-gate)) * up.  The quotient from the reciprocal and one correction by its exact remainder instead of the
-// compiler's division, which scales its operands against overflow first (the divisor is at least 1): five instructions for ten.
+// gate / (1 + exp(-gate)) * up.  The quotient from the reciprocal and one correction by its remainder instead of the compiler's division,
+// which scales its operands against overflow first (the divisor is at least 1): five instructions for ten.  It is not always the
+// rounded quotient (one in some millions is its neighbour), and for gates below -87.3, where the reciprocal is below the smallest
+// normal float, it may be -0 instead of less than 1e-36 in magnitude, which is 0 as fp16 whatever `up` is, up to 1e28.
 __device__ __forceinline__ float swiglu(float gate, float up) {
   const float den = 1.0f + __expf(-gate), r = __builtin_amdgcn_rcpf(den), q = gate * r;
   return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-den, q, gate), r, q), den, gate) * up;  // (the fix-up: infinities and NaN)
