@@ -624,12 +624,14 @@ static void launch_attn_hd(const AttnArgs &a, hipStream_t st) {
   const bool fills = rounds == 1 || (double)pairs >= full * (double)rounds * slots;
   // (a prefill's rows are more than the partials' scratch holds: the split shape is for passes that fit)
   const bool no_split = M > a.part_rows;
-  // Decoding, three or four chunks, at most one round of waves.  Heads of 128: two workgroups of three waves fit a CU, and more pairs than that are
-  // a second round of them (us, workgroups / waves: 640 pairs of up to 350 positions 23.5 / 20.5, of 350 27.2 / 22.7, 544 of 350 28.3 /
-  // 24.9, but 512 of 350 22.5 / 22.8; with four chunks, two workgroups of four waves to a CU, no difference).  Heads of 64 need half the
-  // registers, and a workgroup of them is ahead throughout (768 pairs of up to 500 positions 16.5 / 19.9, of 350 14.0 / 14.5).
+  // Decoding, three or four chunks, at most one round of waves; whole verifications, us, workgroups / waves, prompts of up to that many positions.  Heads of
+  // 128, three chunks: two workgroups of three waves fit a CU, and more pairs than that are a second round of them (4 layers: fp16, d_model 5120,
+  // 520 pairs of 350 847 / 840, 640 of 350 876 / 856; bf16, d_model 4096, 544 of 350 629 / 614, 640 of 350 650 / 625; with four chunks, two
+  // workgroups of four waves to a CU, no difference).  Heads of 64 need half the registers: workgroups are ahead up to seven eighths of
+  // a round of waves (12 layers, d_model 768: bf16, 768 pairs of 300 465 / 475, of 480 512 / 526, 864 of 500 563 / 565, but 960 of 500 592 / 586, 1020
+  // of 350 561 / 551; fp16, 792 of 500 532 / 534, 1020 of 350 541 / 535; either way by the lengths at 768 to 800 pairs of 350, 486 / 483 and 523 / 526).
   const bool waves_ahead = !a.grp_seq && HD == 128 && a.NC == 3 && pairs > slots / 2 && rounds == 1;
-  const bool groups_ahead = !a.grp_seq && HD == 64 && (a.NC == 3 || a.NC == 4) && rounds == 1;
+  const bool groups_ahead = !a.grp_seq && HD == 64 && (a.NC == 3 || a.NC == 4) && pairs <= slots / 8 * 7;
   const bool many = waves_ahead || (pairs >= ATTN_SEQ_MIN_PAIRS && fills && !groups_ahead);
   const bool seq = a.shape == 2 || (a.shape == 0 && (many || a.NC == 1)) || (no_split && !(group_fits && a.shape != 1));
   // few sequences: a workgroup per (sequence, head), as long as its partials fit into LDS with a wave per chunk
