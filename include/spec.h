@@ -47,7 +47,8 @@ enum {
   SPEC_ERR_STATE = 3,       /* call out of order                                      */
   SPEC_ERR_CAPACITY = 4,    /* B, s or sequence length beyond what spec_init reserved */
   SPEC_ERR_UNSUPPORTED = 5, /* model shape / option this build has no kernel for      */
-  SPEC_ERR_HIP = 6          /* a HIP runtime call failed                              */
+  SPEC_ERR_HIP = 6          /* a HIP runtime call failed: a round it happened in is not
+                               to be continued step by step, spec_reset starts anew     */
 };
 
 /* Storage type of the weights handed in and of the KV cache.  Arithmetic: fp32 runs on plain fp32 ALU

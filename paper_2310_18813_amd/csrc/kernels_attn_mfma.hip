@@ -158,7 +158,7 @@ __device__ __forceinline__ void compute_step(const Frags<HD> &f, const QFrags<T,
   for (int i = 0; i < 4; ++i) { sv[i] = s0[i]; sv[4 + i] = s1[i]; }
   // What most steps do not need is left out by tests that are the same for the wave: the mask (no key of the step lies behind a row) and
   // the rescaling (the maximum stays).  Not for bf16 heads of 128, where the stream is the bound and the workgroup shape has no
-  // registers left (with it: 24 sequences of up to 2048 positions x 52 heads 166 -> 207 us).  Heads of 64, 24 x 16 of up to 2048 33.0 -> 31.0
+  // registers left (with it: 24 sequences of up to 2048 positions x 52 heads 166 -> 207 us).  Heads of 64, 24 x 16 of up to 2048 33.0 -> 31.1
   // us; fp16 heads of 128, 16 x 40 of up to 350 21.0 -> 20.3.
   constexpr bool LEAN = HD == 64 || !MfmaA<T>::HILO;
   if (!LEAN || ks + 31 > pmin) {

@@ -232,7 +232,7 @@ __device__ __forceinline__ void f32_epilogue(const F32Gemm &a, f32x4 v, int nt, 
 constexpr size_t f32_lds(int KS, int MT, int NB) { return (size_t)KS * (NB * MT * 1024 + MT * 16 * 4); }
 
 // Workgroup = KS waves, one k-slice each, over NB strips of W and MT row tiles of X; the slices meet in LDS.  Bound by the latencies of a
-// wave's loads (few rows: a slice is 2 to 32 steps) or by the matrix cores (2 x 4 tiles: 256 cycles of MFMA per unit and step
+// wave's loads (few rows; a slice has K / 128 steps, up to K / 16 where that is odd) or by the matrix cores (2 x 4 tiles: 256 cycles of MFMA per unit and step
 // against 96 cycles of L2 reads; 4 x 4 spills); operands of the next steps are in flight while the present ones are multiplied.
 // (A wave per strip over all of k, the rows through LDS, was slower everywhere but for the head at 1 to 5 rows: 8192 x 1024 at 40 rows 44
 // us against 15.6, 32000 x 1024 55 and 53.)
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_f32(F32Gemm a) {
   // Steps in two batches of U, the loads of one in flight while the other is multiplied.  DEEP: inside the loop every load is
   // unconditional (behind a branch the compiler waits, where it joins, for all loads under way), and the multiplies stay
   // in order, so that few of their intermediate sums take registers beside the batches.
-  constexpr int U = DEEP ? (NB + MT <= 5 ? 4 : 2) : NB + MT >= 5 ? 1 : NB + MT >= 3 ? 2 : 4;
+  constexpr int U = DEEP ? 4 : NB + MT >= 5 ? 1 : NB + MT >= 3 ? 2 : 4;  // (DEEP: at most three tiles)
   f32x4 wf[2][U][NB], xf[2][U][MT];
   auto load = [&](f32x4 (&wd)[U][NB], f32x4 (&xd)[U][MT], int kt) {
 #pragma unroll

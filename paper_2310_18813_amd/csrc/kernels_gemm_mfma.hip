@@ -229,6 +229,15 @@ void launch_rope_table(int L, int hd, float theta, float2 *tab, hipStream_t st) 
   hipLaunchKernelGGL(k_rope_table, dim3((total + 255) / 256), dim3(256), 0, st, L, hd, theta, tab);
 }
 
+// f(0), f(1), ... f(N - 1), each number a constant
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void for_each_int(F f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    for_each_int<N, I + 1>(f);
+  }
+}
+
 // ------------------------------------------------------------------------- the kernel
 // Workgroup = KS waves; wave w owns k-slice w of NB consecutive 16-row strips of W (a strip
 // group) and MT 16-row tiles of X (a pass).  Weights and activations are both read in
@@ -241,15 +250,6 @@ void launch_rope_table(int L, int hd, float theta, float2 *tab, hipStream_t st) 
 // With more than one pass the linear workgroup id is decoded so that all passes of a strip
 // group run on the same XCD (workgroups are dealt round-robin to the 8 XCDs): the group's
 // weights are fetched from HBM once and hit that XCD's L2 for the other passes.
-// f(0), f(1), ... f(N - 1), each number a constant
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void for_each_int(F f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    for_each_int<N, I + 1>(f);
-  }
-}
-
 template <class T, int MT, int NB, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_stream(GemmArgs a) {
   extern __shared__ float red[];  // [KS][min(NB*MT, 8)][256]

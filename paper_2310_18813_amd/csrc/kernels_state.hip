@@ -26,9 +26,10 @@ __device__ __forceinline__ void load4(const T *__restrict__ p, size_t i, float (
 // no attention, logits ignored), then gathers the embedding (plus the learned position
 // row for OPT-shape models) into the fp32 residual stream.
 // Verification rows follow Alg. 1's call LLM(S, t_1..t_s): pending token, then proposals.
-// last: a draft head's arg-max whose second stage this kernel is, a launch less a draft step (a whole round of spec_round; a step
-// called by itself has to leave its token).  Rounds, us: 7B width, one sequence, seven draft steps 663 -> 658, six sequences, five steps
-// 718 -> 708, 13B width, 16 sequences 1157 -> 1145; twelve rounds of a d_model 256 target with its 128 draft 2278 -> 2212.
+// last: a draft head's arg-max whose second stage this kernel is, a launch less a draft step, inside spec_round only (a step called by
+// itself has to leave its token).  Rounds of four target layers in steps one by one / through spec_round, us: 7B width, one sequence, seven
+// draft steps 685 / 676, six sequences, five steps 688 / 682, 13B width, 16 sequences, four steps 1079 / 1074; twelve rounds of a
+// d_model 256 target with its 128 draft, through spec_round without and with it, 2278 -> 2212.
 // PREP (models whose RMS norm is folded into the GEMMs): the kernel also leaves what the first layer's QKV GEMM
 // consumes, the fp16 copy of the row in fragment order (the GEMM takes 1 / rms of the row from those values).
 template <class T, bool PREP>

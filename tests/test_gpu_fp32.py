@@ -66,7 +66,7 @@ def test_a_later_row_that_is_not_finite_leaves_the_rows_before_it_alone():
 
 @pytest.mark.parametrize("d,heads,ffn", [(128, 2, 416), (320, 5, 1232), (640, 10, 1024), (1024, 16, 4096)])
 def test_a_row_alone_has_the_bits_of_the_row_among_many(d, heads, ffn):
-    """One row's products keep more steps of a k-slice under way than those of many rows do (slices of 4 to 77 steps here, odd
+    """One row's products keep more steps of a k-slice under way than those of many rows do (slices of 1 to 77 steps here, odd
     ones among them): the same sums, for batches on either side of the row counts where that changes."""
     from paper_2310_18813_amd import binding as B
     desc = si.llama_desc(2, d, heads, ffn, 700, 128)
