@@ -16,14 +16,15 @@
 // wave owns a contiguous segment of the vocabulary and walks it 256 logits at a time, four per lane; lanes, then waves are
 // added in a fixed order by every thread alike, so a draw depends on the row alone.
 //
-// Bound by latency and by what one CU can stream: a row of 32000 logits is 128 KB and a place needs two of them.  While
+// Bound by latency and by reading rows twice (from L2 the second time): a row of 32000 logits is 128 KB, a place needs two of
+// them, and 22 us for that are about 5 bytes per clock and CU, well below what a CU can take from memory.  While
 // they fit the chip, all places of a round are therefore decided at once, each as if its round reached it (draws behind
 // the first rejection are thrown away by k_sample_seal), so that the rows stream through B * (s + 1) CUs instead of one
 // after the other through B; a row is read once for maximum and sum together, and once more (from L2) where a token is
 // drawn from it.  A thread with a contiguous chunk of its own (loads 512 bytes apart across a wave), a pass for each of
 // maximum and sum, and a sequence's places in turn took 87 us for 64 sequences x 4 places of 32000 logits with draft rows;
 // this takes 26 us (30 with a test for -inf and for the end beside every exponential: what is left of a place is about
-// equal parts loads and exponentials).  Larger rounds take places in turn (workgroups_per_sequence).
+// equal parts waiting for loads and exponentials).  Larger rounds take places in turn (workgroups_per_sequence).
 #include "spec_internal.h"
 #include "device_utils.h"
 #include <algorithm>
